@@ -747,7 +747,7 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 4 : 3) void k_adjoint(AdjArgs
   for (int c = threadIdx.x; c < kMaxCond; c += 256)
     for (int w = 0; w < 4; ++w) sdt[w][c] = sdp[w][c] = 0.0;
   __syncthreads();
-  const int64_t nk = a.off[m.n_buckets];
+  const int64_t nk = a.off[m.n_fine];
   const int64_t nbatch = (nk + 63) >> 6;
   const double sqrt2ln2 = sqrt(2.0 * kLN2);
   for (int64_t bt = (int64_t)blockIdx.x * 4 + wave; bt < nbatch; bt += (int64_t)gridDim.x * 4) {

@@ -1,0 +1,644 @@
+// Far field of the profile pass.  Away from a line its profile is smooth on
+// the scale of a grid tile, so tiles at least one tile's width away take it
+// through its values at P Chebyshev nodes of the tile instead of at each of
+// the tile's points; tiles double in size with distance (far_geometry.h), so
+// a window of 5000 points costs a line about 20 tile visits of P nodes, plus
+// the leaves next to its centre, which k_gather takes point by point.  The interpolation error is below 3.4e-14 of the line's
+// value for P = 20 (FP64 form) and 2.2e-8 for P = 12 (FP32 form), reached for
+// an undamped 1/x^2 tail on the nearest admissible tile (the Bernstein ellipse
+// of a tile three half-widths from a pole has rho = 3 + sqrt(8)).
+//
+// What bounds a pass is the number of profile evaluations; measured on the
+// whole call: 1e7 lines, 2e6 points, window 5000 points, FP32 form 14.65 ms
+// point by point, 7.26 ms with expansions (of which the near leaves 4.1, the
+// tiles 0.8, the window ends and sigma 1.05); 1e6 lines, FP64 form 3.33 and
+// 2.62 ms; 48 conditions of 1e6 lines, 2e5 points, FP32 form 113.2 and 17.3 ms.
+//
+// k_far: one wave (2^l waves for a tile of level l, up to eight, then slices)
+//   takes 64 lines at a time, one per lane, evaluates each at the tile's nodes
+//   into P registers of the lane, and adds the lanes once at the end, so a
+//   visit costs neither LDS traffic nor cross-lane sums per line.  The sums
+//   become Chebyshev coefficients (one row of P per tile and slice).
+// k_far_finish: the lines whose windows end inside a tile, then
+//   sigma_k += sum over the levels of the expansion of k's tile.
+#include <algorithm>
+
+#include "far_nodes.h"
+#include "k_voigt.h"
+
+namespace xs {
+
+template <int P>
+struct FarNodes;
+template <>
+struct FarNodes<6> {
+  static constexpr double x[6] = XS_FAR_X6;
+};
+template <>
+struct FarNodes<12> {
+  static constexpr double x[12] = XS_FAR_X12;
+};
+template <>
+struct FarNodes<20> {
+  static constexpr double x[20] = XS_FAR_X20;
+};
+static __device__ const double kFarD6[6 * 6] = XS_FAR_D6;
+static __device__ const double kFarD12[12 * 12] = XS_FAR_D12;
+static __device__ const double kFarD20[20 * 20] = XS_FAR_D20;
+template <int P>
+__device__ __forceinline__ const double* far_dct() {
+  if constexpr (P == 6) return kFarD6;
+  else if constexpr (P == 12) return kFarD12;
+  else return kFarD20;
+}
+
+struct FarArgs {
+  ModelDev m;
+  const CondDev* cond;
+  const double* sb;
+  const int32_t* off;
+  const double* rnu;
+  const float* rgref;
+  const float* rnexp;
+  const double* rgpre;
+  const void* rS;
+  const int32_t* rkc;
+  const float* rdel;
+  const int32_t* rwin;
+  int64_t max_lines;
+  const int32_t* counter;
+  double* rows;       // [n_cond][rows_per_cond][P]
+  int64_t cond_rows;  // rows per condition
+  double* sigma;
+};
+
+// NP node pairs of the Gauss-Hermite rule, two at a time over one reciprocal
+// (FP64; |z|^2 <= ~1e18 where more than two pairs are used).
+template <int NP>
+__device__ __forceinline__ double far_pairs(double x, double y2) {
+  const double* tau = gh_tau<NP>();
+  const double* W = gh_w<NP>();
+  const double u = x * x, y4 = 4.0 * y2;
+  double t = 0.0;
+#pragma unroll
+  for (int j = 0; j + 1 < NP; j += 2) {
+    const double s1 = u + (y2 - tau[j]), s2 = u + (y2 - tau[j + 1]);
+    const double d1 = fma(s1, s1, y4 * tau[j]), d2 = fma(s2, s2, y4 * tau[j + 1]);
+    const double n1 = W[j] * (s1 + 2.0 * tau[j]), n2 = W[j + 1] * (s2 + 2.0 * tau[j + 1]);
+    t = fma(fma(n1, d2, n2 * d1), rcp64(d1 * d2), t);
+  }
+  if constexpr (NP & 1) {
+    constexpr int j = NP - 1;
+    const double s1 = u + (y2 - tau[j]);
+    t = fma(W[j] * (s1 + 2.0 * tau[j]), rcp64(fma(s1, s1, y4 * tau[j])), t);
+  }
+  return t;
+}
+
+// The nodes' rational functions N/D, four over one reciprocal:
+// acc[q] += N(x_q) / D(x_q).
+template <int P, typename F>
+__device__ __forceinline__ void far_rational(double xc, double ah, double (&acc)[P], F nd) {
+#pragma unroll
+  for (int q = 0; q < P; q += 4) {
+    double N[4], D[4];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) nd(fma(FarNodes<P>::x[q + h], ah, xc), N[h], D[h]);
+    const double p01 = D[0] * D[1], p23 = D[2] * D[3];
+    const double r = rcp64(p01 * p23);
+    const double r01 = p23 * r, r23 = p01 * r;
+    acc[q] = fma(N[0], D[1] * r01, acc[q]);
+    acc[q + 1] = fma(N[1], D[0] * r01, acc[q + 1]);
+    acc[q + 2] = fma(N[2], D[3] * r23, acc[q + 2]);
+    acc[q + 3] = fma(N[3], D[2] * r23, acc[q + 3]);
+  }
+}
+
+// Bin means of NP node pairs (or the Lorentzian, NP = 0) at a tile's nodes.
+// The tile is at least 64 bins away, so each arctangent's argument is below
+// h / |x| <= 1/64 and its odd series holds (four terms; two where the wave's
+// largest argument allows: the same bounds as the gather's rows).
+template <int PROF, int NP, int P, typename R>
+__device__ __forceinline__ void far_bins(R xc, R ah, R h, R y, R c0, bool two, R (&acc)[P]) {
+  const R hh = (R)0.5 * h, y2 = y * y, yh = y * h;
+  if constexpr (NP == 0) {
+    const R cl = fma(-hh, hh, (R)1);
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+      const R x = fma((R)FarNodes<P>::x[q], ah, xc);
+      acc[q] = fma(c0, atan_series<R>(h * rcp_r<R>(fma(x, x, cl))), acc[q]);
+    }
+  } else {
+    const double* tau = gh_tau<NP>();
+    if (two) {
+#pragma unroll
+      for (int q = 0; q < P; ++q) {
+        const R x = fma((R)FarNodes<P>::x[q], ah, xc), u = x * x;
+        R t = (R)0;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+          const R Pq = u + (y2 + ((R)tau[j] - hh * hh));
+          const R iD = rcp_r<R>(fma(Pq, Pq, u * (R)(-4.0 * tau[j])));
+          const R A = yh * iD, e1 = (R)2 * Pq * A;
+          t = fma((R)(gh_w<NP>()[j] / kPI), Pq * iD * fma(e1 * e1, (R)(-1.0 / 3.0), (R)1 + yh * A), t);
+        }
+        acc[q] = fma(c0 * ((R)2 * yh), t, acc[q]);
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < P; ++q) {
+        const R x = fma((R)FarNodes<P>::x[q], ah, xc);
+        acc[q] = fma(c0, vpairs_bin<NP, true, R>(x - hh, x + hh, yh, y2), acc[q]);
+      }
+    }
+  }
+}
+
+// One line at the nodes of one tile: xc = x at the tile's centre, ah = half
+// its width in x, so node q is at x = xc + x_q ah.  rho: the smallest |z|^2 on
+// the tile; the choice of rule is the wave's.
+template <int PROF, int P>
+__device__ __forceinline__ void far_line_f32(float xc, float ah, float a, float y, float c0, bool live,
+                                             float (&acc)[P]) {
+  if constexpr (PROF == XS_LORENTZ) {
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+      const float x = fmaf((float)FarNodes<P>::x[q], ah, xc);
+      acc[q] = fmaf(c0, rcp32(fmaf(x, x, 1.0f)), acc[q]);
+    }
+  } else if constexpr (PROF == XS_BIN_LORENTZ) {
+    far_bins<PROF, 0, P, float>(xc, ah, a, y, c0, false, acc);
+  } else {
+    const float xn = fabsf(xc) - ah, rho = fmaf(xn, xn, y * y);
+    if (__ballot(live && !(fabsf(xc) + ah <= 1.0e9f && y <= 1.0e9f))) {
+      // |x| or y beyond FP32's safe range: the FP64 evaluator
+#pragma unroll 1
+      for (int q = 0; q < P; ++q) {
+        const double x = fma(FarNodes<P>::x[q], (double)ah, (double)xc);
+        double v;
+        if constexpr (PROF == XS_VOIGT) v = re_w_f64(x, (double)y);
+        else v = voigt_bin_f64(x, (double)y, 0.5 * (double)a);
+        const float t = live ? (float)((double)c0 * v) : 0.0f;
+#pragma unroll
+        for (int k = 0; k < P; ++k) acc[k] += k == q ? t : 0.0f;
+      }
+      return;
+    }
+    const bool one = __ballot(live && !(rho >= 900.9f)) == 0;
+    if constexpr (PROF == XS_BIN_VOIGT) {
+      const bool two = __ballot(live && !(y * a <= 0.01f * rho)) == 0;
+      if (one) far_bins<PROF, 1, P, float>(xc, ah, a, y, c0, two, acc);
+      else far_bins<PROF, 2, P, float>(xc, ah, a, y, c0, two, acc);
+    } else {
+      const float y2 = y * y, k = c0 * (float)(2.0 / kPI) * y;
+      auto term = [&](double tau, double W, float x) {
+        const float s = fmaf(x, x, y2 - (float)tau), cw = k * (float)W;
+        return fmaf(cw, s, cw * (float)(2.0 * tau)) * rcp32(fmaf(s, s, 4.0f * y2 * (float)tau));
+      };
+      if (one) {
+        const float h = y2 - (float)GH::t2[0], cw = k * (float)GH::w2[0], cwt = cw * (float)(2.0 * GH::t2[0]);
+        const float c = 4.0f * y2 * (float)GH::t2[0];
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+          const float x = fmaf((float)FarNodes<P>::x[q], ah, xc), s = fmaf(x, x, h);
+          acc[q] = fmaf(fmaf(cw, s, cwt), rcp32(fmaf(s, s, c)), acc[q]);
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+          const float x = fmaf((float)FarNodes<P>::x[q], ah, xc);
+          acc[q] += term(GH::t4[0], GH::w4[0], x) + term(GH::t4[1], GH::w4[1], x);
+        }
+      }
+    }
+  }
+}
+
+template <int PROF, int P>
+__device__ __forceinline__ void far_line_f64(double xc, double ah, double a, double y, double c0, bool live,
+                                             double (&acc)[P]) {
+  if constexpr (PROF == XS_LORENTZ) {
+    // the product of four denominators stays finite for |x| <= 1e35
+    if (__ballot(live && !(fabs(xc) + ah <= 1.0e35))) {
+#pragma unroll 1
+      for (int q = 0; q < P; ++q) {
+        const double x = fma(FarNodes<P>::x[q], ah, xc);
+        const double t = live ? c0 * rcp64(fma(x, x, 1.0)) : 0.0;
+#pragma unroll
+        for (int k = 0; k < P; ++k) acc[k] += k == q ? t : 0.0;
+      }
+      return;
+    }
+    far_rational<P>(xc, ah, acc, [&](double x, double& N, double& D) {
+      N = c0;
+      D = fma(x, x, 1.0);
+    });
+  } else if constexpr (PROF == XS_BIN_LORENTZ) {
+    far_bins<PROF, 0, P, double>(xc, ah, a, y, c0, false, acc);
+  } else {
+    const double xn = fabs(xc) - ah, y2 = y * y, rho = fma(xn, xn, y2);
+    if (__ballot(live && !(fabs(xc) + ah <= 1.0e9 && y <= 1.0e9))) {
+#pragma unroll 1
+      for (int q = 0; q < P; ++q) {
+        const double x = fma(FarNodes<P>::x[q], ah, xc);
+        double v;
+        if constexpr (PROF == XS_VOIGT) v = re_w_f64(x, y);
+        else v = voigt_bin_f64(x, y, 0.5 * a);
+        const double t = live ? c0 * v : 0.0;
+#pragma unroll
+        for (int k = 0; k < P; ++k) acc[k] += k == q ? t : 0.0;
+      }
+      return;
+    }
+    auto all = [&](double bound) { return __ballot(live && !(rho >= bound)) == 0; };
+    if constexpr (PROF == XS_BIN_VOIGT) {
+      const bool two = __ballot(live && !(y * a <= 1.25e-4 * rho)) == 0;
+      if (all(9.0e6 * 1.001)) far_bins<PROF, 1, P, double>(xc, ah, a, y, c0, two, acc);
+      else if (all(6400.0 * 1.001)) far_bins<PROF, 2, P, double>(xc, ah, a, y, c0, two, acc);
+      else if (all(400.0 * 1.001)) far_bins<PROF, 3, P, double>(xc, ah, a, y, c0, two, acc);
+      else if (all(144.0 * 1.001)) far_bins<PROF, 4, P, double>(xc, ah, a, y, c0, two, acc);
+      else far_bins<PROF, 6, P, double>(xc, ah, a, y, c0, two, acc);
+    } else {
+      if (all(9.0e6 * 1.001)) {
+        const Pair<double> A = make_pair<double>(c0, y, GH::t2[0], GH::w2[0]);
+        far_rational<P>(xc, ah, acc, [&](double x, double& N, double& D) {
+          const double s = fma(x, x, A.h);
+          N = fma(A.cw, s, A.cwt);
+          D = fma(s, s, A.c);
+        });
+      } else if (all(4.5e4 * 1.001)) {
+        const Poly3 C = make_poly3(c0, y);
+        far_rational<P>(xc, ah, acc, [&](double x, double& N, double& D) { poly3_nd(C, x, N, D); });
+      } else if (all(4000.0 * 1.001)) {
+        const Poly2 B = make_poly2(c0, y);
+        far_rational<P>(xc, ah, acc, [&](double x, double& N, double& D) { poly2_nd(B, x, N, D); });
+      } else {
+        const double k = c0 * (y * (2.0 / kPI));
+        auto pairs = [&](auto np) {
+#pragma unroll
+          for (int q = 0; q < P; ++q)
+            acc[q] = fma(k, far_pairs<decltype(np)::value>(fma(FarNodes<P>::x[q], ah, xc), y2), acc[q]);
+        };
+        if (all(400.0 * 1.001)) pairs(std::integral_constant<int, 3>());
+        else if (all(144.0 * 1.001)) pairs(std::integral_constant<int, 4>());
+        else pairs(std::integral_constant<int, 6>());
+      }
+    }
+  }
+}
+
+// The lane's line and its constants for the tile that begins at point ts and
+// has its centre mid points further on: step a and centre xc in the profile's
+// unit x, width y, factor c0.  A lane without a line (in = false, or S = 0)
+// holds another line's with c0 = 0.
+template <typename Real>
+struct FarLine {
+  Real a, xc, y, c0;
+  bool live;
+};
+template <typename Real, int PROF>
+__device__ __forceinline__ FarLine<Real> far_load(const FarArgs& g, const CondDev& cd, uint32_t p, bool in, int ts,
+                                                  Real mid) {
+  const ModelDev& m = g.m;
+  const int kc = g.rkc[p];
+  const Real S = ((const Real*)g.rS)[(int64_t)cd.slot * g.max_lines + p];
+  const float gr = g.rgref[p], ne = g.rnexp[p];
+  const double gp = g.rgpre ? g.rgpre[p] : 0.0;
+  const double nu = g.rnu[p];
+  FarLine<Real> L;
+  L.live = in && S != (Real)0;
+  L.y = 0;
+  Real inv, del;
+  if constexpr (sizeof(Real) == 4) {
+    del = g.rdel[p];
+    const float gamma = fmaf(gr * __builtin_amdgcn_exp2f(ne * (float)(cd.lnTr / kLN2)), (float)cd.pfac, (float)gp);
+    if constexpr (PROF == XS_LORENTZ || PROF == XS_BIN_LORENTZ) {
+      inv = rcp32(gamma);
+      L.c0 = PROF == XS_LORENTZ ? S * (float)(1.0 / kPI) * inv : S * (float)(1.0 / (kPI * m.dnu));
+    } else {
+      inv = (float)0.83255461115769776 * rcp32((float)nu * (float)cd.dop);  // sqrt(ln2)/alpha
+      L.y = gamma * inv;
+      // 1/(sg sqrt(2 pi)); bin means: 1/(sqrt(pi) dnu)
+      L.c0 = PROF == XS_VOIGT ? S * (float)0.56418958354775628 * inv : S * (float)(0.56418958354775628 / m.dnu);
+    }
+  } else {
+    del = nu - nu_of_bin(m.nu0, m.dnu, kc);
+    const double gamma = (double)gr * exp((double)ne * cd.lnTr) * cd.pfac + gp;
+    if constexpr (PROF == XS_LORENTZ || PROF == XS_BIN_LORENTZ) {
+      inv = 1.0 / gamma;
+      L.c0 = PROF == XS_LORENTZ ? S / (kPI * gamma) : S / (kPI * m.dnu);
+    } else {
+      inv = sqrt(kLN2) / (nu * cd.dop);
+      L.y = gamma * inv;
+      L.c0 = PROF == XS_VOIGT ? S * inv * (1.0 / sqrt(kPI)) : S / (sqrt(kPI) * m.dnu);
+    }
+  }
+  if (!L.live) {
+    L.c0 = 0;
+    L.y = 0;
+  }
+  L.a = (Real)m.dnu * inv;
+  L.xc = fma((Real)(ts - kc) + mid, L.a, -(del * inv));
+  return L;
+}
+
+// Sum of v[0..P) over the wave's lanes: halves of the values are exchanged at
+// the first two steps (35 adds for P = 20 instead of 120).  Afterwards the
+// lane holds P / 4 sums, those of the values far_slot(lane) + i.
+template <int P>
+__device__ __forceinline__ void far_fold(double (&v)[P], int lane) {
+  static_assert(P % 4 == 0, "folded in quarters");
+  const bool u1 = lane & 32, u2 = lane & 16;
+#pragma unroll
+  for (int i = 0; i < P / 2; ++i) {
+    const double send = u1 ? v[i] : v[P / 2 + i], keep = u1 ? v[P / 2 + i] : v[i];
+    v[i] = keep + __shfl_xor(send, 32, 64);
+  }
+#pragma unroll
+  for (int i = 0; i < P / 4; ++i) {
+    const double send = u2 ? v[i] : v[P / 4 + i], keep = u2 ? v[P / 4 + i] : v[i];
+    v[i] = keep + __shfl_xor(send, 16, 64);
+  }
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1)
+#pragma unroll
+    for (int i = 0; i < P / 4; ++i) v[i] += __shfl_xor(v[i], o, 64);
+}
+template <int P>
+__device__ __forceinline__ int far_slot(int lane) {
+  return ((lane >> 5) & 1) * (P / 2) + ((lane >> 4) & 1) * (P / 4);
+}
+
+template <typename Real, int PROF, int P>
+__global__ __launch_bounds__(512, sizeof(Real) == 4 ? 4 : 3) void k_far(FarArgs g) {
+  constexpr bool F32 = sizeof(Real) == 4;
+  __shared__ double sv[8][P], st[8][P];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = blockIdx.y;
+  const CondDev& cd = g.cond[c];
+  const FarCond& fc = cd.far;
+  if (!fc.on || g.counter[kFarOff]) return;
+  const ModelDev& m = g.m;
+  const int nf = m.n_fine;
+  // the block's level: the widest tiles, which have the most lines, first
+  int b = blockIdx.x, l = fc.lmax;
+  for (; l >= 0; --l) {
+    const int nb = far_blocks(nf, l);
+    if (b < nb) break;
+    b -= nb;
+  }
+  if (l < 0) return;
+  const int lw = min(l, 3), nw = 1 << lw, sl = far_slices(l);
+  const int t = l < 3 ? (b << (3 - lw)) + (wave >> lw) : b / sl;
+  const int slice = l < 3 ? 0 : b % sl;
+  // positions of the tile's lines: up to four ranges of sorted lines
+  CellRange r[4];
+  far_tile_ranges(fc, l, t, r);
+  uint32_t cum[4], beg[4], total = 0;
+  const bool live_tile = t < far_tiles(nf, l);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const bool ok = live_tile && r[k].lo <= r[k].hi;
+    const uint32_t p0 = ok ? g.off[r[k].lo] : 0, p1 = ok ? g.off[r[k].hi + 1] : 0;
+    beg[k] = p0 - total;  // position q of the tile is line q + beg of its range
+    total += p1 - p0;
+    cum[k] = total;
+  }
+  double acc64[P];
+  Real acc[P];
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    acc[q] = (Real)0;
+    if (F32) acc64[q] = 0.0;
+  }
+  const int ts = t << (l + 6);                             // the tile's first point
+  const Real mid = (Real)(32 << l) - (Real)0.5, half = (Real)(32 << l);
+  const uint32_t stride = (uint32_t)(nw * sl) * 64u;
+  int since = 0;
+  for (uint32_t q0 = (uint32_t)((wave & (nw - 1)) + slice * nw) * 64u; q0 < total; q0 += stride) {
+    const bool in = q0 + lane < total;
+    const uint32_t q = in ? q0 + lane : total - 1;
+    const uint32_t p = q + (q < cum[0] ? beg[0] : q < cum[1] ? beg[1] : q < cum[2] ? beg[2] : beg[3]);
+    const FarLine<Real> L = far_load<Real, PROF>(g, cd, p, in, ts, mid);
+    if constexpr (F32) {
+      far_line_f32<PROF, P>(L.xc, half * L.a, L.a, L.y, L.c0, L.live, acc);
+      if (++since == 32) {
+        since = 0;
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+          acc64[k] += (double)acc[k];
+          acc[k] = (Real)0;
+        }
+      }
+    } else {
+      far_line_f64<PROF, P>(L.xc, half * L.a, L.a, L.y, L.c0, L.live, acc);
+    }
+  }
+  if constexpr (F32) {
+#pragma unroll
+    for (int k = 0; k < P; ++k) acc64[k] += (double)acc[k];
+  } else {
+#pragma unroll
+    for (int k = 0; k < P; ++k) acc64[k] = acc[k];
+  }
+  far_fold<P>(acc64, lane);
+  if ((lane & 15) == 0) {
+    const int s0 = far_slot<P>(lane);
+#pragma unroll
+    for (int i = 0; i < P / 4; ++i) sv[wave][s0 + i] = acc64[i];
+  }
+  __syncthreads();
+  // the tile's waves, then node values to coefficients
+  const int tid = threadIdx.x, tiles = 8 >> lw;
+  if (tid < tiles * P) {
+    const int tg = tid / P, q = tid - tg * P;
+    double v = 0.0;
+    for (int w = 0; w < nw; ++w) v += sv[tg * nw + w][q];
+    st[tg][q] = v;
+  }
+  __syncthreads();
+  if (tid < tiles * P) {
+    const int tg = tid / P, k = tid - tg * P;
+    const int tt = l < 3 ? (b << (3 - lw)) + tg : t;
+    if (tt < far_tiles(nf, l)) {
+      const double* D = far_dct<P>();
+      double v = 0.0;
+#pragma unroll
+      for (int q = 0; q < P; ++q) v = fma(D[q * P + k], st[tg][q], v);
+      const int64_t row = far_rows_before(nf, l) + (int64_t)tt * sl + slice;
+      g.rows[((int64_t)c * g.cond_rows + row) * P + k] = v;
+    }
+  }
+}
+
+// The tiles that window ends cut, and sigma.  One wave per tile of level
+// `end` and condition.  A line whose window ends inside the tile adds its
+// values at PE nodes to the LDS row of its last (first) point; the sum of the
+// rows of all points from k upwards (downwards) is then, at point k, the
+// nodes' values of exactly the lines that reach k, so a cut costs a line PE
+// evaluations instead of one per point.  (PE = 12, FP64 form, and 6: the tile
+// is at least 17 half-widths away, where these keep 1.3e-14 and 1e-8.)  The
+// row is the wave's own and its lanes add in a fixed order.  Then the
+// expansions of the tiles of every level are added (Clenshaw's recurrence)
+// and sigma is updated once.
+template <int P>
+__device__ __forceinline__ double far_clenshaw(const double (&co)[P], double x) {
+  const double x2 = 2.0 * x;
+  double b1 = 0.0, b2 = 0.0;
+#pragma unroll
+  for (int q = P - 1; q >= 1; --q) {
+    const double b = fma(x2, b1, co[q] - b2);
+    b2 = b1;
+    b1 = b;
+  }
+  return fma(x, b1, co[0] - b2);
+}
+
+constexpr int kFarEndBins = kLeafBins << kFarEndMax;
+
+template <typename Real, int PROF, int P, int PE>
+__global__ __launch_bounds__(64) void k_far_finish(FarArgs g) {
+  constexpr bool F32 = sizeof(Real) == 4;
+  __shared__ __align__(16) Real row[PE * kFarEndBins];
+  const int lane = threadIdx.x, c = blockIdx.y, t = blockIdx.x;
+  const CondDev& cd = g.cond[c];
+  const FarCond& fc = cd.far;
+  if (!fc.on || g.counter[kFarOff]) return;
+  const ModelDev& m = g.m;
+  const int nf = m.n_fine, e = fc.end, n = kLeafBins << e, nb = 1 << e;
+  if (t >= far_tiles(nf, e)) return;
+  const int ts = t << (e + 6);
+  const Real mid = (Real)(32 << e) - (Real)0.5, half = (Real)(32 << e);
+  double v[1 << kFarEndMax];  // the lane's points ts + lane nb + i
+#pragma unroll
+  for (int i = 0; i < (1 << kFarEndMax); ++i) v[i] = 0.0;
+  CellRange cut[2];
+  far_cut(fc, t, cut);
+  for (int side = 0; side < 2; ++side) {
+    if (cut[side].lo > cut[side].hi) continue;
+    const int64_t p0 = g.off[cut[side].lo], p1 = g.off[cut[side].hi + 1];
+    if (p0 >= p1) continue;
+    __syncthreads();
+    for (int i = lane; i < PE * n; i += 64) row[i] = (Real)0;
+    __syncthreads();
+    for (int64_t q0 = p0; q0 < p1; q0 += 64) {
+      const int64_t p = min(q0 + lane, p1 - 1);
+      const int2 win = ((const int2*)g.rwin)[(int64_t)cd.cclass * g.max_lines + p];
+      // the last (side 0) or first (side 1) point of the window in the tile
+      const int j = side == 0 ? min(win.y - ts, n - 1) : max(win.x - ts, 0);
+      const bool in = q0 + lane < p1 && win.x <= win.y && (side == 0 ? j >= 0 : j < n);
+      const FarLine<Real> L = far_load<Real, PROF>(g, cd, (uint32_t)p, in, ts, mid);
+      Real acc[PE];
+#pragma unroll
+      for (int q = 0; q < PE; ++q) acc[q] = (Real)0;
+      if constexpr (F32) far_line_f32<PROF, PE>(L.xc, half * L.a, L.a, L.y, L.c0, L.live, acc);
+      else far_line_f64<PROF, PE>(L.xc, half * L.a, L.a, L.y, L.c0, L.live, acc);
+      if (L.live)
+#pragma unroll
+        for (int q = 0; q < PE; ++q) atomicAdd(&row[q * n + j], acc[q]);
+    }
+    __syncthreads();
+    // sums over the other lanes' points on the far side of this lane's
+    double run[PE];
+#pragma unroll
+    for (int q = 0; q < PE; ++q) {
+      double own = 0.0;
+      for (int i = 0; i < nb; ++i) own += (double)row[q * n + lane * nb + i];
+      double s = own;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const double w = side == 0 ? __shfl_down(s, o, 64) : __shfl_up(s, o, 64);
+        s += (side == 0 ? lane + o < 64 : lane >= o) ? w : 0.0;
+      }
+      run[q] = s - own;
+    }
+    const double* D = far_dct<PE>();
+#pragma unroll
+    for (int ii = 0; ii < (1 << kFarEndMax); ++ii) {
+      if (ii >= nb) break;
+      const int i = side == 0 ? nb - 1 - ii : ii;
+      double co[PE];
+#pragma unroll
+      for (int k = 0; k < PE; ++k) co[k] = 0.0;
+#pragma unroll
+      for (int q = 0; q < PE; ++q) {
+        run[q] += (double)row[q * n + lane * nb + i];
+#pragma unroll
+        for (int k = 0; k < PE; ++k) co[k] = fma(D[q * PE + k], run[q], co[k]);
+      }
+      const double x = ((double)(lane * nb + i) - ((double)half - 0.5)) / (double)half;
+      const double y = far_clenshaw<PE>(co, x);
+#pragma unroll
+      for (int k = 0; k < (1 << kFarEndMax); ++k) v[k] += k == i ? y : 0.0;
+    }
+  }
+  // the levels' expansions: leaf by leaf, the lane at the leaf's point `lane`
+  __syncthreads();
+  double* pts = (double*)row;  // [n]: PE * sizeof(Real) >= 8 bytes per point
+#pragma unroll
+  for (int i = 0; i < (1 << kFarEndMax); ++i)
+    if (i < nb) pts[lane * nb + i] = v[i];
+  __syncthreads();
+  const double scale = F32 ? exp(g.sb[cd.slot]) : 1.0;
+  for (int i = 0; i < nb; ++i) {
+    const int f = (t << e) + i;
+    if (f >= nf) break;
+    double sum = pts[i * kLeafBins + lane];
+    int64_t before = 0;
+    for (int l = 0; l <= fc.lmax; ++l) {
+      const int tl = f >> l, sl = far_slices(l);
+      const double* r = g.rows + ((int64_t)c * g.cond_rows + before + (int64_t)tl * sl) * P;
+      before += (int64_t)far_tiles(nf, l) * sl;
+      double co[P];
+#pragma unroll
+      for (int q = 0; q < P; ++q) co[q] = r[q];
+      for (int s = 1; s < sl; ++s)
+#pragma unroll
+        for (int q = 0; q < P; ++q) co[q] += r[s * P + q];
+      // the point in the tile's variable: (k - centre) / half width
+      const double hw = (double)(32 << l);
+      sum += far_clenshaw<P>(co, ((double)((f - (tl << l)) * kLeafBins + lane) - (hw - 0.5)) / hw);
+    }
+    const int64_t k = (int64_t)f * kLeafBins + lane;
+    if (k < m.n_bins) g.sigma[(int64_t)c * m.n_bins + k] += scale * sum;
+  }
+}
+
+int far_nodes(int prec) { return prec == XS_FP32 ? 12 : 20; }
+
+void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, double* sigma, hipStream_t s) {
+  FarArgs a;
+  a.m = m;
+  a.cond = w.cond;
+  a.sb = w.sb;
+  a.off = w.off;
+  a.rnu = w.rnu;
+  a.rgref = w.rgref;
+  a.rnexp = w.rnexp;
+  a.rgpre = w.rgpre;
+  a.rS = w.rS;
+  a.rkc = w.rkc;
+  a.rdel = w.rdel;
+  a.rwin = w.rwin;
+  a.max_lines = w.max_lines;
+  a.counter = w.counter;
+  a.rows = w.far_rows;
+  a.cond_rows = w.far_cond_rows;
+  a.sigma = sigma;
+  int64_t blocks = 0;
+  for (int l = 0; l <= far_lmax; ++l) blocks += far_blocks(m.n_fine, l);
+  const dim3 grid((unsigned)blocks, m.n_cond), fin((unsigned)far_tiles(m.n_fine, end_min), m.n_cond);
+#define XS_F(PR)                                                                                       \
+  if (m.profile == PR && m.prec == XS_FP32) {                                                          \
+    hipLaunchKernelGGL((k_far<float, PR, 12>), grid, dim3(512), 0, s, a);                              \
+    hipLaunchKernelGGL((k_far_finish<float, PR, 12, 6>), fin, dim3(64), 0, s, a);                      \
+  } else if (m.profile == PR) {                                                                        \
+    hipLaunchKernelGGL((k_far<double, PR, 20>), grid, dim3(512), 0, s, a);                             \
+    hipLaunchKernelGGL((k_far_finish<double, PR, 20, 12>), fin, dim3(64), 0, s, a);                    \
+  }
+  XS_F(XS_VOIGT) XS_F(XS_LORENTZ) XS_F(XS_BIN_VOIGT) XS_F(XS_BIN_LORENTZ)
+#undef XS_F
+}
+
+}  // namespace xs

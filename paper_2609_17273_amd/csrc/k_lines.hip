@@ -542,21 +542,18 @@ void launch_radix_sort(const ModelDev& m, const Work& w, int64_t n, int64_t max_
 }
 
 // ---------------------------------------------------------------------------
-// Bucket offsets from the sorted fine keys (bucket = key / fine_per_bucket,
-// the dropped key n_fine is bucket n_buckets, and position n acts as bucket
-// n_buckets + 1, so every bucket 0..n_buckets gets its start;
-// off[n_buckets] = kept lines),
+// Cell offsets from the sorted keys (the dropped key is n_fine, and position
+// n acts as n_fine + 1, so every cell 0..n_fine gets its start; off[n_fine] =
+// kept lines),
 // and the sorted line records: nu, gamma_ref, n_exp, original index, and the
 // intensity of every slot, S (FP64) or S~ = sign exp(ln|S| - s_b) (FP32).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_offsets(const int32_t* skeys, int64_t n, int nbk, int nfine, int fpb,
-                                                 int32_t* off) {
-  auto bucket = [&](int fk) { return fk >= nfine ? nbk : fk / fpb; };
+__global__ __launch_bounds__(256) void k_offsets(const int32_t* skeys, int64_t n, int nfine, int32_t* off) {
   for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p <= n;
        p += (int64_t)gridDim.x * 256) {
-    const int k = (p < n) ? bucket(skeys[p]) : nbk + 1;
-    const int kp = (p > 0) ? bucket(skeys[p - 1]) : -1;
-    for (int b = kp + 1; b <= k && b <= nbk; ++b) off[b] = (int32_t)p;
+    const int k = (p < n) ? skeys[p] : nfine + 1;
+    const int kp = (p > 0) ? skeys[p - 1] : -1;
+    for (int b = kp + 1; b <= k && b <= nfine; ++b) off[b] = (int32_t)p;
   }
 }
 
@@ -568,11 +565,12 @@ __global__ __launch_bounds__(256) void k_records(ModelDev m, const SlotDev* slot
                                                  float* rnexp, double* rgpre, int32_t* ridx, double* rEs,
                                                  void* rS,
                                                  const double* cut_class, int32_t* rkc, float* rdel,
-                                                 int32_t* rwin) {
+                                                 int32_t* rwin, int32_t* counter) {
   __shared__ double lnQ[kMaxCond];  // ln Q of every slot, once per block
   for (int q = threadIdx.x; q < m.n_slots; q += 256) lnQ[q] = log(Q[q]);
   __syncthreads();
-  const int64_t nk = off[m.n_buckets];
+  const int64_t nk = off[m.n_fine];
+  bool odd = false;
   for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < nk;
        p += (int64_t)gridDim.x * 256) {
     const int32_t i = svals[p];
@@ -610,12 +608,17 @@ __global__ __launch_bounds__(256) void k_records(ModelDev m, const SlotDev* slot
       const SlotDev sd = slots[q];
       int sg;
       const double lS = (base + ln_pop(m.mode, m.pop, ls, nu, sd.T, sd.Tv, sd.Tr, sg)) - lnQ[q] + sc;
+      const double S = sg * exp(m.prec == XS_FP32 ? lS - sb[q] : lS);
       if (m.prec == XS_FP32)
-        ((float*)rS)[(int64_t)q * max_lines + p] = (float)(sg * exp(lS - sb[q]));
+        ((float*)rS)[(int64_t)q * max_lines + p] = (float)S;
       else
-        ((double*)rS)[(int64_t)q * max_lines + p] = sg * exp(lS);
+        ((double*)rS)[(int64_t)q * max_lines + p] = S;
+      odd |= !isfinite(S);
     }
+    odd |= !isfinite(lp.gref) || !isfinite(lp.nexp);
   }
+  // an expansion would spread such a line's infinities into not-a-numbers
+  if (__ballot(odd) && (threadIdx.x & 63) == 0) counter[kFarOff] = 1;
 }
 
 void launch_offsets_records(const ModelDev& m, const Work& w, const StatesView& st,
@@ -623,11 +626,10 @@ void launch_offsets_records(const ModelDev& m, const Work& w, const StatesView& 
                             int64_t n, hipStream_t s) {
   int64_t blocks = (n + 256) / 256;
   if (blocks > 8192) blocks = 8192;
-  hipLaunchKernelGGL(k_offsets, dim3((unsigned)blocks), dim3(256), 0, s, skeys, n, m.n_buckets, m.n_fine,
-                     m.fine_per_bucket, w.off);
+  hipLaunchKernelGGL(k_offsets, dim3((unsigned)blocks), dim3(256), 0, s, skeys, n, m.n_fine, w.off);
   hipLaunchKernelGGL(k_records, dim3((unsigned)blocks), dim3(256), 0, s, m, w.slot, w.Q, w.sb, st,
                      w.lpack, svals, w.off, w.max_lines, w.rnu, w.rgref, w.rnexp, w.rgpre, w.ridx, w.rEs, w.rS,
-                     w.cut_class, w.rkc, w.rdel, w.rwin);
+                     w.cut_class, w.rkc, w.rdel, w.rwin, w.counter);
 }
 
 // ---------------------------------------------------------------------------
@@ -684,9 +686,10 @@ void launch_reset(const Work& w, hipStream_t s) {
   hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, s, w.counter, w.stats);
 }
 
-// Only the work queue (the counters of xs_prepare are kept).
+// Only the work queue (the counters of xs_prepare and its flag are kept).
 __global__ void k_reset_queue(int32_t* counter) {
-  for (int q = threadIdx.x; q < kCounterInts; q += 64) counter[q] = 0;
+  for (int q = threadIdx.x; q < kCounterInts; q += 64)
+    if (q != kFarOff) counter[q] = 0;
 }
 
 void launch_scan_i32(int32_t* a, int64_t n, int32_t* sums, hipStream_t s) { scan_excl(a, n, sums, s); }

@@ -72,6 +72,8 @@ struct xs_plan {
   int64_t last_lines_in = 0;
   bool prepared = false;     // records of an xs_prepare are in the workspace
   std::vector<double> cf_T;  // temperatures of the last cooling-function call (upload source)
+  int far_lmax = -1;         // highest level of the conditions' tile expansions (-1: none)
+  int far_end = 0;           // lowest of their levels of cut tiles
   bool has_tau = false;      // the last xs_prepare had state lifetimes (records hold their widths)
 };
 
@@ -206,6 +208,34 @@ void tiling_for(xs_plan* p, int tile_bins, int persistent, int waves_per_cu, int
   p->tiling = t;
 }
 
+// Does the profile pass take this plan's far tiles through expansions?
+bool far_capable(const xs_plan* p) {
+  const int pr = p->model.profile;
+  return p->model.algo == XS_GATHER &&
+         (pr == XS_LORENTZ || pr == XS_VOIGT || pr == XS_BIN_LORENTZ || pr == XS_BIN_VOIGT);
+}
+
+// Tile expansions of one condition.  A window surely reaches floor(cut / dnu)
+// points less two to each side of the home bin (the line lies within half a
+// step of it; the rest for rounding) and at most two more than that quotient.
+// The Voigt is smooth beyond |x| = 8.08 of the grid's widest line, where the
+// Gauss-Hermite rules hold (a bin and a half is taken off the gap, for the
+// line's place in its bin and a bin mean's edge); a Lorentzian is smooth at
+// any width.
+FarCond far_condition(const xs_plan* p, const CondDev& cd) {
+  const ModelDev& d = p->md;
+  const double r = cd.cut / d.dnu;
+  if (!far_capable(p) || !(r < double(1 << 28))) return FarCond{};
+  double gap = 1.0;
+  if (base_profile(p->model.profile) != XS_LORENTZ) {
+    const double nu_end = d.nu0 + (double)(d.n_bins - 1) * d.dnu;
+    gap = std::ceil((8.08 * nu_end * cd.dop / (std::sqrt(kLN2) * d.dnu) + 1.5) / kLeafBins);
+    if (!(gap < double(1 << 20))) return FarCond{};
+  }
+  const int64_t W = (int64_t)std::floor(r);
+  return far_make(W - 2, W + 2, d.n_fine, std::max<int64_t>(1, (int64_t)gap));
+}
+
 void derive(xs_plan* p) {
   const xs_model& m = p->model;
   ModelDev& d = p->md;
@@ -230,6 +260,7 @@ void derive(xs_plan* p) {
   p->cdev.clear();
   p->cut_class.clear();
   p->cut_mult.clear();
+  p->far_lmax = -1;
   double maxcut = 0.0;
   for (const xs_condition& c : p->conds) {
     SlotDev s;
@@ -292,6 +323,11 @@ void derive(xs_plan* p) {
     }
     cd.cclass = cc;
     cd.pad = 0;
+    cd.far = far_condition(p, cd);
+    if (cd.far.on) {
+      p->far_end = p->far_lmax < 0 ? cd.far.end : std::min(p->far_end, cd.far.end);
+      p->far_lmax = std::max(p->far_lmax, cd.far.lmax);
+    }
     p->cdev.push_back(cd);
   }
   d.n_slots = (int32_t)p->sdev.size();
@@ -302,8 +338,11 @@ void derive(xs_plan* p) {
 // item_target: gather work items aimed at when tiles are split (sizes the
 // partial-row buffer, 2 item_target rows); 0 = kItemsPerCU per compute unit.
 // with_adjoint: carve the adjoint's per-block partial sums (the
-// allocation-free forward path leaves them out).
-size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool with_adjoint = true) {
+// allocation-free forward path leaves them out).  with_far: carve the tile
+// expansions' rows, for as many levels as the grid can use, so that a change
+// of conditions never needs a larger workspace.
+size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool with_adjoint = true,
+              bool with_far = true) {
   const ModelDev& d = p->md;
   const int64_t L = p->max_lines;
   const int nsb = (int)((L + kSortBlock - 1) / kSortBlock);
@@ -355,6 +394,12 @@ size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool wit
     x.item_sums = (int32_t*)take(4 * (size_t)((n_ct + 1) / 1024 + 2));
     x.item_target = item_target > 0 ? item_target : kItemsPerCU * (int64_t)std::max(1, p->n_cu);
     x.part = (double*)take(sizeof(double) * 2 * (size_t)x.item_target * 1024);
+  }
+  x.far_rows = nullptr;
+  x.far_cond_rows = 0;
+  if (with_far && far_capable(p)) {
+    x.far_cond_rows = far_rows_before(d.n_fine, far_levels_of_grid(d.n_fine));
+    x.far_rows = (double*)take(sizeof(double) * d.n_cond * (size_t)x.far_cond_rows * far_nodes(d.prec));
   }
   x.stats = (unsigned long long*)take(8 * 8);
   x.adjpart = with_adjoint ? (double*)take(sizeof(double) * d.n_cond * 2 * kAdjBlocksMax) : nullptr;
@@ -415,11 +460,22 @@ int preprocess(xs_plan* p, const xs_states* st, const xs_lines* ln) {
   return hip_check(hipGetLastError(), "preprocess launch");
 }
 
+// Expansions pay off once the cells hold a few lines each: a tile visit
+// costs a wave the same for one line as for 64.
+constexpr int kFarLinesPerCell = 8;
+bool use_far(const xs_plan* p) {
+  return p->w.far_cond_rows > 0 && p->far_lmax >= 0 &&
+         p->last_lines_in >= (int64_t)kFarLinesPerCell * p->md.n_fine;
+}
+
 int profile_pass(xs_plan* p, double* sigma, int accumulate) {
   if (p->model.algo == XS_SCATTER)
     launch_scatter(p->md, kernel_work(p), sigma, accumulate, 0, p->stream);
-  else
-    launch_gather(p->md, kernel_work(p), p->tiling, sigma, accumulate, p->stream);
+  else {
+    const bool far = use_far(p);
+    launch_gather(p->md, kernel_work(p), p->tiling, sigma, accumulate, far, p->stream);
+    if (far) launch_far(p->md, kernel_work(p), p->far_lmax, p->far_end, sigma, p->stream);
+  }
   return hip_check(hipGetLastError(), "profile launch");
 }
 
@@ -784,7 +840,7 @@ int xs_cross_section_noalloc(xs_plan* p, const xs_states* st, const xs_lines* ln
   if (!sigma) return fail(XS_EINVAL, "sigma is NULL");
   if (accumulate != 0 && accumulate != 1) return fail(XS_EINVAL, "accumulate must be 0 or 1");
   const int64_t items = (int64_t)kNoallocItemsPerCU * std::max(1, p->n_cu);
-  const size_t need = layout(p, nullptr, nullptr, items, false);
+  const size_t need = layout(p, nullptr, nullptr, items, false, false);
   if (need > kScratchBytes)
     return fail(XS_EWORKSPACE, "the plan needs " + std::to_string(need) + " bytes of scratch, more than the " +
                                    std::to_string(kScratchBytes) +
@@ -801,7 +857,7 @@ int xs_cross_section_noalloc(xs_plan* p, const xs_states* st, const xs_lines* ln
   const size_t keep_bytes = p->ws_bytes;
   const bool keep_prepared = p->prepared, keep_tau = p->has_tau;
   const int64_t keep_last = p->last_lines_in;
-  layout(p, (char*)base, &p->w, items, false);
+  layout(p, (char*)base, &p->w, items, false, false);
   p->ws = base;
   p->ws_bytes = kScratchBytes;
   rc = upload(p);

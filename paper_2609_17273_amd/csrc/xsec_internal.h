@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/xsec.h"
+#include "far_geometry.h"
 
 namespace xs {
 
@@ -29,8 +30,10 @@ constexpr int kAdjBlocks = 16384;    // blocks of the adjoint's grid in a new pl
 constexpr int kAdjBlocksMax = 32768;  // the most the configuration allows (sizes the partial sums)
 constexpr int kSortItems = 16;    // keys per thread in the radix sort (4096 per block)
 // Device counters (int32): [0] gather work queue, [2..3] candidate total,
-// [4..5] lines per item, [8] cooling-function runs.
+// [4..5] lines per item, [8] cooling-function runs, [kFarOff] set by the
+// record pass where a line's values are not finite.
 constexpr int kCounterInts = 64;
+constexpr int kFarOff = 9;
 constexpr int kSortBlock = 256 * kSortItems;
 constexpr int kFineBins = 64;  // grid points per sort key (the smallest bucket size)
 
@@ -46,6 +49,7 @@ struct CondDev {
   int32_t wbins;  // bound on |k - k_c| of a nonzero term: ceil(cut / dnu) + 2, less for a narrow Gaussian
   int32_t cclass; // cut-off class (index of the distinct cut-off)
   int32_t pad;
+  FarCond far;    // tile expansions (Lorentzian and Voigt forms)
 };
 
 // Per intensity slot: the temperatures of the populations.
@@ -119,7 +123,7 @@ struct Work {
   int32_t* valB;
   int32_t* hist;            // [256 * n_sort_blocks] (+ scan block sums)
   int32_t* hsum;            // scan block sums
-  int32_t* off;             // [n_buckets + 2] bucket offsets into the sorted records
+  int32_t* off;             // [n_fine + 1] offsets of the cells (64 grid points) into the sorted records
   double* rnu;              // sorted records: nu
   float* rgref;             //                 gamma_ref
   float* rnexp;             //                 n_exp
@@ -140,6 +144,8 @@ struct Work {
   int32_t* item_sums;       // scan block sums
   double* part;             // [2 item_target][1024] partial rows
   int64_t item_target;      // work items aimed at when tiles are split
+  double* far_rows;         // [n_cond][far_cond_rows][nodes] expansion coefficients, or null
+  int64_t far_cond_rows;
   unsigned long long* stats;// [8]
   double* adjpart;          // [n_cond][2][kAdjBlocksMax]
   unsigned long long* gmax; // [n_cond] max |dL/dsigma| per condition (bits; FP32 adjoint's scale)
@@ -176,10 +182,18 @@ void launch_reset_queue(const Work& w, hipStream_t s);
 void launch_scan_i32(int32_t* a, int64_t n, int32_t* sums, hipStream_t s);  // exclusive, in place
 
 // ---- profile pass (k_profile.hip) ----
+// far: leave out the leaves that launch_far's tiles take
 void launch_gather(const ModelDev& m, const Work& w, const Tiling& t, double* sigma,
-                   int accumulate, hipStream_t s);
+                   int accumulate, bool far, hipStream_t s);
 void launch_scatter(const ModelDev& m, const Work& w, double* sigma, int accumulate,
                     int64_t n_lines, hipStream_t s);
+
+// ---- tile expansions (k_far.hip) ----
+int far_nodes(int prec);  // nodes per tile
+// sigma += the expansions of the lines' far tiles (levels up to far_lmax, the
+// conditions' largest)
+// (end_min: the conditions' lowest level of cut tiles)
+void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, double* sigma, hipStream_t s);
 
 // ---- cooling function (k_cooling.hip) ----
 int cooling_chunks(int32_t nT);
