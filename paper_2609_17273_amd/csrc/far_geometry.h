@@ -3,11 +3,13 @@
 // point.  Plain integer functions, shared by the kernels, the host runtime
 // and the host tests.
 //
-// The grid is cut into leaves of 64 points (the sort's cells); a tile of level
-// l is 2^l leaves.  Tile t of level l is apart from cell f (the lines with
-// home bin / 64 = f) when at least one tile and at least `gap` cells lie
-// between them: |(f >> l) - t| >= far_apart(l).  Leaves within `gap` cells of f
-// are f's near leaves and take its lines point by point.  Of the others
+// The grid is cut into leaves of 2^sh points (the sort's cells); a tile of level
+// l is 2^l leaves.  Tile t of level l is apart from cell f (the lines whose
+// home bin is in leaf f) when at least one tile and at least `gap` cells lie
+// between them: |(f >> l) - t| >= far_apart.  gap grows with wavenumber, as the
+// lines' widths do, and is the same for all tiles inside one tile of the top
+// level (and of 256 points).  Cells within gap of a leaf are near it and reach it point by point.
+// Of the other leaves
 //   - a tile of a level above `end` is admissible when it is apart and the
 //     window of every line of the cell covers it;
 //   - a tile of level l <= end when it is apart and the window of some line of
@@ -31,20 +33,22 @@
 namespace xs {
 
 constexpr int kFarLevels = 16;
-constexpr int kLeafBins = 64;
-constexpr int kFarEndMax = 2;  // widest tile a window end may cut: 256 points
+constexpr int kFarEndBins = 256;  // widest tile a window end may cut; the narrowest has 64 points
 
 // Far field of one condition (part of the uploaded condition record).
 struct FarCond {
   int32_t on;      // 0: every line goes point by point
   int32_t lmax;    // levels 0..lmax
   int32_t end;     // level of the tiles that window ends cut
-  int32_t gap;     // near leaves: |leaf - f| <= gap
+  int32_t sh;      // a leaf has 2^sh points
   int32_t n_fine;  // cells of the grid
   // cells whose windows all cover a tile [a, b) of leaves: b - cL <= f <= a + cR;
   // cells whose windows can touch it: a - xL <= f <= b + xR
   int32_t cR, cL, xR, xL;
-  int32_t pad;
+  int32_t gap_max;
+  int32_t glev;    // level of the tiles that share a gap: lmax, and at least 256 points
+  // gap of the tiles up to cell e: (gap0 + e gap1) / 2^32, at least one
+  int64_t gap0, gap1;
 };
 
 struct CellRange {
@@ -55,16 +59,21 @@ XS_HD int32_t far_min(int32_t a, int32_t b) { return a < b ? a : b; }
 XS_HD int32_t far_max(int32_t a, int32_t b) { return a > b ? a : b; }
 XS_HD int32_t far_shl(int32_t a, int l) { return a * (1 << l); }  // a may be negative
 
-XS_HD int32_t far_apart(const FarCond& c, int l) { return 1 + ((c.gap + (1 << l) - 1) >> l); }
+XS_HD int32_t far_gap(const FarCond& c, int l, int32_t t) {
+  const int64_t e = (int64_t)((t >> (c.glev - l)) + 1) << c.glev;
+  const int64_t g = (c.gap0 + e * c.gap1) >> 32;
+  return g < 1 ? 1 : g > c.gap_max ? c.gap_max : (int32_t)g;
+}
+XS_HD int32_t far_apart(int32_t gap, int l) { return 1 + ((gap + (1 << l) - 1) >> l); }
 
 // Cells that tile t of level l admits on its left and on its right.
-XS_HD CellRange far_left(const FarCond& c, int l, int32_t t) {
-  const int32_t hi = far_shl(t - far_apart(c, l) + 1, l) - 1;
+XS_HD CellRange far_left(const FarCond& c, int32_t gap, int l, int32_t t) {
+  const int32_t hi = far_shl(t - far_apart(gap, l) + 1, l) - 1;
   const int32_t lo = l > c.end ? ((t + 1) << l) - c.cL : ((t >> (c.end - l)) << c.end) - c.xL;
   return CellRange{far_max(1, lo), hi};
 }
-XS_HD CellRange far_right(const FarCond& c, int l, int32_t t) {
-  const int32_t lo = far_shl(t + far_apart(c, l), l);
+XS_HD CellRange far_right(const FarCond& c, int32_t gap, int l, int32_t t) {
+  const int32_t lo = far_shl(t + far_apart(gap, l), l);
   const int32_t hi = l > c.end ? (t << l) + c.cR : (((t >> (c.end - l)) + 1) << c.end) + c.xR;
   return CellRange{lo, far_min(c.n_fine - 2, hi)};
 }
@@ -81,7 +90,8 @@ XS_HD void far_subtract(CellRange a, CellRange b, CellRange& r0, CellRange& r1) 
 // Cells of tile t of level `end` whose windows may end inside it (or before
 // it): those on the left ([0]: the windows' upper ends) and on the right ([1]).
 XS_HD void far_cut(const FarCond& c, int32_t t, CellRange r[2]) {
-  const CellRange a = far_left(c, c.end, t), b = far_right(c, c.end, t);
+  const int32_t gap = far_gap(c, c.end, t);
+  const CellRange a = far_left(c, gap, c.end, t), b = far_right(c, gap, c.end, t);
   r[0] = CellRange{a.lo, far_min(a.hi, ((t + 1) << c.end) - c.cL - 1)};
   r[1] = CellRange{far_max(b.lo, (t << c.end) + c.cR + 1), b.hi};
 }
@@ -91,34 +101,38 @@ XS_HD void far_cut(const FarCond& c, int32_t t, CellRange r[2]) {
 XS_HD void far_tile_ranges(const FarCond& c, int l, int32_t t, CellRange r[4]) {
   const CellRange none = {0, -1};
   const bool top = l >= c.lmax;
-  CellRange a = far_left(c, l, t), b = far_right(c, l, t);
+  const int32_t gap = far_gap(c, l, t);
+  CellRange a = far_left(c, gap, l, t), b = far_right(c, gap, l, t);
   if (l == c.end) {
     a.lo = far_max(a.lo, ((t + 1) << l) - c.cL);
     b.hi = far_min(b.hi, (t << l) + c.cR);
   }
-  far_subtract(a, top ? none : far_left(c, l + 1, t >> 1), r[0], r[1]);
-  far_subtract(b, top ? none : far_right(c, l + 1, t >> 1), r[2], r[3]);
+  far_subtract(a, top ? none : far_left(c, gap, l + 1, t >> 1), r[0], r[1]);
+  far_subtract(b, top ? none : far_right(c, gap, l + 1, t >> 1), r[2], r[3]);
 }
 
-// Candidate cells of the leaves [a, b] for the point-by-point part, among the
-// cells [clo, chi] whose windows can reach them: the cells that have near
-// leaves there, and the edge cells.
+// Candidate cells of the leaves [a, b] (inside one tile of 256 points) for
+// the point-by-point part, among the cells [clo, chi] whose windows can reach
+// them: the cells near them, and the edge cells.  Of the lines of segment 0,
+// cell f's take the leaves within gap of f.
 constexpr int kSegs = 3;
 XS_HD void far_segments(const FarCond& c, int32_t a, int32_t b, int32_t clo, int32_t chi, CellRange s[kSegs]) {
-  const int32_t last = c.n_fine - 1;
-  s[0] = CellRange{far_max(far_max(a - c.gap, clo), 1), far_min(far_min(b + c.gap, chi), last - 1)};
+  const int32_t last = c.n_fine - 1, gap = far_gap(c, 0, a);
+  s[0] = CellRange{far_max(far_max(a - gap, clo), 1), far_min(far_min(b + gap, chi), last - 1)};
   s[1] = clo == 0 ? CellRange{0, 0} : CellRange{0, -1};
   s[2] = chi == last ? CellRange{last, last} : CellRange{0, -1};
 }
 
-// Rows of expansion coefficients: level l has one row per tile and slice,
-// slices = 2^(l - 3) above level 3 (a tile's lines are split so that no block
-// takes more than eight waves' share).
+// Waves and rows.  A tile of 64 points or fewer is one wave's, one of 2^j
+// times 64 points takes 2^j waves, up to the eight of a block; above that the
+// tile's lines are cut into slices, a block and a row of coefficients each, so
+// that no wave takes more than eight times another's share.
+XS_HD int far_wide(int sh, int l) { return far_max(0, l + sh - 6); }  // log2 of points / 64, at least 0
 XS_HD int32_t far_tiles(int32_t n_fine, int l) { return (n_fine + (1 << l) - 1) >> l; }
-XS_HD int32_t far_slices(int l) { return l > 3 ? 1 << (l - 3) : 1; }
-XS_HD int64_t far_rows_before(int32_t n_fine, int l) {
+XS_HD int32_t far_slices(int sh, int l) { return far_wide(sh, l) > 3 ? 1 << (far_wide(sh, l) - 3) : 1; }
+XS_HD int64_t far_rows_before(int32_t n_fine, int sh, int l) {
   int64_t r = 0;
-  for (int k = 0; k < l; ++k) r += (int64_t)far_tiles(n_fine, k) * far_slices(k);
+  for (int k = 0; k < l; ++k) r += (int64_t)far_tiles(n_fine, k) * far_slices(sh, k);
   return r;
 }
 // most levels a grid of n_fine cells can use (a tile two away must exist)
@@ -127,36 +141,43 @@ XS_HD int far_levels_of_grid(int32_t n_fine) {
   while (l < kFarLevels && (n_fine >> l) >= 3) ++l;
   return l;
 }
-
-// Blocks of eight waves: a block takes 8 >> l tiles of level l < 3, else one
-// slice of one tile.
-XS_HD int32_t far_blocks(int32_t n_fine, int l) {
-  return l < 3 ? (far_tiles(n_fine, l) + (8 >> l) - 1) / (8 >> l) : far_tiles(n_fine, l) * far_slices(l);
+// blocks of a level: 8 >> far_wide tiles each, or one slice of one tile
+XS_HD int32_t far_blocks(int32_t n_fine, int sh, int l) {
+  const int w = far_wide(sh, l);
+  return w < 3 ? (far_tiles(n_fine, l) + (8 >> w) - 1) / (8 >> w) : far_tiles(n_fine, l) * far_slices(sh, l);
 }
 
 // The far field of one condition: windows surely reach W points to each side
-// of the home bin and at most Wx; the profile is smooth over a tile `gap`
-// cells away.  `end` is the widest level (up to kFarEndMax) whose tiles a
-// window end finds at least 18 half-widths away, with everything closer than
-// far_apart covered: there few nodes serve (k_far.hip).  Off where no level
-// does.
-inline FarCond far_make(int64_t W, int64_t Wx, int32_t n_fine, int64_t gap) {
+// of the home bin and at most Wx; a line at cell e (as a real number) is
+// smooth from g0 + g1 e cells on.  `end` is the widest level (64 to
+// kFarEndBins points) whose tiles a window end finds at least 18 half-widths
+// away, with everything closer than far_apart covered: there few nodes serve
+// (k_far.hip).  Off where no level does.
+inline FarCond far_make(int64_t W, int64_t Wx, int32_t n_fine, int sh, double g0, double g1) {
   FarCond c = {};
   const int levels = far_levels_of_grid(n_fine);
-  if (W < kLeafBins || levels < 1 || gap < 1 || gap > W / kLeafBins) return c;
+  const int64_t leaf = (int64_t)1 << sh;
+  // a tile's lines lie up to a window beyond the tile
+  const double reach = (double)Wx / (double)leaf + 1.0;
+  const double most = g0 + g1 * ((double)n_fine + reach);
+  if (W < leaf || levels < 1 || !(most >= 0.0) || !(most + 1.0 <= (double)W / (double)leaf)) return c;
   c.n_fine = n_fine;
-  c.gap = (int32_t)gap;
-  c.cR = (int32_t)((W - 63) / 64);
-  c.cL = (int32_t)((W + 1) / 64);
-  c.xR = (int32_t)((Wx - 1) / 64);
-  c.xL = (int32_t)((Wx + 63) / 64);
+  c.sh = sh;
+  c.gap_max = (int32_t)most + 1;
+  c.gap1 = (int64_t)(g1 * 4294967296.0) + 1;
+  c.gap0 = (int64_t)((g0 + g1 * reach + 1.0) * 4294967296.0);
+  c.cR = (int32_t)((W - leaf + 1) >> sh);
+  c.cL = (int32_t)((W + 1) >> sh);
+  c.xR = (int32_t)((Wx - 1) >> sh);
+  c.xL = (int32_t)((Wx + leaf - 1) >> sh);
   int e = -1;
-  for (int l = 0; l <= kFarEndMax && l < levels; ++l)
-    if (W >= (int64_t)18 * (32 << l) && W >= (int64_t)64 * (far_apart(c, l) << l)) e = l;
+  for (int l = 0; (leaf << l) <= kFarEndBins && l < levels; ++l)
+    if ((leaf << l) >= 64 && W >= 9 * (leaf << l) && W >= leaf * (int64_t)(far_apart(c.gap_max, l) << l)) e = l;
   if (e < 0) return c;
   c.end = e;
   c.lmax = e;
-  while (c.lmax + 1 < levels && (far_apart(c, c.lmax + 1) << (c.lmax + 1)) <= c.cR) ++c.lmax;
+  while (c.lmax + 1 < levels && (far_apart(c.gap_max, c.lmax + 1) << (c.lmax + 1)) <= c.cR) ++c.lmax;
+  c.glev = far_max(c.lmax, 8 - sh);
   c.on = 1;
   return c;
 }

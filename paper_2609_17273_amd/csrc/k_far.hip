@@ -2,17 +2,18 @@
 // the scale of a grid tile, so tiles at least one tile's width away take it
 // through its values at P Chebyshev nodes of the tile instead of at each of
 // the tile's points; tiles double in size with distance (far_geometry.h), so
-// a window of 5000 points costs a line about 20 tile visits of P nodes, plus
-// the leaves next to its centre, which k_gather takes point by point.  The interpolation error is below 3.4e-14 of the line's
-// value for P = 20 (FP64 form) and 2.2e-8 for P = 12 (FP32 form), reached for
-// an undamped 1/x^2 tail on the nearest admissible tile (the Bernstein ellipse
-// of a tile three half-widths from a pole has rho = 3 + sqrt(8)).
+// a window of 5000 points costs a line 20 to 26 tile visits of P nodes, plus the
+// leaves next to its centre, which k_near takes point by point.  The
+// interpolation error is below 3.4e-14 of the line's value for P = 20 (FP64
+// form) and 2.2e-8 for P = 12 (FP32 form), reached for an undamped 1/x^2 tail
+// on the nearest admissible tile (the Bernstein ellipse of a tile three
+// half-widths from a pole has rho = 3 + sqrt(8)).
 //
 // What bounds a pass is the number of profile evaluations; measured on the
-// whole call: 1e7 lines, 2e6 points, window 5000 points, FP32 form 14.65 ms
-// point by point, 7.26 ms with expansions (of which the near leaves 4.1, the
-// tiles 0.8, the window ends and sigma 1.05); 1e6 lines, FP64 form 3.33 and
-// 2.62 ms; 48 conditions of 1e6 lines, 2e5 points, FP32 form 113.2 and 17.3 ms.
+// whole call, point by point and with expansions: 1e7 lines, 2e6 points, window
+// 5000 points, FP32 form 14.65 and 5.6 ms (near leaves 2.2, tiles 1.24, window
+// ends and sigma 0.78); 1e6 lines, FP64 form 3.33 and 2.1 ms; 48 conditions of
+// 1e6 lines, 2e5 points, FP32 form 113.2 and 13.0 ms.
 //
 // k_far: one wave (2^l waves for a tile of level l, up to eight, then slices)
 //   takes 64 lines at a time, one per lane, evaluates each at the tile's nodes
@@ -72,29 +73,6 @@ struct FarArgs {
   double* sigma;
 };
 
-// NP node pairs of the Gauss-Hermite rule, two at a time over one reciprocal
-// (FP64; |z|^2 <= ~1e18 where more than two pairs are used).
-template <int NP>
-__device__ __forceinline__ double far_pairs(double x, double y2) {
-  const double* tau = gh_tau<NP>();
-  const double* W = gh_w<NP>();
-  const double u = x * x, y4 = 4.0 * y2;
-  double t = 0.0;
-#pragma unroll
-  for (int j = 0; j + 1 < NP; j += 2) {
-    const double s1 = u + (y2 - tau[j]), s2 = u + (y2 - tau[j + 1]);
-    const double d1 = fma(s1, s1, y4 * tau[j]), d2 = fma(s2, s2, y4 * tau[j + 1]);
-    const double n1 = W[j] * (s1 + 2.0 * tau[j]), n2 = W[j + 1] * (s2 + 2.0 * tau[j + 1]);
-    t = fma(fma(n1, d2, n2 * d1), rcp64(d1 * d2), t);
-  }
-  if constexpr (NP & 1) {
-    constexpr int j = NP - 1;
-    const double s1 = u + (y2 - tau[j]);
-    t = fma(W[j] * (s1 + 2.0 * tau[j]), rcp64(fma(s1, s1, y4 * tau[j])), t);
-  }
-  return t;
-}
-
 // The nodes' rational functions N/D, four over one reciprocal:
 // acc[q] += N(x_q) / D(x_q).
 template <int P, typename F>
@@ -129,21 +107,10 @@ __device__ __forceinline__ void far_bins(R xc, R ah, R h, R y, R c0, bool two, R
       acc[q] = fma(c0, atan_series<R>(h * rcp_r<R>(fma(x, x, cl))), acc[q]);
     }
   } else {
-    const double* tau = gh_tau<NP>();
     if (two) {
 #pragma unroll
-      for (int q = 0; q < P; ++q) {
-        const R x = fma((R)FarNodes<P>::x[q], ah, xc), u = x * x;
-        R t = (R)0;
-#pragma unroll
-        for (int j = 0; j < NP; ++j) {
-          const R Pq = u + (y2 + ((R)tau[j] - hh * hh));
-          const R iD = rcp_r<R>(fma(Pq, Pq, u * (R)(-4.0 * tau[j])));
-          const R A = yh * iD, e1 = (R)2 * Pq * A;
-          t = fma((R)(gh_w<NP>()[j] / kPI), Pq * iD * fma(e1 * e1, (R)(-1.0 / 3.0), (R)1 + yh * A), t);
-        }
-        acc[q] = fma(c0 * ((R)2 * yh), t, acc[q]);
-      }
+      for (int q = 0; q < P; ++q)
+        acc[q] = fma(c0, vpairs_bin_two<NP, R>(fma((R)FarNodes<P>::x[q], ah, xc), hh, yh, y2), acc[q]);
     } else {
 #pragma unroll
       for (int q = 0; q < P; ++q) {
@@ -273,11 +240,20 @@ __device__ __forceinline__ void far_line_f64(double xc, double ah, double a, dou
         const Poly2 B = make_poly2(c0, y);
         far_rational<P>(xc, ah, acc, [&](double x, double& N, double& D) { poly2_nd(B, x, N, D); });
       } else {
-        const double k = c0 * (y * (2.0 / kPI));
+        const double k = c0 * (y * (2.0 / kPI)), y4 = 4.0 * y2;
+        // two nodes over one reciprocal (|x| < 64 on the tile's nearer side and
+        // below 5 times that on it, or y beyond: the products stay finite)
         auto pairs = [&](auto np) {
 #pragma unroll
-          for (int q = 0; q < P; ++q)
-            acc[q] = fma(k, far_pairs<decltype(np)::value>(fma(FarNodes<P>::x[q], ah, xc), y2), acc[q]);
+          for (int q = 0; q < P; q += 2) {
+            const double x0 = fma(FarNodes<P>::x[q], ah, xc), x1 = fma(FarNodes<P>::x[q + 1], ah, xc);
+            double N0, D0, N1, D1;
+            gh_nd<decltype(np)::value>(x0 * x0, y2, y4, N0, D0);
+            gh_nd<decltype(np)::value>(x1 * x1, y2, y4, N1, D1);
+            const double r = k * rcp64(D0 * D1);
+            acc[q] = fma(N0 * D1, r, acc[q]);
+            acc[q + 1] = fma(N1 * D0, r, acc[q + 1]);
+          }
         };
         if (all(400.0 * 1.001)) pairs(std::integral_constant<int, 3>());
         else if (all(144.0 * 1.001)) pairs(std::integral_constant<int, 4>());
@@ -285,6 +261,16 @@ __device__ __forceinline__ void far_line_f64(double xc, double ah, double a, dou
       }
     }
   }
+}
+
+// The profile is defined at the rounded grid points fl(nu0 + k dnu); the nodes
+// lie on the exact grid.  exact - rounded at point k (FP64 form: up to an ulp
+// of nu_k, which moves a value at distance d by a relative 2 ulp / d).
+__device__ __forceinline__ double far_grid_residue(double nu0, double dnu, int64_t k) {
+#pragma clang fp contract(off)
+  const double kd = (double)k, p = kd * dnu, s = nu0 + p, b = s - nu0;
+  const double es = (nu0 - (s - b)) + (p - b);
+  return es + __builtin_fma(kd, dnu, -p);
 }
 
 // The lane's line and its constants for the tile that begins at point ts and
@@ -322,7 +308,8 @@ __device__ __forceinline__ FarLine<Real> far_load(const FarArgs& g, const CondDe
       L.c0 = PROF == XS_VOIGT ? S * (float)0.56418958354775628 * inv : S * (float)(0.56418958354775628 / m.dnu);
     }
   } else {
-    del = nu - nu_of_bin(m.nu0, m.dnu, kc);
+    // from the exact grid point of the home bin
+    del = (nu - nu_of_bin(m.nu0, m.dnu, kc)) - far_grid_residue(m.nu0, m.dnu, kc);
     const double gamma = (double)gr * exp((double)ne * cd.lnTr) * cd.pfac + gp;
     if constexpr (PROF == XS_LORENTZ || PROF == XS_BIN_LORENTZ) {
       inv = 1.0 / gamma;
@@ -384,14 +371,14 @@ __global__ __launch_bounds__(512, sizeof(Real) == 4 ? 4 : 3) void k_far(FarArgs 
   // the block's level: the widest tiles, which have the most lines, first
   int b = blockIdx.x, l = fc.lmax;
   for (; l >= 0; --l) {
-    const int nb = far_blocks(nf, l);
+    const int nb = far_blocks(nf, fc.sh, l);
     if (b < nb) break;
     b -= nb;
   }
   if (l < 0) return;
-  const int lw = min(l, 3), nw = 1 << lw, sl = far_slices(l);
-  const int t = l < 3 ? (b << (3 - lw)) + (wave >> lw) : b / sl;
-  const int slice = l < 3 ? 0 : b % sl;
+  const int lw = min(far_wide(fc.sh, l), 3), nw = 1 << lw, sl = far_slices(fc.sh, l);
+  const int t = lw < 3 ? (b << (3 - lw)) + (wave >> lw) : b / sl;
+  const int slice = lw < 3 ? 0 : b % sl;
   // positions of the tile's lines: up to four ranges of sorted lines
   CellRange r[4];
   far_tile_ranges(fc, l, t, r);
@@ -412,8 +399,8 @@ __global__ __launch_bounds__(512, sizeof(Real) == 4 ? 4 : 3) void k_far(FarArgs 
     acc[q] = (Real)0;
     if (F32) acc64[q] = 0.0;
   }
-  const int ts = t << (l + 6);                             // the tile's first point
-  const Real mid = (Real)(32 << l) - (Real)0.5, half = (Real)(32 << l);
+  const int ts = t << (l + fc.sh);  // the tile's first point
+  const Real half = (Real)(1 << (l + fc.sh)) * (Real)0.5, mid = half - (Real)0.5;
   const uint32_t stride = (uint32_t)(nw * sl) * 64u;
   int since = 0;
   for (uint32_t q0 = (uint32_t)((wave & (nw - 1)) + slice * nw) * 64u; q0 < total; q0 += stride) {
@@ -460,13 +447,13 @@ __global__ __launch_bounds__(512, sizeof(Real) == 4 ? 4 : 3) void k_far(FarArgs 
   __syncthreads();
   if (tid < tiles * P) {
     const int tg = tid / P, k = tid - tg * P;
-    const int tt = l < 3 ? (b << (3 - lw)) + tg : t;
+    const int tt = lw < 3 ? (b << (3 - lw)) + tg : t;
     if (tt < far_tiles(nf, l)) {
       const double* D = far_dct<P>();
       double v = 0.0;
 #pragma unroll
       for (int q = 0; q < P; ++q) v = fma(D[q * P + k], st[tg][q], v);
-      const int64_t row = far_rows_before(nf, l) + (int64_t)tt * sl + slice;
+      const int64_t row = far_rows_before(nf, fc.sh, l) + (int64_t)tt * sl + slice;
       g.rows[((int64_t)c * g.cond_rows + row) * P + k] = v;
     }
   }
@@ -495,24 +482,39 @@ __device__ __forceinline__ double far_clenshaw(const double (&co)[P], double x) 
   return fma(x, b1, co[0] - b2);
 }
 
-constexpr int kFarEndBins = kLeafBins << kFarEndMax;
+// the derivative of the same sum
+template <int P>
+__device__ __forceinline__ double far_clenshaw_slope(const double (&co)[P], double x) {
+  // sum c_m T_m' = sum m c_m U_(m-1)
+  const double x2 = 2.0 * x;
+  double b1 = 0.0, b2 = 0.0;
+#pragma unroll
+  for (int q = P - 1; q >= 1; --q) {
+    const double b = fma(x2, b1, fma((double)q, co[q], -b2));
+    b2 = b1;
+    b1 = b;
+  }
+  return b1;
+}
+
+constexpr int kFarEndPer = kFarEndBins / 64;  // most points of a lane
 
 template <typename Real, int PROF, int P, int PE>
 __global__ __launch_bounds__(64) void k_far_finish(FarArgs g) {
   constexpr bool F32 = sizeof(Real) == 4;
-  __shared__ __align__(16) Real row[PE * kFarEndBins];
+  __shared__ double row[PE * kFarEndBins];  // FP64 in both forms: FP32 adds to LDS are several times slower
   const int lane = threadIdx.x, c = blockIdx.y, t = blockIdx.x;
   const CondDev& cd = g.cond[c];
   const FarCond& fc = cd.far;
   if (!fc.on || g.counter[kFarOff]) return;
   const ModelDev& m = g.m;
-  const int nf = m.n_fine, e = fc.end, n = kLeafBins << e, nb = 1 << e;
+  const int nf = m.n_fine, e = fc.end, n = 1 << (e + fc.sh), nb = n >> 6;
   if (t >= far_tiles(nf, e)) return;
-  const int ts = t << (e + 6);
-  const Real mid = (Real)(32 << e) - (Real)0.5, half = (Real)(32 << e);
-  double v[1 << kFarEndMax];  // the lane's points ts + lane nb + i
+  const int ts = t * n;
+  const Real half = (Real)n * (Real)0.5, mid = half - (Real)0.5;
+  double v[kFarEndPer];  // the lane's points ts + lane nb + i
 #pragma unroll
-  for (int i = 0; i < (1 << kFarEndMax); ++i) v[i] = 0.0;
+  for (int i = 0; i < kFarEndPer; ++i) v[i] = 0.0;
   CellRange cut[2];
   far_cut(fc, t, cut);
   for (int side = 0; side < 2; ++side) {
@@ -520,7 +522,7 @@ __global__ __launch_bounds__(64) void k_far_finish(FarArgs g) {
     const int64_t p0 = g.off[cut[side].lo], p1 = g.off[cut[side].hi + 1];
     if (p0 >= p1) continue;
     __syncthreads();
-    for (int i = lane; i < PE * n; i += 64) row[i] = (Real)0;
+    for (int i = lane; i < PE * n; i += 64) row[i] = 0.0;
     __syncthreads();
     for (int64_t q0 = p0; q0 < p1; q0 += 64) {
       const int64_t p = min(q0 + lane, p1 - 1);
@@ -536,7 +538,7 @@ __global__ __launch_bounds__(64) void k_far_finish(FarArgs g) {
       else far_line_f64<PROF, PE>(L.xc, half * L.a, L.a, L.y, L.c0, L.live, acc);
       if (L.live)
 #pragma unroll
-        for (int q = 0; q < PE; ++q) atomicAdd(&row[q * n + j], acc[q]);
+        for (int q = 0; q < PE; ++q) atomicAdd(&row[q * n + j], (double)acc[q]);
     }
     __syncthreads();
     // sums over the other lanes' points on the far side of this lane's
@@ -544,7 +546,7 @@ __global__ __launch_bounds__(64) void k_far_finish(FarArgs g) {
 #pragma unroll
     for (int q = 0; q < PE; ++q) {
       double own = 0.0;
-      for (int i = 0; i < nb; ++i) own += (double)row[q * n + lane * nb + i];
+      for (int i = 0; i < nb; ++i) own += row[q * n + lane * nb + i];
       double s = own;
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
@@ -555,7 +557,7 @@ __global__ __launch_bounds__(64) void k_far_finish(FarArgs g) {
     }
     const double* D = far_dct<PE>();
 #pragma unroll
-    for (int ii = 0; ii < (1 << kFarEndMax); ++ii) {
+    for (int ii = 0; ii < kFarEndPer; ++ii) {
       if (ii >= nb) break;
       const int i = side == 0 ? nb - 1 - ii : ii;
       double co[PE];
@@ -563,31 +565,35 @@ __global__ __launch_bounds__(64) void k_far_finish(FarArgs g) {
       for (int k = 0; k < PE; ++k) co[k] = 0.0;
 #pragma unroll
       for (int q = 0; q < PE; ++q) {
-        run[q] += (double)row[q * n + lane * nb + i];
+        run[q] += row[q * n + lane * nb + i];
 #pragma unroll
         for (int k = 0; k < PE; ++k) co[k] = fma(D[q * PE + k], run[q], co[k]);
       }
       const double x = ((double)(lane * nb + i) - ((double)half - 0.5)) / (double)half;
       const double y = far_clenshaw<PE>(co, x);
 #pragma unroll
-      for (int k = 0; k < (1 << kFarEndMax); ++k) v[k] += k == i ? y : 0.0;
+      for (int k = 0; k < kFarEndPer; ++k) v[k] += k == i ? y : 0.0;
     }
   }
   // the levels' expansions: leaf by leaf, the lane at the leaf's point `lane`
   __syncthreads();
-  double* pts = (double*)row;  // [n]: PE * sizeof(Real) >= 8 bytes per point
+  double* pts = row;
 #pragma unroll
-  for (int i = 0; i < (1 << kFarEndMax); ++i)
+  for (int i = 0; i < kFarEndPer; ++i)
     if (i < nb) pts[lane * nb + i] = v[i];
   __syncthreads();
   const double scale = F32 ? exp(g.sb[cd.slot]) : 1.0;
   for (int i = 0; i < nb; ++i) {
-    const int f = (t << e) + i;
-    if (f >= nf) break;
-    double sum = pts[i * kLeafBins + lane];
+    const int k = ts + i * 64 + lane;
+    if (k - lane >= m.n_bins) break;
+    double sum = pts[i * 64 + lane];
+    double slope = 0.0;  // FP64 form: in units of 1 / dnu
     int64_t before = 0;
     for (int l = 0; l <= fc.lmax; ++l) {
-      const int tl = f >> l, sl = far_slices(l);
+      // tiles of 64 points or more hold all of the wave's points: their
+      // coefficients are the wave's (scalar loads)
+      const int lg = l + fc.sh, sl = far_slices(fc.sh, l);
+      const int tl = lg >= 6 ? __builtin_amdgcn_readfirstlane(k >> lg) : min(k >> lg, far_tiles(nf, l) - 1);
       const double* r = g.rows + ((int64_t)c * g.cond_rows + before + (int64_t)tl * sl) * P;
       before += (int64_t)far_tiles(nf, l) * sl;
       double co[P];
@@ -597,10 +603,13 @@ __global__ __launch_bounds__(64) void k_far_finish(FarArgs g) {
 #pragma unroll
         for (int q = 0; q < P; ++q) co[q] += r[s * P + q];
       // the point in the tile's variable: (k - centre) / half width
-      const double hw = (double)(32 << l);
-      sum += far_clenshaw<P>(co, ((double)((f - (tl << l)) * kLeafBins + lane) - (hw - 0.5)) / hw);
+      const double hw = 0.5 * (double)(1 << lg);
+      const double x = ((double)(k - (tl << lg)) - (hw - 0.5)) / hw;
+      sum += far_clenshaw<P>(co, x);
+      if constexpr (!F32) slope = fma(far_clenshaw_slope<P>(co, x), 1.0 / hw, slope);
     }
-    const int64_t k = (int64_t)f * kLeafBins + lane;
+    // from the exact grid point to the rounded one
+    if constexpr (!F32) sum = fma(slope, -far_grid_residue(m.nu0, m.dnu, k) / m.dnu, sum);
     if (k < m.n_bins) g.sigma[(int64_t)c * m.n_bins + k] += scale * sum;
   }
 }
@@ -627,7 +636,7 @@ void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, dou
   a.cond_rows = w.far_cond_rows;
   a.sigma = sigma;
   int64_t blocks = 0;
-  for (int l = 0; l <= far_lmax; ++l) blocks += far_blocks(m.n_fine, l);
+  for (int l = 0; l <= far_lmax; ++l) blocks += far_blocks(m.n_fine, m.fine_sh, l);
   const dim3 grid((unsigned)blocks, m.n_cond), fin((unsigned)far_tiles(m.n_fine, end_min), m.n_cond);
 #define XS_F(PR)                                                                                       \
   if (m.profile == PR && m.prec == XS_FP32) {                                                          \

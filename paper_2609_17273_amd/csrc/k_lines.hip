@@ -94,7 +94,7 @@ void launch_q_out(const ModelDev& m, const Work& w, double* Q, double* dQ, hipSt
 
 // ---------------------------------------------------------------------------
 // Intensity pass 1: nu_i = E_u - E_l; keep lines with nu > 0 whose window
-// (widest cut-off) reaches the grid; key = k_c / kFineBins for the home bin
+// (widest cut-off) reaches the grid; key = k_c >> fine_sh for the home bin
 // k_c = rint((nu - nu0)/dnu), clamped to the grid (lines past either end
 // keep their wings, section "Spectral synthesis"); dropped lines get key
 // n_fine.  FP32 form: running max of ln|S| per slot.  Counters:
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(256) void k_lines_pass1(ModelDev m, const SlotDev* 
     int64_t a, b;
     if (nu > 0.0 && line_window(nu, m.max_cut, m.nu0, m.dnu, m.n_bins, a, b)) {
       int64_t kc = home_bin(nu, m.nu0, m.dnu);
-      int64_t fk = kc < 0 ? 0 : kc / kFineBins;
+      int64_t fk = kc < 0 ? 0 : kc >> m.fine_sh;
       kk = (int32_t)(fk < m.n_fine - 1 ? fk : m.n_fine - 1);
       ++kept;
       LinePack lp;

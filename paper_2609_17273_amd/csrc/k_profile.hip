@@ -157,62 +157,23 @@ struct GatherArgs {
   int32_t persistent;
   int64_t chunk_cfg;        // requested lines per work item (0: automatic)
   int64_t item_target;      // work items aimed at when tiles are split
-  int32_t far;              // leave out the leaves that the tile expansions take
 };
 
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ bool meets(int lo, int hi, const KRange& r) { return hi >= r.lo && lo <= r.hi; }
 
 // Candidate lines of tile t under condition cd: the buckets within the
-// cut-off reach of the tile; with tile expansions, the cells that have near
-// leaves in the tile and the edge cells, in up to kSegs segments.
-// Position q of the candidates is line q + beg[k] of segment k, cum[k - 1] <= q < cum[k].
-struct Candidates {
-  int64_t tlo, thi;
-  int64_t beg[kSegs], cum[kSegs];
-  bool far;
-};
-__device__ __forceinline__ Candidates tile_candidates(const GatherArgs& g, const CondDev& cd, int t) {
+// cut-off reach of the tile.
+__device__ __forceinline__ void tile_candidates(const GatherArgs& g, const CondDev& cd, int t, int64_t& tlo,
+                                                int64_t& thi, int64_t& plo, int64_t& phi) {
   const ModelDev& m = g.m;
-  Candidates r;
-  r.tlo = (int64_t)t * g.tile_bins;
-  r.thi = min(r.tlo + g.tile_bins, m.n_bins) - 1;
-  const int64_t lo = r.tlo - cd.wbins, hi = r.thi + cd.wbins;
-  r.far = g.far && cd.far.on && !g.counter[kFarOff];
-  CellRange s[kSegs];
-  if (r.far) {
-    far_segments(cd.far, (int32_t)(r.tlo / kLeafBins), (int32_t)((r.tlo + g.tile_bins - 1) / kLeafBins),
-                 lo >= 0 ? (int32_t)(lo / kLeafBins) : 0, (int32_t)min<int64_t>(m.n_fine - 1, hi / kLeafBins), s);
-  } else {
-    const int64_t blo = lo >= 0 ? lo / m.bucket_bins : 0;
-    const int64_t bhi = min<int64_t>(m.n_buckets - 1, hi / m.bucket_bins);
-    s[0].lo = (int32_t)(blo * m.fine_per_bucket);
-    s[0].hi = (int32_t)min<int64_t>((bhi + 1) * m.fine_per_bucket, m.n_fine) - 1;
-#pragma unroll
-    for (int k = 1; k < kSegs; ++k) s[k] = CellRange{0, -1};
-  }
-  int64_t total = 0;
-#pragma unroll
-  for (int k = 0; k < kSegs; ++k) {
-    const bool ok = s[k].lo <= s[k].hi;
-    const int64_t p0 = ok ? g.off[s[k].lo] : 0, p1 = ok ? g.off[s[k].hi + 1] : 0;
-    r.beg[k] = p0 - total;
-    total += p1 - p0;
-    r.cum[k] = total;
-  }
-  return r;
-}
-
-// The line at position q of the candidates; near: one of segment 0, whose
-// window is clipped to the cell's near leaves.
-__device__ __forceinline__ int64_t candidate_line(const Candidates& cs, int64_t q, bool& near) {
-  near = q < cs.cum[0];
-  return q + (near ? cs.beg[0] : q < cs.cum[1] ? cs.beg[1] : cs.beg[2]);
-}
-__device__ __forceinline__ void clip_near(int gap, int kc, int2& win) {
-  const int f = kc >> 6;
-  win.x = max(win.x, (f - gap) * kLeafBins);
-  win.y = min(win.y, (f + gap + 1) * kLeafBins - 1);
+  tlo = (int64_t)t * g.tile_bins;
+  thi = min(tlo + g.tile_bins, m.n_bins) - 1;
+  const int64_t lo = tlo - cd.wbins;
+  const int64_t blo = max<int64_t>(0, lo >= 0 ? lo / m.bucket_bins : -1);
+  const int64_t bhi = min<int64_t>(m.n_buckets - 1, (thi + cd.wbins) / m.bucket_bins);
+  plo = g.off[blo * m.fine_per_bucket];
+  phi = g.off[min((bhi + 1) * (int64_t)m.fine_per_bucket, (int64_t)m.n_fine)];
 }
 
 // Bin range where |x| < X, relative to k_c, in FP32 (the one-bin margin
@@ -287,9 +248,6 @@ __device__ int stage_line(const GatherArgs& g, const CondDev& cd, const LineIn<L
   r.kc = kc;
   const int lo = (int)tlo, hi = lo + rowb - 1;
   const bool inside = klo <= lo && khi >= hi;
-  // the points of the row's 64-point chunks that meet the window: a masked
-  // row evaluates these only, so its class is theirs
-  const int elo = lo + ((klo - lo) & ~63), ehi = lo + ((khi - lo) | 63);
   // Gaussian: the nonzero range nz; first formula when the row lies inside it.
   // Voigt: first formula when the row avoids n1, second when it avoids n2.
   KRange nz = KRange{klo, khi}, n1 = KRange{0x7fffffff, -0x7fffffff}, n2 = n1;
@@ -343,7 +301,7 @@ __device__ int stage_line(const GatherArgs& g, const CondDev& cd, const LineIn<L
       if (!(xmax <= 1.0e9f) || !(y <= 1.0e9f)) r.flag = 1;
       // a row in the one-pair region needs nothing more (lines are sorted by
       // home bin, so whole batches far from the tile stop here together)
-      if (!r.flag && !meets(elo, ehi, r.rB)) return inside ? kRowF1 : kRowF1M;
+      if (!r.flag && !meets(lo, hi, r.rB)) return inside ? kRowF1 : kRowF1M;
       r.B1 = make(GH::t4[0], GH::w4[0]);
       r.B2 = make(GH::t4[1], GH::w4[1]);
       r.rC = x_range_f(sqrtf(fmaxf(64.064f - y2, 0.0f)), a, b, kc, klo, khi);
@@ -381,11 +339,11 @@ __device__ int stage_line(const GatherArgs& g, const CondDev& cd, const LineIn<L
       const double xmax = fmax(fabs((double)(klo - kc) * a - b), fabs((double)(khi - kc) * a - b));
       if (!(xmax <= 1.0e9) || !(lp.y <= 1.0e9)) r.flag = 1;
       r.r[0] = xr(9.0e6 * 1.001);
-      if (!r.flag && !meets(elo, ehi, r.r[0])) {  // one-pair row
+      if (!r.flag && !meets(lo, hi, r.r[0])) {  // one-pair row
         r.A = make_pair<double>(lp.c0, lp.y, GH::t2[0], GH::w2[0]);
         return inside ? kRowF1 : kRowF1M;
       }
-      if (!r.flag && !meets(elo, ehi, xr(4.5e4 * 1.001))) {  // three-point row
+      if (!r.flag && !meets(lo, hi, xr(4.5e4 * 1.001))) {  // three-point row
         r.C = make_poly3(lp.c0, lp.y);
         return inside ? kRowF15 : kRowF15M;
       }
@@ -399,13 +357,13 @@ __device__ int stage_line(const GatherArgs& g, const CondDev& cd, const LineIn<L
       can2 = true;
     }
   }
-  if (!meets(elo, ehi, nz)) return kRowSkip;
+  if (!meets(lo, hi, nz)) return kRowSkip;
   if (r.flag) return kRowGeneral;
   if (gauss) return (inside && nz.lo <= lo && nz.hi >= hi) ? kRowF1 : kRowGeneral;
-  if (!meets(elo, ehi, n1)) return inside ? kRowF1 : kRowF1M;
-  if (can2 && !meets(elo, ehi, n2)) return inside ? kRowF2 : kRowF2M;
+  if (!meets(lo, hi, n1)) return inside ? kRowF1 : kRowF1M;
+  if (can2 && !meets(lo, hi, n2)) return inside ? kRowF2 : kRowF2M;
   if constexpr (sizeof(Rec) == sizeof(RecD)) {
-    if (PROF == XS_VOIGT && !meets(elo, ehi, r.r[2])) return inside ? kRowF3 : kRowF3M;
+    if (PROF == XS_VOIGT && !meets(lo, hi, r.r[2])) return inside ? kRowF3 : kRowF3M;
   }
   return kRowGeneral;
 }
@@ -438,9 +396,6 @@ __device__ int stage_line_bin(const GatherArgs& g, const CondDev& cd, const Line
   r.kc = kc;
   const int lo = (int)tlo, hi = lo + rowb - 1;
   const bool inside = klo <= lo && khi >= hi;
-  // the points of the row's 64-point chunks that meet the window: a masked
-  // row evaluates these only, so its class is theirs
-  const int elo = lo + ((klo - lo) & ~63), ehi = lo + ((khi - lo) | 63);
   const KRange none = KRange{0x7fffffff, -0x7fffffff}, all = KRange{klo, khi};
   KRange nz = all, n1 = none, n2 = none, n3 = all;
   bool can2 = false, gauss = false;
@@ -499,7 +454,7 @@ __device__ int stage_line_bin(const GatherArgs& g, const CondDev& cd, const Line
       nz = r.rB;
       gauss = true;
     } else {
-      const double xr0 = (double)(elo - kc) * a - b, xr1 = (double)(ehi - kc) * a - b;
+      const double xr0 = (double)(lo - kc) * a - b, xr1 = (double)(hi - kc) * a - b;
       if (BASE == XS_LORENTZ) {
         // series where 1 + x_a x_b >= h / 0.1, i.e. |x| >= sqrt(10 h - 1 + hh^2)
         r.rB = x_range_f(sqrtf(fmaxf(10.0f * a - 1.0f + hh * hh, 0.0f)) * 1.001f, a, b, kc, klo, khi);
@@ -512,7 +467,7 @@ __device__ int stage_line_bin(const GatherArgs& g, const CondDev& cd, const Line
         const float xmax = fmaxf(fabsf((float)(klo - kc) * a - b), fabsf((float)(khi - kc) * a - b)) + hh;
         if (!(xmax <= 1.0e9f) || !(y <= 1.0e9f)) r.flag = 1;
         nt1 = terms(row_t(xr0, xr1, hh, y, GH::s2[0]), true);
-        if (!r.flag && nt1 && !meets(elo, ehi, r.rB)) {  // a one-pair row: nothing more needed
+        if (!r.flag && nt1 && !meets(lo, hi, r.rB)) {  // a one-pair row: nothing more needed
           r.pad0 = nt1;
           return inside ? kRowF1 : kRowF1M;
         }
@@ -556,7 +511,7 @@ __device__ int stage_line_bin(const GatherArgs& g, const CondDev& cd, const Line
       nz = r.r[0];
       gauss = true;
     } else {
-      const double xr0 = (double)(elo - kc) * a - b, xr1 = (double)(ehi - kc) * a - b;
+      const double xr0 = (double)(lo - kc) * a - b, xr1 = (double)(hi - kc) * a - b;
       if (BASE == XS_LORENTZ) {
         // series where 1 + x_a x_b >= h / 0.02
         r.r[0] = x_range(sqrt(fmax(50.0 * a - 1.0 + hh * hh, 0.0)) * 1.001, a, b, kc, klo, khi);
@@ -582,17 +537,17 @@ __device__ int stage_line_bin(const GatherArgs& g, const CondDev& cd, const Line
       }
     }
   }
-  if (!meets(elo, ehi, nz)) return kRowSkip;
+  if (!meets(lo, hi, nz)) return kRowSkip;
   if (r.flag) return kRowGeneral;
   if (gauss) return (inside && nz.lo <= lo && nz.hi >= hi) ? kRowF1 : kRowGeneral;
   // the uniform classes carry their series length in pad0
   r.pad0 = nt1;
-  if (!meets(elo, ehi, n1)) return inside ? kRowF1 : kRowF1M;
+  if (!meets(lo, hi, n1)) return inside ? kRowF1 : kRowF1M;
   r.pad0 = nt2;
-  if (can2 && !meets(elo, ehi, n2)) return inside ? kRowF2 : kRowF2M;
+  if (can2 && !meets(lo, hi, n2)) return inside ? kRowF2 : kRowF2M;
   if constexpr (sizeof(Rec) == sizeof(RecD)) {
     r.pad0 = nt3;
-    if (BASE == XS_VOIGT && !meets(elo, ehi, n3)) return inside ? kRowF3 : kRowF3M;
+    if (BASE == XS_VOIGT && !meets(lo, hi, n3)) return inside ? kRowF3 : kRowF3M;
   }
   return kRowGeneral;
 }
@@ -616,9 +571,6 @@ __device__ int stage_line_pv(const GatherArgs& g, const CondDev& cd, const LineI
   r.kc = kc;
   const int lo = (int)tlo, hi = lo + rowb - 1;
   const bool inside = klo <= lo && khi >= hi;
-  // the points of the row's 64-point chunks that meet the window: a masked
-  // row evaluates these only, so its class is theirs
-  const int elo = lo + ((klo - lo) & ~63), ehi = lo + ((khi - lo) | 63);
   const double nu = in.nu;
   const double S = (double)in.S;
   if (S == 0.0) return kRowSkip;
@@ -643,7 +595,7 @@ __device__ int stage_line_pv(const GatherArgs& g, const CondDev& cd, const LineI
     r.r[0] = x_range(sqrt(1100.0), a, b, kc, klo, khi);
     gz = r.r[0];
   }
-  if (!meets(elo, ehi, gz)) return inside ? kRowF1 : kRowF1M;
+  if (!meets(lo, hi, gz)) return inside ? kRowF1 : kRowF1M;
   return kRowGeneral;
 }
 
@@ -694,7 +646,6 @@ __global__ __launch_bounds__(64, sizeof(Real) == 8 ? 3 : (PROF == XS_BIN_VOIGT ?
   using Rec = typename std::conditional<sizeof(Real) == 4, RecF, RecD>::type;
   constexpr bool F32 = sizeof(Real) == 4;
   constexpr int ROWB = 64 * M;
-  constexpr bool FARP = PROF == XS_LORENTZ || PROF == XS_VOIGT || PROF == XS_BIN_LORENTZ || PROF == XS_BIN_VOIGT;
   __shared__ Rec srec[64];
   // FP32 Voigt: the points of a core chunk with |z|^2 < 36 go to a queue and
   // are evaluated 64 at a time by the rational approximation, their values
@@ -754,10 +705,10 @@ __global__ __launch_bounds__(64, sizeof(Real) == 8 ? 3 : (PROF == XS_BIN_VOIGT ?
     const int nch = g.ib[ct + 1] - g.ib[ct];
     const int c = ct % m.n_cond, t = ct / m.n_cond;
     const CondDev cd = g.cond[c];
-    const Candidates cs = tile_candidates(g, cd, t);
-    const int64_t tlo = cs.tlo, thi = cs.thi;
-    const int64_t q0 = (int64_t)jpart * chunk;
-    const int64_t q1 = min(cs.cum[kSegs - 1], q0 + chunk);
+    int64_t tlo, thi, plo, phi;
+    tile_candidates(g, cd, t, tlo, thi, plo, phi);
+    const int64_t q0 = plo + (int64_t)jpart * chunk;
+    const int64_t q1 = min(phi, q0 + chunk);
     const int row_lo = (int)tlo;
     const int my0 = row_lo + lane;  // bin of chunk 0 of this lane
     // a masked row skips its 64-point chunks that lie wholly outside the
@@ -855,11 +806,9 @@ __global__ __launch_bounds__(64, sizeof(Real) == 8 ? 3 : (PROF == XS_BIN_VOIGT ?
       // ---- stage: exact window test and class, compaction into LDS by class ----
       Rec r;
       int cls = kRowSkip;
-      if (p0 + lane < q1) {
-        bool near = false;
-        const int64_t p = FARP ? candidate_line(cs, p0 + lane, near) : p0 + lane + cs.beg[0];
-        LineIn<Real> in = load_line<Real, PROF>(g, cd, p);
-        if (FARP && cs.far && near) clip_near(cd.far.gap, in.kc, in.win);
+      const int64_t p = p0 + lane;
+      if (p < q1) {
+        const LineIn<Real> in = load_line<Real, PROF>(g, cd, p);
         if constexpr (PROF >= XS_PV_THOMPSON) cls = stage_line_pv<Rec, PROF>(g, cd, in, tlo, thi, ROWB, r);
         else if constexpr (PROF >= XS_BIN_DOPPLER) cls = stage_line_bin<Rec, PROF>(g, cd, in, tlo, thi, ROWB, r);
         else cls = stage_line<Rec, PROF>(g, cd, in, tlo, thi, ROWB, r);
@@ -1390,34 +1339,22 @@ __global__ __launch_bounds__(64, sizeof(Real) == 8 ? 3 : (PROF == XS_BIN_VOIGT ?
               // the product stays finite for |x|, y <= 1e9 (staging sends
               // wider lines to the general path).
               const double a = rr.a, xb = rr.xb;
-              auto nd = [&](int jj, double& N, double& D) {
-                const double x = fma(lane_d[jj], a, xb);
-                if constexpr (NN == 2) {
-                  const double sv = fma(x, x, rr.A.h);
-                  N = fma(rr.A.cw, sv, rr.A.cwt);
-                  D = fma(sv, sv, rr.A.c);
-                } else if constexpr (NN == 3) {
-                  poly3_nd(rr.C, x, N, D);
-                } else {
-                  poly2_nd(rr.B, x, N, D);
-                }
-              };
-              // masked rows: only the chunks that meet the window (its class
-              // holds on these), a reciprocal for each
-#pragma unroll
-              for (int j = 0; j < M && masked; ++j) {
-                if (off_chunk(masked, j, klo, khi)) continue;
-                double N, D;
-                nd(j, N, D);
-                const int k = my0 + 64 * j;
-                if (k >= klo && k <= khi) acc64[j] = fma(N, rcp64(D), acc64[j]);
-              }
-              if (masked) continue;
 #pragma unroll
               for (int j = 0; j < M; j += 4) {
                 double N[4], D[4];
 #pragma unroll
-                for (int h = 0; h < 4; ++h) nd(j + h, N[h], D[h]);
+                for (int h = 0; h < 4; ++h) {
+                  const double x = fma(lane_d[j + h], a, xb);
+                  if constexpr (NN == 2) {
+                    const double sv = fma(x, x, rr.A.h);
+                    N[h] = fma(rr.A.cw, sv, rr.A.cwt);
+                    D[h] = fma(sv, sv, rr.A.c);
+                  } else if constexpr (NN == 3) {
+                    poly3_nd(rr.C, x, N[h], D[h]);
+                  } else {
+                    poly2_nd(rr.B, x, N[h], D[h]);
+                  }
+                }
                 const double p01 = D[0] * D[1], p23 = D[2] * D[3];
                 const double r = rcp64(p01 * p23);
                 const double r01 = p23 * r, r23 = p01 * r;
@@ -1429,8 +1366,6 @@ __global__ __launch_bounds__(64, sizeof(Real) == 8 ? 3 : (PROF == XS_BIN_VOIGT ?
             } else {
 #pragma unroll
               for (int j = 0; j < M; ++j) {
-                t[j] = 0.0;
-                if (off_chunk(masked, j, klo, khi)) continue;
                 const double u = xs[j] * xs[j];
                 if (PROF == XS_LORENTZ) t[j] = rr.c0 * rcp64(fma(xs[j], xs[j], 1.0));
                 else if (PROF == XS_DOPPLER || PROF == XS_GAUSSIAN) t[j] = rr.c0 * exp2(-u);
@@ -1566,9 +1501,10 @@ __global__ __launch_bounds__(256) void k_items_count(GatherArgs g, int32_t* cnt)
   unsigned long long local = 0;
   for (int64_t ct = (int64_t)blockIdx.x * 256 + threadIdx.x; ct < g.n_ct; ct += (int64_t)gridDim.x * 256) {
     const int c = (int)(ct % g.m.n_cond), t = (int)(ct / g.m.n_cond);
-    const int64_t n = tile_candidates(g, g.cond[c], t).cum[kSegs - 1];
-    cnt[ct] = (int32_t)n;
-    local += (unsigned long long)n;
+    int64_t tlo, thi, plo, phi;
+    tile_candidates(g, g.cond[c], t, tlo, thi, plo, phi);
+    cnt[ct] = (int32_t)(phi - plo);
+    local += (unsigned long long)(phi - plo);
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) local += __shfl_xor(local, o, 64);
@@ -1629,7 +1565,7 @@ static void gather_dispatch(const GatherArgs& a, int M, int blocks, hipStream_t 
 }
 
 void launch_gather(const ModelDev& m, const Work& w, const Tiling& t, double* sigma,
-                   int accumulate, bool far, hipStream_t s) {
+                   int accumulate, hipStream_t s) {
   GatherArgs a;
   a.m = m;
   a.cond = w.cond;
@@ -1656,7 +1592,6 @@ void launch_gather(const ModelDev& m, const Work& w, const Tiling& t, double* si
   a.persistent = t.persistent;
   a.chunk_cfg = t.chunk_lines;
   a.item_target = w.item_target;
-  a.far = far;
   // plan the work items
   launch_reset_queue(w, s);
   const int cb = (int)std::min<int64_t>(1024, (a.n_ct + 255) / 256);

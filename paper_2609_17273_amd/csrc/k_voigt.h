@@ -152,4 +152,62 @@ __device__ __forceinline__ double poly2_term(const Poly2& B, double x) {
   return N * rcp64(D);
 }
 
+// NP node pairs of Re w without the factor 2 y / pi, as one fraction N/D
+// (FP64: D is a product of NP terms below ~1e37 for |x|, y <= 1e9).
+template <int NP>
+__device__ __forceinline__ void gh_nd(double u, double y2, double y4, double& N, double& D) {
+  const double* tau = gh_tau<NP>();
+  const double* W = gh_w<NP>();
+#pragma unroll
+  for (int j = 0; j + 1 < NP; j += 2) {
+    const double s1 = u + (y2 - tau[j]), s2 = u + (y2 - tau[j + 1]);
+    const double d1 = fma(s1, s1, y4 * tau[j]), d2 = fma(s2, s2, y4 * tau[j + 1]);
+    const double n1 = fma(W[j], s1, 2.0 * tau[j] * W[j]), n2 = fma(W[j + 1], s2, 2.0 * tau[j + 1] * W[j + 1]);
+    const double n = fma(n1, d2, n2 * d1), d = d1 * d2;
+    N = j ? fma(N, d, n * D) : n;
+    D = j ? D * d : d;
+  }
+  if constexpr (NP & 1) {
+    constexpr int j = NP - 1;
+    const double s1 = u + (y2 - tau[j]);
+    const double d = fma(s1, s1, y4 * tau[j]), n = fma(W[j], s1, 2.0 * tau[j] * W[j]);
+    N = j ? fma(N, d, n * D) : n;
+    D = j ? D * d : d;
+  }
+}
+// the same, FP32, a reciprocal per pair
+template <int NP>
+__device__ __forceinline__ float gh_f32(float u, float y2, float y4) {
+  const double* tau = gh_tau<NP>();
+  const double* W = gh_w<NP>();
+  float t = 0.0f;
+#pragma unroll
+  for (int j = 0; j < NP; ++j) {
+    const float s = u + (y2 - (float)tau[j]);
+    t = fmaf(fmaf((float)W[j], s, (float)(2.0 * tau[j] * W[j])), rcp32(fmaf(s, s, y4 * (float)tau[j])), t);
+  }
+  return t;
+}
+
+// Bin mean of NP node pairs (in the convention of vpairs_bin) with two terms
+// of the arctangents' series: a pair +-s takes one reciprocal, den-+ =
+// P -+ 2 s x with P = x^2 + (y^2 + s^2 - hh^2), D = den- den+ = P^2 - 4 s^2 x^2,
+// t+ + t- = 2 y h P / D, t+ t- = (y h)^2 / D and
+// atan(t+) + atan(t-) = (t+ + t-)(1 - (t+ + t-)^2/3 + t+ t-) + O(t^5):
+// relative error below 1e-16 for t <= 2.5e-4, 3e-8 for t <= 0.02.
+template <int NP, typename R>
+__device__ __forceinline__ R vpairs_bin_two(R x, R hh, R yh, R y2) {
+  const double* tau = gh_tau<NP>();
+  const R u = x * x;
+  R t = (R)0;
+#pragma unroll
+  for (int j = 0; j < NP; ++j) {
+    const R P = u + (y2 + ((R)tau[j] - hh * hh));
+    const R iD = rcp_r<R>(fma(P, P, u * (R)(-4.0 * tau[j])));
+    const R A = yh * iD, e1 = (R)2 * P * A;
+    t = fma((R)(gh_w<NP>()[j] / kPI), P * iD * fma(e1 * e1, (R)(-1.0 / 3.0), (R)1 + yh * A), t);
+  }
+  return ((R)2 * yh) * t;
+}
+
 }  // namespace xs

@@ -73,6 +73,7 @@ struct xs_plan {
   bool prepared = false;     // records of an xs_prepare are in the workspace
   std::vector<double> cf_T;  // temperatures of the last cooling-function call (upload source)
   int far_lmax = -1;         // highest level of the conditions' tile expansions (-1: none)
+  bool no_far = false;       // in the allocation-free call
   int far_end = 0;           // lowest of their levels of cut tiles
   bool has_tau = false;      // the last xs_prepare had state lifetimes (records hold their widths)
 };
@@ -211,29 +212,32 @@ void tiling_for(xs_plan* p, int tile_bins, int persistent, int waves_per_cu, int
 // Does the profile pass take this plan's far tiles through expansions?
 bool far_capable(const xs_plan* p) {
   const int pr = p->model.profile;
-  return p->model.algo == XS_GATHER &&
+  return !p->no_far && p->model.algo == XS_GATHER &&
          (pr == XS_LORENTZ || pr == XS_VOIGT || pr == XS_BIN_LORENTZ || pr == XS_BIN_VOIGT);
 }
+
+// Points of a sort key as a power of two: the leaves of the tile expansions
+// where the plan can use them.
+int leaf_sh(const xs_plan* p) { return far_capable(p) ? (p->model.precision == XS_FP32 ? kLeafSh32 : kLeafSh64) : kFineSh; }
 
 // Tile expansions of one condition.  A window surely reaches floor(cut / dnu)
 // points less two to each side of the home bin (the line lies within half a
 // step of it; the rest for rounding) and at most two more than that quotient.
-// The Voigt is smooth beyond |x| = 8.08 of the grid's widest line, where the
-// Gauss-Hermite rules hold (a bin and a half is taken off the gap, for the
-// line's place in its bin and a bin mean's edge); a Lorentzian is smooth at
-// any width.
+// The Voigt of a line at nu is smooth beyond |x| = 8.08, where the
+// Gauss-Hermite rules hold (with a bin and a half more, for the line's place
+// in its bin and a bin mean's edge); a Lorentzian is smooth at any width.
 FarCond far_condition(const xs_plan* p, const CondDev& cd) {
   const ModelDev& d = p->md;
   const double r = cd.cut / d.dnu;
   if (!far_capable(p) || !(r < double(1 << 28))) return FarCond{};
-  double gap = 1.0;
+  double g0 = 0.0, g1 = 0.0;
   if (base_profile(p->model.profile) != XS_LORENTZ) {
-    const double nu_end = d.nu0 + (double)(d.n_bins - 1) * d.dnu;
-    gap = std::ceil((8.08 * nu_end * cd.dop / (std::sqrt(kLN2) * d.dnu) + 1.5) / kLeafBins);
-    if (!(gap < double(1 << 20))) return FarCond{};
+    g1 = 8.08 * cd.dop / std::sqrt(kLN2);
+    g0 = (g1 * d.nu0 / d.dnu + 1.5) / (double)(1 << d.fine_sh);
+    if (!(std::fabs(g0) < double(1 << 28)) || !(g1 < 1.0)) return FarCond{};
   }
   const int64_t W = (int64_t)std::floor(r);
-  return far_make(W - 2, W + 2, d.n_fine, std::max<int64_t>(1, (int64_t)gap));
+  return far_make(W - 2, W + 2, d.n_fine, d.fine_sh, g0, g1);
 }
 
 void derive(xs_plan* p) {
@@ -253,8 +257,12 @@ void derive(xs_plan* p) {
   d.n_cond = (int32_t)p->conds.size();
   d.bucket_bins = p->bucket_bins;
   d.n_buckets = (int32_t)((p->grid.n_bins + p->bucket_bins - 1) / p->bucket_bins);
-  d.n_fine = (int32_t)((p->grid.n_bins + kFineBins - 1) / kFineBins);
-  d.fine_per_bucket = p->bucket_bins / kFineBins;
+  auto cells = [&](int sh) {
+    d.fine_sh = sh;
+    d.n_fine = (int32_t)((p->grid.n_bins + ((int64_t)1 << sh) - 1) >> sh);
+    d.fine_per_bucket = p->bucket_bins >> sh;
+  };
+  cells(leaf_sh(p));
   // intensity slots: distinct population temperatures
   p->sdev.clear();
   p->cdev.clear();
@@ -330,6 +338,7 @@ void derive(xs_plan* p) {
     }
     p->cdev.push_back(cd);
   }
+  if (p->far_lmax < 0) cells(kFineSh);  // no condition uses expansions
   d.n_slots = (int32_t)p->sdev.size();
   d.n_cut_classes = (int32_t)p->cut_class.size();
   d.max_cut = maxcut;
@@ -370,9 +379,11 @@ size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool wit
   x.valB = (int32_t*)take(4 * L);
   x.hist = (int32_t*)take(4 * (size_t)256 * nsb);
   x.hsum = (int32_t*)take(4 * ((size_t)256 * nsb / 1024 + 2));
-  // sized for the finest bucket (64 points), so a change of bucket size never
-  // needs a larger workspace
-  x.off = (int32_t*)take(4 * (size_t)((p->grid.n_bins + 63) / 64 + 2));
+  // cell offsets: the smallest cells the plan may use, so neither a change of
+  // bucket size nor one of conditions needs a larger workspace
+  const int sh = with_far ? leaf_sh(p) : kFineSh;
+  const int64_t cells = (p->grid.n_bins + ((int64_t)1 << sh) - 1) >> sh;
+  x.off = (int32_t*)take(4 * (size_t)(cells + 2));
   x.rnu = (double*)take(8 * L);
   x.rgref = (float*)take(4 * L);
   x.rnexp = (float*)take(4 * L);
@@ -398,7 +409,7 @@ size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool wit
   x.far_rows = nullptr;
   x.far_cond_rows = 0;
   if (with_far && far_capable(p)) {
-    x.far_cond_rows = far_rows_before(d.n_fine, far_levels_of_grid(d.n_fine));
+    x.far_cond_rows = far_rows_before((int32_t)cells, sh, far_levels_of_grid((int32_t)cells));
     x.far_rows = (double*)take(sizeof(double) * d.n_cond * (size_t)x.far_cond_rows * far_nodes(d.prec));
   }
   x.stats = (unsigned long long*)take(8 * 8);
@@ -460,21 +471,23 @@ int preprocess(xs_plan* p, const xs_states* st, const xs_lines* ln) {
   return hip_check(hipGetLastError(), "preprocess launch");
 }
 
-// Expansions pay off once the cells hold a few lines each: a tile visit
+// Expansions pay off once 64 grid points hold a few lines: a tile visit
 // costs a wave the same for one line as for 64.
 constexpr int kFarLinesPerCell = 8;
 bool use_far(const xs_plan* p) {
   return p->w.far_cond_rows > 0 && p->far_lmax >= 0 &&
-         p->last_lines_in >= (int64_t)kFarLinesPerCell * p->md.n_fine;
+         2 * p->w.item_target * 1024 >= (int64_t)near_row_doubles() &&
+         p->last_lines_in >= (int64_t)kFarLinesPerCell * ((p->grid.n_bins + 63) / 64);
 }
 
 int profile_pass(xs_plan* p, double* sigma, int accumulate) {
   if (p->model.algo == XS_SCATTER)
     launch_scatter(p->md, kernel_work(p), sigma, accumulate, 0, p->stream);
-  else {
-    const bool far = use_far(p);
-    launch_gather(p->md, kernel_work(p), p->tiling, sigma, accumulate, far, p->stream);
-    if (far) launch_far(p->md, kernel_work(p), p->far_lmax, p->far_end, sigma, p->stream);
+  else if (!use_far(p)) {
+    launch_gather(p->md, kernel_work(p), p->tiling, sigma, accumulate, p->stream);
+  } else {
+    launch_near(p->md, kernel_work(p), sigma, accumulate, p->stream);
+    launch_far(p->md, kernel_work(p), p->far_lmax, p->far_end, sigma, p->stream);
   }
   return hip_check(hipGetLastError(), "profile launch");
 }
@@ -857,12 +870,17 @@ int xs_cross_section_noalloc(xs_plan* p, const xs_states* st, const xs_lines* ln
   const size_t keep_bytes = p->ws_bytes;
   const bool keep_prepared = p->prepared, keep_tau = p->has_tau;
   const int64_t keep_last = p->last_lines_in;
+  // (its sort keys are the plain ones: without expansions no finer leaves)
+  p->no_far = true;
+  derive(p);
   layout(p, (char*)base, &p->w, items, false, false);
   p->ws = base;
   p->ws_bytes = kScratchBytes;
   rc = upload(p);
   if (!rc) rc = preprocess(p, st, ln);
   if (!rc) rc = profile_pass(p, sigma, accumulate);
+  p->no_far = false;
+  derive(p);
   p->w = keep_w;
   p->ws = keep_ws;
   p->ws_bytes = keep_bytes;

@@ -30,12 +30,21 @@ constexpr int kAdjBlocks = 16384;    // blocks of the adjoint's grid in a new pl
 constexpr int kAdjBlocksMax = 32768;  // the most the configuration allows (sizes the partial sums)
 constexpr int kSortItems = 16;    // keys per thread in the radix sort (4096 per block)
 // Device counters (int32): [0] gather work queue, [2..3] candidate total,
-// [4..5] lines per item, [8] cooling-function runs, [kFarOff] set by the
+// [4..5] lines per item or part, [6] parts beyond
+// tiles' first, [8] cooling-function runs, [kFarOff] set by the
 // record pass where a line's values are not finite.
 constexpr int kCounterInts = 64;
 constexpr int kFarOff = 9;
 constexpr int kSortBlock = 256 * kSortItems;
-constexpr int kFineBins = 64;  // grid points per sort key (the smallest bucket size)
+// Lines are sorted by home bin >> sh: 64 points per key (the smallest bucket
+// size), or the leaves of the tile expansions.
+constexpr int kFineSh = 6;
+// Leaves of 16 points (FP32 form) and 64 (FP64): smaller leaves leave fewer
+// points to the near kernel and give the tiles a level more.  Measured near +
+// tile kernels with 16 / 32 / 64 points: 1e7 lines FP32 3.45 / 3.90 / 4.02 ms,
+// 48 conditions x 1e6 lines FP32 11.1 / 11.2 / 12.4; 1e6 lines FP64 2.28 /
+// 1.79 / 1.61, 3.9e5 FP64 bin means 2.17 / 1.89 / 2.07 (20 nodes to a tile).
+constexpr int kLeafSh32 = 4, kLeafSh64 = 6;
 
 // Per-condition scalars, uploaded with the workspace.
 struct CondDev {
@@ -65,10 +74,10 @@ struct ModelDev {
   double T_ref, P_ref, hwhm_fixed, mass_amu;
   int32_t n_cond, n_slots;
   int32_t bucket_bins, n_buckets;  // lines bucketed by k_c / bucket_bins
-  // Lines are sorted by the finer key k_c / kFineBins (key n_fine = dropped),
+  // Lines are sorted by the finer key k_c >> fine_sh (key n_fine = dropped),
   // whatever the bucket size, so that neighbouring sorted lines have nearly
   // equal home bins; a bucket is fine_per_bucket consecutive fine keys.
-  int32_t n_fine, fine_per_bucket;
+  int32_t n_fine, fine_per_bucket, fine_sh;
   int32_t n_cut_classes;           // distinct cut-offs (window statistics)
   double max_cut;
 };
@@ -123,7 +132,7 @@ struct Work {
   int32_t* valB;
   int32_t* hist;            // [256 * n_sort_blocks] (+ scan block sums)
   int32_t* hsum;            // scan block sums
-  int32_t* off;             // [n_fine + 1] offsets of the cells (64 grid points) into the sorted records
+  int32_t* off;             // [n_fine + 1] offsets of the cells (2^fine_sh grid points) into the sorted records
   double* rnu;              // sorted records: nu
   float* rgref;             //                 gamma_ref
   float* rnexp;             //                 n_exp
@@ -182,11 +191,16 @@ void launch_reset_queue(const Work& w, hipStream_t s);
 void launch_scan_i32(int32_t* a, int64_t n, int32_t* sums, hipStream_t s);  // exclusive, in place
 
 // ---- profile pass (k_profile.hip) ----
-// far: leave out the leaves that launch_far's tiles take
 void launch_gather(const ModelDev& m, const Work& w, const Tiling& t, double* sigma,
-                   int accumulate, bool far, hipStream_t s);
+                   int accumulate, hipStream_t s);
 void launch_scatter(const ModelDev& m, const Work& w, double* sigma, int accumulate,
                     int64_t n_lines, hipStream_t s);
+
+// ---- near leaves (k_near.hip) ----
+size_t near_row_doubles();  // what it takes of Work::part
+// sigma = (or +=) the points near each line, for the conditions with tile
+// expansions, and every point of the others
+void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate, hipStream_t s);
 
 // ---- tile expansions (k_far.hip) ----
 int far_nodes(int prec);  // nodes per tile

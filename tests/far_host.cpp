@@ -4,11 +4,18 @@ using namespace xs;
 extern "C" {
 // how often cell f's lines reach each leaf of [0, n_fine): whole, through a
 // tile (far[leaf]); through a tile that the window may cut (cut[leaf]); point
-// by point through the segments of the rows of row_leaves leaves (direct[leaf])
-int far_count(int64_t W, int64_t Wx, int32_t n_fine, int64_t gap, int32_t row_leaves, int32_t f, int32_t reach,
-              int32_t* far, int32_t* cut, int32_t* direct) {
-  const FarCond c = far_make(W, Wx, n_fine, gap);
-  for (int i = 0; i < n_fine; ++i) far[i] = cut[i] = direct[i] = 0;
+// by point through the segments of the rows of row_leaves leaves
+// (direct[leaf]).  gap[leaf]: cells that are near the leaf; info: on, points of
+// a cut tile.
+int far_count(int64_t W, int64_t Wx, int32_t n_fine, int32_t sh, double g0, double g1, int32_t row_leaves, int32_t f,
+              int32_t reach, int32_t* far, int32_t* cut, int32_t* direct, int32_t* gap, int32_t* info) {
+  const FarCond c = far_make(W, Wx, n_fine, sh, g0, g1);
+  for (int i = 0; i < n_fine; ++i) {
+    far[i] = cut[i] = direct[i] = 0;
+    gap[i] = c.on ? far_gap(c, 0, i) : 0;
+  }
+  info[0] = c.on;
+  info[1] = c.on ? 1 << (c.sh + c.end) : 0;
   if (c.on)
     for (int l = 0; l <= c.lmax; ++l)
       for (int t = 0; t < far_tiles(n_fine, l); ++t) {
@@ -30,11 +37,12 @@ int far_count(int64_t W, int64_t Wx, int32_t n_fine, int64_t gap, int32_t row_le
     if (chi > n_fine - 1) chi = n_fine - 1;
     CellRange s[kSegs] = {{clo, chi}, {0, -1}, {0, -1}};
     if (c.on) far_segments(c, a, b, clo, chi, s);
+    const int g = c.on ? far_gap(c, 0, a) : 0;
     for (int k = 0; k < kSegs; ++k) {
       if (f < s[k].lo || f > s[k].hi) continue;
       const bool near = c.on && k == 0;
       for (int leaf = a; leaf <= b && leaf < n_fine; ++leaf)
-        if (!near || (leaf >= f - c.gap && leaf <= f + c.gap)) direct[leaf]++;
+        if (!near || (leaf >= f - g && leaf <= f + g)) direct[leaf]++;
     }
   }
   return c.on;
