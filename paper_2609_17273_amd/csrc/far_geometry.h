@@ -59,6 +59,8 @@ XS_HD int32_t far_min(int32_t a, int32_t b) { return a < b ? a : b; }
 XS_HD int32_t far_max(int32_t a, int32_t b) { return a > b ? a : b; }
 XS_HD int32_t far_shl(int32_t a, int l) { return a * (1 << l); }  // a may be negative
 
+XS_HD int32_t far_tiles(int32_t n_fine, int l) { return (n_fine + (1 << l) - 1) >> l; }
+
 XS_HD int32_t far_gap(const FarCond& c, int l, int32_t t) {
   const int64_t e = (int64_t)((t >> (c.glev - l)) + 1) << c.glev;
   const int64_t g = (c.gap0 + e * c.gap1) >> 32;
@@ -76,6 +78,16 @@ XS_HD CellRange far_right(const FarCond& c, int32_t gap, int l, int32_t t) {
   const int32_t lo = far_shl(t + far_apart(gap, l), l);
   const int32_t hi = l > c.end ? (t << l) + c.cR : (((t >> (c.end - l)) + 1) << c.end) + c.xR;
   return CellRange{lo, far_min(c.n_fine - 2, hi)};
+}
+
+// The leaves near cell f, n0..n1 (gap grows by at most one from a tile of level
+// glev to the next, so they are one range).
+XS_HD void far_near(const FarCond& c, int32_t f, int32_t& n0, int32_t& n1) {
+  const int32_t gap = far_gap(c, 0, f);
+  n0 = f - gap;
+  n1 = f + gap;
+  while (n0 < f && n0 >= 0 && f - n0 > far_gap(c, 0, n0)) ++n0;
+  while (n1 + 1 - f <= far_gap(c, 0, n1 + 1)) ++n1;
 }
 
 // a minus b as up to two ranges
@@ -111,6 +123,27 @@ XS_HD void far_tile_ranges(const FarCond& c, int l, int32_t t, CellRange r[4]) {
   far_subtract(b, top ? none : far_right(c, gap, l + 1, t >> 1), r[2], r[3]);
 }
 
+// Tiles of level l that may take lines of the cells [f0, f1] whole (a
+// superset: far_tile_ranges decides), and those of level `end` that their
+// windows may cut on the right ([0]) and on the left ([1]).
+XS_HD CellRange far_candidates(const FarCond& c, int l, int32_t f0, int32_t f1) {
+  int32_t lo, hi;
+  if (l < c.end) {  // beside the parents that are not apart
+    const int32_t k = 2 * far_apart(c.gap_max, l + 1) + 1;
+    lo = (f0 >> l) - k;
+    hi = (f1 >> l) + k;
+  } else {
+    lo = (f0 - c.cR) >> l;
+    hi = (f1 + c.cL) >> l;
+  }
+  return CellRange{far_max(lo, 0), far_min(hi, far_tiles(c.n_fine, l) - 1)};
+}
+XS_HD void far_cut_candidates(const FarCond& c, int32_t f0, int32_t f1, CellRange r[2]) {
+  const int32_t last = far_tiles(c.n_fine, c.end) - 1;
+  r[0] = CellRange{far_max((f0 + c.cL) >> c.end, 0), far_min((f1 + c.xL) >> c.end, last)};
+  r[1] = CellRange{far_max(((f0 - c.xR) >> c.end) - 1, 0), far_min((f1 - c.cR - 1) >> c.end, last)};
+}
+
 // Candidate cells of the leaves [a, b] (inside one tile of 256 points) for
 // the point-by-point part, among the cells [clo, chi] whose windows can reach
 // them: the cells near them, and the edge cells.  Of the lines of segment 0,
@@ -128,7 +161,6 @@ XS_HD void far_segments(const FarCond& c, int32_t a, int32_t b, int32_t clo, int
 // tile's lines are cut into slices, a block and a row of coefficients each, so
 // that no wave takes more than eight times another's share.
 XS_HD int far_wide(int sh, int l) { return far_max(0, l + sh - 6); }  // log2 of points / 64, at least 0
-XS_HD int32_t far_tiles(int32_t n_fine, int l) { return (n_fine + (1 << l) - 1) >> l; }
 XS_HD int32_t far_slices(int sh, int l) { return far_wide(sh, l) > 3 ? 1 << (far_wide(sh, l) - 3) : 1; }
 XS_HD int64_t far_rows_before(int32_t n_fine, int sh, int l) {
   int64_t r = 0;
@@ -161,6 +193,8 @@ inline FarCond far_make(int64_t W, int64_t Wx, int32_t n_fine, int sh, double g0
   const double reach = (double)Wx / (double)leaf + 1.0;
   const double most = g0 + g1 * ((double)n_fine + reach);
   if (W < leaf || levels < 1 || !(most >= 0.0) || !(most + 1.0 <= (double)W / (double)leaf)) return c;
+  // gap grows by at most one from a tile of level glev to the next
+  if (!(g1 * (double)(256 >> sh) < 1.0)) return c;
   c.n_fine = n_fine;
   c.sh = sh;
   c.gap_max = (int32_t)most + 1;
@@ -176,7 +210,8 @@ inline FarCond far_make(int64_t W, int64_t Wx, int32_t n_fine, int sh, double g0
   if (e < 0) return c;
   c.end = e;
   c.lmax = e;
-  while (c.lmax + 1 < levels && (far_apart(c.gap_max, c.lmax + 1) << (c.lmax + 1)) <= c.cR) ++c.lmax;
+  while (c.lmax + 1 < levels && g1 * (double)(2 << c.lmax) < 1.0 && (far_apart(c.gap_max, c.lmax + 1) << (c.lmax + 1)) <= c.cR)
+    ++c.lmax;
   c.glev = far_max(c.lmax, 8 - sh);
   c.on = 1;
   return c;

@@ -13,6 +13,10 @@
 // FP32 partial sums are flushed to FP64.  Blocks own fixed line sets and the
 // per-condition scalars are reduced in a fixed order, so results are
 // deterministic.
+#include <algorithm>
+#include <type_traits>
+
+#include "far_tables.h"
 #include "k_common.h"
 
 namespace xs {
@@ -124,8 +128,21 @@ struct AdjArgs {
   double* dgref;
   double* dnexp;
   double* dls;
-  double* part;   // [n_cond][2][gridDim.x]
+  double* part;   // [n_cond][2][n_part], this kernel's blocks from part0 on
+  int32_t n_part, part0;
+  double* fline;  // [3][max_lines] the far part's line gradients, sorted order
+  int32_t far;    // take the windows' far tiles through their moments
+  const int32_t* counter;
+  const int32_t* rkc;
+  const void* mom;    // [n_cond][far_cond_rows][P] moments of every tile
+  int64_t cond_rows;
+  const void* cut;    // [n_cond][cut_rows][2][PE] moments of the parts of cut tiles
+  int64_t cut_rows;   // groups of kCutGroup points
 };
+
+// Points of a group of a cut tile: its groups before (after) a window's last
+// (first) one enter through moments, that group point by point.
+constexpr int kCutGroup = kCutRowBins;
 
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
@@ -290,6 +307,7 @@ struct GSrc {
   double gs;         // power-of-two scale applied to g (FP32 form: max |g gs| in [1/2, 1))
   int64_t nb;        // grid points
   int kcmin;         // smallest home bin of the wave's active lanes
+  int span;          // largest home bin less kcmin
   bool lds;
   R* buf;            // [2 kFlush] LDS slice of the wave
 };
@@ -325,195 +343,157 @@ struct GSrc {
 // the sum's own terms do.  A point costs u, d, 1/d and four sums (12 VALU
 // instructions against 16.5 for the per-point form).
 template <typename R, int PROF, int NP, bool SY = false, bool C0 = false, bool UF = false>
-__device__ __forceinline__ void fast_range(const AdjLine<R>& L, const GSrc<R>& G, int r0, int r1,
-                                           double& sA, double& sB, double& sC) {
+struct FastSums {
   static_assert(!C0 || (SY && NP == 2 && sizeof(R) == 8), "the node at 0 has its own form in FP64 block sums");
   static_assert(!UF || (!SY && NP == 1), "the u-form is the one-pair level's");
-  // the lanes running this loop (the wave's active lines) share the refills
-  const unsigned long long act = __ballot(1);
-  const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(act >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)act, 0u));
-  const int nact = __popcll(act);
-  // x at r = rb + j4 + jj as fma(rb + j4, a, nb + jj a): one conversion per
-  // four points (nb + jj a rounds once, relative 6e-8 of at most 3.5 a, so x
-  // keeps a relative error below 5e-7 for every r != 0)
-  R nbj[4];
-#pragma unroll
-  for (int jj = 0; jj < 4; ++jj) nbj[jj] = fma((R)jj, L.a, L.nb);
-  // SY: per pair h = q/2 (exact) and c = 4 y^2 tau = -k2 y^2
-  R hS[NP], cS[NP];
-#pragma unroll
-  for (int q = 0; q < NP; ++q) {
-    hS[q] = (R)0.5 * L.P[q].q;
-    cS[q] = (R)(-(double)L.P[q].k2 * L.y * L.y);
-  }
-  for (int rb = r0; rb <= r1; rb += kFlush) {
-    const int n = min(kFlush, r1 - rb + 1);
-    R s1 = 0, s2 = 0, s3 = 0, s4 = 0;
-    R B[SY ? NP : 1][4];  // SY: S0..S3 per pair
+  R hS[NP], cS[NP];  // SY: per pair h = q/2 (exact) and c = 4 y^2 tau = -k2 y^2
+  R s1, s2, s3, s4;
+  R B[SY ? NP : 1][4];  // SY: S0..S3 per pair
+
+  __device__ __forceinline__ void clear() {
+    s1 = s2 = s3 = s4 = 0;
 #pragma unroll
     for (int q = 0; q < (SY ? NP : 1); ++q) B[q][0] = B[q][1] = B[q][2] = B[q][3] = 0;
-    auto body = [&](R x, R gk) {
-      const R u = x * x;
-      if (PROF == XS_DOPPLER || PROF == XS_GAUSSIAN) {
-        R e;
-        if constexpr (sizeof(R) == 4) e = __builtin_amdgcn_exp2f(-u);
-        else e = exp2(-u);
-        const R ge = gk * e;
-        s1 += ge;
-        s2 = fma(ge, u, s2);
-      } else if (PROF == XS_LORENTZ) {
-        const R iq = arcp(u + (R)1);
-        const R gi = gk * iq;
-        s1 += gi;
-        s2 = fma(gi, iq, s2);
-      } else if constexpr (SY) {
-        R sx[NP], rd[NP];
+  }
+  __device__ __forceinline__ void begin(const AdjLine<R>& L) {
 #pragma unroll
-        for (int q = 0; q < NP; ++q) sx[q] = fma(x, x, hS[q]);
-        if constexpr (sizeof(R) == 8 && NP >= 2) {
-          // FP64: one reciprocal (and Newton step) for the first two pairs,
-          // 1/d0 = d1/(d0 d1) and 1/d1 = d0/(d0 d1); d0 d1 stays finite
-          // (C0: rd[1] = 1/v, v = sx[1])
-          const R d0 = fma(sx[0], sx[0], cS[0]), d1 = C0 ? sx[1] : fma(sx[1], sx[1], cS[1]);
-          const R r = arcp(d0 * d1);
-          rd[0] = d1 * r;
-          rd[1] = d0 * r;
-          if constexpr (NP == 3) rd[2] = arcp(fma(sx[2], sx[2], cS[2]));
+    for (int q = 0; q < NP; ++q) {
+      hS[q] = (R)0.5 * L.P[q].q;
+      cS[q] = (R)(-(double)L.P[q].k2 * L.y * L.y);
+    }
+    clear();
+  }
+  // one point at x with cotangent gk
+  __device__ __forceinline__ void add(const AdjLine<R>& L, R x, R gk) {
+    const R u = x * x;
+    if (PROF == XS_DOPPLER || PROF == XS_GAUSSIAN) {
+      R e;
+      if constexpr (sizeof(R) == 4) e = __builtin_amdgcn_exp2f(-u);
+      else e = exp2(-u);
+      const R ge = gk * e;
+      s1 += ge;
+      s2 = fma(ge, u, s2);
+    } else if (PROF == XS_LORENTZ) {
+      const R iq = arcp(u + (R)1);
+      const R gi = gk * iq;
+      s1 += gi;
+      s2 = fma(gi, iq, s2);
+    } else if constexpr (SY) {
+      R sx[NP], rd[NP];
+#pragma unroll
+      for (int q = 0; q < NP; ++q) sx[q] = fma(x, x, hS[q]);
+      if constexpr (sizeof(R) == 8 && NP >= 2) {
+        // FP64: one reciprocal (and Newton step) for the first two pairs,
+        // 1/d0 = d1/(d0 d1) and 1/d1 = d0/(d0 d1); d0 d1 stays finite
+        // (C0: rd[1] = 1/v, v = sx[1])
+        const R d0 = fma(sx[0], sx[0], cS[0]), d1 = C0 ? sx[1] : fma(sx[1], sx[1], cS[1]);
+        const R r = arcp(d0 * d1);
+        rd[0] = d1 * r;
+        rd[1] = d0 * r;
+        if constexpr (NP == 3) rd[2] = arcp(fma(sx[2], sx[2], cS[2]));
+      } else {
+#pragma unroll
+        for (int q = 0; q < NP; ++q) rd[q] = arcp(fma(sx[q], sx[q], cS[q]));
+      }
+#pragma unroll
+      for (int q = 0; q < (C0 ? 1 : NP); ++q) {
+        const R grd = gk * rd[q], v = grd * rd[q];
+        B[q][0] += grd;
+        B[q][1] = fma(grd, sx[q], B[q][1]);
+        B[q][2] += v;
+        B[q][3] = fma(v, sx[q], B[q][3]);
+      }
+      if constexpr (C0) {
+        const R gv = gk * rd[1];
+        B[1][0] = fma(gv, rd[1], B[1][0]);
+        B[1][1] += gv;
+      }
+    } else if constexpr (UF) {
+      // s1 = S0, s2 = U1, s3 = U2, s4 = U3
+      const PairD<R>& P = L.P[0];
+      const R rd = arcp(fma(u, u + P.q, P.p2));
+      const R gr = gk * rd;
+      s1 += gr;
+      s2 = fma(gr, u, s2);
+      const R v = (gr * rd) * u;
+      s3 += v;
+      s4 = fma(v, u, s4);
+    } else if constexpr (NP == 1) {
+      // s1 = sum g e, s2 = sum g t, s3 = sum g / d, s4 = sum g e^2
+      R e, rd, t;
+      pair_adj<R>(L.P[0], u, e, rd, t);
+      const R ge = gk * e;
+      s1 += ge;
+      s2 = fma(gk, t, s2);
+      s3 = fma(gk, rd, s3);
+      s4 = fma(ge, e, s4);
+    } else {
+      R E = 0, RD = 0, E2 = 0, T = 0;
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        R e, rd, t;
+        pair_adj<R>(L.P[q], u, e, rd, t);
+        const R Ke = L.P[q].K * e;
+        E += Ke;
+        RD = fma(L.P[q].K, rd, RD);
+        E2 = fma(Ke, e, E2);
+        T = fma(L.P[q].K, t, T);
+      }
+      s1 = fma(gk, E, s1);
+      s2 = fma(gk, T, s2);
+      s3 = fma(gk, RD, s3);
+      s4 = fma(gk, E2, s4);
+    }
+  }
+  // FP64 block-summed one-pair, three-point and two-pair levels: four points
+  // share one reciprocal (with its Newton step) of the product of their
+  // denominators P_h (d_0, d_0 v or d_0 d_1): r = 1/(P_0 P_1 P_2 P_3),
+  // 1/P_0 = P_1 (P_2 P_3 r) and so on (the hardware FP64 reciprocal issues at a
+  // quarter of the FMA rate)
+  static constexpr bool kFour = sizeof(R) == 8 && SY && NP <= 2 && PROF == XS_VOIGT;
+  __device__ __forceinline__ void add4(const R (&x)[4], const R (&gk)[4]) {
+    if constexpr (kFour) {
+      R sx[4][NP], d[4][NP], P[4];
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+          sx[h][q] = fma(x[h], x[h], hS[q]);
+          d[h][q] = (C0 && q == 1) ? sx[h][q] : fma(sx[h][q], sx[h][q], cS[q]);
+        }
+        P[h] = NP == 2 ? d[h][0] * d[h][NP - 1] : d[h][0];
+      }
+      const R p01 = P[0] * P[1], p23 = P[2] * P[3];
+      const R r = arcp(p01 * p23);
+      const R r01 = p23 * r, r23 = p01 * r;
+      const R iP[4] = {P[1] * r01, P[0] * r01, P[3] * r23, P[2] * r23};
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        R rd[NP];
+        if constexpr (NP == 2) {
+          rd[0] = d[h][1] * iP[h];
+          rd[1] = d[h][0] * iP[h];
         } else {
-#pragma unroll
-          for (int q = 0; q < NP; ++q) rd[q] = arcp(fma(sx[q], sx[q], cS[q]));
+          rd[0] = iP[h];
         }
 #pragma unroll
         for (int q = 0; q < (C0 ? 1 : NP); ++q) {
-          const R grd = gk * rd[q], v = grd * rd[q];
+          const R grd = gk[h] * rd[q], v = grd * rd[q];
           B[q][0] += grd;
-          B[q][1] = fma(grd, sx[q], B[q][1]);
+          B[q][1] = fma(grd, sx[h][q], B[q][1]);
           B[q][2] += v;
-          B[q][3] = fma(v, sx[q], B[q][3]);
+          B[q][3] = fma(v, sx[h][q], B[q][3]);
         }
         if constexpr (C0) {
-          const R gv = gk * rd[1];
+          const R gv = gk[h] * rd[1];
           B[1][0] = fma(gv, rd[1], B[1][0]);
           B[1][1] += gv;
         }
-      } else if constexpr (UF) {
-        // s1 = S0, s2 = U1, s3 = U2, s4 = U3
-        const PairD<R>& P = L.P[0];
-        const R rd = arcp(fma(u, u + P.q, P.p2));
-        const R gr = gk * rd;
-        s1 += gr;
-        s2 = fma(gr, u, s2);
-        const R v = (gr * rd) * u;
-        s3 += v;
-        s4 = fma(v, u, s4);
-      } else if constexpr (NP == 1) {
-        // s1 = sum g e, s2 = sum g t, s3 = sum g / d, s4 = sum g e^2
-        R e, rd, t;
-        pair_adj<R>(L.P[0], u, e, rd, t);
-        const R ge = gk * e;
-        s1 += ge;
-        s2 = fma(gk, t, s2);
-        s3 = fma(gk, rd, s3);
-        s4 = fma(ge, e, s4);
-      } else {
-        R E = 0, RD = 0, E2 = 0, T = 0;
-#pragma unroll
-        for (int q = 0; q < NP; ++q) {
-          R e, rd, t;
-          pair_adj<R>(L.P[q], u, e, rd, t);
-          const R Ke = L.P[q].K * e;
-          E += Ke;
-          RD = fma(L.P[q].K, rd, RD);
-          E2 = fma(Ke, e, E2);
-          T = fma(L.P[q].K, t, T);
-        }
-        s1 = fma(gk, E, s1);
-        s2 = fma(gk, T, s2);
-        s3 = fma(gk, RD, s3);
-        s4 = fma(gk, E2, s4);
       }
-    };
-    // FP64 block-summed one-pair, three-point and two-pair levels: the four
-    // points of a step share one reciprocal (with its Newton step) of the
-    // product of their denominators P_h (d_0, d_0 v or d_0 d_1):
-    // r = 1/(P_0 P_1 P_2 P_3), 1/P_0 = P_1 (P_2 P_3 r) and so on (the
-    // hardware FP64 reciprocal issues at a quarter of the FMA rate)
-    auto body4 = [&](R rf, auto gsrc, int j) {
-      if constexpr (sizeof(R) == 8 && SY && NP <= 2 && PROF == XS_VOIGT) {
-        R sx[4][NP], d[4][NP], P[4], gk[4];
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-          const R x = fma(rf, L.a, nbj[h]);
-          gk[h] = gsrc(j + h);
-#pragma unroll
-          for (int q = 0; q < NP; ++q) {
-            sx[h][q] = fma(x, x, hS[q]);
-            d[h][q] = (C0 && q == 1) ? sx[h][q] : fma(sx[h][q], sx[h][q], cS[q]);
-          }
-          P[h] = NP == 2 ? d[h][0] * d[h][1] : d[h][0];
-        }
-        const R p01 = P[0] * P[1], p23 = P[2] * P[3];
-        const R r = arcp(p01 * p23);
-        const R r01 = p23 * r, r23 = p01 * r;
-        const R iP[4] = {P[1] * r01, P[0] * r01, P[3] * r23, P[2] * r23};
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-          R rd[NP];
-          if constexpr (NP == 2) {
-            rd[0] = d[h][1] * iP[h];
-            rd[1] = d[h][0] * iP[h];
-          } else {
-            rd[0] = iP[h];
-          }
-#pragma unroll
-          for (int q = 0; q < (C0 ? 1 : NP); ++q) {
-            const R grd = gk[h] * rd[q], v = grd * rd[q];
-            B[q][0] += grd;
-            B[q][1] = fma(grd, sx[h][q], B[q][1]);
-            B[q][2] += v;
-            B[q][3] = fma(v, sx[h][q], B[q][3]);
-          }
-          if constexpr (C0) {
-            const R gv = gk[h] * rd[1];
-            B[1][0] = fma(gv, rd[1], B[1][0]);
-            B[1][1] += gv;
-          }
-        }
-      }
-    };
-    auto run = [&](auto gsrc) {
-      int j = 0;
-      if (sizeof(R) == 8 && SY && NP <= 2 && PROF == XS_VOIGT && L.share4) {
-        for (; j + 4 <= n; j += 4) body4((R)(rb + j), gsrc, j);
-      } else {
-        for (; j + 4 <= n; j += 4) {
-          const R rf = (R)(rb + j);
-#pragma unroll
-          for (int jj = 0; jj < 4; ++jj) body(fma(rf, L.a, nbj[jj]), gsrc(j + jj));
-        }
-      }
-      for (; j < n; ++j) body(fma((R)(rb + j), L.a, L.nb), gsrc(j));
-    };
-    if (G.lds) {
-      // refill the wave's slice with g[kcmin + rb + t], t < 2 kFlush
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      const int64_t kb = (int64_t)G.kcmin + rb;
-      for (int t = rank; t < 2 * kFlush; t += nact) {
-        const int64_t k = kb + t;
-        G.buf[t] = (k >= 0 && k < G.nb) ? (R)(G.gc[k] * G.gs) : (R)0;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      const R* gl = G.buf + (L.kc - G.kcmin);
-      run([&](int j) { return gl[j]; });
-    } else {
-      const double* gp = G.gc + (L.kc + rb);
-      if constexpr (sizeof(R) == 4) run([&](int j) { return (R)(gp[j] * G.gs); });
-      else run([&](int j) { return (R)gp[j]; });
     }
-    // to the general-path convention
+  }
+  // the sums so far in the general path's convention
+  __device__ __forceinline__ void flush(const AdjLine<R>& L, double& sA, double& sB, double& sC) const {
     if (PROF == XS_DOPPLER || PROF == XS_GAUSSIAN) {
       sA += (double)s1;
       sB += 2.0 * kLN2 * (double)s2 - (double)s1;
@@ -554,25 +534,99 @@ __device__ __forceinline__ void fast_range(const AdjLine<R>& L, const GSrc<R>& G
       sC -= w;                            // Im w' = -dRe w/dy
     }
   }
+};
+
+// MASK: lanes outside their own window (r not in [rlo, rhi]) take part with a
+// cotangent of zero; their x lies further out, where the level's form holds.
+template <typename R, int PROF, int NP, bool SY = false, bool C0 = false, bool UF = false>
+__device__ __forceinline__ void fast_range(const AdjLine<R>& L, const GSrc<R>& G, int r0, int r1, bool mask,
+                                           double& sA, double& sB, double& sC) {
+  // the lanes running this loop (the wave's active lines) share the refills
+  const unsigned long long act = __ballot(1);
+  const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(act >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)act, 0u));
+  const int nact = __popcll(act);
+  // x at r = rb + j4 + jj as fma(rb + j4, a, nb + jj a): one conversion per
+  // four points (nb + jj a rounds once, relative 6e-8 of at most 3.5 a, so x
+  // keeps a relative error below 5e-7 for every r != 0)
+  R nbj[4];
+#pragma unroll
+  for (int jj = 0; jj < 4; ++jj) nbj[jj] = fma((R)jj, L.a, L.nb);
+  using Sums = FastSums<R, PROF, NP, SY, C0, UF>;
+  Sums S;
+  S.begin(L);
+  for (int rb = r0; rb <= r1; rb += kFlush) {
+    const int n = min(kFlush, r1 - rb + 1);
+    S.clear();
+    auto run = [&](auto gsrc) {
+      int j = 0;
+      if (Sums::kFour && L.share4) {
+        for (; j + 4 <= n; j += 4) {
+          R x[4], gk[4];
+#pragma unroll
+          for (int h = 0; h < 4; ++h) {
+            x[h] = fma((R)(rb + j), L.a, nbj[h]);
+            gk[h] = gsrc(j + h);
+          }
+          S.add4(x, gk);
+        }
+      } else {
+        for (; j + 4 <= n; j += 4) {
+          const R rf = (R)(rb + j);
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj) S.add(L, fma(rf, L.a, nbj[jj]), gsrc(j + jj));
+        }
+      }
+      for (; j < n; ++j) S.add(L, fma((R)(rb + j), L.a, L.nb), gsrc(j));
+    };
+    if (G.lds) {
+      // refill the wave's slice with g[kcmin + rb + t], t < 2 kFlush
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      const int64_t kb = (int64_t)G.kcmin + rb;
+      const int need = min(2 * kFlush, n + G.span);
+      for (int t = rank; t < need; t += nact) {
+        const int64_t k = kb + t;
+        G.buf[t] = (k >= 0 && k < G.nb) ? (R)(G.gc[k] * G.gs) : (R)0;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      const R* gl = G.buf + (L.kc - G.kcmin);
+      if (mask) {
+        const int lo = L.rlo - rb, hi = L.rhi - rb;
+        run([&](int j) { return j >= lo && j <= hi ? gl[j] : (R)0; });
+      } else {
+        run([&](int j) { return gl[j]; });
+      }
+    } else if (mask) {
+      const int lo = L.rlo - rb, hi = L.rhi - rb;
+      run([&](int j) { return j >= lo && j <= hi ? (R)(G.gc[L.kc + rb + j] * G.gs) : (R)0; });
+    } else {
+      const double* gp = G.gc + (L.kc + rb);
+      if constexpr (sizeof(R) == 4) run([&](int j) { return (R)(gp[j] * G.gs); });
+      else run([&](int j) { return (R)gp[j]; });
+    }
+    S.flush(L, sA, sB, sC);
+  }
 }
 
 // Level l of Levels<R> (the caller has put the level's pairs in L.P; the
 // node at 0 of the FP64 three-point level is L.P[1]).
 template <typename R, int PROF>
-__device__ __forceinline__ void fast_level(int level, const AdjLine<R>& L, const GSrc<R>& G, int r0, int r1,
+__device__ __forceinline__ void fast_level(int level, const AdjLine<R>& L, const GSrc<R>& G, int r0, int r1, bool mask,
                                            double& sA, double& sB, double& sC, bool blocksum = false) {
   if (PROF == XS_VOIGT && blocksum) {
-    if (level == 0) fast_range<R, PROF, 1, true>(L, G, r0, r1, sA, sB, sC);
-    else if constexpr (sizeof(R) == 4) fast_range<R, PROF, 2, true>(L, G, r0, r1, sA, sB, sC);
-    else if (level == 1) fast_range<R, PROF, 2, true, true>(L, G, r0, r1, sA, sB, sC);
-    else if (level == 2) fast_range<R, PROF, 2, true>(L, G, r0, r1, sA, sB, sC);
-    else fast_range<R, PROF, 3, true>(L, G, r0, r1, sA, sB, sC);
+    if (level == 0) fast_range<R, PROF, 1, true>(L, G, r0, r1, mask, sA, sB, sC);
+    else if constexpr (sizeof(R) == 4) fast_range<R, PROF, 2, true>(L, G, r0, r1, mask, sA, sB, sC);
+    else if (level == 1) fast_range<R, PROF, 2, true, true>(L, G, r0, r1, mask, sA, sB, sC);
+    else if (level == 2) fast_range<R, PROF, 2, true>(L, G, r0, r1, mask, sA, sB, sC);
+    else fast_range<R, PROF, 3, true>(L, G, r0, r1, mask, sA, sB, sC);
     return;
   }
-  if (PROF == XS_VOIGT && level == 0) fast_range<R, PROF, 1, false, false, true>(L, G, r0, r1, sA, sB, sC);
-  else if (PROF != XS_VOIGT || level == 0) fast_range<R, PROF, 1>(L, G, r0, r1, sA, sB, sC);
-  else if (sizeof(R) == 4 || level <= 2) fast_range<R, PROF, 2>(L, G, r0, r1, sA, sB, sC);
-  else if constexpr (sizeof(R) == 8) fast_range<R, PROF, 3>(L, G, r0, r1, sA, sB, sC);
+  if (PROF == XS_VOIGT && level == 0) fast_range<R, PROF, 1, false, false, true>(L, G, r0, r1, mask, sA, sB, sC);
+  else if (PROF != XS_VOIGT || level == 0) fast_range<R, PROF, 1>(L, G, r0, r1, mask, sA, sB, sC);
+  else if (sizeof(R) == 4 || level <= 2) fast_range<R, PROF, 2>(L, G, r0, r1, mask, sA, sB, sC);
+  else if constexpr (sizeof(R) == 8) fast_range<R, PROF, 3>(L, G, r0, r1, mask, sA, sB, sC);
 }
 
 // r-range of the bins where |x| < X (widened by one bin), clipped to
@@ -645,7 +699,9 @@ __device__ __forceinline__ Sums3 window_sums(bool on, int64_t klo, int64_t khi, 
       if (PROF == XS_VOIGT) X = sqrt(fmax(Levels<R>::rho[l] * 1.001 - y * y, 0.0));
       else if (PROF == XS_LORENTZ) X = 0.0;  // one level, no inner region
       else X = (sizeof(R) == 4) ? sqrt(160.0) : sqrt(1100.0);  // Gaussian: nonzero range
-      r_range(X, L.ad, L.bd, L.rlo, L.rhi, rl, rh);
+      // over the wave's whole run: a masked lane must not meet its inner
+      // region in a level's loop
+      r_range(X, L.ad, L.bd, Rmin, Rmax, rl, rh);
     }
     Hlo[l] = wave_min(rl);
     Hhi[l] = wave_max(rh);
@@ -656,7 +712,9 @@ __device__ __forceinline__ Sums3 window_sums(bool on, int64_t klo, int64_t khi, 
   G.gs = gs;
   G.nb = nbins;
   G.kcmin = wave_min(on ? L.kc : 0x7fffffff);
-  G.lds = (int64_t)wave_max(on ? L.kc : -0x7fffffff) - G.kcmin <= kFlush;
+  const int64_t span = (int64_t)wave_max(on ? L.kc : -0x7fffffff) - G.kcmin;
+  G.lds = span <= kFlush;
+  G.span = (int)min<int64_t>(span, kFlush);
   G.buf = gbuf;
   // levels whose block-summed form every line of the wave allows (bit l:
   // y^2 at most half of level l's rho bound)
@@ -668,17 +726,20 @@ __device__ __forceinline__ Sums3 window_sums(bool on, int64_t klo, int64_t khi, 
     int r = Rmin;
     while (r <= Rmax) {
       int end, mode;  // mode: -2 skip, -1 general, l >= 0 fast level l
-      if (any_wide || r < Alo || r > Ahi) {
+      // outside [Alo, Ahi] some lanes are beyond their own window
+      const bool mask = r < Alo || r > Ahi;
+      const int lim = r < Alo ? min(Alo - 1, Rmax) : r > Ahi ? Rmax : Ahi;
+      if (any_wide) {
         mode = -1;
-        end = (any_wide || r > Ahi) ? Rmax : Alo - 1;
+        end = Rmax;
       } else if (PROF == XS_DOPPLER || PROF == XS_GAUSSIAN) {
         // outside the nonzero hull every lane's Gaussian is exactly 0
-        if (Hlo[0] > Hhi[0] || r > Hhi[0]) { mode = -2; end = Ahi; }
-        else if (r < Hlo[0]) { mode = -2; end = Hlo[0] - 1; }
-        else { mode = 0; end = min(Hhi[0], Ahi); }
+        if (Hlo[0] > Hhi[0] || r > Hhi[0]) { mode = -2; end = lim; }
+        else if (r < Hlo[0]) { mode = -2; end = min(Hlo[0] - 1, lim); }
+        else { mode = 0; end = min(Hhi[0], lim); }
       } else if (PROF == XS_LORENTZ) {
         mode = 0;
-        end = Ahi;
+        end = lim;
       } else {
         // deepest level whose hull holds r
         int l = 0;
@@ -687,12 +748,12 @@ __device__ __forceinline__ Sums3 window_sums(bool on, int64_t klo, int64_t khi, 
           if (l == q && Hlo[q] <= r && r <= Hhi[q]) l = q + 1;
         if (l == NL) {
           mode = -1;
-          end = min(Hhi[NL - 1], Ahi);
+          end = min(Hhi[NL - 1], lim);
         } else {
           mode = l;
           if (Hlo[l] <= Hhi[l] && r < Hlo[l]) end = Hlo[l] - 1;   // up to the next inner hull
-          else end = (l == 0) ? Ahi : Hhi[l - 1];                  // to the end of this hull
-          end = min(end, Ahi);
+          else end = (l == 0) ? lim : Hhi[l - 1];                  // to the end of this hull
+          end = min(end, lim);
         }
       }
       if (mode >= 0) {
@@ -713,9 +774,9 @@ __device__ __forceinline__ Sums3 window_sums(bool on, int64_t klo, int64_t khi, 
             L.P[1] = pair_d<R>(y, GH::t6[1], GH::w6[1]);
             L.P[2] = pair_d<R>(y, GH::t6[2], GH::w6[2]);
           }
-          fast_level<R, PROF>(mode, L, G, r, end, sA, sB, sC, (blk >> mode) & 1);
+          fast_level<R, PROF>(mode, L, G, r, end, mask, sA, sB, sC, (blk >> mode) & 1);
         } else {
-          fast_level<R, PROF>(0, L, G, r, end, sA, sB, sC);
+          fast_level<R, PROF>(0, L, G, r, end, mask, sA, sB, sC);
         }
       } else if (mode == -1) {
         for (int rr = r; rr <= end; ++rr) {
@@ -731,41 +792,458 @@ __device__ __forceinline__ Sums3 window_sums(bool on, int64_t klo, int64_t khi, 
   return Sums3{sA, sB, sC};
 }
 
+// ---- far tiles ---------------------------------------------------------------
+// With tile expansions (far_geometry.h) sigma takes a tile's line as its values
+// at P nodes; the transpose of that interpolation weights the line's values
+// at the nodes with the tile's moments mu_q = sum_k g_k l_q(x_k) (l_q the
+// interpolant of node q), computed once for every tile.  So a lane's window
+// sums take P terms per tile instead of one per point, with the cotangent
+// replaced by mu_q: uniform loads, no LDS.  A window end cuts one tile of at
+// most 256 points on each side: the groups of 16 points before the end enter
+// through their own moments (PE nodes), the end's group point by point.
+// Measured on 1e7 lines, FP32 form, window 5000 points: 15.5 ms point by point;
+// 6.1 ms with tiles (near part 3.0, tiles and ends 2.9, moments 0.2); 2e5
+// lines FP64: 0.90 and 0.44 ms.
+
+// Moments of every tile of a level (blockIdx.y: condition): a wave takes one
+// tile of 64 points or more, or 64 points' worth of smaller ones.
+template <typename R, int P>
+__device__ __forceinline__ void cheb_row(double x, double gk, double (&acc)[P]) {
+  double t0 = 1.0, t1 = x;
+  acc[0] += gk;
+#pragma unroll
+  for (int q = 1; q < P; ++q) {
+    acc[q] = fma(gk, t1, acc[q]);
+    const double t2 = fma(2.0 * x, t1, -t0);
+    t0 = t1;
+    t1 = t2;
+  }
+}
+__device__ __forceinline__ double adj_scale(const unsigned long long* gmax, int c, double& igs) {
+  // the power of two that brings the largest cotangent into [1/2, 1)
+  double gs = 1.0;
+  igs = 1.0;
+  const double gm = __longlong_as_double((long long)gmax[c]);
+  if (gm > 0.0 && gm <= 1.7976931348623157e308) {
+    int e;
+    (void)frexp(gm, &e);
+    e = max(e, -1000);
+    gs = ldexp(1.0, -e);
+    igs = ldexp(1.0, e);
+  }
+  return gs;
+}
+
+template <typename R, int P>
+__global__ __launch_bounds__(256) void k_adj_moments(AdjArgs a, int lmax) {
+  const ModelDev& m = a.m;
+  const int c = blockIdx.y, lane = threadIdx.x & 63;
+  const FarCond& fc = a.cond[c].far;
+  if (!fc.on || a.counter[kFarOff]) return;
+  // the wave's level: the widest tiles first
+  int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  int l = min(lmax, fc.lmax);
+  for (; l >= 0; --l) {
+    const int n = far_wide(fc.sh, l) > 0 ? far_tiles(m.n_fine, l) : (int)((m.n_bins + 63) / 64);
+    if (w < n) break;
+    w -= n;
+  }
+  if (l < 0) return;
+  const int lg = l + fc.sh, n = 1 << lg;
+  double igs = 1.0;
+  const double gs = sizeof(R) == 4 ? adj_scale(a.gmax, c, igs) : 1.0;
+  const double* gc = a.g + (int64_t)c * m.n_bins;
+  const double ih = 2.0 / (double)n;
+  double acc[P];
+#pragma unroll
+  for (int q = 0; q < P; ++q) acc[q] = 0.0;
+  const int64_t k0 = lg >= 6 ? (int64_t)w << lg : (int64_t)w * 64;
+  for (int o = 0; o < max(n, 64); o += 64) {
+    const int64_t k = k0 + o + lane;
+    const double gk = k < m.n_bins ? gc[k] * gs : 0.0;
+    const int i = (o + lane) & (n - 1);
+    cheb_row<R, P>(((double)i + 0.5) * ih - 1.0, gk, acc);
+  }
+#pragma unroll
+  for (int s = 1; s < 64; s <<= 1)
+    if (s < n)
+#pragma unroll
+      for (int q = 0; q < P; ++q) acc[q] += __shfl_xor(acc[q], s, 64);
+  const int gl = min(n, 64), q = lane & (gl - 1), t = (int)((k0 + lane) >> lg);
+  if (q < P && t < far_tiles(m.n_fine, l)) {
+    const double* D = far_dct<P>();
+    double v = 0.0;
+#pragma unroll
+    for (int k = 0; k < P; ++k) v = fma(D[q * P + k], acc[k], v);
+    int64_t row = t;
+    for (int k = 0; k < l; ++k) row += far_tiles(m.n_fine, k);
+    ((R*)a.mom)[((int64_t)c * a.cond_rows + row) * P + q] = (R)v;
+  }
+}
+
+// Moments of the parts of the tiles that window ends cut: for every group of
+// kCutGroup points of a tile of level `end`, those of the tile's groups before
+// it ([0]) and after it ([1]).  One wave per tile.
+template <typename R, int PE>
+__global__ __launch_bounds__(64) void k_adj_cut(AdjArgs a) {
+  constexpr int kGroups = kFarEndBins / kCutGroup;
+  __shared__ double tau[kGroups][PE], node[kGroups][PE];
+  const ModelDev& m = a.m;
+  const int c = blockIdx.y, lane = threadIdx.x, t = blockIdx.x;
+  const FarCond& fc = a.cond[c].far;
+  if (!fc.on || a.counter[kFarOff] || t >= far_tiles(m.n_fine, fc.end)) return;
+  const int n = 1 << (fc.end + fc.sh), ng = n / kCutGroup;
+  double igs = 1.0;
+  const double gs = sizeof(R) == 4 ? adj_scale(a.gmax, c, igs) : 1.0;
+  const double* gc = a.g + (int64_t)c * m.n_bins;
+  const int64_t k0 = (int64_t)t * n;
+  for (int o = 0; o < n; o += 64) {
+    const int64_t k = k0 + o + lane;
+    double acc[PE];
+#pragma unroll
+    for (int q = 0; q < PE; ++q) acc[q] = 0.0;
+    cheb_row<R, PE>(((double)(o + lane) + 0.5) * (2.0 / (double)n) - 1.0, k < m.n_bins ? gc[k] * gs : 0.0, acc);
+#pragma unroll
+    for (int s = 1; s < kCutGroup; s <<= 1)
+#pragma unroll
+      for (int q = 0; q < PE; ++q) acc[q] += __shfl_xor(acc[q], s, 64);
+    if ((lane & (kCutGroup - 1)) == 0)
+#pragma unroll
+      for (int q = 0; q < PE; ++q) tau[(o + lane) / kCutGroup][q] = acc[q];
+  }
+  __syncthreads();
+  // to the nodes, then the running sums from either end
+  const double* D = far_dct<PE>();
+  for (int i = lane; i < ng * PE; i += 64) {
+    const int j = i / PE, q = i % PE;
+    double v = 0.0;
+#pragma unroll
+    for (int k = 0; k < PE; ++k) v = fma(D[q * PE + k], tau[j][k], v);
+    node[j][q] = v;
+  }
+  __syncthreads();
+  if (lane < 2 * PE) {
+    const int side = lane / PE, q = lane % PE;
+    double run = 0.0;
+    for (int h = 0; h < ng; ++h) {
+      const int j = side == 0 ? h : ng - 1 - h;
+      const int64_t row = (int64_t)t * ng + j;
+      if (row < a.cut_rows) ((R*)a.cut)[(((int64_t)c * a.cut_rows + row) * 2 + side) * PE + q] = (R)run;
+      run += node[j][q];
+    }
+  }
+}
+
+// The far sums of one wave's lines.  The forms that most tiles take -- FP32:
+// one pair, as block sums or in the u-form, and two pairs as block sums --
+// add up over all tiles and are flushed once; the others flush per tile.
+template <typename R, int PROF>
+struct FarSums {
+  FastSums<R, PROF, 1, PROF == XS_VOIGT> one;
+  FastSums<R, PROF, 1, false, false, PROF == XS_VOIGT> uform;
+  FastSums<R, PROF, PROF == XS_VOIGT ? 2 : 1, PROF == XS_VOIGT> two;
+  bool one_sy, two_sy;  // the wave's y allow the block sums
+  double A, B, C;
+};
+template <typename R, int PROF>
+__device__ __forceinline__ void far_pair(AdjLine<R>& L, int level) {
+  if (level == 0) {
+    L.P[0] = pair_d<R>(L.y, GH::t2[0], GH::w2[0]);
+  } else {
+    L.P[0] = pair_d<R>(L.y, GH::t4[0], GH::w4[0]);
+    L.P[1] = pair_d<R>(L.y, GH::t4[1], GH::w4[1]);
+  }
+}
+template <typename R, int PROF>
+__device__ __forceinline__ void far_begin(AdjLine<R>& L, FarSums<R, PROF>& F, bool share) {
+  F.A = F.B = F.C = 0.0;
+  F.one_sy = F.two_sy = true;
+  if constexpr (PROF == XS_VOIGT) {
+    const double y2 = L.y * L.y;
+    F.one_sy = __ballot(share && !(y2 <= 0.5 * Levels<R>::rho[0])) == 0;
+    F.two_sy = __ballot(share && !(y2 <= 32.0)) == 0;
+    if constexpr (sizeof(R) == 4) {
+      far_pair<R, PROF>(L, 1);
+      F.two.begin(L);
+    }
+    far_pair<R, PROF>(L, 0);  // stays in L: the u-form reads it
+  }
+  F.one.begin(L);
+  F.uform.clear();
+}
+template <typename R, int PROF>
+__device__ __forceinline__ void far_end(AdjLine<R>& L, FarSums<R, PROF>& F) {
+  if (F.one_sy) F.one.flush(L, F.A, F.B, F.C);
+  else F.uform.flush(L, F.A, F.B, F.C);
+  if constexpr (PROF == XS_VOIGT && sizeof(R) == 4) {
+    if (F.two_sy) {
+      far_pair<R, PROF>(L, 1);
+      F.two.flush(L, F.A, F.B, F.C);
+    }
+  }
+}
+
+// N terms (x, weight) of a tile or a cut, with the form the wave's smallest
+// |z|^2 on it (rho) allows.  Every lane of the wave takes part; a lane without
+// a share has weights 0 and any finite x.
+template <typename R, int PROF, int N, typename FX, typename FW>
+__device__ __forceinline__ void far_terms(AdjLine<R>& L, FarSums<R, PROF>& F, bool share, bool wide, double rho, FX xof,
+                                          FW wof) {
+  auto add = [&](auto& S) {
+    // a few terms at a time: unrolled further the loads of all terms are live
+    // at once and spill
+    constexpr int kStep = N % 4 == 0 ? 4 : 2;
+#pragma unroll 1
+    for (int q = 0; q < N; q += kStep) {
+      if (std::remove_reference_t<decltype(S)>::kFour && kStep == 4 && L.share4) {
+        const R x[4] = {xof(q), xof(q + 1), xof(q + 2), xof(q + 3)};
+        const R w[4] = {wof(q), wof(q + 1), wof(q + 2), wof(q + 3)};
+        S.add4(x, w);
+      } else {
+#pragma unroll
+        for (int j = 0; j < kStep; ++j) S.add(L, xof(q + j), wof(q + j));
+      }
+    }
+  };
+  if constexpr (PROF == XS_LORENTZ) {
+    add(F.one);
+  } else {
+    const double y = L.y, y2 = y * y;
+    if (sizeof(R) == 4 && wide) {
+#pragma unroll 1
+      for (int q = 0; q < N; ++q) {
+        const Grad3<double> v = voigt_grad<double>((double)xof(q), y, 0);
+        const double w = (double)wof(q);
+        if (w != 0.0) {
+          F.A = fma(w, v.f, F.A);
+          F.B = fma(w, v.fs, F.B);
+          F.C = fma(w, v.fg, F.C);
+        }
+      }
+      return;
+    }
+    auto all = [&](double r) { return __ballot(share && !(rho >= r * 1.001)) == 0; };
+    using LV = Levels<R>;
+    if (all(LV::rho[0])) {
+      if (F.one_sy) add(F.one);
+      else add(F.uform);
+      return;
+    }
+    // forms that flush per tile; L's one pair is put back afterwards
+    auto once = [&](auto S) {
+      S.begin(L);
+      add(S);
+      S.flush(L, F.A, F.B, F.C);
+      far_pair<R, PROF>(L, 0);
+    };
+    if constexpr (sizeof(R) == 4) {
+      if (F.two_sy) {
+        add(F.two);
+      } else {
+        far_pair<R, PROF>(L, 1);
+        once(FastSums<R, PROF, 2>());
+      }
+    } else {
+      auto sy = [&](double r) { return __ballot(share && !(y2 <= 0.5 * r)) == 0; };
+      if (all(LV::rho[1])) {
+        L.P[0] = pair_d<R>(y, GH::t3[0], GH::w3[0]);
+        L.P[1] = pair_d<R>(y, 0.0, 0.5 * GH::w3c);
+        if (sy(LV::rho[1])) once(FastSums<R, PROF, 2, true, true>());
+        else once(FastSums<R, PROF, 2>());
+      } else if (all(LV::rho[2])) {
+        far_pair<R, PROF>(L, 1);
+        if (sy(LV::rho[2])) once(FastSums<R, PROF, 2, true>());
+        else once(FastSums<R, PROF, 2>());
+      } else if (all(LV::rho[3])) {
+        L.P[0] = pair_d<R>(y, GH::t6[0], GH::w6[0]);
+        L.P[1] = pair_d<R>(y, GH::t6[1], GH::w6[1]);
+        L.P[2] = pair_d<R>(y, GH::t6[2], GH::w6[2]);
+        if (sy(LV::rho[3])) once(FastSums<R, PROF, 3, true>());
+        else once(FastSums<R, PROF, 3>());
+      } else {
+        const bool four = all(144.0);
+#pragma unroll 1
+        for (int q = 0; q < N; ++q) {
+          const double w = (double)wof(q), x = (double)xof(q);
+          const Grad3<double> v = voigt_grad<double>(x, y, four ? 4 : 6);
+          F.A = fma(w, v.f, F.A);
+          F.B = fma(w, v.fs, F.B);
+          F.C = fma(w, v.fg, F.C);
+        }
+      }
+    }
+  }
+}
+
+// Far part of the window sums of the wave's lines (general-path convention).
+// far: the lane has a line in a cell with far tiles; f its cell.
+template <typename R, int PROF, int P, int PE>
+__device__ __forceinline__ Sums3 far_window_sums(const AdjArgs& a, const CondDev& cd, int c, bool far, int f, int kc,
+                                              int klo, int khi, double nu, double inv, double y, double gs) {
+  const ModelDev& m = a.m;
+  const FarCond& fc = cd.far;
+  const int lane = threadIdx.x & 63;
+  const int f0 = wave_min(far ? f : 0x7fffffff), f1 = wave_max(far ? f : -0x7fffffff);
+  if (f0 > f1) return Sums3{0.0, 0.0, 0.0};
+  AdjLine<R> L;
+  L.kc = far ? kc : f0 << fc.sh;
+  L.ad = far ? m.dnu * inv : 1.0;
+  L.bd = far ? (nu - nu_of_bin(m.nu0, m.dnu, kc)) * inv : 0.0;
+  L.y = far ? y : 1.0;
+  L.a = (R)L.ad;
+  L.nb = (R)(-L.bd);
+  const double xmax = fmax(fabs((double)(klo - kc) * L.ad - L.bd), fabs((double)(khi - kc) * L.ad - L.bd));
+  const bool wide_any = PROF == XS_VOIGT && __ballot(far && !(xmax <= 1.0e9 && y <= 1.0e9)) != 0;
+  L.share4 = !wide_any;
+  FarSums<R, PROF> F;
+  far_begin<R, PROF>(L, F, far);
+  // x of a point that lies d points from kc; smallest |z|^2 over n points from ts
+  auto xat = [&](R d) -> R { return fma(d, L.a, L.nb); };
+  auto rho_of = [&](int ts, int n) {
+    const double lo = fma((double)(ts - L.kc), L.ad, -L.bd), hi = fma((double)(ts + n - 1 - L.kc), L.ad, -L.bd);
+    const double xn = lo > 0.0 ? lo : hi < 0.0 ? -hi : 0.0;
+    return fma(xn, xn, L.y * L.y);
+  };
+  // ---- tiles taken whole.  64 candidates are examined at a time, one per lane ----
+  int done = 0;
+  for (;;) {
+    int l = -1, t = 0, total = 0;
+    for (int k = 0; k <= fc.lmax; ++k) {
+      const CellRange cr = far_candidates(fc, k, f0, f1);
+      const int n = max(0, cr.hi - cr.lo + 1), i = done + lane - total;
+      if (i >= 0 && i < n) {
+        l = k;
+        t = cr.lo + i;
+      }
+      total += n;
+    }
+    CellRange r[4] = {{0, -1}, {0, -1}, {0, -1}, {0, -1}};
+    if (l >= 0) far_tile_ranges(fc, l, t, r);
+    bool hit = false;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) hit |= r[k].lo <= r[k].hi && r[k].lo <= f1 && r[k].hi >= f0;
+    unsigned long long hits = __ballot(hit);
+    while (hits) {
+      const int s = __builtin_ctzll(hits);
+      hits &= hits - 1;
+      const int tl = __builtin_amdgcn_readlane(l, s), tt = __builtin_amdgcn_readlane(t, s);
+      bool mine = false;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int lo = __builtin_amdgcn_readlane(r[k].lo, s), hi = __builtin_amdgcn_readlane(r[k].hi, s);
+        mine |= f >= lo && f <= hi;
+      }
+      mine = mine && far;
+      if (__ballot(mine) == 0) continue;
+      const int lg = tl + fc.sh, ts = tt << lg;
+      const R half = (R)(1 << lg) * (R)0.5;
+      const R xc = xat((R)(ts - L.kc) + (half - (R)0.5)), ah = half * L.a;
+      int64_t row = tt;
+      for (int k = 0; k < tl; ++k) row += far_tiles(m.n_fine, k);
+      const R* mu = (const R*)a.mom + ((int64_t)c * a.cond_rows + row) * P;
+      // (a lane without a line takes the weights as well: its sums are dropped)
+      if (__ballot(far && !mine) == 0)
+        far_terms<R, PROF, P>(
+            L, F, mine, wide_any, rho_of(ts, 1 << lg), [&](int q) -> R { return fma(far_x<R, P>()[q], ah, xc); },
+            [&](int q) { return mu[q]; });
+      else
+        far_terms<R, PROF, P>(
+            L, F, mine, wide_any, rho_of(ts, 1 << lg), [&](int q) -> R { return fma(far_x<R, P>()[q], ah, xc); },
+            [&](int q) { return mine ? mu[q] : (R)0; });
+    }
+    done += 64;
+    if (done >= total) break;
+  }
+  // ---- tiles that window ends cut ----
+  CellRange cc[2];
+  far_cut_candidates(fc, f0, f1, cc);
+  const int n = 1 << (fc.end + fc.sh);
+  const R half = (R)n * (R)0.5;
+#pragma unroll 1
+  for (int side = 0; side < 2; ++side) {
+    for (int t = cc[side].lo; t <= cc[side].hi; ++t) {
+      CellRange r[2];
+      far_cut(fc, t, r);
+      const int ts = t * n;
+      // the window's last (first) point in the tile
+      const int ke = side == 0 ? min(khi, ts + n - 1) : max(klo, ts);
+      const bool mine = far && f >= r[side].lo && f <= r[side].hi && (side == 0 ? khi >= ts : klo <= ts + n - 1);
+      if (__ballot(mine) == 0) continue;
+      const int j = mine ? (ke - ts) / kCutGroup : 0;
+      const double rho = rho_of(ts, n);
+      const R xc = xat((R)(ts - L.kc) + (half - (R)0.5)), ah = half * L.a;
+      const R* mu = (const R*)a.cut + (((int64_t)c * a.cut_rows + (int64_t)t * (n / kCutGroup) + j) * 2 + side) * PE;
+      far_terms<R, PROF, PE>(
+          L, F, mine, wide_any, rho, [&](int q) -> R { return fma(far_x<R, PE>()[q], ah, xc); },
+          [&](int q) { return mine ? mu[q] : (R)0; });
+      const int k0 = ts + j * kCutGroup;
+      const double* gc = a.g + (int64_t)c * m.n_bins;
+      const int p0 = side == 0 ? k0 : ke, p1 = side == 0 ? ke : min(k0 + kCutGroup - 1, (int)m.n_bins - 1);
+      far_terms<R, PROF, kCutGroup>(
+          L, F, mine, wide_any, rho, [&](int q) { return xat((R)(k0 + q - L.kc)); },
+          [&](int q) { return mine && k0 + q >= p0 && k0 + q <= p1 ? (R)(gc[k0 + q] * gs) : (R)0; });
+    }
+  }
+  far_end<R, PROF>(L, F);
+  return far ? Sums3{F.A, F.B, F.C} : Sums3{0.0, 0.0, 0.0};
+}
+
 // One wave owns 64 consecutive sorted lines (one per lane) and walks all of
 // their windows together in steps of r = k - k_c.  Lanes of a wave hold lines
 // of nearly equal wavenumber and width, so at a given r they need the same
 // formula: the r axis is cut into uniform runs (far-region levels, the
 // general core, masked window ends) decided once per wave.
-template <typename R, int PROF>
-__global__ __launch_bounds__(256, sizeof(R) == 4 ? 4 : 3) void k_adjoint(AdjArgs a) {
+//
+// FAR: the part of the window sums that tile expansions take, a kernel of its
+// own (one kernel with both parts spills more than 150 registers).  It leaves
+// the lines' gradients in a.fline, sorted order, and its blocks' sums after
+// those of the other part, which starts from them.
+// Waves per SIMD asked for.  The Voigt kernels spill at four (FP32) and three
+// (FP64): measured with 4 / 3 / 2 waves on 1e7 lines FP32, near part 3.44 /
+// 3.02 / 3.02 ms, far part 2.92 / 3.25 / 3.85; with 3 / 2 waves on 2e5 lines
+// FP64, near 0.203 / 0.191 ms, far 0.308 / 0.214.
+template <typename R, int PROF, bool FAR>
+constexpr int adj_waves() {
+  if (PROF != XS_VOIGT) return sizeof(R) == 4 ? 4 : 3;
+  return sizeof(R) == 8 ? 2 : FAR ? 4 : 3;
+}
+template <typename R, int PROF, bool FAR>
+__global__ __launch_bounds__(256, (adj_waves<R, PROF, FAR>())) void k_adjoint(AdjArgs a) {
+  constexpr bool FARP = PROF == XS_VOIGT || PROF == XS_LORENTZ;
   __shared__ double sdt[4][kMaxCond];
   __shared__ double sdp[4][kMaxCond];
-  __shared__ R s_g[4][2 * kFlush];  // per-wave cotangent slices
+  __shared__ R s_g[4][FAR ? 1 : 2 * kFlush];  // per-wave cotangent slices
   const ModelDev& m = a.m;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int c = threadIdx.x; c < kMaxCond; c += 256)
+  for (int c = threadIdx.x; c < m.n_cond; c += 256)
     for (int w = 0; w < 4; ++w) sdt[w][c] = sdp[w][c] = 0.0;
   __syncthreads();
-  const int64_t nk = a.off[m.n_fine];
+  const bool far_on = FARP && a.far && !a.counter[kFarOff];
+  const int64_t nk = (FAR && !far_on) ? 0 : a.off[m.n_fine];
   const int64_t nbatch = (nk + 63) >> 6;
   const double sqrt2ln2 = sqrt(2.0 * kLN2);
   for (int64_t bt = (int64_t)blockIdx.x * 4 + wave; bt < nbatch; bt += (int64_t)gridDim.x * 4) {
     const int64_t p = bt * 64 + lane;
     const bool have = p < nk;
     double nu = 0.0, gref = 0.0, nexp = 0.0, gpre = 0.0, Es = 0.0;
-    int32_t i = 0;
+    double dls = 0.0, dgr = 0.0, dne = 0.0;
     if (have) {
       nu = a.rnu[p];
       gref = (double)a.rgref[p];
       nexp = (double)a.rnexp[p];
       gpre = a.rgpre ? a.rgpre[p] : 0.0;
-      i = a.ridx[p];
       Es = a.rEs[p];
+      if (!FAR && far_on) {
+        dls = a.fline[p];
+        dgr = a.fline[a.max_lines + p];
+        dne = a.fline[2 * a.max_lines + p];
+      }
     }
-    double dls = 0.0, dgr = 0.0, dne = 0.0;
     for (int c = 0; c < m.n_cond; ++c) {
-      const CondDev cd = a.cond[c];
+      const CondDev& cd = a.cond[c];
+      const bool use_far = far_on && cd.far.on;
+      if (FAR && !use_far) continue;
       int64_t klo = 0, khi = -1;
       bool on = have && line_window(nu, cd.cut, m.nu0, m.dnu, m.n_bins, klo, khi);
       double S = 0.0;
@@ -774,6 +1252,23 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 4 : 3) void k_adjoint(AdjArgs
                 ? (double)((const float*)a.rS)[(int64_t)cd.slot * a.max_lines + p] * exp(a.sb[cd.slot])
                 : ((const double*)a.rS)[(int64_t)cd.slot * a.max_lines + p];
         on = S != 0.0;
+      }
+      // with tile expansions the lines of all but the edge cells split their
+      // windows: the near leaves point by point, the rest through tiles
+      int f = 0, kc = 0;
+      bool split = false;
+      if (use_far && on) {
+        kc = a.rkc[p];
+        f = kc >> cd.far.sh;
+        split = f >= 1 && f <= cd.far.n_fine - 2;
+        if (!FAR && split) {
+          int32_t n0, n1;
+          far_near(cd.far, f, n0, n1);
+          klo = max(klo, (int64_t)n0 << cd.far.sh);
+          khi = min(khi, ((int64_t)(n1 + 1) << cd.far.sh) - 1);
+          on = klo <= khi;
+        }
+        if (FAR) on = split;
       }
       if (__ballot(on) == 0) continue;
       const double alpha = (PROF == XS_GAUSSIAN) ? cd.hwhm : nu * cd.dop;
@@ -796,18 +1291,14 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 4 : 3) void k_adjoint(AdjArgs
       // the normal range whatever the loss's magnitude; the sums are
       // unscaled exactly in FP64.  (FP64: gs = 1.)
       double gs = 1.0, igs = 1.0;
-      if (sizeof(R) == 4) {
-        const double gm = __longlong_as_double((long long)a.gmax[c]);
-        if (gm > 0.0 && gm <= 1.7976931348623157e308) {
-          int e;
-          (void)frexp(gm, &e);
-          e = max(e, -1000);
-          gs = ldexp(1.0, -e);
-          igs = ldexp(1.0, e);
-        }
-      }
-      const Sums3 ws = window_sums<R, PROF>(on, klo, khi, nu, inv, y, a.g + (int64_t)c * m.n_bins, gs, m.nu0,
-                                            m.dnu, m.n_bins, s_g[wave]);
+      if (sizeof(R) == 4) gs = adj_scale(a.gmax, c, igs);
+      Sums3 ws;
+      if constexpr (FAR)
+        ws = far_window_sums<R, PROF, sizeof(R) == 4 ? 12 : 20, sizeof(R) == 4 ? 6 : 12>(a, cd, c, on, f, kc, (int)klo,
+                                                                                          (int)khi, nu, inv, y, gs);
+      else
+        ws = window_sums<R, PROF>(on, klo, khi, nu, inv, y, a.g + (int64_t)c * m.n_bins, gs, m.nu0, m.dnu, m.n_bins,
+                                  s_g[wave]);
       const double sA = ws.A * igs, sB = ws.B * igs, sC = ws.C * igs;
       // scale to the unit-area profile and its derivatives
       double A, B, C;
@@ -849,35 +1340,43 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 4 : 3) void k_adjoint(AdjArgs
       }
     }
     if (have) {
-      a.dls[i] = dls;
-      if (a.dgref) a.dgref[i] = dgr;
-      if (a.dnexp) a.dnexp[i] = dne;
+      if (FAR) {
+        a.fline[p] = dls;
+        a.fline[a.max_lines + p] = dgr;
+        a.fline[2 * a.max_lines + p] = dne;
+      } else {
+        const int32_t i = a.ridx[p];
+        a.dls[i] = dls;
+        if (a.dgref) a.dgref[i] = dgr;
+        if (a.dnexp) a.dnexp[i] = dne;
+      }
     }
   }
   __syncthreads();
   for (int c = threadIdx.x; c < m.n_cond; c += 256) {
     const double t = ((sdt[0][c] + sdt[1][c]) + sdt[2][c]) + sdt[3][c];
     const double q = ((sdp[0][c] + sdp[1][c]) + sdp[2][c]) + sdp[3][c];
-    a.part[((int64_t)c * 2 + 0) * gridDim.x + blockIdx.x] = t;
-    a.part[((int64_t)c * 2 + 1) * gridDim.x + blockIdx.x] = q;
+    const int64_t at = a.part0 + blockIdx.x;
+    a.part[((int64_t)c * 2 + 0) * a.n_part + at] = t;
+    a.part[((int64_t)c * 2 + 1) * a.n_part + at] = q;
   }
 }
 
-__global__ __launch_bounds__(256) void k_adj_final(const double* part, int n_cond, int nblk, double* dT,
-                                                   double* dP) {
-  __shared__ double sh[256];
-  const int c = blockIdx.x;
-  for (int which = 0; which < 2; ++which) {
-    double v = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += 256) v += part[((int64_t)c * 2 + which) * nblk + b];
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-      if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) (which ? dP : dT)[c] = sh[0];
-    __syncthreads();
+// Sum of the blocks' parts, in a fixed order.  One block per condition and
+// output; 1024 threads, since the parts (tens of thousands) come from memory.
+__global__ __launch_bounds__(1024) void k_adj_final(const double* part, int nblk, double* dT, double* dP) {
+  __shared__ double sh[16];
+  const int c = blockIdx.x, which = blockIdx.y;
+  const double* p = part + ((int64_t)c * 2 + which) * nblk;
+  double v = 0.0;
+  for (int b = threadIdx.x; b < nblk; b += 1024) v += p[b];
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = 0.0;
+    for (int w = 0; w < 16; ++w) s += sh[w];
+    (which ? dP : dT)[c] = s;
   }
 }
 
@@ -913,7 +1412,7 @@ __global__ __launch_bounds__(256) void k_gmax(const double* g, int64_t n_bins, u
 
 void launch_adjoint(const ModelDev& m, const Work& w, const StatesView& st, const LinesView& ln,
                     const double* g, double* dT, double* dP, double* dgref, double* dnexp,
-                    double* dls, int64_t n_lines, int adj_blocks, hipStream_t s) {
+                    double* dls, int64_t n_lines, int adj_blocks, int far_lmax, int end_min, hipStream_t s) {
   hipLaunchKernelGGL(k_zero3, dim3(2048), dim3(256), 0, s, dgref, dnexp, dls, n_lines, w.gmax, m.n_cond);
   if (m.prec == XS_FP32) {
     const int64_t gb = std::min<int64_t>((m.n_bins + 1023) / 1024, 512);
@@ -940,17 +1439,48 @@ void launch_adjoint(const ModelDev& m, const Work& w, const StatesView& st, cons
   a.dnexp = dnexp;
   a.dls = dls;
   a.part = w.adjpart;
-#define XS_A(R, P)                                                                      \
-  if (m.profile == P) {                                                                 \
-    hipLaunchKernelGGL((k_adjoint<R, P>), dim3(adj_blocks), dim3(256), 0, s, a);         \
+  a.far = far_lmax >= 0;
+  a.counter = w.counter;
+  a.rkc = w.rkc;
+  a.mom = w.far_rows;
+  a.cond_rows = w.far_cond_rows;
+  a.cut = w.cut_rows;
+  a.cut_rows = w.n_cut_rows;
+  if (a.far) {
+    int64_t waves = 0;
+    for (int l = 0; l <= far_lmax; ++l)
+      waves += far_wide(m.fine_sh, l) > 0 ? far_tiles(m.n_fine, l) : (m.n_bins + 63) / 64;
+    const dim3 mg((unsigned)((waves + 3) / 4), m.n_cond), cg((unsigned)far_tiles(m.n_fine, end_min), m.n_cond);
+    if (m.prec == XS_FP32) {
+      hipLaunchKernelGGL((k_adj_moments<float, 12>), mg, dim3(256), 0, s, a, far_lmax);
+      hipLaunchKernelGGL((k_adj_cut<float, 6>), cg, dim3(64), 0, s, a);
+    } else {
+      hipLaunchKernelGGL((k_adj_moments<double, 20>), mg, dim3(256), 0, s, a, far_lmax);
+      hipLaunchKernelGGL((k_adj_cut<double, 12>), cg, dim3(64), 0, s, a);
+    }
   }
+  a.fline = (double*)w.lpack;  // free after the record pass: 64 bytes per line
+  a.n_part = a.far ? 2 * adj_blocks : adj_blocks;
+#define XS_A(R, P, F) \
+  if (m.profile == P) hipLaunchKernelGGL((k_adjoint<R, P, F>), dim3(adj_blocks), dim3(256), 0, s, a);
+  if (a.far) {
+    a.part0 = adj_blocks;
+    if (m.prec == XS_FP32) {
+      XS_A(float, XS_LORENTZ, true) XS_A(float, XS_VOIGT, true)
+    } else {
+      XS_A(double, XS_LORENTZ, true) XS_A(double, XS_VOIGT, true)
+    }
+  }
+  a.part0 = 0;
   if (m.prec == XS_FP32) {
-    XS_A(float, XS_DOPPLER) XS_A(float, XS_GAUSSIAN) XS_A(float, XS_LORENTZ) XS_A(float, XS_VOIGT)
+    XS_A(float, XS_DOPPLER, false) XS_A(float, XS_GAUSSIAN, false) XS_A(float, XS_LORENTZ, false)
+    XS_A(float, XS_VOIGT, false)
   } else {
-    XS_A(double, XS_DOPPLER) XS_A(double, XS_GAUSSIAN) XS_A(double, XS_LORENTZ) XS_A(double, XS_VOIGT)
+    XS_A(double, XS_DOPPLER, false) XS_A(double, XS_GAUSSIAN, false) XS_A(double, XS_LORENTZ, false)
+    XS_A(double, XS_VOIGT, false)
   }
 #undef XS_A
-  hipLaunchKernelGGL(k_adj_final, dim3(m.n_cond), dim3(256), 0, s, w.adjpart, m.n_cond, adj_blocks, dT, dP);
+  hipLaunchKernelGGL(k_adj_final, dim3(m.n_cond, 2), dim3(1024), 0, s, w.adjpart, a.n_part, dT, dP);
 }
 
 }  // namespace xs

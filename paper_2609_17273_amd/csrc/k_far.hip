@@ -24,34 +24,10 @@
 //   sigma_k += sum over the levels of the expansion of k's tile.
 #include <algorithm>
 
-#include "far_nodes.h"
+#include "far_tables.h"
 #include "k_voigt.h"
 
 namespace xs {
-
-template <int P>
-struct FarNodes;
-template <>
-struct FarNodes<6> {
-  static constexpr double x[6] = XS_FAR_X6;
-};
-template <>
-struct FarNodes<12> {
-  static constexpr double x[12] = XS_FAR_X12;
-};
-template <>
-struct FarNodes<20> {
-  static constexpr double x[20] = XS_FAR_X20;
-};
-static __device__ const double kFarD6[6 * 6] = XS_FAR_D6;
-static __device__ const double kFarD12[12 * 12] = XS_FAR_D12;
-static __device__ const double kFarD20[20 * 20] = XS_FAR_D20;
-template <int P>
-__device__ __forceinline__ const double* far_dct() {
-  if constexpr (P == 6) return kFarD6;
-  else if constexpr (P == 12) return kFarD12;
-  else return kFarD20;
-}
 
 struct FarArgs {
   ModelDev m;

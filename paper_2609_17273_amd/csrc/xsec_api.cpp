@@ -216,6 +216,10 @@ bool far_capable(const xs_plan* p) {
          (pr == XS_LORENTZ || pr == XS_VOIGT || pr == XS_BIN_LORENTZ || pr == XS_BIN_VOIGT);
 }
 
+bool adjoint_capable(const xs_plan* p) {
+  return p->model.population == XS_LTE && p->model.profile < XS_BIN_DOPPLER;
+}
+
 // Points of a sort key as a power of two: the leaves of the tile expansions
 // where the plan can use them.
 int leaf_sh(const xs_plan* p) { return far_capable(p) ? (p->model.precision == XS_FP32 ? kLeafSh32 : kLeafSh64) : kFineSh; }
@@ -406,14 +410,19 @@ size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool wit
     x.item_target = item_target > 0 ? item_target : kItemsPerCU * (int64_t)std::max(1, p->n_cu);
     x.part = (double*)take(sizeof(double) * 2 * (size_t)x.item_target * 1024);
   }
-  x.far_rows = nullptr;
-  x.far_cond_rows = 0;
+  x.far_rows = x.cut_rows = nullptr;
+  x.far_cond_rows = x.n_cut_rows = 0;
   if (with_far && far_capable(p)) {
     x.far_cond_rows = far_rows_before((int32_t)cells, sh, far_levels_of_grid((int32_t)cells));
     x.far_rows = (double*)take(sizeof(double) * d.n_cond * (size_t)x.far_cond_rows * far_nodes(d.prec));
+    if (adjoint_capable(p)) {
+      // rows of whole tiles (the last one may pass the grid's end)
+      x.n_cut_rows = (p->grid.n_bins + kFarEndBins) / kCutRowBins;
+      x.cut_rows = (double*)take((size_t)(d.prec == XS_FP32 ? 4 * 6 : 8 * 12) * 2 * d.n_cond * (size_t)x.n_cut_rows);
+    }
   }
   x.stats = (unsigned long long*)take(8 * 8);
-  x.adjpart = with_adjoint ? (double*)take(sizeof(double) * d.n_cond * 2 * kAdjBlocksMax) : nullptr;
+  x.adjpart = with_adjoint ? (double*)take(sizeof(double) * d.n_cond * 2 * 2 * kAdjBlocksMax) : nullptr;
   x.gmax = (unsigned long long*)take(sizeof(unsigned long long) * d.n_cond);
   x.cut_class = (double*)take(sizeof(double) * d.n_cut_classes);
   x.cut_mult = (int32_t*)take(sizeof(int32_t) * d.n_cut_classes);
@@ -700,7 +709,7 @@ int xs_profile_adjoint(xs_plan* p, const xs_states* st, const xs_lines* ln, cons
   if (!g || !dT || !dP || !dls) return fail(XS_EINVAL, "adjoint: dL_dsigma, dL_dT, dL_dP and dL_dlog_scale are required");
   if (ln->n != p->last_lines_in) return fail(XS_EINVAL, "adjoint: lines differ from the prepared ones");
   launch_adjoint(p->md, kernel_work(p), view(st), view(ln), g, dT, dP, dgref, dnexp, dls, ln->n,
-                 p->tiling.adj_blocks, p->stream);
+                 p->tiling.adj_blocks, use_far(p) ? p->far_lmax : -1, p->far_end, p->stream);
   return hip_check(hipGetLastError(), "adjoint launch");
 }
 
@@ -716,7 +725,7 @@ int xs_cross_section_adjoint(xs_plan* p, const xs_states* st, const xs_lines* ln
   if (!g || !dT || !dP || !dls) return fail(XS_EINVAL, "adjoint: dL_dsigma, dL_dT, dL_dP and dL_dlog_scale are required");
   if ((rc = preprocess(p, st, ln))) return rc;
   launch_adjoint(p->md, kernel_work(p), view(st), view(ln), g, dT, dP, dgref, dnexp, dls, ln->n,
-                 p->tiling.adj_blocks, p->stream);
+                 p->tiling.adj_blocks, use_far(p) ? p->far_lmax : -1, p->far_end, p->stream);
   return hip_check(hipGetLastError(), "adjoint launch");
 }
 
@@ -1012,14 +1021,15 @@ int xs_plan_autotune(xs_plan* p, const xs_states* st, const xs_lines* ln, double
   if (!rc && p->model.population == XS_LTE && p->model.profile < XS_BIN_DOPPLER) {
     if ((rc = xs_plan_set_config(p, &best)) == XS_OK && !p->prepared) rc = preprocess(p, st, ln);
     const int cand[4] = {4096, 8192, 16384, 32768};
-    double* outs = (double*)p->w.lpack;  // 64 B per line: room for three gradients
+    // 64 B per line: room for three gradients after the far part's three
+    double* outs = (double*)p->w.lpack + 3 * p->max_lines;
     double* dTP = p->w.part;             // dL/dT, dL/dP
     float adj_best = 1e30f;
     for (int ci = 0; ci < 4 && !rc; ++ci) {
       float ms_best;
       time3([&]() {
         launch_adjoint(p->md, kernel_work(p), view(st), view(ln), sigma, dTP, dTP + p->conds.size(), outs,
-                       outs + ln->n, outs + 2 * ln->n, ln->n, cand[ci], p->stream);
+                       outs + ln->n, outs + 2 * ln->n, ln->n, cand[ci], use_far(p) ? p->far_lmax : -1, p->far_end, p->stream);
         return hip_check(hipGetLastError(), "adjoint launch");
       }, ms_best);
       if (!rc && ms_best < adj_best) {

@@ -155,8 +155,10 @@ struct Work {
   int64_t item_target;      // work items aimed at when tiles are split
   double* far_rows;         // [n_cond][far_cond_rows][nodes] expansion coefficients, or null
   int64_t far_cond_rows;
+  double* cut_rows;         // [n_cond][n_cut_rows][2][nodes] moments of the cotangent over parts of cut tiles
+  int64_t n_cut_rows;
   unsigned long long* stats;// [8]
-  double* adjpart;          // [n_cond][2][kAdjBlocksMax]
+  double* adjpart;          // [n_cond][2][2 kAdjBlocksMax]: the near and the far part's blocks
   unsigned long long* gmax; // [n_cond] max |dL/dsigma| per condition (bits; FP32 adjoint's scale)
   double* cut_class;        // [n_cut_classes] distinct cut-offs
   int32_t* cut_mult;        // [n_cut_classes] conditions sharing each cut-off
@@ -215,8 +217,10 @@ void launch_cooling(const ModelDev& m, const Work& w, const StatesView& st, cons
                     const double* T_dev, int32_t nT, double* W, double* Q, hipStream_t s);
 
 // ---- adjoint (k_adjoint.hip) ----
+// far_lmax, end_min: as launch_far's; far_lmax < 0: every window point by point
+constexpr int kCutRowBins = 16;  // grid points per row of Work::cut_rows
 void launch_adjoint(const ModelDev& m, const Work& w, const StatesView& st, const LinesView& ln,
                     const double* g, double* dT, double* dP, double* dgref, double* dnexp,
-                    double* dls, int64_t n_lines, int adj_blocks, hipStream_t s);
+                    double* dls, int64_t n_lines, int adj_blocks, int far_lmax, int end_min, hipStream_t s);
 
 }  // namespace xs

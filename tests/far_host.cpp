@@ -6,7 +6,8 @@ extern "C" {
 // tile (far[leaf]); through a tile that the window may cut (cut[leaf]); point
 // by point through the segments of the rows of row_leaves leaves
 // (direct[leaf]).  gap[leaf]: cells that are near the leaf; info: on, points of
-// a cut tile.
+// a cut tile, the near leaves of the cell, tiles missing from the candidates of
+// the cells [f, f + 2].
 int far_count(int64_t W, int64_t Wx, int32_t n_fine, int32_t sh, double g0, double g1, int32_t row_leaves, int32_t f,
               int32_t reach, int32_t* far, int32_t* cut, int32_t* direct, int32_t* gap, int32_t* info) {
   const FarCond c = far_make(W, Wx, n_fine, sh, g0, g1);
@@ -16,16 +17,25 @@ int far_count(int64_t W, int64_t Wx, int32_t n_fine, int32_t sh, double g0, doub
   }
   info[0] = c.on;
   info[1] = c.on ? 1 << (c.sh + c.end) : 0;
+  info[2] = info[3] = info[4] = 0;
+  if (c.on) far_near(c, f, info[2], info[3]);
   if (c.on)
     for (int l = 0; l <= c.lmax; ++l)
       for (int t = 0; t < far_tiles(n_fine, l); ++t) {
         CellRange r[4], e[2];
         far_tile_ranges(c, l, t, r);
+        const CellRange cand = far_candidates(c, l, f, f + 2);
+        for (auto& q : r)
+          if (q.lo <= q.hi && q.lo <= f + 2 && q.hi >= f && (t < cand.lo || t > cand.hi)) info[4]++;
         for (auto& q : r)
           if (q.lo <= f && f <= q.hi)
             for (int leaf = t << l; leaf < ((t + 1) << l) && leaf < n_fine; ++leaf) far[leaf]++;
         if (l != c.end) continue;
         far_cut(c, t, e);
+        CellRange cc[2];
+        far_cut_candidates(c, f, f + 2, cc);
+        for (int k = 0; k < 2; ++k)
+          if (e[k].lo <= e[k].hi && e[k].lo <= f + 2 && e[k].hi >= f && (t < cc[k].lo || t > cc[k].hi)) info[4]++;
         for (auto& q : e)
           if (q.lo <= f && f <= q.hi)
             for (int leaf = t << l; leaf < ((t + 1) << l) && leaf < n_fine; ++leaf) cut[leaf]++;

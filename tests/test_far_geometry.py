@@ -45,7 +45,7 @@ def test_every_leaf_once(far, W, nf, sh, g0, g1, on, row_points):
         if f < 0 or f >= nf:
             continue
         fr, cu, di, gap = (np.zeros(nf, np.int32) for _ in range(4))
-        info = np.zeros(2, np.int32)
+        info = np.zeros(5, np.int32)
         far.far_count(W, Wx, nf, sh, g0, g1, row_points >> sh, int(f), (Wx + n - 1) // n + 1, ptr(fr), ptr(cu),
                       ptr(di), ptr(gap), ptr(info))
         assert info[0] == on
@@ -61,6 +61,8 @@ def test_every_leaf_once(far, W, nf, sh, g0, g1, on, row_points):
         assert np.all(fr[~covered] == 0)
         near = np.abs(leaf - f) <= gap
         assert np.all((fr + cu)[near] == 0)
+        assert np.array_equal(near, (leaf >= info[2]) & (leaf <= info[3]))
+        assert info[4] == 0
         assert np.all(di[~near] == 0)
         # as many cells as the lines of the cell need
         assert np.all((gap >= g0 + g1 * f)[touched]) and np.all(gap >= 1)

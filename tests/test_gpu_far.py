@@ -85,3 +85,36 @@ def test_lines_that_are_not_finite():
     assert np.array_equal(np.isfinite(got), np.isfinite(ref))
     m = np.isfinite(ref)
     assert np.max(np.abs(got[m] - ref[m]) / ref[m]) <= TOL[FP64]
+
+
+@pytest.mark.parametrize("case", list(CASES))
+@pytest.mark.parametrize("prec", [FP64, FP32])
+@pytest.mark.parametrize("profile", [synth.LORENTZ, synth.VOIGT])
+def test_adjoint_against_points(profile, prec, case):
+    """The adjoint with expansions (a gather plan's) against point by point (a
+    scatter plan's).  Both sum the same terms; a term keeps about 3e-12 of
+    itself in the FP64 form and 3e-6 in the FP32 form, and cotangents of random
+    signs leave a gradient's norm at least a tenth of its terms' norm: 1e-10 and
+    1e-4 of the norm are asked for."""
+    import torch
+    P = X()
+    (nu0, dnu, n), conds = CASES[case]
+    wl = workload("voigt_1e7", n_states=20000, n_lines=30011, nu_hi=600.0, seed=4242)
+    ln = wl.lines()
+    ds, dl = gpu_inputs(wl, ln)
+    rng = np.random.default_rng(7)
+    g = torch.as_tensor(rng.standard_normal((len(conds), n)), device="cuda")
+    out = []
+    for algo in (0, 1):
+        plan = P.Plan(profile, 0, 0, prec, _Grid(nu0, dnu, n), conds, ln.n, mass_amu=wl.mass_amu, algo=algo)
+        r = plan.adjoint(ds, dl, g)
+        torch.cuda.synchronize()
+        out.append({k: v.cpu().numpy() for k, v in r.items()})
+        plan.close()
+    tol = {FP64: 1e-10, FP32: 1e-4}[prec]
+    for k in out[0]:
+        e = float(np.linalg.norm(out[0][k] - out[1][k]) / max(np.linalg.norm(out[1][k]), 1e-300))
+        log(f"[far adjoint] profile {profile} prec {prec} {case} {k}: {e:.2e}")
+        assert np.all(np.isfinite(out[0][k]))
+        assert e <= tol
+        assert np.array_equal(out[0][k] == 0.0, out[1][k] == 0.0)
