@@ -156,10 +156,11 @@ XS_HD void far_segments(const FarCond& c, int32_t a, int32_t b, int32_t clo, int
   s[2] = chi == last ? CellRange{last, last} : CellRange{0, -1};
 }
 
-// Waves and rows.  A tile of 64 points or fewer is one wave's, one of 2^j
-// times 64 points takes 2^j waves, up to the eight of a block; above that the
-// tile's lines are cut into slices, a block and a row of coefficients each, so
-// that no wave takes more than eight times another's share.
+// Waves and rows.  A tile of 64 points or fewer is one wave's, one of 128 takes
+// two, wider ones a block's four; above 512 points the tile's lines are cut
+// into slices, a block and a row of coefficients each, so that no wave takes
+// more than four times another's share.  (Blocks of four waves: one of eight
+// fits a compute unit only once at three waves per SIMD.)
 XS_HD int far_wide(int sh, int l) { return far_max(0, l + sh - 6); }  // log2 of points / 64, at least 0
 XS_HD int32_t far_slices(int sh, int l) { return far_wide(sh, l) > 3 ? 1 << (far_wide(sh, l) - 3) : 1; }
 XS_HD int64_t far_rows_before(int32_t n_fine, int sh, int l) {
@@ -173,10 +174,10 @@ XS_HD int far_levels_of_grid(int32_t n_fine) {
   while (l < kFarLevels && (n_fine >> l) >= 3) ++l;
   return l;
 }
-// blocks of a level: 8 >> far_wide tiles each, or one slice of one tile
+// blocks of a level: 4 >> far_wide tiles each, or one slice of one tile
 XS_HD int32_t far_blocks(int32_t n_fine, int sh, int l) {
   const int w = far_wide(sh, l);
-  return w < 3 ? (far_tiles(n_fine, l) + (8 >> w) - 1) / (8 >> w) : far_tiles(n_fine, l) * far_slices(sh, l);
+  return w < 2 ? (far_tiles(n_fine, l) + (4 >> w) - 1) / (4 >> w) : far_tiles(n_fine, l) * far_slices(sh, l);
 }
 
 // The far field of one condition: windows surely reach W points to each side

@@ -15,7 +15,7 @@
 // ends and sigma 0.78); 1e6 lines, FP64 form 3.33 and 2.1 ms; 48 conditions of
 // 1e6 lines, 2e5 points, FP32 form 113.2 and 13.0 ms.
 //
-// k_far: one wave (2^l waves for a tile of level l, up to eight, then slices)
+// k_far: one wave (up to four for wider tiles, then slices of their lines)
 //   takes 64 lines at a time, one per lane, evaluates each at the tile's nodes
 //   into P registers of the lane, and adds the lanes once at the end, so a
 //   visit costs neither LDS traffic nor cross-lane sums per line.  The sums
@@ -258,21 +258,39 @@ struct FarLine {
   Real a, xc, y, c0;
   bool live;
 };
+template <typename Real>
+struct FarIn {
+  int kc;
+  Real S;
+  float gr, ne, del;
+  double gp, nu;
+};
+template <typename Real>
+__device__ __forceinline__ FarIn<Real> far_load(const FarArgs& g, const CondDev& cd, uint32_t p) {
+  FarIn<Real> in;
+  in.kc = g.rkc[p];
+  in.S = ((const Real*)g.rS)[(int64_t)cd.slot * g.max_lines + p];
+  in.gr = g.rgref[p];
+  in.ne = g.rnexp[p];
+  in.gp = g.rgpre ? g.rgpre[p] : 0.0;
+  in.nu = g.rnu[p];
+  in.del = sizeof(Real) == 4 ? g.rdel[p] : 0.0f;
+  return in;
+}
 template <typename Real, int PROF>
-__device__ __forceinline__ FarLine<Real> far_load(const FarArgs& g, const CondDev& cd, uint32_t p, bool in, int ts,
-                                                  Real mid) {
+__device__ __forceinline__ FarLine<Real> far_line(const FarArgs& g, const CondDev& cd, const FarIn<Real>& v, bool in,
+                                                  int ts, Real mid) {
   const ModelDev& m = g.m;
-  const int kc = g.rkc[p];
-  const Real S = ((const Real*)g.rS)[(int64_t)cd.slot * g.max_lines + p];
-  const float gr = g.rgref[p], ne = g.rnexp[p];
-  const double gp = g.rgpre ? g.rgpre[p] : 0.0;
-  const double nu = g.rnu[p];
+  const int kc = v.kc;
+  const Real S = v.S;
+  const float gr = v.gr, ne = v.ne;
+  const double gp = v.gp, nu = v.nu;
   FarLine<Real> L;
   L.live = in && S != (Real)0;
   L.y = 0;
   Real inv, del;
   if constexpr (sizeof(Real) == 4) {
-    del = g.rdel[p];
+    del = v.del;
     const float gamma = fmaf(gr * __builtin_amdgcn_exp2f(ne * (float)(cd.lnTr / kLN2)), (float)cd.pfac, (float)gp);
     if constexpr (PROF == XS_LORENTZ || PROF == XS_BIN_LORENTZ) {
       inv = rcp32(gamma);
@@ -289,11 +307,11 @@ __device__ __forceinline__ FarLine<Real> far_load(const FarArgs& g, const CondDe
     const double gamma = (double)gr * exp((double)ne * cd.lnTr) * cd.pfac + gp;
     if constexpr (PROF == XS_LORENTZ || PROF == XS_BIN_LORENTZ) {
       inv = 1.0 / gamma;
-      L.c0 = PROF == XS_LORENTZ ? S / (kPI * gamma) : S / (kPI * m.dnu);
+      L.c0 = PROF == XS_LORENTZ ? S * inv * (1.0 / kPI) : S * (1.0 / (kPI * m.dnu));
     } else {
-      inv = sqrt(kLN2) / (nu * cd.dop);
+      inv = sqrt(kLN2) * rcp64(nu * cd.dop);
       L.y = gamma * inv;
-      L.c0 = PROF == XS_VOIGT ? S * inv * (1.0 / sqrt(kPI)) : S / (sqrt(kPI) * m.dnu);
+      L.c0 = PROF == XS_VOIGT ? S * inv * (1.0 / sqrt(kPI)) : S * (1.0 / (sqrt(kPI) * m.dnu));
     }
   }
   if (!L.live) {
@@ -305,9 +323,22 @@ __device__ __forceinline__ FarLine<Real> far_load(const FarArgs& g, const CondDe
   return L;
 }
 
+// The lane's value moved by a data-parallel-primitive control word (within its
+// row of 16 lanes; 0 where no lane of the row is the source).
+template <int CTRL>
+__device__ __forceinline__ double far_dpp(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+constexpr int kDppShl = 0x100, kDppShr = 0x110;  // + n: from n lanes further on, further back
+
 // Sum of v[0..P) over the wave's lanes: halves of the values are exchanged at
-// the first two steps (35 adds for P = 20 instead of 120).  Afterwards the
-// lane holds P / 4 sums, those of the values far_slot(lane) + i.
+// the first two steps (35 adds for P = 20 instead of 120), the rows of 16
+// lanes add up without the LDS.  Afterwards the lane holds P / 4 sums, those
+// of the values far_slot(lane) + i.
 template <int P>
 __device__ __forceinline__ void far_fold(double (&v)[P], int lane) {
   static_assert(P % 4 == 0, "folded in quarters");
@@ -323,9 +354,12 @@ __device__ __forceinline__ void far_fold(double (&v)[P], int lane) {
     v[i] = keep + __shfl_xor(send, 16, 64);
   }
 #pragma unroll
-  for (int o = 8; o > 0; o >>= 1)
-#pragma unroll
-    for (int i = 0; i < P / 4; ++i) v[i] += __shfl_xor(v[i], o, 64);
+  for (int i = 0; i < P / 4; ++i) {
+    v[i] += far_dpp<kDppXor1>(v[i]);
+    v[i] += far_dpp<kDppXor2>(v[i]);
+    v[i] += far_dpp<kDppHalfMirror>(v[i]);
+    v[i] += far_dpp<kDppMirror>(v[i]);
+  }
 }
 template <int P>
 __device__ __forceinline__ int far_slot(int lane) {
@@ -333,9 +367,9 @@ __device__ __forceinline__ int far_slot(int lane) {
 }
 
 template <typename Real, int PROF, int P>
-__global__ __launch_bounds__(512, sizeof(Real) == 4 ? 4 : 3) void k_far(FarArgs g) {
+__global__ __launch_bounds__(256, sizeof(Real) == 4 ? 4 : 3) void k_far(FarArgs g) {
   constexpr bool F32 = sizeof(Real) == 4;
-  __shared__ double sv[8][P], st[8][P];
+  __shared__ double sv[4][P], st[4][P];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = blockIdx.y;
@@ -352,9 +386,9 @@ __global__ __launch_bounds__(512, sizeof(Real) == 4 ? 4 : 3) void k_far(FarArgs 
     b -= nb;
   }
   if (l < 0) return;
-  const int lw = min(far_wide(fc.sh, l), 3), nw = 1 << lw, sl = far_slices(fc.sh, l);
-  const int t = lw < 3 ? (b << (3 - lw)) + (wave >> lw) : b / sl;
-  const int slice = lw < 3 ? 0 : b % sl;
+  const int lw = min(far_wide(fc.sh, l), 2), nw = 1 << lw, sl = far_slices(fc.sh, l);
+  const int t = lw < 2 ? (b << (2 - lw)) + (wave >> lw) : b / sl;
+  const int slice = lw < 2 ? 0 : b % sl;
   // positions of the tile's lines: up to four ranges of sorted lines
   CellRange r[4];
   far_tile_ranges(fc, l, t, r);
@@ -379,11 +413,17 @@ __global__ __launch_bounds__(512, sizeof(Real) == 4 ? 4 : 3) void k_far(FarArgs 
   const Real half = (Real)(1 << (l + fc.sh)) * (Real)0.5, mid = half - (Real)0.5;
   const uint32_t stride = (uint32_t)(nw * sl) * 64u;
   int since = 0;
-  for (uint32_t q0 = (uint32_t)((wave & (nw - 1)) + slice * nw) * 64u; q0 < total; q0 += stride) {
-    const bool in = q0 + lane < total;
-    const uint32_t q = in ? q0 + lane : total - 1;
-    const uint32_t p = q + (q < cum[0] ? beg[0] : q < cum[1] ? beg[1] : q < cum[2] ? beg[2] : beg[3]);
-    const FarLine<Real> L = far_load<Real, PROF>(g, cd, p, in, ts, mid);
+  auto at = [&](uint32_t q0) {
+    const uint32_t q = min(q0 + lane, total - 1);
+    return q + (q < cum[0] ? beg[0] : q < cum[1] ? beg[1] : q < cum[2] ? beg[2] : beg[3]);
+  };
+  uint32_t q0 = (uint32_t)((wave & (nw - 1)) + slice * nw) * 64u;
+  FarIn<Real> next;
+  if (q0 < total) next = far_load<Real>(g, cd, at(q0));
+  for (; q0 < total; q0 += stride) {
+    const FarIn<Real> cur = next;
+    if (q0 + stride < total) next = far_load<Real>(g, cd, at(q0 + stride));  // a batch ahead of its use
+    const FarLine<Real> L = far_line<Real, PROF>(g, cd, cur, q0 + lane < total, ts, mid);
     if constexpr (F32) {
       far_line_f32<PROF, P>(L.xc, half * L.a, L.a, L.y, L.c0, L.live, acc);
       if (++since == 32) {
@@ -413,7 +453,7 @@ __global__ __launch_bounds__(512, sizeof(Real) == 4 ? 4 : 3) void k_far(FarArgs 
   }
   __syncthreads();
   // the tile's waves, then node values to coefficients
-  const int tid = threadIdx.x, tiles = 8 >> lw;
+  const int tid = threadIdx.x, tiles = 4 >> lw;
   if (tid < tiles * P) {
     const int tg = tid / P, q = tid - tg * P;
     double v = 0.0;
@@ -423,7 +463,7 @@ __global__ __launch_bounds__(512, sizeof(Real) == 4 ? 4 : 3) void k_far(FarArgs 
   __syncthreads();
   if (tid < tiles * P) {
     const int tg = tid / P, k = tid - tg * P;
-    const int tt = lw < 3 ? (b << (3 - lw)) + tg : t;
+    const int tt = lw < 2 ? (b << (2 - lw)) + tg : t;
     if (tt < far_tiles(nf, l)) {
       const double* D = far_dct<P>();
       double v = 0.0;
@@ -435,16 +475,19 @@ __global__ __launch_bounds__(512, sizeof(Real) == 4 ? 4 : 3) void k_far(FarArgs 
   }
 }
 
-// The tiles that window ends cut, and sigma.  One wave per tile of level
-// `end` and condition.  A line whose window ends inside the tile adds its
-// values at PE nodes to the LDS row of its last (first) point; the sum of the
-// rows of all points from k upwards (downwards) is then, at point k, the
+// The tiles that window ends cut, and sigma.  One block of four waves per tile
+// of level `end` and condition.  A line whose window ends inside the tile adds
+// its values at PE nodes to the LDS row of its last (first) point; the sum of
+// the rows of all points from k upwards (downwards) is then, at point k, the
 // nodes' values of exactly the lines that reach k, so a cut costs a line PE
 // evaluations instead of one per point.  (PE = 12, FP64 form, and 6: the tile
-// is at least 17 half-widths away, where these keep 1.3e-14 and 1e-8.)  The
-// row is the wave's own and its lanes add in a fixed order.  Then the
-// expansions of the tiles of every level are added (Clenshaw's recurrence)
-// and sigma is updated once.
+// is at least 17 half-widths away, where these keep 1.3e-14 and 1e-8.)  One
+// wave takes the upper ends and one the lower ends, each with rows of its own
+// and its lanes adding in a fixed order; then every thread has a point, sums
+// the rows (16 points at a time in registers, then the groups) and adds the
+// expansions of the tiles of every level (Clenshaw's recurrence), and sigma is
+// updated once.  (On one wave its chains of sums are exposed: 0.30 ms against 0.20 on 1e6
+// lines FP64, 2e6 points; 0.79 against 0.27 on 1e7 lines FP32.)
 template <int P>
 __device__ __forceinline__ double far_clenshaw(const double (&co)[P], double x) {
   const double x2 = 2.0 * x;
@@ -473,40 +516,54 @@ __device__ __forceinline__ double far_clenshaw_slope(const double (&co)[P], doub
   return b1;
 }
 
-constexpr int kFarEndPer = kFarEndBins / 64;  // most points of a lane
-
 template <typename Real, int PROF, int P, int PE>
-__global__ __launch_bounds__(64) void k_far_finish(FarArgs g) {
+__global__ __launch_bounds__(256) void k_far_finish(FarArgs g) {
   constexpr bool F32 = sizeof(Real) == 4;
-  __shared__ double row[PE * kFarEndBins];  // FP64 in both forms: FP32 adds to LDS are several times slower
-  const int lane = threadIdx.x, c = blockIdx.y, t = blockIdx.x;
+  // FP64 rows in both forms: FP32 adds to LDS are several times slower
+  __shared__ double row[2][PE * kFarEndBins];
+  __shared__ double tot[2][kFarEndBins / 16][PE];
+  const int tid = threadIdx.x, lane = tid & 63, c = blockIdx.y, t = blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const CondDev& cd = g.cond[c];
   const FarCond& fc = cd.far;
   if (!fc.on || g.counter[kFarOff]) return;
   const ModelDev& m = g.m;
-  const int nf = m.n_fine, e = fc.end, n = 1 << (e + fc.sh), nb = n >> 6;
+  const int nf = m.n_fine, e = fc.end, n = 1 << (e + fc.sh);
   if (t >= far_tiles(nf, e)) return;
   const int ts = t * n;
   const Real half = (Real)n * (Real)0.5, mid = half - (Real)0.5;
-  double v[kFarEndPer];  // the lane's points ts + lane nb + i
-#pragma unroll
-  for (int i = 0; i < kFarEndPer; ++i) v[i] = 0.0;
   CellRange cut[2];
   far_cut(fc, t, cut);
-  for (int side = 0; side < 2; ++side) {
-    if (cut[side].lo > cut[side].hi) continue;
-    const int64_t p0 = g.off[cut[side].lo], p1 = g.off[cut[side].hi + 1];
-    if (p0 >= p1) continue;
-    __syncthreads();
-    for (int i = lane; i < PE * n; i += 64) row[i] = 0.0;
-    __syncthreads();
-    for (int64_t q0 = p0; q0 < p1; q0 += 64) {
-      const int64_t p = min(q0 + lane, p1 - 1);
-      const int2 win = ((const int2*)g.rwin)[(int64_t)cd.cclass * g.max_lines + p];
+  int64_t p0[2], p1[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const bool any = cut[s].lo <= cut[s].hi;
+    p0[s] = any ? g.off[cut[s].lo] : 0;
+    p1[s] = any ? g.off[cut[s].hi + 1] : 0;
+    if (p0[s] < p1[s])
+      for (int i = tid; i < PE * n; i += 256) row[s][i] = 0.0;
+  }
+  __syncthreads();
+  if (wave < 2) {
+    const int side = wave;
+    double* rw = row[side];
+    const int64_t a0 = side == 0 ? p0[0] : p0[1], a1 = side == 0 ? p1[0] : p1[1];
+    FarIn<Real> next;
+    int2 nwin = {0, -1};
+    auto fetch = [&](int64_t q0) {
+      const int64_t p = min(q0 + lane, a1 - 1);
+      nwin = ((const int2*)g.rwin)[(int64_t)cd.cclass * g.max_lines + p];
+      next = far_load<Real>(g, cd, (uint32_t)p);
+    };
+    if (a0 < a1) fetch(a0);
+    for (int64_t q0 = a0; q0 < a1; q0 += 64) {
+      const FarIn<Real> cur = next;
+      const int2 win = nwin;
+      if (q0 + 64 < a1) fetch(q0 + 64);
       // the last (side 0) or first (side 1) point of the window in the tile
       const int j = side == 0 ? min(win.y - ts, n - 1) : max(win.x - ts, 0);
-      const bool in = q0 + lane < p1 && win.x <= win.y && (side == 0 ? j >= 0 : j < n);
-      const FarLine<Real> L = far_load<Real, PROF>(g, cd, (uint32_t)p, in, ts, mid);
+      const bool in = q0 + lane < a1 && win.x <= win.y && (side == 0 ? j >= 0 : j < n);
+      const FarLine<Real> L = far_line<Real, PROF>(g, cd, cur, in, ts, mid);
       Real acc[PE];
 #pragma unroll
       for (int q = 0; q < PE; ++q) acc[q] = (Real)0;
@@ -514,79 +571,89 @@ __global__ __launch_bounds__(64) void k_far_finish(FarArgs g) {
       else far_line_f64<PROF, PE>(L.xc, half * L.a, L.a, L.y, L.c0, L.live, acc);
       if (L.live)
 #pragma unroll
-        for (int q = 0; q < PE; ++q) atomicAdd(&row[q * n + j], (double)acc[q]);
+        for (int q = 0; q < PE; ++q) atomicAdd(&rw[q * n + j], (double)acc[q]);
+    }
+  }
+  __syncthreads();
+  const bool own = tid < n;  // whole waves: n is 64, 128 or 256
+  double sum = 0.0;
+#pragma unroll
+  for (int side = 0; side < 2; ++side) {
+    if (p0[side] >= p1[side]) continue;  // the block's
+    double s[PE];
+    if (own) {
+#pragma unroll
+      for (int q = 0; q < PE; ++q) {
+        double v = row[side][q * n + tid];
+        if (side == 0) {
+          v += far_dpp<kDppShl + 1>(v);
+          v += far_dpp<kDppShl + 2>(v);
+          v += far_dpp<kDppShl + 4>(v);
+          v += far_dpp<kDppShl + 8>(v);
+        } else {
+          v += far_dpp<kDppShr + 1>(v);
+          v += far_dpp<kDppShr + 2>(v);
+          v += far_dpp<kDppShr + 4>(v);
+          v += far_dpp<kDppShr + 8>(v);
+        }
+        s[q] = v;
+        if ((tid & 15) == (side == 0 ? 0 : 15)) tot[side][tid >> 4][q] = v;
+      }
     }
     __syncthreads();
-    // sums over the other lanes' points on the far side of this lane's
-    double run[PE];
-#pragma unroll
-    for (int q = 0; q < PE; ++q) {
-      double own = 0.0;
-      for (int i = 0; i < nb; ++i) own += row[q * n + lane * nb + i];
-      double s = own;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const double w = side == 0 ? __shfl_down(s, o, 64) : __shfl_up(s, o, 64);
-        s += (side == 0 ? lane + o < 64 : lane >= o) ? w : 0.0;
+    if (tid < PE) {  // groups beyond (before) each group
+      double run = 0.0;
+      for (int h = 0; h < n / 16; ++h) {
+        const int gr = side == 0 ? n / 16 - 1 - h : h;
+        const double v = tot[side][gr][tid];
+        tot[side][gr][tid] = run;
+        run += v;
       }
-      run[q] = s - own;
     }
-    const double* D = far_dct<PE>();
-#pragma unroll
-    for (int ii = 0; ii < kFarEndPer; ++ii) {
-      if (ii >= nb) break;
-      const int i = side == 0 ? nb - 1 - ii : ii;
+    __syncthreads();
+    if (own) {
+      const double* D = far_dct<PE>();
       double co[PE];
 #pragma unroll
       for (int k = 0; k < PE; ++k) co[k] = 0.0;
 #pragma unroll
       for (int q = 0; q < PE; ++q) {
-        run[q] += row[q * n + lane * nb + i];
+        const double v = s[q] + tot[side][tid >> 4][q];
 #pragma unroll
-        for (int k = 0; k < PE; ++k) co[k] = fma(D[q * PE + k], run[q], co[k]);
+        for (int k = 0; k < PE; ++k) co[k] = fma(D[q * PE + k], v, co[k]);
       }
-      const double x = ((double)(lane * nb + i) - ((double)half - 0.5)) / (double)half;
-      const double y = far_clenshaw<PE>(co, x);
-#pragma unroll
-      for (int k = 0; k < kFarEndPer; ++k) v[k] += k == i ? y : 0.0;
+      sum += far_clenshaw<PE>(co, ((double)tid - ((double)half - 0.5)) / (double)half);
     }
   }
-  // the levels' expansions: leaf by leaf, the lane at the leaf's point `lane`
-  __syncthreads();
-  double* pts = row;
+  if (!own) return;
+  const int k = ts + tid;
+  if (k - lane >= m.n_bins) return;
+  double slope = 0.0;  // FP64 form: in units of 1 / dnu
+  int64_t before = 0;
+  for (int l = 0; l <= fc.lmax; ++l) {
+    // tiles of 64 points or more hold all of the wave's points: their
+    // coefficients are the wave's (scalar loads)
+    const int lg = l + fc.sh, sl = far_slices(fc.sh, l);
+    const int tl = lg >= 6 ? __builtin_amdgcn_readfirstlane(k >> lg) : min(k >> lg, far_tiles(nf, l) - 1);
+    const double* r = g.rows + ((int64_t)c * g.cond_rows + before + (int64_t)tl * sl) * P;
+    before += (int64_t)far_tiles(nf, l) * sl;
+    double co[P];
 #pragma unroll
-  for (int i = 0; i < kFarEndPer; ++i)
-    if (i < nb) pts[lane * nb + i] = v[i];
-  __syncthreads();
-  const double scale = F32 ? exp(g.sb[cd.slot]) : 1.0;
-  for (int i = 0; i < nb; ++i) {
-    const int k = ts + i * 64 + lane;
-    if (k - lane >= m.n_bins) break;
-    double sum = pts[i * 64 + lane];
-    double slope = 0.0;  // FP64 form: in units of 1 / dnu
-    int64_t before = 0;
-    for (int l = 0; l <= fc.lmax; ++l) {
-      // tiles of 64 points or more hold all of the wave's points: their
-      // coefficients are the wave's (scalar loads)
-      const int lg = l + fc.sh, sl = far_slices(fc.sh, l);
-      const int tl = lg >= 6 ? __builtin_amdgcn_readfirstlane(k >> lg) : min(k >> lg, far_tiles(nf, l) - 1);
-      const double* r = g.rows + ((int64_t)c * g.cond_rows + before + (int64_t)tl * sl) * P;
-      before += (int64_t)far_tiles(nf, l) * sl;
-      double co[P];
+    for (int q = 0; q < P; ++q) co[q] = r[q];
+    for (int s = 1; s < sl; ++s)
 #pragma unroll
-      for (int q = 0; q < P; ++q) co[q] = r[q];
-      for (int s = 1; s < sl; ++s)
-#pragma unroll
-        for (int q = 0; q < P; ++q) co[q] += r[s * P + q];
-      // the point in the tile's variable: (k - centre) / half width
-      const double hw = 0.5 * (double)(1 << lg);
-      const double x = ((double)(k - (tl << lg)) - (hw - 0.5)) / hw;
-      sum += far_clenshaw<P>(co, x);
-      if constexpr (!F32) slope = fma(far_clenshaw_slope<P>(co, x), 1.0 / hw, slope);
-    }
-    // from the exact grid point to the rounded one
-    if constexpr (!F32) sum = fma(slope, -far_grid_residue(m.nu0, m.dnu, k) / m.dnu, sum);
-    if (k < m.n_bins) g.sigma[(int64_t)c * m.n_bins + k] += scale * sum;
+      for (int q = 0; q < P; ++q) co[q] += r[s * P + q];
+    // the point in the tile's variable: (k - centre) / half width
+    const double hw = 0.5 * (double)(1 << lg);
+    const double x = ((double)(k - (tl << lg)) - (hw - 0.5)) / hw;
+    sum += far_clenshaw<P>(co, x);
+    if constexpr (!F32) slope = fma(far_clenshaw_slope<P>(co, x), 1.0 / hw, slope);
+  }
+  // from the exact grid point to the rounded one
+  if constexpr (!F32) sum = fma(slope, -far_grid_residue(m.nu0, m.dnu, k) / m.dnu, sum);
+  if (k < m.n_bins) {
+    const double scale = F32 ? exp(g.sb[cd.slot]) : 1.0;
+    g.sigma[(int64_t)c * m.n_bins + k] += scale * sum;
   }
 }
 
@@ -616,11 +683,11 @@ void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, dou
   const dim3 grid((unsigned)blocks, m.n_cond), fin((unsigned)far_tiles(m.n_fine, end_min), m.n_cond);
 #define XS_F(PR)                                                                                       \
   if (m.profile == PR && m.prec == XS_FP32) {                                                          \
-    hipLaunchKernelGGL((k_far<float, PR, 12>), grid, dim3(512), 0, s, a);                              \
-    hipLaunchKernelGGL((k_far_finish<float, PR, 12, 6>), fin, dim3(64), 0, s, a);                      \
+    hipLaunchKernelGGL((k_far<float, PR, 12>), grid, dim3(256), 0, s, a);                              \
+    hipLaunchKernelGGL((k_far_finish<float, PR, 12, 6>), fin, dim3(256), 0, s, a);                     \
   } else if (m.profile == PR) {                                                                        \
-    hipLaunchKernelGGL((k_far<double, PR, 20>), grid, dim3(512), 0, s, a);                             \
-    hipLaunchKernelGGL((k_far_finish<double, PR, 20, 12>), fin, dim3(64), 0, s, a);                    \
+    hipLaunchKernelGGL((k_far<double, PR, 20>), grid, dim3(256), 0, s, a);                             \
+    hipLaunchKernelGGL((k_far_finish<double, PR, 20, 12>), fin, dim3(256), 0, s, a);                   \
   }
   XS_F(XS_VOIGT) XS_F(XS_LORENTZ) XS_F(XS_BIN_VOIGT) XS_F(XS_BIN_LORENTZ)
 #undef XS_F

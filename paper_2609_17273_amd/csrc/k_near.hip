@@ -4,7 +4,8 @@
 // k_far's.
 //
 // A block of four waves owns 256 grid points of one condition and takes the
-// lines whose near leaves meet them, 64 at a time and one per lane.  A lane
+// lines whose near leaves meet them, 64 at a time and one per lane (2^ks lanes
+// where there are few).  A lane
 // walks its own line's points region by region -- the core first, where the
 // rational approximation of w is needed, then the rings where six, four,
 // three, two or one node pairs serve -- and adds each value to the wave's row
@@ -132,17 +133,27 @@ constexpr int kNearPart = kNearBins / 4 + 16;
 constexpr int kNearRow = 4 * kNearPart;
 __device__ __forceinline__ int near_place(int o) { return (o & 3) * kNearPart + (o >> 2); }
 
-// k in [lo, hi] but not in [slo, shi]: lane's points, from its own place on.
+// The lanes of a line: 2^ks of them, this one the sub-th of the slot-th line of
+// the wave.  Lane sub takes every 2^ks-th point, from its own place on.
+struct NearLane {
+  int slot, sub, ks;
+};
+__device__ __forceinline__ int near_count(const NearLane& ln, int n) {
+  return n > ln.sub ? (n - ln.sub + (1 << ln.ks) - 1) >> ln.ks : 0;
+}
+__device__ __forceinline__ int near_first(const NearLane& ln, int cnt) { return (ln.slot * cnt << ln.ks) >> 6; }
+
+// k in [lo, hi] but not in [slo, shi]: the lane's points.
 struct Ring {
   int lo, hi, slo, shi;
 };
 template <typename F>
-__device__ __forceinline__ void near_sweep(const Ring& r, int lane, double* row, int tlo, F value) {
+__device__ __forceinline__ void near_sweep(const Ring& r, const NearLane& ln, double* row, int tlo, F value) {
   const int skip = max(0, r.shi - r.slo + 1);
-  const int n = r.hi - r.lo + 1 - skip;
-  int i = n > 0 ? (lane * n) >> 6 : 0;
+  const int n = near_count(ln, r.hi - r.lo + 1 - skip);
+  int i = near_first(ln, n);
   for (int it = 0; it < n; ++it) {
-    int k = r.lo + i;
+    int k = r.lo + (i << ln.ks) + ln.sub;
     if (skip && k >= r.slo) k += skip;
     atomicAdd(&row[near_place(k - tlo)], value(k));
     i = i + 1 == n ? 0 : i + 1;
@@ -168,12 +179,12 @@ __device__ __forceinline__ void near_range(R X, R a, R b, int kc, int klo, int k
 // As near_sweep over groups of four points k0..k0+3 (k0 a multiple of four):
 // every ring edge lies between groups.  value4 fills the four values.
 template <typename F>
-__device__ __forceinline__ void near_sweep4(const Ring& r, int lane, double* row, int tlo, F value4) {
+__device__ __forceinline__ void near_sweep4(const Ring& r, const NearLane& ln, double* row, int tlo, F value4) {
   const int glo = (r.lo - tlo) >> 2, skip = max(0, r.shi - r.slo + 1) >> 2, gs = (r.slo - tlo) >> 2;
-  const int n = ((r.hi - r.lo + 1) >> 2) - skip;
-  int i = n > 0 ? (lane * n) >> 6 : 0;
+  const int n = near_count(ln, ((r.hi - r.lo + 1) >> 2) - skip);
+  int i = near_first(ln, n);
   for (int it = 0; it < n; ++it) {
-    int gr = glo + i;
+    int gr = glo + (i << ln.ks) + ln.sub;
     if (skip && gr >= gs) gr += skip;
     double v[4];
     value4(tlo + 4 * gr, v);
@@ -194,7 +205,7 @@ __device__ __forceinline__ void near_align(int& lo, int& hi) {
 
 // One lane's line over its points [klo, khi] of the tile.
 template <int PROF>
-__device__ __forceinline__ void near_line_f32(const ModelDev& m, const CondDev& cd, int lane, int kc, int klo, int khi,
+__device__ __forceinline__ void near_line_f32(const ModelDev& m, const CondDev& cd, const NearLane& lane, int kc, int klo, int khi,
                                               float del, float nu, float S, float gref, float nexp, float gpre,
                                               double* row, int tlo) {
   const float gamma = fmaf(gref * __builtin_amdgcn_exp2f(nexp * (float)(cd.lnTr / kLN2)), (float)cd.pfac, gpre);
@@ -291,7 +302,7 @@ __device__ __forceinline__ void near_line_f32(const ModelDev& m, const CondDev& 
 }
 
 template <int PROF>
-__device__ __forceinline__ void near_line_f64(const ModelDev& m, const CondDev& cd, int lane, int kc, int klo, int khi,
+__device__ __forceinline__ void near_line_f64(const ModelDev& m, const CondDev& cd, const NearLane& lane, int kc, int klo, int khi,
                                               double nu, double S, double gref, double nexp, double gpre,
                                               double* row, int tlo) {
   const double gamma = gref * exp(nexp * cd.lnTr) * cd.pfac + gpre;
@@ -429,8 +440,12 @@ __global__ __launch_bounds__(256) void k_near(NearArgs g) {
 #pragma unroll
   for (int j = 0; j < kNearRow / 64; ++j) row[lane + 64 * j] = 0.0;
   __syncthreads();
-  for (int64_t b0 = q0 + 64 * wave; b0 < q1; b0 += 256) {
-    const int64_t q = b0 + lane;
+  // few lines are spread over the block's lanes, up to a wave to a line
+  int ks = 0;
+  while (ks < 6 && ((q1 - q0) << (ks + 1)) <= 256) ++ks;
+  const NearLane ln = {lane >> ks, lane & ((1 << ks) - 1), ks};
+  for (int64_t b0 = q0; b0 < q1; b0 += 256 >> ks) {
+    const int64_t q = b0 + (tid >> ks);
     if (q < q1) {
       const bool near = q < sg.cum[0];
       const int64_t p = q + (near ? sg.beg[0] : q < sg.cum[1] ? sg.beg[1] : sg.beg[2]);
@@ -448,9 +463,9 @@ __global__ __launch_bounds__(256) void k_near(NearArgs g) {
       }
       if (win.x <= win.y && klo <= khi && S != (Real)0) {
         if constexpr (sizeof(Real) == 4)
-          near_line_f32<PROF>(m, cd, lane, kc, klo, khi, g.rdel[p], (float)nu, S, gref, nexp, (float)gpre, row, tlo);
+          near_line_f32<PROF>(m, cd, ln, kc, klo, khi, g.rdel[p], (float)nu, S, gref, nexp, (float)gpre, row, tlo);
         else
-          near_line_f64<PROF>(m, cd, lane, kc, klo, khi, nu, S, (double)gref, (double)nexp, gpre, row, tlo);
+          near_line_f64<PROF>(m, cd, ln, kc, klo, khi, nu, S, (double)gref, (double)nexp, gpre, row, tlo);
       }
     }
   }

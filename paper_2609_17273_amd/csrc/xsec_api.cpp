@@ -480,13 +480,17 @@ int preprocess(xs_plan* p, const xs_states* st, const xs_lines* ln) {
   return hip_check(hipGetLastError(), "preprocess launch");
 }
 
-// Expansions pay off once 64 grid points hold a few lines: a tile visit
-// costs a wave the same for one line as for 64.
-constexpr int kFarLinesPerCell = 8;
+// Expansions pay off once 64 grid points hold a few lines: a tile visit costs a
+// wave nearly the same for one line as for 64.  Measured on 1e6 points, window
+// 5000, point by point and with expansions: FP32 form with 2, 4, 8 lines on 64
+// points 334 / 438, 480 / 449, 754 / 476 us; FP64 form with 4, 8, 16 lines 505 /
+// 740, 822 / 770, 1042 / 866 us (blocks of four waves since then: less still).
+constexpr int kFarLines32 = 4, kFarLines64 = 8;
 bool use_far(const xs_plan* p) {
   return p->w.far_cond_rows > 0 && p->far_lmax >= 0 &&
          2 * p->w.item_target * 1024 >= (int64_t)near_row_doubles() &&
-         p->last_lines_in >= (int64_t)kFarLinesPerCell * ((p->grid.n_bins + 63) / 64);
+         p->last_lines_in >=
+             (p->model.precision == XS_FP32 ? kFarLines32 : kFarLines64) * ((p->grid.n_bins + 63) / 64);
 }
 
 int profile_pass(xs_plan* p, double* sigma, int accumulate) {
