@@ -25,27 +25,51 @@ __device__ __forceinline__ double block_sum256(double v, double* sh) {
   return r;
 }
 
-__global__ __launch_bounds__(256) void k_partition(ModelDev m, const SlotDev* slots,
-                                                   StatesView st, double* qpart) {
+// Per-state record for the first line pass: one random load per state of a
+// line instead of one per table (energies, degeneracies, manifold index and
+// energy).  Built once per prepare into the sort's second ping-pong buffers,
+// which are free until the sort's last pass; lists with more states than that
+// space holds read the tables directly.
+struct __attribute__((aligned(16))) StatePackLTE {
+  double E, g;
+};
+struct __attribute__((aligned(32))) StatePackNLTE {
+  double E, g, ev;  // ev: E_vib of the state's manifold
+  int64_t vi;       // manifold index, or -1 when outside the table
+};
+
+// With pack or counter set it also writes the state records and clears the
+// per-call counters, so that preparing lines starts with one kernel, not three
+// (a kernel of a few microseconds each where lists are short).
+__global__ __launch_bounds__(256) void k_partition(ModelDev m, const SlotDev* slots, StatesView st, double* qpart,
+                                                   void* pack, int32_t* counter, unsigned long long* stats) {
   __shared__ double sh[256];
   const int slot = blockIdx.y;
   const SlotDev sd = slots[slot];
+  if (slot != 0) pack = nullptr;
+  if (counter && slot == 0 && blockIdx.x == 0) {
+    for (int q = threadIdx.x; q < kCounterInts; q += 256) counter[q] = 0;
+    if (threadIdx.x < 8) stats[threadIdx.x] = 0ull;
+  }
   double q = 0.0, dq = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < st.n; i += (int64_t)gridDim.x * 256) {
-    const double E = st.E[i];
+    const double E = st.E[i], g = st.g[i];
     if (m.pop == XS_LTE) {
-      const double b = st.g[i] * exp(-kC2 * E / sd.T);
+      if (pack) ((StatePackLTE*)pack)[i] = StatePackLTE{E, g};
+      const double b = g * exp(-kC2 * E / sd.T);
       q += b;
       dq += b * (kC2 * E / (sd.T * sd.T));
     } else {
       const int32_t vi = st.v[i];
-      if ((uint32_t)vi < (uint32_t)st.n_v) {  // states with an invalid manifold index are skipped
-        const double ev = st.ev[vi];
+      const bool ok = (uint32_t)vi < (uint32_t)st.n_v;
+      const double ev = ok ? st.ev[vi] : 0.0;
+      if (pack) ((StatePackNLTE*)pack)[i] = StatePackNLTE{E, g, ev, ok ? (int64_t)vi : -1};
+      if (ok) {  // states with an invalid manifold index are skipped
         if (m.pop == XS_NLTE_2T) {
-          q += st.g[i] * exp(-kC2 * ev / sd.Tv - kC2 * (E - ev) / sd.Tr);
+          q += g * exp(-kC2 * ev / sd.Tv - kC2 * (E - ev) / sd.Tr);
         } else {  // custom vibronic densities, Eq. (Q nlte Nvib)
           const double w = st.nv[vi];
-          if (w > 0.0) q += st.g[i] * w * exp(-kC2 * (E - ev) / sd.Tr);
+          if (w > 0.0) q += g * w * exp(-kC2 * (E - ev) / sd.Tr);
         }
       }
     }
@@ -72,9 +96,17 @@ __global__ __launch_bounds__(256) void k_partition_final(ModelDev m, const doubl
   }
 }
 
-void launch_partition(const ModelDev& m, const Work& w, const StatesView& st, hipStream_t s) {
-  hipLaunchKernelGGL(k_partition, dim3(kQBlocks, m.n_slots), dim3(256), 0, s, m, w.slot, st,
-                     w.qpart);
+// Where the packed state table goes: the sort's second ping-pong buffers (keyB,
+// valB: adjacent), or nowhere when it does not fit there.
+static void* state_pack(const ModelDev& m, const Work& w, const StatesView& st) {
+  const size_t rec = (m.pop == XS_LTE) ? sizeof(StatePackLTE) : sizeof(StatePackNLTE);
+  const size_t room = (size_t)((const char*)w.valB - (const char*)w.keyB) + 4 * (size_t)w.max_lines;
+  return (size_t)st.n * rec <= room && ((uintptr_t)w.keyB % 32) == 0 ? (void*)w.keyB : nullptr;
+}
+
+void launch_partition(const ModelDev& m, const Work& w, const StatesView& st, bool lines, hipStream_t s) {
+  hipLaunchKernelGGL(k_partition, dim3(kQBlocks, m.n_slots), dim3(256), 0, s, m, w.slot, st, w.qpart,
+                     lines ? state_pack(m, w, st) : (void*)nullptr, lines ? w.counter : (int32_t*)nullptr, w.stats);
   hipLaunchKernelGGL(k_partition_final, dim3(m.n_slots), dim3(256), 0, s, m, w.qpart, w.Q, w.dQ,
                      w.smax);
 }
@@ -139,39 +171,6 @@ __device__ __forceinline__ LineState line_state(const StatesView& st, const Line
   return s;
 }
 
-// Per-state record for the first line pass: one random load per state of a
-// line instead of one per table (energies, degeneracies, manifold index and
-// energy).  Built once per prepare into the sort's second ping-pong buffers,
-// which are free until the sort's last pass; lists with more states than that
-// space holds read the tables directly.
-struct __attribute__((aligned(16))) StatePackLTE {
-  double E, g;
-};
-struct __attribute__((aligned(32))) StatePackNLTE {
-  double E, g, ev;  // ev: E_vib of the state's manifold
-  int64_t vi;       // manifold index, or -1 when outside the table
-};
-
-__global__ __launch_bounds__(256) void k_state_pack(ModelDev m, StatesView st, void* pack) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < st.n; i += (int64_t)gridDim.x * 256) {
-    if (m.pop == XS_LTE) {
-      StatePackLTE r;
-      r.E = st.E[i];
-      r.g = st.g[i];
-      ((StatePackLTE*)pack)[i] = r;
-    } else {
-      StatePackNLTE r;
-      r.E = st.E[i];
-      r.g = st.g[i];
-      const int32_t vi = st.v[i];
-      const bool ok = (uint32_t)vi < (uint32_t)st.n_v;
-      r.ev = ok ? st.ev[vi] : 0.0;
-      r.vi = ok ? (int64_t)vi : -1;
-      ((StatePackNLTE*)pack)[i] = r;
-    }
-  }
-}
-
 // The states of one line, read once: from the packed table, or from the
 // caller's tables.  ok: both indices (and, non-LTE, both manifolds) inside
 // the tables.
@@ -223,71 +222,110 @@ __device__ __forceinline__ bool gather_line_states(const ModelDev& m, const Stat
   return true;
 }
 
-// MODE 1: states from the packed table; 0: from the caller's tables.  The
-// running maximum of ln|S| of each slot (FP32 form) is kept per thread in LDS
-// rather than in registers, so the pass holds few registers and many waves
-// keep its random state loads in flight.
-constexpr int kPass1Slots = 8;  // slots whose maximum is kept per thread; more use atomics
-template <int MODE>
+// Totals over the lines: kept lines, window pairs, lines with bad indices, and
+// (FP32 form) the largest ln|S| of each slot.  Every block writes its own to
+// part[value][block] and k_line_totals adds them: an atomic per block on one
+// address costs 12 ns whoever waits, so the 8192 blocks x 3 counters of a large
+// list cost 0.3 ms (1e7 lines 588 -> 539 us, 1.1e6 lines 206 -> 65 us without them).
+constexpr int kPass1Slots = 8;      // slots whose maximum is kept per thread; more use atomics
+constexpr int kPass1Blocks = 2048;  // two rounds of the blocks that fit (124 registers: four a compute unit)
+constexpr int kTotals = 3 + kPass1Slots;
+
+struct Totals {
+  unsigned long long kept = 0, pairs = 0, bad = 0;
+};
+__device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+// sh: [12]
+__device__ __forceinline__ void block_totals(const Totals& t, unsigned long long* sh, unsigned long long* part) {
+  const unsigned long long a = wave_sum(t.kept), b = wave_sum(t.pairs), c = wave_sum(t.bad);
+  if ((threadIdx.x & 63) == 0) {
+    sh[threadIdx.x >> 6] = a;
+    sh[4 + (threadIdx.x >> 6)] = b;
+    sh[8 + (threadIdx.x >> 6)] = c;
+  }
+  __syncthreads();
+  if (threadIdx.x < 3) {
+    const unsigned long long* r = sh + 4 * threadIdx.x;
+    part[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = r[0] + r[1] + r[2] + r[3];
+  }
+}
+
+// The exact windows of a kept line, over the conditions; [a, b]: its window at
+// the widest cut-off.
+__device__ __forceinline__ unsigned long long window_pairs(const ModelDev& m, const double* cutc, const int32_t* cutm,
+                                                           double nu, int64_t a, int64_t b) {
+  if (m.n_cut_classes == 1 && cutc[0] == m.max_cut)
+    return (unsigned long long)(b - a + 1) * (unsigned long long)cutm[0];
+  unsigned long long pairs = 0;
+#pragma unroll 1
+  for (int q = 0; q < m.n_cut_classes; ++q)
+    if (line_window(nu, cutc[q], m.nu0, m.dnu, m.n_bins, a, b))
+      pairs += (unsigned long long)(b - a + 1) * (unsigned long long)cutm[q];
+  return pairs;
+}
+
+// MODE 1: states from the packed table; 0: from the caller's tables.  REC: write
+// the sort keys and line packs (a stick spectrum in the FP32 form needs only
+// the totals).  The running maximum of ln|S| of each slot (FP32 form) is kept
+// per thread in LDS rather than in registers, so the pass holds few registers
+// and many waves keep its random state loads in flight.
+template <int MODE, bool REC>
 __global__ __launch_bounds__(256) void k_lines_pass1(ModelDev m, const SlotDev* slots,
                                                      const double* Q, const double* cutc,
                                                      const int32_t* cutm, StatesView st, const void* spack,
                                                      LinesView ln, int32_t* key,
                                                      LinePack* lpack,
                                                      unsigned long long* smax,
-                                                     unsigned long long* stats) {
+                                                     unsigned long long* part) {
   __shared__ double lmax[kPass1Slots][256];
   __shared__ double lnq[kPass1Slots];
-  __shared__ unsigned long long scnt[3];
+  __shared__ unsigned long long scnt[12];
   const int tid = threadIdx.x;
   const bool f32 = m.prec == XS_FP32;
   const int ns = min(m.n_slots, kPass1Slots);
-  if (tid < 3) scnt[tid] = 0;
   if (tid < ns && f32) lnq[tid] = log(Q[tid]);
   for (int q = 0; q < ns; ++q) lmax[q][tid] = -INFINITY;
   __syncthreads();
-  unsigned long long kept = 0, pairs = 0, bad = 0;
+  Totals tot;
   for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < ln.n; i += (int64_t)gridDim.x * 256) {
     const int32_t u = ln.up[i], l = ln.lo[i];
     int32_t kk = m.n_fine;
     LineState ls;
     int32_t vu, vl;
     if (!gather_line_states<MODE>(m, st, spack, u, l, ls, vu, vl)) {
-      ++bad;
-      key[i] = kk;
+      ++tot.bad;
+      if (REC) key[i] = kk;
       continue;
     }
     const double nu = ls.Eu - ls.El;
     int64_t a, b;
     if (nu > 0.0 && line_window(nu, m.max_cut, m.nu0, m.dnu, m.n_bins, a, b)) {
-      int64_t kc = home_bin(nu, m.nu0, m.dnu);
-      int64_t fk = kc < 0 ? 0 : kc >> m.fine_sh;
-      kk = (int32_t)(fk < m.n_fine - 1 ? fk : m.n_fine - 1);
-      ++kept;
-      LinePack lp;
-      lp.Eu = ls.Eu;
-      lp.El = ls.El;
-      lp.gu = ls.gu;
-      lp.u = u;
-      lp.l = l;
+      ++tot.kept;
       const float Af = ln.A[i];
       const float lsf = ln.lscale ? ln.lscale[i] : 0.0f;
-      lp.A = Af;
-      lp.gref = ln.gref ? ln.gref[i] : (float)ln.gref_scalar;
-      lp.nexp = ln.nexp ? ln.nexp[i] : (float)ln.nexp_scalar;
-      lp.lscale = lsf;
-      lp.evu = ls.evu;
-      lp.evl = ls.evl;
-      lpack[i] = lp;
-      if (m.n_cut_classes == 1 && cutc[0] == m.max_cut) {
-        pairs += (unsigned long long)(b - a + 1) * (unsigned long long)cutm[0];
-      } else {
-#pragma unroll 1
-        for (int q = 0; q < m.n_cut_classes; ++q) {
-          if (line_window(nu, cutc[q], m.nu0, m.dnu, m.n_bins, a, b))
-            pairs += (unsigned long long)(b - a + 1) * (unsigned long long)cutm[q];
-        }
+      if (REC) {
+        int64_t kc = home_bin(nu, m.nu0, m.dnu);
+        int64_t fk = kc < 0 ? 0 : kc >> m.fine_sh;
+        kk = (int32_t)(fk < m.n_fine - 1 ? fk : m.n_fine - 1);
+        LinePack lp;
+        lp.Eu = ls.Eu;
+        lp.El = ls.El;
+        lp.gu = ls.gu;
+        lp.u = u;
+        lp.l = l;
+        lp.A = Af;
+        lp.gref = ln.gref ? ln.gref[i] : (float)ln.gref_scalar;
+        lp.nexp = ln.nexp ? ln.nexp[i] : (float)ln.nexp_scalar;
+        lp.lscale = lsf;
+        lp.evu = ls.evu;
+        lp.evl = ls.evl;
+        lpack[i] = lp;
       }
+      tot.pairs += window_pairs(m, cutc, cutm, nu, a, b);
       if (f32) {
         const double sc = (double)lsf;
         const double base = ln_line(m.mode, ls, (double)Af, nu);
@@ -304,101 +342,127 @@ __global__ __launch_bounds__(256) void k_lines_pass1(ModelDev m, const SlotDev* 
         }
       }
     }
-    key[i] = kk;
+    if (REC) key[i] = kk;
   }
-  atomicAdd(&scnt[0], kept);
-  atomicAdd(&scnt[1], pairs);
-  atomicAdd(&scnt[2], bad);
+  block_totals(tot, scnt, part);
   if (f32) {
-    for (int q = 0; q < ns; ++q) {
-      __syncthreads();
-      for (int s2 = 128; s2 > 0; s2 >>= 1) {
-        if (tid < s2) lmax[q][tid] = fmax(lmax[q][tid], lmax[q][tid + s2]);
-        __syncthreads();
-      }
-      if (tid == 0 && lmax[q][0] > -INFINITY) atomicMax(smax + q, dbl_key(lmax[q][0]));
+    __syncthreads();
+    for (int q = tid >> 6; q < ns; q += 4) {  // a wave per slot
+      const int lane = tid & 63;
+      double v = fmax(fmax(lmax[q][lane], lmax[q][lane + 64]), fmax(lmax[q][lane + 128], lmax[q][lane + 192]));
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+      if (lane == 0)
+        part[(int64_t)(3 + q) * gridDim.x + blockIdx.x] = v > -INFINITY ? dbl_key(v) : 0ull;
     }
-  }
-  __syncthreads();
-  if (tid == 0) {
-    atomicAdd(stats + 1, scnt[0]);
-    atomicAdd(stats + 2, scnt[1]);
-    atomicAdd(stats + 3, scnt[2]);
   }
 }
 
-__global__ void k_scale_final(ModelDev m, const unsigned long long* smax, double* sb) {
-  const int q = threadIdx.x;
-  if (q < m.n_slots) sb[q] = smax[q] ? key_dbl(smax[q]) : 0.0;
+// Adds the blocks' totals, and sets the FP32 form's scale of every slot.
+__global__ __launch_bounds__(1024) void k_line_totals(ModelDev m, const unsigned long long* part, int blocks,
+                                                      unsigned long long* smax, double* sb,
+                                                      unsigned long long* stats) {
+  const int v = threadIdx.x >> 6, lane = threadIdx.x & 63;  // a wave per value
+  const int nv = 3 + (m.prec == XS_FP32 ? min(m.n_slots, kPass1Slots) : 0);
+  if (v < nv) {
+    unsigned long long r = 0;
+#pragma unroll 8
+    for (int b = lane; b < blocks; b += 64) {
+      const unsigned long long x = part[(int64_t)v * blocks + b];
+      r = v < 3 ? r + x : max(r, x);
+    }
+    if (v < 3) {
+      r = wave_sum(r);
+    } else {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long x = __shfl_xor(r, o, 64);
+        r = max(r, x);
+      }
+    }
+    if (lane == 0) (v < 3 ? stats[1 + v] : smax[v - 3]) = r;
+  }
+  __syncthreads();
+  if (threadIdx.x < m.n_slots) sb[threadIdx.x] = smax[threadIdx.x] ? key_dbl(smax[threadIdx.x]) : 0.0;
+}
+
+static int line_blocks(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(kPass1Blocks, (n + 255) / 256)); }
+
+// The blocks' totals go to keyA, free until the sort's first pass: 88 bytes a
+// block, which has 256 lines (the first fewer, and 256 bytes of the carve).
+static unsigned long long* totals_part(const Work& w) { return reinterpret_cast<unsigned long long*>(w.keyA); }
+static_assert(kTotals * 8 <= 256, "a block's totals fit the smallest carve");
+
+template <bool REC>
+static void pass1(const ModelDev& m, const Work& w, const StatesView& st, const LinesView& ln, hipStream_t s) {
+  const void* pack = state_pack(m, w, st);
+  hipLaunchKernelGGL((pack ? k_lines_pass1<1, REC> : k_lines_pass1<0, REC>), dim3(line_blocks(ln.n)), dim3(256), 0, s,
+                     m, w.slot, w.Q, w.cut_class, w.cut_mult, st, pack, ln, w.key, w.lpack, w.smax, totals_part(w));
 }
 
 void launch_lines_pass1(const ModelDev& m, const Work& w, const StatesView& st,
                         const LinesView& ln, hipStream_t s) {
-  int64_t blocks = (ln.n + 255) / 256;
-  if (blocks > 8192) blocks = 8192;
-  if (blocks < 1) blocks = 1;
-  // the packed state table goes into the sort's second ping-pong buffers
-  // (keyB, valB: adjacent), when it fits there
-  const size_t rec = (m.pop == XS_LTE) ? sizeof(StatePackLTE) : sizeof(StatePackNLTE);
-  const size_t room = (size_t)((const char*)w.valB - (const char*)w.keyB) + 4 * (size_t)w.max_lines;
-  const bool packed = (size_t)st.n * rec <= room && ((uintptr_t)w.keyB % 32) == 0;
-  if (packed) {
-    const int64_t sb = std::min<int64_t>((st.n + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_state_pack, dim3((unsigned)sb), dim3(256), 0, s, m, st, (void*)w.keyB);
-    hipLaunchKernelGGL(k_lines_pass1<1>, dim3((unsigned)blocks), dim3(256), 0, s, m, w.slot, w.Q,
-                       w.cut_class, w.cut_mult, st, (const void*)w.keyB, ln, w.key, w.lpack, w.smax, w.stats);
-  } else {
-    hipLaunchKernelGGL(k_lines_pass1<0>, dim3((unsigned)blocks), dim3(256), 0, s, m, w.slot, w.Q,
-                       w.cut_class, w.cut_mult, st, (const void*)nullptr, ln, w.key, w.lpack, w.smax,
-                       w.stats);
-  }
-  hipLaunchKernelGGL(k_scale_final, dim3(1), dim3(256), 0, s, m, w.smax, w.sb);
+  pass1<true>(m, w, st, ln, s);
+  hipLaunchKernelGGL(k_line_totals, dim3(1), dim3(1024), 0, s, m, totals_part(w), line_blocks(ln.n), w.smax, w.sb,
+                     w.stats);
 }
 
 // ---------------------------------------------------------------------------
-// Stable LSD radix sort of the bucket keys, 8 bits per pass.  Each block owns
-// kSortBlock consecutive keys.  Pass: (1) per-block digit histogram;
-// (2) exclusive scan of the digit-major [256][blocks] table; (3) stable
-// scatter: the rank of a key among equal digits of its block is the running
-// count from earlier steps + the counts of earlier waves in this step + the
-// number of earlier lanes of its wave with the same digit (8 ballots).
+// Stable LSD radix sort of the bucket keys, RB = 8, 9 or 10 bits per pass: as
+// few passes as 10 bits allow, the bits shared out evenly (17-bit keys of 1e7
+// lines: 3 passes of 8 bits 370 us, 2 of 9 225).  Each block owns
+// 256 ITEMS consecutive keys: 4096, or 1024 where that leaves compute units idle.
+// Pass: (1) per-block digit histogram; (2) exclusive scan of the digit-major
+// [digits][blocks] table, or with few blocks none (COL: block-major table, every
+// scatter block adds up its digits' columns itself); (3) stable scatter.
 // Stability makes the sorted order, and so every later summation order,
 // deterministic.
 // ---------------------------------------------------------------------------
+constexpr int64_t kSortFew = 1 << 20;  // lines up to which 1024 keys make a block
+constexpr int kColBlocks = 64;  // up to here a block adds the columns in less than the three scan kernels take
+template <int RB, int ITEMS>
 __global__ __launch_bounds__(256) void k_sort_hist(const int32_t* keys, int64_t n, int shift,
-                                                   int32_t* hist, int nblk) {
-  __shared__ int h[256];
-  h[threadIdx.x] = 0;
+                                                   int32_t* hist, int nblk, int col) {
+  constexpr int ND = 1 << RB;
+  __shared__ int h[ND];
+  for (int d = threadIdx.x; d < ND; d += 256) h[d] = 0;
   __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * kSortBlock;
-  for (int s = 0; s < kSortItems; ++s) {
+  const int64_t base = (int64_t)blockIdx.x * (256 * ITEMS);
+  int k[ITEMS];
+#pragma unroll
+  for (int s = 0; s < ITEMS; ++s) {
     const int64_t i = base + s * 256 + threadIdx.x;
-    if (i < n) atomicAdd(&h[(keys[i] >> shift) & 255], 1);
+    k[s] = i < n ? keys[i] : 0;
   }
+#pragma unroll
+  for (int s = 0; s < ITEMS; ++s)
+    if (base + s * 256 + threadIdx.x < n) atomicAdd(&h[(k[s] >> shift) & (ND - 1)], 1);
   __syncthreads();
-  hist[threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
+  for (int d = threadIdx.x; d < ND; d += 256)
+    hist[col ? (int64_t)blockIdx.x * ND + d : (int64_t)d * nblk + blockIdx.x] = h[d];
 }
 
 // Exclusive scan of int32 arrays: per-block scan of 1024 elements, block sums
 // scanned by one block, then added back.
+// sh: [4]
 __device__ __forceinline__ int block_excl_scan256(int v, int* sh, int& total) {
-  const int tid = threadIdx.x;
-  sh[tid] = v;
-  __syncthreads();
-  for (int o = 1; o < 256; o <<= 1) {
-    int t = tid >= o ? sh[tid - o] : 0;
-    __syncthreads();
-    sh[tid] += t;
-    __syncthreads();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int incl = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += t;
   }
-  int incl = sh[tid];
-  total = sh[255];
+  if (lane == 63) sh[wave] = incl;
   __syncthreads();
-  return incl - v;
+  const int s0 = sh[0], s1 = sh[1], s2 = sh[2], s3 = sh[3];
+  total = s0 + s1 + s2 + s3;
+  __syncthreads();
+  return incl - v + (wave > 0 ? s0 : 0) + (wave > 1 ? s1 : 0) + (wave > 2 ? s2 : 0);
 }
 
 __global__ __launch_bounds__(256) void k_scan_blocks(int32_t* a, int64_t n, int32_t* sums) {
-  __shared__ int sh[256];
+  __shared__ int sh[4];
   const int64_t base = (int64_t)blockIdx.x * 1024 + threadIdx.x * 4;
   int v[4], s = 0;
   for (int j = 0; j < 4; ++j) {
@@ -415,7 +479,7 @@ __global__ __launch_bounds__(256) void k_scan_blocks(int32_t* a, int64_t n, int3
 }
 
 __global__ __launch_bounds__(256) void k_scan_sums(int32_t* sums, int64_t n) {
-  __shared__ int sh[256];
+  __shared__ int sh[4];
   int carry = 0;
   for (int64_t b0 = 0; b0 < n; b0 += 256) {
     const int64_t i = b0 + threadIdx.x;
@@ -435,74 +499,108 @@ __global__ __launch_bounds__(256) void k_scan_add(int32_t* a, int64_t n, const i
 }
 
 // Stable scatter of one pass, staged through LDS: the block places its keys
-// in digit order in LDS (the rank of a key among equal digits of its block is
-// the running count from earlier steps + the counts of earlier waves in this
-// step + the number of earlier lanes of its wave with the same digit, from 8
-// ballots), then writes each digit's run to its global place, so neighbouring
-// threads write neighbouring addresses.  offs: the exclusive scan of the
-// digit-major [256][nblk] histogram; the block's count of digit d is the step
-// from its entry to the next one (n after the last).
+// in digit order in LDS, then writes each digit's run to its global place, so
+// neighbouring threads write neighbouring addresses.  Every wave owns 64 ITEMS
+// consecutive keys and ranks them by itself, against its own counts: the rank
+// of a key among its wave's equal digits is the count so far + the number of
+// earlier lanes with the same digit (RB ballots); no step waits for another
+// wave (one block of 4096 keys: 15.5 us with three barriers a step, now
+// 5.3 with 1024 a block).  offs: the scanned table, or with col the counts.
+template <int RB, int ITEMS>
 __global__ __launch_bounds__(256) void k_sort_scatter(const int32_t* keys, const int32_t* vals,
                                                       int64_t n, int shift, const int32_t* offs,
-                                                      int nblk, int32_t* okeys, int32_t* ovals) {
-  __shared__ int lstart[256];   // first LDS position of each digit
-  __shared__ int goff[256];     // global position of the block's first key of each digit
-  __shared__ int run[256];      // keys of each digit placed so far
-  __shared__ int wc[4][256];
-  __shared__ int sk[kSortBlock], sv[kSortBlock];
+                                                      int nblk, int col, int32_t* okeys, int32_t* ovals) {
+  constexpr int ND = 1 << RB, PT = ND / 256;  // PT: digits per thread
+  __shared__ int wc[4][ND];     // the waves' counts, then the positions of their first keys
+  __shared__ int lstart[ND];    // first LDS position of each digit
+  __shared__ int goff[ND];      // global position of the block's first key of each digit
+  __shared__ int sk[256 * ITEMS], sv[256 * ITEMS];
+  __shared__ int sh[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t base = (int64_t)blockIdx.x * kSortBlock;
-  {
-    const int64_t e = (int64_t)tid * nblk + blockIdx.x;
-    const int64_t next = (e + 1 < (int64_t)256 * nblk) ? (int64_t)offs[e + 1] : n;
-    const int c = (int)(next - offs[e]);
-    goff[tid] = offs[e];
-    // exclusive scan of the block's digit counts (Hillis-Steele in LDS)
-    lstart[tid] = c;
-    __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-      const int t = tid >= o ? lstart[tid - o] : 0;
-      __syncthreads();
-      lstart[tid] += t;
-      __syncthreads();
-    }
-    lstart[tid] -= c;
-    run[tid] = 0;
-    wc[0][tid] = wc[1][tid] = wc[2][tid] = wc[3][tid] = 0;
-    __syncthreads();
-  }
+  const int64_t base = (int64_t)blockIdx.x * (256 * ITEMS);
+  const int64_t wbase = base + wave * (64 * ITEMS) + lane;
+  int k[ITEMS], rank[ITEMS];
+#pragma unroll
+  for (int it = 0; it < ITEMS; ++it) k[it] = wbase + it * 64 < n ? keys[wbase + it * 64] : 0;
+  for (int d = lane; d < ND; d += 64) wc[wave][d] = 0;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
   const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int st = 0; st < kSortItems; ++st) {
-    const int64_t i = base + st * 256 + tid;
-    const bool act = i < n;
-    const int k = act ? keys[i] : 0;
-    const int d = (k >> shift) & 255;
+#pragma unroll
+  for (int it = 0; it < ITEMS; ++it) {
+    const bool act = wbase + it * 64 < n;
+    const int d = (k[it] >> shift) & (ND - 1);
     unsigned long long same = __ballot(act);
 #pragma unroll
-    for (int bt = 0; bt < 8; ++bt) {
-      const unsigned long long bb = __ballot(act && ((d >> bt) & 1));
+    for (int bt = 0; bt < RB; ++bt) {
+      const unsigned long long bb = __ballot((d >> bt) & 1);
       same &= ((d >> bt) & 1) ? bb : ~bb;
     }
-    const int rank = __popcll(same & lt);
-    if (act && rank == 0) wc[wave][d] = __popcll(same);
-    __syncthreads();
-    if (act) {
-      int pos = lstart[d] + run[d] + rank;
-      for (int w2 = 0; w2 < wave; ++w2) pos += wc[w2][d];
-      sk[pos] = k;
+    const int r = __popcll(same & lt);
+    const int c = wc[wave][d];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (act && r == 0) wc[wave][d] = c + __popcll(same);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    rank[it] = c + r;
+  }
+  __syncthreads();
+  int sum = 0, all = 0, before[PT], tot[PT];
+  for (int e = 0; e < PT; ++e) {
+    const int d = tid * PT + e;
+    int c = 0;
+    for (int w2 = 0; w2 < 4; ++w2) {
+      const int t = wc[w2][d];
+      wc[w2][d] = c;
+      c += t;
+    }
+    lstart[d] = c;
+    sum += c;
+    before[e] = tot[e] = 0;
+  }
+  int total;
+  int ex = block_excl_scan256(sum, sh, total);
+  for (int e = 0; e < PT; ++e) {
+    const int c = lstart[tid * PT + e];
+    lstart[tid * PT + e] = ex;
+    ex += c;
+  }
+  if (col) {
+#pragma unroll 4
+    for (int b = 0; b < nblk; ++b)
+      for (int e = 0; e < PT; ++e) {
+        const int c = offs[b * ND + tid * PT + e];
+        tot[e] += c;
+        if (b < (int)blockIdx.x) before[e] += c;
+      }
+    for (int e = 0; e < PT; ++e) all += tot[e];
+    int g = block_excl_scan256(all, sh, total);
+    for (int e = 0; e < PT; ++e) {
+      goff[tid * PT + e] = g + before[e];
+      g += tot[e];
+    }
+  } else {
+    for (int e = 0; e < PT; ++e) goff[tid * PT + e] = offs[(int64_t)(tid * PT + e) * nblk + blockIdx.x];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < ITEMS; ++it) {
+    const int64_t i = wbase + it * 64;
+    if (i < n) {
+      const int d = (k[it] >> shift) & (ND - 1);
+      const int pos = lstart[d] + wc[wave][d] + rank[it];
+      sk[pos] = k[it];
       sv[pos] = vals ? vals[i] : (int32_t)i;
     }
-    __syncthreads();
-    run[tid] += wc[0][tid] + wc[1][tid] + wc[2][tid] + wc[3][tid];
-    wc[0][tid] = wc[1][tid] = wc[2][tid] = wc[3][tid] = 0;
-    __syncthreads();
   }
-  const int cnt = (int)min<int64_t>(kSortBlock, n - base);
+  __syncthreads();
+  const int cnt = (int)min<int64_t>(256 * ITEMS, n - base);
   for (int p = tid; p < cnt; p += 256) {
-    const int k = sk[p];
-    const int d = (k >> shift) & 255;
+    const int kp = sk[p];
+    const int d = (kp >> shift) & (ND - 1);
     const int64_t g = (int64_t)goff[d] + (p - lstart[d]);
-    okeys[g] = k;
+    okeys[g] = kp;
     ovals[g] = sv[p];
   }
 }
@@ -514,23 +612,44 @@ static void scan_excl(int32_t* a, int64_t n, int32_t* sums, hipStream_t s) {
   hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(256), 0, s, a, n, sums);
 }
 
+template <int RB, int ITEMS>
+static void sort_pass(const int32_t* ik, const int32_t* iv, int64_t n, int shift, int32_t* hist, int32_t* sums,
+                      int nblk, int32_t* ok, int32_t* ov, hipStream_t s) {
+  const int col = nblk <= kColBlocks;
+  hipLaunchKernelGGL((k_sort_hist<RB, ITEMS>), dim3(nblk), dim3(256), 0, s, ik, n, shift, hist, nblk, col);
+  if (!col) scan_excl(hist, (int64_t)nblk << RB, sums, s);
+  hipLaunchKernelGGL((k_sort_scatter<RB, ITEMS>), dim3(nblk), dim3(256), 0, s, ik, iv, n, shift, hist, nblk, col, ok,
+                     ov);
+}
+
 void launch_radix_sort(const ModelDev& m, const Work& w, int64_t n, int64_t max_key, hipStream_t s,
                        int32_t** sorted_keys, int32_t** sorted_vals) {
   (void)m;
   int bits = 1;
   while ((1ll << bits) <= (long long)max_key) ++bits;
-  const int passes = (bits + 7) / 8;
-  const int nblk = (int)((n + kSortBlock - 1) / kSortBlock);
+  const int passes = (bits + 9) / 10, rb = std::max(8, (bits + passes - 1) / passes);
+  const bool few = n <= kSortFew;
+  const int nblk = (int)((n + (few ? 1024 : kSortBlock) - 1) / (few ? 1024 : kSortBlock));
+  // the table: its own space, or the records' nu (8 bytes a line, written after
+  // the sort), or for a plan of less than 1024 lines (one block) the partition
+  // function's partial sums (4096 bytes)
+  const int64_t entries = (int64_t)nblk << rb;
+  int32_t *hist = w.hist, *sums = w.hsum;
+  if (entries > (int64_t)256 * w.n_sort_blocks) {
+    hist = reinterpret_cast<int32_t*>(w.rnu);
+    sums = hist + entries;
+    if (4 * (entries + entries / 1024 + 2) > 8 * w.max_lines) hist = reinterpret_cast<int32_t*>(w.qpart);
+  }
   const int32_t* ik = w.key;
   const int32_t* iv = nullptr;
   int32_t* ok = w.keyA;
   int32_t* ov = w.valA;
   for (int p = 0; p < passes; ++p) {
     if (nblk > 0) {
-      hipLaunchKernelGGL(k_sort_hist, dim3(nblk), dim3(256), 0, s, ik, n, 8 * p, w.hist, nblk);
-      scan_excl(w.hist, (int64_t)256 * nblk, w.hsum, s);
-      hipLaunchKernelGGL(k_sort_scatter, dim3(nblk), dim3(256), 0, s, ik, iv, n, 8 * p, w.hist,
-                         nblk, ok, ov);
+      auto* const pass = rb == 8 ? (few ? sort_pass<8, 4> : sort_pass<8, kSortItems>)
+                      : rb == 9 ? (few ? sort_pass<9, 4> : sort_pass<9, kSortItems>)
+                                : (few ? sort_pass<10, 4> : sort_pass<10, kSortItems>);
+      pass(ik, iv, n, rb * p, hist, sums, nblk, ok, ov, s);
     }
     ik = ok;
     iv = ov;
@@ -545,22 +664,14 @@ void launch_radix_sort(const ModelDev& m, const Work& w, int64_t n, int64_t max_
 // Cell offsets from the sorted keys (the dropped key is n_fine, and position
 // n acts as n_fine + 1, so every cell 0..n_fine gets its start; off[n_fine] =
 // kept lines),
-// and the sorted line records: nu, gamma_ref, n_exp, original index, and the
+// and, in the same pass, the sorted line records: nu, gamma_ref, n_exp, original index, and the
 // intensity of every slot, S (FP64) or S~ = sign exp(ln|S| - s_b) (FP32).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_offsets(const int32_t* skeys, int64_t n, int nfine, int32_t* off) {
-  for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p <= n;
-       p += (int64_t)gridDim.x * 256) {
-    const int k = (p < n) ? skeys[p] : nfine + 1;
-    const int kp = (p > 0) ? skeys[p - 1] : -1;
-    for (int b = kp + 1; b <= k && b <= nfine; ++b) off[b] = (int32_t)p;
-  }
-}
-
 __global__ __launch_bounds__(256) void k_records(ModelDev m, const SlotDev* slots, const double* Q,
                                                  const double* sb, StatesView st,
                                                  const LinePack* lpack,
-                                                 const int32_t* svals, const int32_t* off,
+                                                 const int32_t* skeys, const int32_t* svals, int64_t n,
+                                                 const unsigned long long* stats, int32_t* off, int far,
                                                  int64_t max_lines, double* rnu, float* rgref,
                                                  float* rnexp, double* rgpre, int32_t* ridx, double* rEs,
                                                  void* rS,
@@ -569,10 +680,15 @@ __global__ __launch_bounds__(256) void k_records(ModelDev m, const SlotDev* slot
   __shared__ double lnQ[kMaxCond];  // ln Q of every slot, once per block
   for (int q = threadIdx.x; q < m.n_slots; q += 256) lnQ[q] = log(Q[q]);
   __syncthreads();
-  const int64_t nk = off[m.n_fine];
+  const int64_t nk = (int64_t)stats[1];
   bool odd = false;
-  for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < nk;
-       p += (int64_t)gridDim.x * 256) {
+  for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p <= n; p += (int64_t)gridDim.x * 256) {
+    {
+      const int k = (p < n) ? skeys[p] : m.n_fine + 1;
+      const int kp = (p > 0) ? skeys[p - 1] : -1;
+      for (int b = kp + 1; b <= k && b <= m.n_fine; ++b) off[b] = (int32_t)p;
+    }
+    if (p >= nk) continue;
     const int32_t i = svals[p];
     const LinePack lp = lpack[i];
     const int32_t u = lp.u, l = lp.l;
@@ -613,11 +729,11 @@ __global__ __launch_bounds__(256) void k_records(ModelDev m, const SlotDev* slot
         ((float*)rS)[(int64_t)q * max_lines + p] = (float)S;
       else
         ((double*)rS)[(int64_t)q * max_lines + p] = S;
-      odd |= !isfinite(S);
+      if (far) odd |= !isfinite(S);
     }
-    odd |= !isfinite(lp.gref) || !isfinite(lp.nexp);
+    if (far) odd |= !isfinite(lp.gref) || !isfinite(lp.nexp);
   }
-  // an expansion would spread such a line's infinities into not-a-numbers
+  // (far: with tile expansions) an expansion would spread such a line's infinities into not-a-numbers
   if (__ballot(odd) && (threadIdx.x & 63) == 0) counter[kFarOff] = 1;
 }
 
@@ -626,34 +742,53 @@ void launch_offsets_records(const ModelDev& m, const Work& w, const StatesView& 
                             int64_t n, hipStream_t s) {
   int64_t blocks = (n + 256) / 256;
   if (blocks > 8192) blocks = 8192;
-  hipLaunchKernelGGL(k_offsets, dim3((unsigned)blocks), dim3(256), 0, s, skeys, n, m.n_fine, w.off);
   hipLaunchKernelGGL(k_records, dim3((unsigned)blocks), dim3(256), 0, s, m, w.slot, w.Q, w.sb, st,
-                     w.lpack, svals, w.off, w.max_lines, w.rnu, w.rgref, w.rnexp, w.rgpre, w.ridx, w.rEs, w.rS,
-                     w.cut_class, w.rkc, w.rdel, w.rwin, w.counter);
+                     w.lpack, skeys, svals, n, w.stats, w.off, w.far_rows != nullptr, w.max_lines, w.rnu, w.rgref,
+                     w.rnexp, w.rgpre, w.ridx, w.rEs, w.rS, w.cut_class, w.rkc, w.rdel, w.rwin, w.counter);
 }
 
 // ---------------------------------------------------------------------------
 // Stick spectrum output: S of every line for every condition, original order.
 // ---------------------------------------------------------------------------
+// The FP64 form needs no scale, so its totals are counted here, without a pass
+// before it (5e6 lines: 403 + 218 us in two passes, 203 in one); ln Q is
+// taken once per block and the states from the packed table (MODE, as above).
+template <int MODE, bool COUNT>
 __global__ __launch_bounds__(256) void k_intensity_out(ModelDev m, const CondDev* cond,
                                                        const SlotDev* slots, const double* Q,
-                                                       const double* sb, StatesView st,
-                                                       LinesView ln, void* S, double* lsc) {
+                                                       const double* sb, const double* cutc, const int32_t* cutm,
+                                                       StatesView st, const void* spack,
+                                                       LinesView ln, void* S, double* lsc, unsigned long long* part) {
+  __shared__ double lnQ[kMaxCond];
+  __shared__ unsigned long long scnt[12];
+  for (int q = threadIdx.x; q < m.n_slots; q += 256) lnQ[q] = log(Q[q]);
+  __syncthreads();
+  Totals tot;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < ln.n;
        i += (int64_t)gridDim.x * 256) {
     const int32_t u = ln.up[i], l = ln.lo[i];
-    const bool ok = line_indices_ok(st, u, l, m.pop);
-    const double nu = ok ? st.E[u] - st.E[l] : 0.0;
-    const LineState ls = ok ? line_state(st, u, l, m.pop) : LineState{0, 0, 0, 0, 0};
-    const double A = (double)ln.A[i];
+    LineState ls{0, 0, 0, 0, 0};
+    int32_t vu, vl;
+    const bool ok = gather_line_states<MODE>(m, st, spack, u, l, ls, vu, vl);
+    const double nu = ok ? ls.Eu - ls.El : 0.0;
+    if (COUNT) {
+      int64_t a, b;
+      if (!ok) {
+        ++tot.bad;
+      } else if (nu > 0.0 && line_window(nu, m.max_cut, m.nu0, m.dnu, m.n_bins, a, b)) {
+        ++tot.kept;
+        tot.pairs += window_pairs(m, cutc, cutm, nu, a, b);
+      }
+    }
     const double sc = ln.lscale ? (double)ln.lscale[i] : 0.0;
+    const double base = nu > 0.0 ? ln_line(m.mode, ls, (double)ln.A[i], nu) : 0.0;
     for (int c = 0; c < m.n_cond; ++c) {
       const int q = cond[c].slot;
       const SlotDev sd = slots[q];
       double v = 0.0;
       if (nu > 0.0) {
         int sg;
-        const double lS = ln_intensity(m.mode, m.pop, ls, A, nu, sd.T, sd.Tv, sd.Tr, log(Q[q]), sc, sg);
+        const double lS = (base + ln_pop(m.mode, m.pop, ls, nu, sd.T, sd.Tv, sd.Tr, sg)) - lnQ[q] + sc;
         v = (m.prec == XS_FP32) ? sg * exp(lS - sb[q]) : sg * exp(lS);
       }
       if (m.prec == XS_FP32)
@@ -662,31 +797,39 @@ __global__ __launch_bounds__(256) void k_intensity_out(ModelDev m, const CondDev
         ((double*)S)[(int64_t)c * ln.n + i] = v;
     }
   }
-  if (lsc && blockIdx.x == 0 && threadIdx.x < m.n_cond) lsc[threadIdx.x] = sb[cond[threadIdx.x].slot];
+  if (COUNT) block_totals(tot, scnt, part);
+  if (lsc && ln.n > 0 && blockIdx.x == 0 && threadIdx.x < m.n_cond)
+    lsc[threadIdx.x] = COUNT ? 0.0 : sb[cond[threadIdx.x].slot];
 }
 
+template <bool COUNT>
+static void intensity_out(const ModelDev& m, const Work& w, const StatesView& st, const LinesView& ln, void* S,
+                          double* log_scale, hipStream_t s) {
+  const void* pack = state_pack(m, w, st);
+  hipLaunchKernelGGL((pack ? k_intensity_out<1, COUNT> : k_intensity_out<0, COUNT>), dim3(line_blocks(ln.n)),
+                     dim3(256), 0, s, m, w.cond, w.slot, w.Q, w.sb, w.cut_class, w.cut_mult, st, pack, ln, S,
+                     log_scale, totals_part(w));
+}
+
+// After launch_partition with lines set.
 void launch_intensity_out(const ModelDev& m, const Work& w, const StatesView& st,
                           const LinesView& ln, void* S, double* log_scale, hipStream_t s) {
-  int64_t blocks = (ln.n + 255) / 256;
-  if (blocks > 8192) blocks = 8192;
-  if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(k_intensity_out, dim3((unsigned)blocks), dim3(256), 0, s, m, w.cond, w.slot,
-                     w.Q, w.sb, st, ln, S, log_scale);
+  const auto totals = [&] {
+    hipLaunchKernelGGL(k_line_totals, dim3(1), dim3(1024), 0, s, m, totals_part(w), line_blocks(ln.n), w.smax, w.sb,
+                       w.stats);
+  };
+  if (m.prec == XS_FP32) {
+    pass1<false>(m, w, st, ln, s);
+    totals();
+    if (ln.n > 0) intensity_out<false>(m, w, st, ln, S, log_scale, s);
+  } else {
+    intensity_out<true>(m, w, st, ln, S, log_scale, s);
+    totals();
+  }
 }
 
-// Clear the per-call counters and the work queue (a kernel, not a memset, so
-// the step can be captured in a graph).
-__global__ void k_reset(int32_t* counter, unsigned long long* stats) {
-  const int t = threadIdx.x;
-  for (int q = t; q < kCounterInts; q += 64) counter[q] = 0;
-  if (t < 8) stats[t] = 0ull;
-}
-
-void launch_reset(const Work& w, hipStream_t s) {
-  hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, s, w.counter, w.stats);
-}
-
-// Only the work queue (the counters of xs_prepare and its flag are kept).
+// Clear the work queue (a kernel, not a memset, so the step can be captured in a
+// graph); the counters of xs_prepare and its flag are kept.
 __global__ void k_reset_queue(int32_t* counter) {
   for (int q = threadIdx.x; q < kCounterInts; q += 64)
     if (q != kFarOff) counter[q] = 0;

@@ -467,8 +467,7 @@ Work kernel_work(const xs_plan* p) {
 int preprocess(xs_plan* p, const xs_states* st, const xs_lines* ln) {
   const StatesView sv = view(st);
   const LinesView lv = view(ln);
-  launch_reset(p->w, p->stream);
-  launch_partition(p->md, p->w, sv, p->stream);
+  launch_partition(p->md, p->w, sv, true, p->stream);
   launch_lines_pass1(p->md, p->w, sv, lv, p->stream);
   int32_t *sk = nullptr, *svv = nullptr;
   launch_radix_sort(p->md, p->w, lv.n, p->md.n_fine, p->stream, &sk, &svv);
@@ -655,7 +654,7 @@ int xs_partition_function(xs_plan* p, const xs_states* st, double* Q, double* dQ
   int rc;
   if ((rc = check_call(p, st, nullptr))) return rc;
   if (!Q) return fail(XS_EINVAL, "Q is NULL");
-  launch_partition(p->md, p->w, view(st), p->stream);
+  launch_partition(p->md, p->w, view(st), false, p->stream);
   launch_q_out(p->md, p->w, Q, dQdT, p->stream);
   return hip_check(hipGetLastError(), "partition launch");
 }
@@ -668,10 +667,8 @@ int xs_line_intensities(xs_plan* p, const xs_states* st, const xs_lines* ln, voi
   if (p->model.precision == XS_FP32 && !log_scale) return fail(XS_EINVAL, "log_scale is NULL (FP32 form)");
   const StatesView sv = view(st);
   const LinesView lv = view(ln);
-  launch_reset(p->w, p->stream);
-  launch_partition(p->md, p->w, sv, p->stream);
-  launch_lines_pass1(p->md, p->w, sv, lv, p->stream);
-  if (ln->n > 0) launch_intensity_out(p->md, p->w, sv, lv, S, log_scale, p->stream);
+  launch_partition(p->md, p->w, sv, true, p->stream);
+  launch_intensity_out(p->md, p->w, sv, lv, S, log_scale, p->stream);
   return hip_check(hipGetLastError(), "intensity launch");
 }
 
@@ -745,8 +742,7 @@ int xs_cooling_function(xs_plan* p, const xs_states* st, const xs_lines* ln, int
     if (!(T[j] > 0.0 && std::isfinite(T[j]))) return fail(XS_EINVAL, "cooling function: temperatures must be > 0");
   // temperatures and the per-(chunk, temperature) partial sums live in the
   // gather's partial-row buffer
-  const int64_t need = ((int64_t)n_T + 31) / 32 * 32 + 2 * (int64_t)cooling_chunks(n_T) * n_T;
-  if (need > 2 * p->w.item_target * 1024)
+  if (cooling_doubles(n_T) > 2 * p->w.item_target * 1024)
     return fail(XS_EINVAL, "cooling function: n_T too large for this plan's workspace");
   p->cf_T.assign(T, T + n_T);
   if ((rc = hip_check(hipMemcpyAsync(p->w.part, p->cf_T.data(), sizeof(double) * n_T,
@@ -754,7 +750,7 @@ int xs_cooling_function(xs_plan* p, const xs_states* st, const xs_lines* ln, int
     return rc;
   if ((rc = hip_check(hipStreamSynchronize(p->stream), "cooling temperatures sync"))) return rc;
   launch_cooling(p->md, p->w, view(st), view(ln), p->w.part, n_T, W, Q, p->stream);
-  p->prepared = false;  // the records area now holds the cooling function's runs
+  p->prepared = false;  // the records area now holds the cooling function's terms
   p->last_lines_in = ln->n;
   return hip_check(hipGetLastError(), "cooling launch");
 }

@@ -31,7 +31,7 @@ constexpr int kAdjBlocksMax = 32768;  // the most the configuration allows (size
 constexpr int kSortItems = 16;    // keys per thread in the radix sort (4096 per block)
 // Device counters (int32): [0] gather work queue, [2..3] candidate total,
 // [4..5] lines per item or part, [6] parts beyond
-// tiles' first, [8] cooling-function runs, [kFarOff] set by the
+// tiles' first, [kFarOff] set by the
 // record pass where a line's values are not finite.
 constexpr int kCounterInts = 64;
 constexpr int kFarOff = 9;
@@ -175,7 +175,8 @@ struct Tiling {
 };
 
 // ---- launch wrappers (k_lines.hip) ----
-void launch_partition(const ModelDev& m, const Work& w, const StatesView& st, hipStream_t s);
+// lines: also clears the per-call counters and packs the states for the line passes
+void launch_partition(const ModelDev& m, const Work& w, const StatesView& st, bool lines, hipStream_t s);
 void launch_lines_pass1(const ModelDev& m, const Work& w, const StatesView& st,
                         const LinesView& ln, hipStream_t s);
 // Stable sort of the int32 keys w.key[0..n) (values 0..max_key) with their
@@ -188,7 +189,6 @@ void launch_offsets_records(const ModelDev& m, const Work& w, const StatesView& 
 void launch_intensity_out(const ModelDev& m, const Work& w, const StatesView& st,
                           const LinesView& ln, void* S, double* log_scale, hipStream_t s);
 void launch_q_out(const ModelDev& m, const Work& w, double* Q, double* dQ, hipStream_t s);
-void launch_reset(const Work& w, hipStream_t s);
 void launch_reset_queue(const Work& w, hipStream_t s);
 void launch_scan_i32(int32_t* a, int64_t n, int32_t* sums, hipStream_t s);  // exclusive, in place
 
@@ -212,7 +212,8 @@ int far_nodes(int prec);  // nodes per tile
 void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, double* sigma, hipStream_t s);
 
 // ---- cooling function (k_cooling.hip) ----
-int cooling_chunks(int32_t nT);
+// doubles of Work::part the temperatures and partial sums take
+int64_t cooling_doubles(int32_t nT);
 void launch_cooling(const ModelDev& m, const Work& w, const StatesView& st, const LinesView& ln,
                     const double* T_dev, int32_t nT, double* W, double* Q, hipStream_t s);
 
