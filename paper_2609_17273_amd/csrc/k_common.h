@@ -25,99 +25,186 @@ __device__ __forceinline__ bool in_window(double nuk, double nui, double cut) {
   return fabs(nuk - nui) <= cut;
 }
 
+// a / d for a step d that every line of a loop shares: a product with 1 / d (formed
+// outside the loop) and one correction, four operations for a division's dozen.
+__device__ __forceinline__ double quotient(double a, double d) {
+  const double inv = 1.0 / d, q = a * inv;
+  return inv < 1e300 ? fma(fma(-q, d, a), inv, q) : a / d;
+}
+
 // First/last bin of the window clipped to [0, nb-1]; false if empty.  The
 // closed-form bounds widened by two bins are tightened by the exact predicate
 // (the window is contiguous because nu_k and the rounded difference are
-// monotone in k).
+// monotone in k).  Bins are whole numbers in FP64 here: no conversions.
 __device__ inline bool line_window(double nui, double cut, double nu0, double dnu, int64_t nb,
                                    int64_t& klo, int64_t& khi) {
 #pragma clang fp contract(off)
-  double lo = ceil((nui - cut - nu0) / dnu) - 2.0;
-  double hi = floor((nui + cut - nu0) / dnu) + 2.0;
-  if (!(hi >= 0.0) || !(lo <= (double)(nb - 1))) return false;
-  int64_t a = lo < 0.0 ? 0 : (int64_t)lo;
-  int64_t b = hi > (double)(nb - 1) ? nb - 1 : (int64_t)hi;
-  while (a <= b && !in_window(nu_of_bin(nu0, dnu, a), nui, cut)) ++a;
-  while (b >= a && !in_window(nu_of_bin(nu0, dnu, b), nui, cut)) --b;
-  klo = a;
-  khi = b;
+  const double last = (double)(nb - 1);
+  const double lo = ceil(quotient(nui - cut - nu0, dnu)) - 2.0;
+  const double hi = floor(quotient(nui + cut - nu0, dnu)) + 2.0;
+  if (!(hi >= 0.0) || !(lo <= last)) return false;
+  double a = lo < 0.0 ? 0.0 : lo;
+  double b = hi > last ? last : hi;
+  while (a <= b && !in_window(nu0 + a * dnu, nui, cut)) a += 1.0;
+  while (b >= a && !in_window(nu0 + b * dnu, nui, cut)) b -= 1.0;
+  klo = (int64_t)a;
+  khi = (int64_t)b;
   return a <= b;
 }
 
 // Nearest grid index of nu (the line's home bin) and the residual
 // delta = nu - nu_{k_c} in [-dnu/2, dnu/2] up to rounding.
 __device__ __forceinline__ int64_t home_bin(double nui, double nu0, double dnu) {
-  double t = rint((nui - nu0) / dnu);
+  double t = rint(quotient(nui - nu0, dnu));
   t = fmin(fmax(t, -4.0e18), 4.0e18);
   return (int64_t)t;
 }
 
-// ---------------------------------------------------------------------------
-// Line intensity in log form, ln|S| and its sign (nu > 0 assumed):
-//  absorption LTE  (Eq. abs intensity lte):
-//     ln(g_u A / (8 pi c nu^2)) - c2 E_l / T + ln(1 - exp(-c2 nu / T)) - ln Q
-//  absorption 2T   (Eqs. nlte v, nlte ab 2T):
-//     ... - c2 E_l,vib/Tv - c2 E_l,rot/Tr + ln|1 - exp(-c2 (nu_vib/Tv + nu_rot/Tr))| - ln Q
-//     (negative intensity under population inversion)
-//  emission LTE    (Eq. ems intensity lte):  ln(g_u h c A nu / (4 pi)) - c2 E_u / T - ln Q
-//  emission 2T     (Eq. nlte em 2T):         ... - c2 E_u,vib/Tv - c2 E_u,rot/Tr - ln Q
-//  absorption, custom densities (Eq. nlte ab pop density):
-//     ln(g_u A / (8 pi c nu^2)) + ln n_vib(v_l) - c2 E_l,rot/Tr + ln(1 - exp(-c2 nu/Tr)) - ln Q
-//  emission, custom densities (Eq. nlte em pop density):
-//     ln(g_u h c A nu / (4 pi)) + ln n_vib(v_u) - c2 E_u,rot/Tr - ln Q
-//     (a weight that is not > 0 gives ln S = -inf: no intensity)
-// (1 - exp(-x)) is formed as -expm1(-x); a per-line log scale s adds s.
-// ---------------------------------------------------------------------------
-// A line is usable only if its state indices (and, for two temperatures,
-// their manifold indices) are inside the caller's tables.
-__device__ __forceinline__ bool line_indices_ok(const StatesView& st, int32_t u, int32_t l, int pop) {
-  if ((uint32_t)u >= (uint64_t)st.n || (uint32_t)l >= (uint64_t)st.n) return false;
-  if (pop != XS_LTE &&
-      ((uint32_t)st.v[u] >= (uint32_t)st.n_v || (uint32_t)st.v[l] >= (uint32_t)st.n_v))
-    return false;
-  return true;
+// 2^r - 1 over r, |r| <= 1/2: the Chebyshev interpolant of 2^r of degree 11, with
+// its constant term exactly 1 (error 5e-18 of 2^r).
+__device__ __forceinline__ double exp2m1_over(double r) {
+  double p = 4.4558179083360645e-10;
+  p = fma(p, r, 7.074194297288521e-09);
+  p = fma(p, r, 1.0178057087733941e-07);
+  p = fma(p, r, 1.3215432535912375e-06);
+  p = fma(p, r, 1.5252733841556773e-05);
+  p = fma(p, r, 0.00015403530463724353);
+  p = fma(p, r, 0.001333355814640647);
+  p = fma(p, r, 0.009618129107587256);
+  p = fma(p, r, 0.055504108664821625);
+  p = fma(p, r, 0.24022650695910158);
+  p = fma(p, r, 0.6931471805599453);
+  return p;
 }
 
+// ---------------------------------------------------------------------------
+// Line intensity (nu > 0 assumed):
+//  absorption LTE  (Eq. abs intensity lte):
+//     g_u A / (8 pi c nu^2) exp(-c2 E_l / T) (1 - exp(-c2 nu / T)) / Q
+//  absorption 2T   (Eqs. nlte v, nlte ab 2T):
+//     ... exp(-c2 E_l,vib/Tv - c2 E_l,rot/Tr) (1 - exp(-c2 (nu_vib/Tv + nu_rot/Tr))) / Q
+//     (negative intensity under population inversion)
+//  emission LTE    (Eq. ems intensity lte):  g_u h c A nu / (4 pi) exp(-c2 E_u / T) / Q
+//  emission 2T     (Eq. nlte em 2T):         ... exp(-c2 E_u,vib/Tv - c2 E_u,rot/Tr) / Q
+//  absorption, custom densities (Eq. nlte ab pop density):
+//     g_u A / (8 pi c nu^2) n_vib(v_l) exp(-c2 E_l,rot/Tr) (1 - exp(-c2 nu/Tr)) / Q
+//  emission, custom densities (Eq. nlte em pop density):
+//     g_u h c A nu / (4 pi) n_vib(v_u) exp(-c2 E_u,rot/Tr) / Q
+//     (a weight that is not > 0: no intensity)
+// times exp(s) for a per-line log scale s, and in the FP32 form exp(-s_b).  All
+// exponents are collected in powers of two, S = m 2^-t, t = k + r: what is far from
+// 1 stays in k, so nothing overflows or underflows on the way, and the rate
+// c2 / (T ln 2) is held in two parts, so that r carries no more than its own
+// rounding however large t is.  No logarithms: with them (ln|S|, three logs, an
+// expm1 and six divisions a line) the two line passes ran at 950 VALU operations
+// a line.
+// ---------------------------------------------------------------------------
 struct LineState {
   double Eu, El, gu, evu, evl;
   double nvu, nvl;  // vibronic densities of the upper and lower manifolds
 };
 
-// The part of ln|S| that no temperature enters: ln(g_u A / (8 pi c nu^2))
-// (absorption) or ln(g_u h c A nu / (4 pi)) (emission).
-__device__ inline double ln_line(int mode, const LineState& ls, double A, double nu) {
-  if (mode == XS_ABSORPTION) return log(ls.gu * A) - log(8.0 * kPI * kC) - 2.0 * log(nu);
-  return log(ls.gu * kH * kC * A * nu / (4.0 * kPI));
-}
-
-// The population (and stimulated-emission) part of ln|S| for one slot's
-// temperatures, and the sign of S.
-__device__ inline double ln_pop(int mode, int pop, const LineState& ls, double nu, double T, double Tv,
-                                double Tr, int& sign) {
-  sign = 1;
-  if (mode == XS_ABSORPTION) {
-    if (pop == XS_LTE) return -kC2 * ls.El / T + log(-expm1(-kC2 * nu / T));
-    if (pop == XS_NLTE_DENSITY)
-      return (ls.nvl > 0.0 ? log(ls.nvl) : -INFINITY) - kC2 * (ls.El - ls.evl) / Tr +
-             log(-expm1(-kC2 * nu / Tr));
-    const double nuv = ls.evu - ls.evl;
-    const double nur = (ls.Eu - ls.evu) - (ls.El - ls.evl);
-    const double x = kC2 * (nuv / Tv + nur / Tr);
-    const double st = -expm1(-x);
-    if (st < 0.0) sign = -1;
-    return -kC2 * ls.evl / Tv - kC2 * (ls.El - ls.evl) / Tr + log(fabs(st));
+// One line's factors.  LTE: er is the energy of the state whose population enters,
+// xr = nu.  Otherwise ev, er are its vibrational and rotational energies and
+// xv, xr those of the stimulated-emission exponent (custom densities: of E_rot
+// and nu alone, the density is a factor of P).
+struct LineFac {
+  double P, ev, er, xv, xr;
+};
+__device__ __forceinline__ LineFac line_fac(int mode, int pop, const LineState& ls, double A, double nu) {
+  LineFac f{0.0, 0.0, 0.0, 0.0, nu};
+  const bool ab = mode == XS_ABSORPTION;
+  const double gA = ls.gu * A;
+  f.P = ab ? gA * (1.0 / (8.0 * kPI * kC)) / (nu * nu) : gA * (kH * kC / (4.0 * kPI)) * nu;
+  if (gA < 0.0) f.P = __longlong_as_double(0x7ff8000000000000ll);
+  f.er = ab ? ls.El : ls.Eu;
+  if (pop != XS_LTE) {
+    const double v = ab ? ls.evl : ls.evu;
+    f.er -= v;
+    if (pop == XS_NLTE_2T) {
+      f.ev = v;
+      f.xv = ls.evu - ls.evl;
+      f.xr = (ls.Eu - ls.evu) - (ls.El - ls.evl);
+    } else {
+      const double w = ab ? ls.nvl : ls.nvu;
+      f.P *= w > 0.0 ? w : 0.0;
+    }
   }
-  if (pop == XS_LTE) return -kC2 * ls.Eu / T;
-  if (pop == XS_NLTE_DENSITY) return (ls.nvu > 0.0 ? log(ls.nvu) : -INFINITY) - kC2 * (ls.Eu - ls.evu) / Tr;
-  return -kC2 * ls.evu / Tv - kC2 * (ls.Eu - ls.evu) / Tr;
+  return f;
 }
 
-// ln|S| = ln_line + ln_pop - ln Q + s (the loops over slots take ln_line
-// once per line and ln Q once per slot).
-__device__ inline double ln_intensity(int mode, int pop, const LineState& ls, double A,
-                                      double nu, double T, double Tv, double Tr, double lnQ,
-                                      double lscale, int& sign) {
-  return (ln_line(mode, ls, A, nu) + ln_pop(mode, pop, ls, nu, T, Tv, Tr, sign)) - lnQ + lscale;
+// One slot's factors: c2 / (T ln 2) for T_rot (or T) and T_vib, in two parts.
+struct SlotFac {
+  double rh, rl, vh, vl;
+  double iQ;
+  double lnQ;  // (for ln|S|)
+  double sb2;  // s_b / ln 2; 0 in the FP64 form
+};
+__device__ __forceinline__ void two_part_rate(double T, double& h, double& l) {
+  // c2 / ln 2 in two parts, over T; kept finite (beyond 1e100 every product with an
+  // energy is past the exponents' range)
+  constexpr double ch = kC2 / kLN2;
+  constexpr double cl = -1.207550277746768e-16;
+  h = fmin(ch / T, 1e100);
+  l = h < 1e100 ? (fma(-h, T, ch) + cl) / T : 0.0;
+}
+__device__ __forceinline__ SlotFac slot_fac(const SlotDev& sd, int pop, double Q, double sb) {
+  SlotFac f;
+  two_part_rate(pop == XS_LTE ? sd.T : sd.Tr, f.rh, f.rl);
+  two_part_rate(pop == XS_NLTE_2T ? sd.Tv : 1.0, f.vh, f.vl);
+  f.iQ = 1.0 / Q;
+  f.lnQ = log(Q);
+  f.sb2 = sb / kLN2;
+  return f;
+}
+
+// 1 - 2^-x, x >= 0, to full relative precision (x = h + l).
+__device__ __forceinline__ double one_minus_exp2(double h, double l) {
+  const double k = rint(h);
+  const double r = h < 1e9 ? (k - h) - l : (h >= 1e9 ? 0.0 : h);  // (a NaN stays one)
+  const double s = ldexp(1.0, -(int)fmin(k, 4000.0));
+  return (1.0 - s) - s * (r * exp2m1_over(r));
+}
+
+// The line in one slot: S = m 2^-t, t = th + tl (without Q, s and s_b).
+struct Intensity {
+  double m, th, tl;
+};
+template <bool LTE>
+__device__ __forceinline__ Intensity intensity(int mode, int pop, const LineFac& f, const SlotFac& q) {
+  Intensity o;
+  o.m = f.P;
+  o.th = f.er * q.rh;
+  o.tl = fabs(o.th) < 1e300 ? fma(f.er, q.rl, fma(f.er, q.rh, -o.th)) : 0.0;
+  double xh = f.xr * q.rh, xl = fma(f.xr, q.rl, fma(f.xr, q.rh, -xh));
+  if (!LTE && pop == XS_NLTE_2T) {
+    o.th = fma(f.ev, q.vh, o.th);
+    xh = fma(f.xv, q.vh, xh);
+    xl = 0.0;
+  }
+  if (mode == XS_ABSORPTION) {
+    if (!LTE && xh < 0.0) {  // inverted: 1 - 2^x = -2^x (1 - 2^-x), the power going to t
+      o.m = -o.m * one_minus_exp2(-xh, -xl);
+      o.th += xh;
+    } else {
+      o.m *= one_minus_exp2(xh, xl);
+    }
+  }
+  return o;
+}
+
+// S, or S~ = S exp(-s_b)
+__device__ __forceinline__ double intensity_value(const Intensity& o, const SlotFac& q, double sc) {
+  const double sc2 = sc * (1.0 / kLN2);
+  const double t = (o.th - sc2) + q.sb2;
+  const double k = fmin(fmax(rint(t), -5000.0), 5000.0);
+  const double r = fabs(t) >= 5000.0 ? 0.0 : (((o.th - k) - sc2) + q.sb2) + o.tl;  // (a NaN stays one)
+  return ldexp(o.m * q.iQ * fma(-r, exp2m1_over(-r), 1.0), -(int)k);
+}
+
+// ln|S|, with the log scale
+__device__ __forceinline__ double intensity_log(const Intensity& o, const SlotFac& q, double sc) {
+  return (log(fabs(o.m)) - kLN2 * (o.th + o.tl)) - q.lnQ + sc;
 }
 
 // Order-preserving map of doubles to unsigned keys (for an atomic max).

@@ -89,24 +89,10 @@ __global__ __launch_bounds__(256) void k_cf_runs(const int32_t* sk, const double
   }
 }
 
-// exp(x log2) for x = t = k + r, |r| <= 1/2: the Chebyshev interpolant of 2^r of
-// degree 11 (error 5e-18 of it, in exact arithmetic) times 2^k; the rounding of
-// the twelve terms leaves 1 ulp.  t is finite or a NaN.
+// 2^t; t is finite or a NaN.
 __device__ __forceinline__ double exp2_poly(double t) {
   const double k = rint(t), r = t - k;
-  double p = 4.4558179083360645e-10;
-  p = fma(p, r, 7.074194297288521e-09);
-  p = fma(p, r, 1.0178057087733941e-07);
-  p = fma(p, r, 1.3215432535912375e-06);
-  p = fma(p, r, 1.5252733841556773e-05);
-  p = fma(p, r, 0.00015403530463724353);
-  p = fma(p, r, 0.001333355814640647);
-  p = fma(p, r, 0.009618129107587256);
-  p = fma(p, r, 0.055504108664821625);
-  p = fma(p, r, 0.24022650695910158);
-  p = fma(p, r, 0.6931471805599453);
-  p = fma(p, r, 1.0);
-  return ldexp(p, (int)k);
+  return ldexp(fma(r, exp2m1_over(r), 1.0), (int)k);
 }
 
 // part[c][0..1][j] (+)= sums over chunk c of the states: g_i exp(-c2 E_i / T_j), and

@@ -132,53 +132,15 @@ void launch_q_out(const ModelDev& m, const Work& w, double* Q, double* dQ, hipSt
 // n_fine.  FP32 form: running max of ln|S| per slot.  Counters:
 // kept lines and window pairs (exact windows per distinct cut-off).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ LineState line_state(const StatesView& st, int32_t u, int32_t l,
-                                                int pop) {
-  LineState s;
-  s.Eu = st.E[u];
-  s.El = st.E[l];
-  s.gu = st.g[u];
-  if (pop != XS_LTE) {
-    s.evu = st.ev[st.v[u]];
-    s.evl = st.ev[st.v[l]];
-  } else {
-    s.evu = s.evl = 0.0;
-  }
-  if (pop == XS_NLTE_DENSITY) {
-    s.nvu = st.nv[st.v[u]];
-    s.nvl = st.nv[st.v[l]];
-  } else {
-    s.nvu = s.nvl = 1.0;
-  }
-  return s;
-}
-
-// As line_state, with the energies, degeneracy and manifold energies from
-// the line's pack (the state tables are read only for the custom densities).
-__device__ __forceinline__ LineState line_state(const StatesView& st, const LinePack& lp, int pop) {
-  LineState s;
-  s.Eu = lp.Eu;
-  s.El = lp.El;
-  s.gu = lp.gu;
-  s.evu = lp.evu;
-  s.evl = lp.evl;
-  if (pop == XS_NLTE_DENSITY) {
-    s.nvu = st.nv[st.v[lp.u]];
-    s.nvl = st.nv[st.v[lp.l]];
-  } else {
-    s.nvu = s.nvl = 1.0;
-  }
-  return s;
-}
-
 // The states of one line, read once: from the packed table, or from the
 // caller's tables.  ok: both indices (and, non-LTE, both manifolds) inside
 // the tables.
-template <int MODE>
+template <int MODE, bool LTE>
 __device__ __forceinline__ bool gather_line_states(const ModelDev& m, const StatesView& st, const void* pack,
-                                                   int32_t u, int32_t l, LineState& ls, int32_t& vu, int32_t& vl) {
+                                                   int32_t u, int32_t l, LineState& ls) {
+  int32_t vu = 0, vl = 0;
   if ((uint32_t)u >= (uint64_t)st.n || (uint32_t)l >= (uint64_t)st.n) return false;
-  if (m.pop == XS_LTE) {
+  if (LTE) {
     if (MODE) {
       const StatePackLTE a = ((const StatePackLTE*)pack)[u], b = ((const StatePackLTE*)pack)[l];
       ls.Eu = a.E;
@@ -190,7 +152,6 @@ __device__ __forceinline__ bool gather_line_states(const ModelDev& m, const Stat
       ls.El = st.E[l];
     }
     ls.evu = ls.evl = 0.0;
-    vu = vl = 0;
   } else {
     if (MODE) {
       const StatePackNLTE a = ((const StatePackNLTE*)pack)[u], b = ((const StatePackNLTE*)pack)[l];
@@ -213,7 +174,7 @@ __device__ __forceinline__ bool gather_line_states(const ModelDev& m, const Stat
       ls.evl = st.ev[vl];
     }
   }
-  if (m.pop == XS_NLTE_DENSITY) {
+  if (!LTE && m.pop == XS_NLTE_DENSITY) {
     ls.nvu = st.nv[vu];
     ls.nvl = st.nv[vl];
   } else {
@@ -222,14 +183,11 @@ __device__ __forceinline__ bool gather_line_states(const ModelDev& m, const Stat
   return true;
 }
 
-// Totals over the lines: kept lines, window pairs, lines with bad indices, and
-// (FP32 form) the largest ln|S| of each slot.  Every block writes its own to
-// part[value][block] and k_line_totals adds them: an atomic per block on one
-// address costs 12 ns whoever waits, so the 8192 blocks x 3 counters of a large
-// list cost 0.3 ms (1e7 lines 588 -> 539 us, 1.1e6 lines 206 -> 65 us without them).
-constexpr int kPass1Slots = 8;      // slots whose maximum is kept per thread; more use atomics
-constexpr int kPass1Blocks = 2048;  // two rounds of the blocks that fit (124 registers: four a compute unit)
-constexpr int kTotals = 3 + kPass1Slots;
+// Totals over the lines: kept lines, window pairs, lines with bad indices.
+// Every block writes its own to part[value][block] and k_line_totals adds them: an
+// atomic per block on one address costs 12 ns whoever waits, and 8192 blocks with
+// 3 counters each bound shorter lists (1.1e6 lines 206 -> 65 us without them).
+constexpr int kPass1Blocks = 2048;
 
 struct Totals {
   unsigned long long kept = 0, pairs = 0, bad = 0;
@@ -268,35 +226,53 @@ __device__ __forceinline__ unsigned long long window_pairs(const ModelDev& m, co
   return pairs;
 }
 
+__device__ __forceinline__ void put_pack(LinePackLTE* p, const LineFac& f, double nu, float gref, float nexp) {
+  *p = LinePackLTE{f.P, f.er, nu, gref, nexp};
+}
+__device__ __forceinline__ void put_pack(LinePack* p, const LineFac& f, double nu, float gref, float nexp) {
+  *p = LinePack{f.P, f.ev, f.er, f.xv, f.xr, nu, gref, nexp};
+}
+__device__ __forceinline__ LineFac pack_fac(const LinePackLTE& p) { return LineFac{p.P, 0.0, p.er, 0.0, p.nu}; }
+__device__ __forceinline__ LineFac pack_fac(const LinePack& p) { return LineFac{p.P, p.ev, p.er, p.xv, p.xr}; }
+template <bool LTE>
+struct PackOf {
+  using type = LinePack;
+};
+template <>
+struct PackOf<true> {
+  using type = LinePackLTE;
+};
+
 // MODE 1: states from the packed table; 0: from the caller's tables.  REC: write
 // the sort keys and line packs (a stick spectrum in the FP32 form needs only
-// the totals).  The running maximum of ln|S| of each slot (FP32 form) is kept
-// per thread in LDS rather than in registers, so the pass holds few registers
-// and many waves keep its random state loads in flight.
-template <int MODE, bool REC>
+// the totals).  Bound by memory: a line's two random state loads miss the L2 where
+// the table is larger (64 bytes each), and its pack is written and read once
+// more (1e7 lines, 3e5 states: 1.2 GB fetched, 397 us; 588 with logarithms and
+// packs of 64 bytes, the record pass 307, before 435).
+template <int MODE, bool REC, bool LTE>
 __global__ __launch_bounds__(256) void k_lines_pass1(ModelDev m, const SlotDev* slots,
                                                      const double* Q, const double* cutc,
                                                      const int32_t* cutm, StatesView st, const void* spack,
                                                      LinesView ln, int32_t* key,
-                                                     LinePack* lpack,
+                                                     void* lpack,
                                                      unsigned long long* smax,
                                                      unsigned long long* part) {
-  __shared__ double lmax[kPass1Slots][256];
-  __shared__ double lnq[kPass1Slots];
+  __shared__ SlotFac sf[kMaxCond];
+  __shared__ unsigned long long bmax[kMaxCond];  // the block's largest ln|S| of every slot (FP32 form)
   __shared__ unsigned long long scnt[12];
-  const int tid = threadIdx.x;
   const bool f32 = m.prec == XS_FP32;
-  const int ns = min(m.n_slots, kPass1Slots);
-  if (tid < ns && f32) lnq[tid] = log(Q[tid]);
-  for (int q = 0; q < ns; ++q) lmax[q][tid] = -INFINITY;
+  if (f32)
+    for (int q = threadIdx.x; q < m.n_slots; q += 256) {
+      sf[q] = slot_fac(slots[q], m.pop, Q[q], 0.0);
+      bmax[q] = 0ull;
+    }
   __syncthreads();
   Totals tot;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < ln.n; i += (int64_t)gridDim.x * 256) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < ln.n; i += (int64_t)gridDim.x * 256) {
     const int32_t u = ln.up[i], l = ln.lo[i];
     int32_t kk = m.n_fine;
     LineState ls;
-    int32_t vu, vl;
-    if (!gather_line_states<MODE>(m, st, spack, u, l, ls, vu, vl)) {
+    if (!gather_line_states<MODE, LTE>(m, st, spack, u, l, ls)) {
       ++tot.bad;
       if (REC) key[i] = kk;
       continue;
@@ -305,106 +281,72 @@ __global__ __launch_bounds__(256) void k_lines_pass1(ModelDev m, const SlotDev* 
     int64_t a, b;
     if (nu > 0.0 && line_window(nu, m.max_cut, m.nu0, m.dnu, m.n_bins, a, b)) {
       ++tot.kept;
-      const float Af = ln.A[i];
-      const float lsf = ln.lscale ? ln.lscale[i] : 0.0f;
+      const LineFac f = line_fac(m.mode, LTE ? XS_LTE : m.pop, ls, (double)ln.A[i], nu);
       if (REC) {
         int64_t kc = home_bin(nu, m.nu0, m.dnu);
         int64_t fk = kc < 0 ? 0 : kc >> m.fine_sh;
         kk = (int32_t)(fk < m.n_fine - 1 ? fk : m.n_fine - 1);
-        LinePack lp;
-        lp.Eu = ls.Eu;
-        lp.El = ls.El;
-        lp.gu = ls.gu;
-        lp.u = u;
-        lp.l = l;
-        lp.A = Af;
-        lp.gref = ln.gref ? ln.gref[i] : (float)ln.gref_scalar;
-        lp.nexp = ln.nexp ? ln.nexp[i] : (float)ln.nexp_scalar;
-        lp.lscale = lsf;
-        lp.evu = ls.evu;
-        lp.evl = ls.evl;
-        lpack[i] = lp;
+        put_pack((typename PackOf<LTE>::type*)lpack + i, f, nu, ln.gref ? ln.gref[i] : (float)ln.gref_scalar,
+                 ln.nexp ? ln.nexp[i] : (float)ln.nexp_scalar);
       }
       tot.pairs += window_pairs(m, cutc, cutm, nu, a, b);
       if (f32) {
-        const double sc = (double)lsf;
-        const double base = ln_line(m.mode, ls, (double)Af, nu);
+        const double sc = ln.lscale ? (double)ln.lscale[i] : 0.0;
 #pragma unroll 1
         for (int q = 0; q < m.n_slots; ++q) {
-          const SlotDev sd = slots[q];
-          int sg;
-          const double lS = base + ln_pop(m.mode, m.pop, ls, nu, sd.T, sd.Tv, sd.Tr, sg) + sc;
-          if (q < kPass1Slots) {
-            lmax[q][tid] = fmax(lmax[q][tid], lS - lnq[q]);
-          } else if (lS - log(Q[q]) > -INFINITY) {  // rare: more than kPass1Slots temperatures
-            atomicMax(smax + q, dbl_key(lS - log(Q[q])));
-          }
+          const double lS = intensity_log(intensity<LTE>(m.mode, m.pop, f, sf[q]), sf[q], sc);
+          // (a stale maximum only costs an atomic that changes nothing)
+          if (lS > -INFINITY && dbl_key(lS) > bmax[q]) atomicMax(&bmax[q], dbl_key(lS));
         }
       }
     }
     if (REC) key[i] = kk;
   }
-  block_totals(tot, scnt, part);
-  if (f32) {
-    __syncthreads();
-    for (int q = tid >> 6; q < ns; q += 4) {  // a wave per slot
-      const int lane = tid & 63;
-      double v = fmax(fmax(lmax[q][lane], lmax[q][lane + 64]), fmax(lmax[q][lane + 128], lmax[q][lane + 192]));
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-      if (lane == 0)
-        part[(int64_t)(3 + q) * gridDim.x + blockIdx.x] = v > -INFINITY ? dbl_key(v) : 0ull;
-    }
-  }
+  block_totals(tot, scnt, part);  // (and a barrier)
+  if (f32)
+    for (int q = threadIdx.x; q < m.n_slots; q += 256)
+      if (bmax[q] > __hip_atomic_load(smax + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(smax + q, bmax[q]);
 }
 
 // Adds the blocks' totals, and sets the FP32 form's scale of every slot.
-__global__ __launch_bounds__(1024) void k_line_totals(ModelDev m, const unsigned long long* part, int blocks,
-                                                      unsigned long long* smax, double* sb,
-                                                      unsigned long long* stats) {
+__global__ __launch_bounds__(256) void k_line_totals(ModelDev m, const unsigned long long* part, int blocks,
+                                                     const unsigned long long* smax, double* sb,
+                                                     unsigned long long* stats) {
   const int v = threadIdx.x >> 6, lane = threadIdx.x & 63;  // a wave per value
-  const int nv = 3 + (m.prec == XS_FP32 ? min(m.n_slots, kPass1Slots) : 0);
-  if (v < nv) {
+  if (v < 3) {
     unsigned long long r = 0;
 #pragma unroll 8
-    for (int b = lane; b < blocks; b += 64) {
-      const unsigned long long x = part[(int64_t)v * blocks + b];
-      r = v < 3 ? r + x : max(r, x);
-    }
-    if (v < 3) {
-      r = wave_sum(r);
-    } else {
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        const unsigned long long x = __shfl_xor(r, o, 64);
-        r = max(r, x);
-      }
-    }
-    if (lane == 0) (v < 3 ? stats[1 + v] : smax[v - 3]) = r;
+    for (int b = lane; b < blocks; b += 64) r += part[(int64_t)v * blocks + b];
+    r = wave_sum(r);
+    if (lane == 0) stats[1 + v] = r;
   }
-  __syncthreads();
   if (threadIdx.x < m.n_slots) sb[threadIdx.x] = smax[threadIdx.x] ? key_dbl(smax[threadIdx.x]) : 0.0;
 }
 
 static int line_blocks(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(kPass1Blocks, (n + 255) / 256)); }
 
-// The blocks' totals go to keyA, free until the sort's first pass: 88 bytes a
-// block, which has 256 lines (the first fewer, and 256 bytes of the carve).
+// The blocks' totals go to keyA, free until the sort's first pass: 24 bytes a
+// block, which has 256 lines (the last fewer; the carve is at least 256 bytes).
 static unsigned long long* totals_part(const Work& w) { return reinterpret_cast<unsigned long long*>(w.keyA); }
-static_assert(kTotals * 8 <= 256, "a block's totals fit the smallest carve");
+static void line_totals(const ModelDev& m, const Work& w, int64_t n, hipStream_t s) {
+  hipLaunchKernelGGL(k_line_totals, dim3(1), dim3(256), 0, s, m, totals_part(w), line_blocks(n), w.smax, w.sb,
+                     w.stats);
+}
 
 template <bool REC>
 static void pass1(const ModelDev& m, const Work& w, const StatesView& st, const LinesView& ln, hipStream_t s) {
   const void* pack = state_pack(m, w, st);
-  hipLaunchKernelGGL((pack ? k_lines_pass1<1, REC> : k_lines_pass1<0, REC>), dim3(line_blocks(ln.n)), dim3(256), 0, s,
-                     m, w.slot, w.Q, w.cut_class, w.cut_mult, st, pack, ln, w.key, w.lpack, w.smax, totals_part(w));
+  const bool lte = m.pop == XS_LTE;
+  auto* const k = pack ? (lte ? k_lines_pass1<1, REC, true> : k_lines_pass1<1, REC, false>)
+                       : (lte ? k_lines_pass1<0, REC, true> : k_lines_pass1<0, REC, false>);
+  hipLaunchKernelGGL(k, dim3(line_blocks(ln.n)), dim3(256), 0, s, m, w.slot, w.Q, w.cut_class, w.cut_mult, st, pack,
+                     ln, w.key, (void*)w.lpack, w.smax, totals_part(w));
 }
 
 void launch_lines_pass1(const ModelDev& m, const Work& w, const StatesView& st,
                         const LinesView& ln, hipStream_t s) {
   pass1<true>(m, w, st, ln, s);
-  hipLaunchKernelGGL(k_line_totals, dim3(1), dim3(1024), 0, s, m, totals_part(w), line_blocks(ln.n), w.smax, w.sb,
-                     w.stats);
+  line_totals(m, w, ln.n, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -667,20 +609,22 @@ void launch_radix_sort(const ModelDev& m, const Work& w, int64_t n, int64_t max_
 // and, in the same pass, the sorted line records: nu, gamma_ref, n_exp, original index, and the
 // intensity of every slot, S (FP64) or S~ = sign exp(ln|S| - s_b) (FP32).
 // ---------------------------------------------------------------------------
+template <bool LTE>
 __global__ __launch_bounds__(256) void k_records(ModelDev m, const SlotDev* slots, const double* Q,
-                                                 const double* sb, StatesView st,
-                                                 const LinePack* lpack,
-                                                 const int32_t* skeys, const int32_t* svals, int64_t n,
+                                                 const double* sb, StatesView st, LinesView ln,
+                                                 const void* lpack,
+                                                 const int32_t* skeys, const int32_t* svals,
                                                  const unsigned long long* stats, int32_t* off, int far,
                                                  int64_t max_lines, double* rnu, float* rgref,
                                                  float* rnexp, double* rgpre, int32_t* ridx, double* rEs,
                                                  void* rS,
                                                  const double* cut_class, int32_t* rkc, float* rdel,
                                                  int32_t* rwin, int32_t* counter) {
-  __shared__ double lnQ[kMaxCond];  // ln Q of every slot, once per block
-  for (int q = threadIdx.x; q < m.n_slots; q += 256) lnQ[q] = log(Q[q]);
+  __shared__ SlotFac sf[kMaxCond];
+  for (int q = threadIdx.x; q < m.n_slots; q += 256)
+    sf[q] = slot_fac(slots[q], m.pop, Q[q], m.prec == XS_FP32 ? sb[q] : 0.0);
   __syncthreads();
-  const int64_t nk = (int64_t)stats[1];
+  const int64_t n = ln.n, nk = (int64_t)stats[1];
   bool odd = false;
   for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p <= n; p += (int64_t)gridDim.x * 256) {
     {
@@ -690,19 +634,18 @@ __global__ __launch_bounds__(256) void k_records(ModelDev m, const SlotDev* slot
     }
     if (p >= nk) continue;
     const int32_t i = svals[p];
-    const LinePack lp = lpack[i];
-    const int32_t u = lp.u, l = lp.l;
-    const double nu = lp.Eu - lp.El;
+    const auto lp = ((const typename PackOf<LTE>::type*)lpack)[i];
+    const double nu = lp.nu;
     rnu[p] = nu;
     rgref[p] = lp.gref;
     rnexp[p] = lp.nexp;
     if (rgpre) {
       // natural width of a predissociating upper state: HWHM 1/(4 pi c tau)
-      const double tau = st.tau[u];
+      const double tau = st.tau[ln.up[i]];
       rgpre[p] = (tau > 0.0 && tau < INFINITY) ? 1.0 / (4.0 * kPI * kC * tau) : 0.0;
     }
     ridx[p] = i;
-    rEs[p] = (m.mode == XS_ABSORPTION) ? lp.El : lp.Eu;
+    if (LTE) rEs[p] = lp.er;
     // home bin, offset from it, and the exact window of every cut-off class
     const int64_t kc = home_bin(nu, m.nu0, m.dnu);
     rkc[p] = (int32_t)kc;
@@ -713,18 +656,12 @@ __global__ __launch_bounds__(256) void k_records(ModelDev m, const SlotDev* slot
         klo = 1;
         khi = 0;
       }
-      rwin[((int64_t)q * max_lines + p) * 2] = (int32_t)klo;
-      rwin[((int64_t)q * max_lines + p) * 2 + 1] = (int32_t)khi;
+      ((int2*)rwin)[(int64_t)q * max_lines + p] = make_int2((int)klo, (int)khi);
     }
-    const LineState ls = line_state(st, lp, m.pop);
-    const double A = (double)lp.A;
-    const double sc = (double)lp.lscale;
-    const double base = ln_line(m.mode, ls, A, nu);
+    const LineFac f = pack_fac(lp);
+    const double sc = ln.lscale ? (double)ln.lscale[i] : 0.0;
     for (int q = 0; q < m.n_slots; ++q) {
-      const SlotDev sd = slots[q];
-      int sg;
-      const double lS = (base + ln_pop(m.mode, m.pop, ls, nu, sd.T, sd.Tv, sd.Tr, sg)) - lnQ[q] + sc;
-      const double S = sg * exp(m.prec == XS_FP32 ? lS - sb[q] : lS);
+      const double S = intensity_value(intensity<LTE>(m.mode, m.pop, f, sf[q]), sf[q], sc);
       if (m.prec == XS_FP32)
         ((float*)rS)[(int64_t)q * max_lines + p] = (float)S;
       else
@@ -738,38 +675,37 @@ __global__ __launch_bounds__(256) void k_records(ModelDev m, const SlotDev* slot
 }
 
 void launch_offsets_records(const ModelDev& m, const Work& w, const StatesView& st,
-                            const LinesView& ln, const int32_t* skeys, const int32_t* svals,
-                            int64_t n, hipStream_t s) {
-  int64_t blocks = (n + 256) / 256;
+                            const LinesView& ln, const int32_t* skeys, const int32_t* svals, hipStream_t s) {
+  int64_t blocks = (ln.n + 256) / 256;
   if (blocks > 8192) blocks = 8192;
-  hipLaunchKernelGGL(k_records, dim3((unsigned)blocks), dim3(256), 0, s, m, w.slot, w.Q, w.sb, st,
-                     w.lpack, skeys, svals, n, w.stats, w.off, w.far_rows != nullptr, w.max_lines, w.rnu, w.rgref,
-                     w.rnexp, w.rgpre, w.ridx, w.rEs, w.rS, w.cut_class, w.rkc, w.rdel, w.rwin, w.counter);
+  hipLaunchKernelGGL((m.pop == XS_LTE ? k_records<true> : k_records<false>), dim3((unsigned)blocks), dim3(256), 0, s,
+                     m, w.slot, w.Q, w.sb, st, ln, (const void*)w.lpack, skeys, svals, w.stats, w.off,
+                     w.far_rows != nullptr, w.max_lines, w.rnu, w.rgref, w.rnexp, w.rgpre, w.ridx, w.rEs, w.rS,
+                     w.cut_class, w.rkc, w.rdel, w.rwin, w.counter);
 }
 
 // ---------------------------------------------------------------------------
 // Stick spectrum output: S of every line for every condition, original order.
 // ---------------------------------------------------------------------------
 // The FP64 form needs no scale, so its totals are counted here, without a pass
-// before it (5e6 lines: 403 + 218 us in two passes, 203 in one); ln Q is
+// before it (5e6 lines: 403 + 218 us in two passes with logarithms, 155 in one); ln Q is
 // taken once per block and the states from the packed table (MODE, as above).
-template <int MODE, bool COUNT>
+template <int MODE, bool COUNT, bool LTE>
 __global__ __launch_bounds__(256) void k_intensity_out(ModelDev m, const CondDev* cond,
                                                        const SlotDev* slots, const double* Q,
                                                        const double* sb, const double* cutc, const int32_t* cutm,
                                                        StatesView st, const void* spack,
                                                        LinesView ln, void* S, double* lsc, unsigned long long* part) {
-  __shared__ double lnQ[kMaxCond];
+  __shared__ SlotFac sf[kMaxCond];
   __shared__ unsigned long long scnt[12];
-  for (int q = threadIdx.x; q < m.n_slots; q += 256) lnQ[q] = log(Q[q]);
+  for (int q = threadIdx.x; q < m.n_slots; q += 256) sf[q] = slot_fac(slots[q], m.pop, Q[q], COUNT ? 0.0 : sb[q]);
   __syncthreads();
   Totals tot;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < ln.n;
        i += (int64_t)gridDim.x * 256) {
     const int32_t u = ln.up[i], l = ln.lo[i];
-    LineState ls{0, 0, 0, 0, 0};
-    int32_t vu, vl;
-    const bool ok = gather_line_states<MODE>(m, st, spack, u, l, ls, vu, vl);
+    LineState ls{0, 0, 0, 0, 0, 0, 0};
+    const bool ok = gather_line_states<MODE, LTE>(m, st, spack, u, l, ls);
     const double nu = ok ? ls.Eu - ls.El : 0.0;
     if (COUNT) {
       int64_t a, b;
@@ -781,16 +717,10 @@ __global__ __launch_bounds__(256) void k_intensity_out(ModelDev m, const CondDev
       }
     }
     const double sc = ln.lscale ? (double)ln.lscale[i] : 0.0;
-    const double base = nu > 0.0 ? ln_line(m.mode, ls, (double)ln.A[i], nu) : 0.0;
+    const LineFac f = line_fac(m.mode, LTE ? XS_LTE : m.pop, ls, (double)ln.A[i], nu);
     for (int c = 0; c < m.n_cond; ++c) {
-      const int q = cond[c].slot;
-      const SlotDev sd = slots[q];
-      double v = 0.0;
-      if (nu > 0.0) {
-        int sg;
-        const double lS = (base + ln_pop(m.mode, m.pop, ls, nu, sd.T, sd.Tv, sd.Tr, sg)) - lnQ[q] + sc;
-        v = (m.prec == XS_FP32) ? sg * exp(lS - sb[q]) : sg * exp(lS);
-      }
+      const SlotFac& q = sf[cond[c].slot];
+      const double v = nu > 0.0 ? intensity_value(intensity<LTE>(m.mode, m.pop, f, q), q, sc) : 0.0;
       if (m.prec == XS_FP32)
         ((float*)S)[(int64_t)c * ln.n + i] = (float)v;
       else
@@ -806,25 +736,23 @@ template <bool COUNT>
 static void intensity_out(const ModelDev& m, const Work& w, const StatesView& st, const LinesView& ln, void* S,
                           double* log_scale, hipStream_t s) {
   const void* pack = state_pack(m, w, st);
-  hipLaunchKernelGGL((pack ? k_intensity_out<1, COUNT> : k_intensity_out<0, COUNT>), dim3(line_blocks(ln.n)),
-                     dim3(256), 0, s, m, w.cond, w.slot, w.Q, w.sb, w.cut_class, w.cut_mult, st, pack, ln, S,
-                     log_scale, totals_part(w));
+  const bool lte = m.pop == XS_LTE;
+  auto* const k = pack ? (lte ? k_intensity_out<1, COUNT, true> : k_intensity_out<1, COUNT, false>)
+                       : (lte ? k_intensity_out<0, COUNT, true> : k_intensity_out<0, COUNT, false>);
+  hipLaunchKernelGGL(k, dim3(line_blocks(ln.n)), dim3(256), 0, s, m, w.cond, w.slot, w.Q, w.sb, w.cut_class,
+                     w.cut_mult, st, pack, ln, S, log_scale, totals_part(w));
 }
 
 // After launch_partition with lines set.
 void launch_intensity_out(const ModelDev& m, const Work& w, const StatesView& st,
                           const LinesView& ln, void* S, double* log_scale, hipStream_t s) {
-  const auto totals = [&] {
-    hipLaunchKernelGGL(k_line_totals, dim3(1), dim3(1024), 0, s, m, totals_part(w), line_blocks(ln.n), w.smax, w.sb,
-                       w.stats);
-  };
   if (m.prec == XS_FP32) {
     pass1<false>(m, w, st, ln, s);
-    totals();
+    line_totals(m, w, ln.n, s);
     if (ln.n > 0) intensity_out<false>(m, w, st, ln, S, log_scale, s);
   } else {
     intensity_out<true>(m, w, st, ln, S, log_scale, s);
-    totals();
+    line_totals(m, w, ln.n, s);
   }
 }
 

@@ -472,7 +472,7 @@ int preprocess(xs_plan* p, const xs_states* st, const xs_lines* ln) {
   int32_t *sk = nullptr, *svv = nullptr;
   launch_radix_sort(p->md, p->w, lv.n, p->md.n_fine, p->stream, &sk, &svv);
   p->has_tau = st->lifetime != nullptr;
-  launch_offsets_records(p->md, kernel_work(p), sv, lv, sk ? sk : p->w.keyA, svv ? svv : p->w.valA, lv.n,
+  launch_offsets_records(p->md, kernel_work(p), sv, lv, sk ? sk : p->w.keyA, svv ? svv : p->w.valA,
                          p->stream);
   p->last_lines_in = lv.n;
   p->prepared = true;

@@ -104,15 +104,18 @@ struct LinesView {
   double gref_scalar, nexp_scalar;
 };
 
-// One line's inputs and the energies and degeneracy of its states, packed
-// by the first line pass in input order, so that the record pass, which
-// visits the lines in wavenumber order, fetches one 64-byte block per line
-// instead of a cache line from each input array and state table.
+// What the record pass takes of one line, packed by the first line pass in
+// input order: that pass visits the lines in wavenumber order and so fetches one
+// block per line instead of a cache line from each input array and state table.
+// The factors are those of LineFac (k_common.h); ev, er, xv, xr only where the
+// populations are not LTE's.
+struct __attribute__((aligned(32))) LinePackLTE {
+  double P, er, nu;
+  float gref, nexp;
+};
 struct __attribute__((aligned(64))) LinePack {
-  double Eu, El, gu;
-  float A, gref, nexp, lscale;
-  int32_t u, l;
-  double evu, evl;  // E_vib of the upper and lower manifolds (non-LTE; 0 for LTE)
+  double P, ev, er, xv, xr, nu;
+  float gref, nexp;
 };
 
 // Workspace pointers (carved by the host runtime from the caller's buffer).
@@ -184,8 +187,7 @@ void launch_lines_pass1(const ModelDev& m, const Work& w, const StatesView& st,
 void launch_radix_sort(const ModelDev& m, const Work& w, int64_t n, int64_t max_key, hipStream_t s,
                        int32_t** sorted_keys, int32_t** sorted_vals);
 void launch_offsets_records(const ModelDev& m, const Work& w, const StatesView& st,
-                            const LinesView& ln, const int32_t* skeys, const int32_t* svals,
-                            int64_t n, hipStream_t s);
+                            const LinesView& ln, const int32_t* skeys, const int32_t* svals, hipStream_t s);
 void launch_intensity_out(const ModelDev& m, const Work& w, const StatesView& st,
                           const LinesView& ln, void* S, double* log_scale, hipStream_t s);
 void launch_q_out(const ModelDev& m, const Work& w, double* Q, double* dQ, hipStream_t s);
