@@ -18,9 +18,8 @@
 // is split into parts whose rows k_reduce adds in order, so the sums do not
 // depend on scheduling.  Bound by VALU issue and by
 // the LDS adds.  Measured against the gather's rows clipped to the near leaves
-// (64 points): 1e7 lines FP32 4.07 -> 2.21 ms with leaves of 16 points (3.07
-// with 64), 1e6 lines FP64 1.30 -> 0.82 ms, 48 conditions x 1e6 lines FP32
-// 9.39 -> 4.74 ms.
+// (64 points): 1e7 lines FP32 4.07 -> 1.32 ms with leaves of 16 points, 1e6 lines
+// FP64 1.30 -> 0.68 ms, 48 conditions x 1e6 lines FP32 9.39 -> 2.73 ms.
 #include <algorithm>
 
 #include "k_voigt.h"
@@ -51,6 +50,7 @@ struct NearArgs {
   double* sigma;
   int32_t accumulate;
   int32_t n_ct;             // tiles * n_cond; ct = tile * n_cond + condition
+  int32_t extra_blocks;     // the first blocks of k_near's grid, which take the parts beyond the first
 };
 
 // Lines of tile t: segments of sorted lines.
@@ -87,8 +87,11 @@ __device__ __forceinline__ NearSegs near_segments(const NearArgs& g, const CondD
 // least kNearChunk lines, and so many that the parts beyond the first stay
 // under kNearExtra: an even list is not split, and a list whose lines crowd
 // into a few tiles is spread over the chip.
-constexpr int64_t kNearChunk = 4096;
-constexpr int kNearExtra = 4096;
+// The parts beyond the first run before the tiles, since a grid that ends with
+// its largest blocks leaves compute units waiting for them (parts of 4096 lines
+// at the end of the grid: a third of the CU cycles of 1e7 lines idle, 2.22 -> 1.51 ms).
+constexpr int64_t kNearChunk = 1024;
+constexpr int kNearExtra = 8192;
 
 __global__ __launch_bounds__(256) void k_near_count(NearArgs g) {
   unsigned long long local = 0;
@@ -138,6 +141,16 @@ __device__ __forceinline__ int near_place(int o) { return (o & 3) * kNearPart + 
 struct NearLane {
   int slot, sub, ks;
 };
+// The place of a wave's line in the order of beginnings.  The FP32 form reverses
+// its bits, so that neighbouring lanes, whose adds the LDS takes together, begin
+// far apart: over a ring of three points 64 lanes in order are 16 adds to one
+// address at a time, reversed 6 (48 conditions x 1e6 lines 4.79 -> 2.73 ms, 1e7 lines
+// 1.56 -> 1.32).  The FP64 form is not bound by the adds (0.68 ms at 1e6 lines either
+// way, bin means 1.30 and 1.34).
+template <typename Real>
+__device__ __forceinline__ int near_slot(int v, int ks) {
+  return sizeof(Real) == 4 ? (int)(__builtin_bitreverse32((unsigned)v) >> 1 >> (25 + ks)) : v;
+}
 __device__ __forceinline__ int near_count(const NearLane& ln, int n) {
   return n > ln.sub ? (n - ln.sub + (1 << ln.ks) - 1) >> ln.ks : 0;
 }
@@ -419,70 +432,79 @@ __global__ __launch_bounds__(256) void k_near(NearArgs g) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const ModelDev& m = g.m;
-  // blocks 0..n_ct - 1: the tiles' first parts; then the other parts
-  int ct = blockIdx.x, part = 0;
-  if (ct >= g.n_ct) {
-    const int e = ct - g.n_ct;
-    if (e >= g.counter[6]) return;
-    ct = g.extra[2 * e];
-    part = g.extra[2 * e + 1];
-  }
-  const int np = g.parts[ct];
-  const int c = ct % m.n_cond, t = ct / m.n_cond;
-  const CondDev& cd = g.cond[c];
-  const NearSegs sg = near_segments(g, cd, t);
-  const int gap = cd.far.on ? far_gap(cd.far, 0, t * (kNearBins >> m.fine_sh)) : 0;
-  const int tlo = t * kNearBins, thi = (int)min<int64_t>((int64_t)tlo + kNearBins, m.n_bins) - 1;
-  const int64_t chunk = *(const int64_t*)(g.counter + 4);
-  const int64_t q0 = np > 1 ? part * chunk : 0;
-  const int64_t q1 = np > 1 ? min(sg.cum[kSegs - 1], q0 + chunk) : sg.cum[kSegs - 1];
   double* row = rows[wave];
+  // the grid's first blocks take the parts beyond tiles' first, the others one
+  // tile each
+  const bool extras = (int)blockIdx.x < g.extra_blocks;
+  const int items = extras ? g.counter[6] : (int)gridDim.x;
+  for (int item = blockIdx.x; item < items; item += extras ? g.extra_blocks : (int)gridDim.x) {
+    int ct = item - g.extra_blocks, part = 0;
+    if (extras) {
+      ct = g.extra[2 * item];
+      part = g.extra[2 * item + 1];
+    } else {
+      // each tile begins with another condition: blocks go to the eight dies in
+      // turn, and with a multiple of eight conditions a die had the same ones
+      const int t = ct / m.n_cond;
+      ct = t * m.n_cond + (ct + t) % m.n_cond;
+    }
+    const int np = g.parts[ct];
+    const int c = ct % m.n_cond, t = ct / m.n_cond;
+    const CondDev& cd = g.cond[c];
+    const NearSegs sg = near_segments(g, cd, t);
+    const int gap = cd.far.on ? far_gap(cd.far, 0, t * (kNearBins >> m.fine_sh)) : 0;
+    const int tlo = t * kNearBins, thi = (int)min<int64_t>((int64_t)tlo + kNearBins, m.n_bins) - 1;
+    const int64_t chunk = *(const int64_t*)(g.counter + 4);
+    const int64_t q0 = np > 1 ? part * chunk : 0;
+    const int64_t q1 = np > 1 ? min(sg.cum[kSegs - 1], q0 + chunk) : sg.cum[kSegs - 1];
 #pragma unroll
-  for (int j = 0; j < kNearRow / 64; ++j) row[lane + 64 * j] = 0.0;
-  __syncthreads();
-  // few lines are spread over the block's lanes, up to a wave to a line
-  int ks = 0;
-  while (ks < 6 && ((q1 - q0) << (ks + 1)) <= 256) ++ks;
-  const NearLane ln = {lane >> ks, lane & ((1 << ks) - 1), ks};
-  for (int64_t b0 = q0; b0 < q1; b0 += 256 >> ks) {
-    const int64_t q = b0 + (tid >> ks);
-    if (q < q1) {
-      const bool near = q < sg.cum[0];
-      const int64_t p = q + (near ? sg.beg[0] : q < sg.cum[1] ? sg.beg[1] : sg.beg[2]);
-      const int2 win = ((const int2*)g.rwin)[(int64_t)cd.cclass * g.max_lines + p];
-      const int kc = g.rkc[p];
-      const Real S = ((const Real*)g.rS)[(int64_t)cd.slot * g.max_lines + p];
-      const double nu = g.rnu[p];
-      const float gref = g.rgref[p], nexp = g.rnexp[p];
-      const double gpre = g.rgpre ? g.rgpre[p] : 0.0;
-      int klo = max(win.x, tlo), khi = min(win.y, thi);
-      if (near) {
-        const int f = kc >> m.fine_sh;
-        klo = max(klo, (f - gap) << m.fine_sh);
-        khi = min(khi, ((f + gap + 1) << m.fine_sh) - 1);
-      }
-      if (win.x <= win.y && klo <= khi && S != (Real)0) {
-        if constexpr (sizeof(Real) == 4)
-          near_line_f32<PROF>(m, cd, ln, kc, klo, khi, g.rdel[p], (float)nu, S, gref, nexp, (float)gpre, row, tlo);
-        else
-          near_line_f64<PROF>(m, cd, ln, kc, klo, khi, nu, S, (double)gref, (double)nexp, gpre, row, tlo);
+    for (int j = 0; j < kNearRow / 64; ++j) row[lane + 64 * j] = 0.0;
+    __syncthreads();
+    // few lines are spread over the block's lanes, up to a wave to a line
+    int ks = 0;
+    while (ks < 6 && ((q1 - q0) << (ks + 1)) <= 256) ++ks;
+    const NearLane ln = {near_slot<Real>(lane >> ks, ks), lane & ((1 << ks) - 1), ks};
+    for (int64_t b0 = q0; b0 < q1; b0 += 256 >> ks) {
+      const int64_t q = b0 + (tid >> ks);
+      if (q < q1) {
+        const bool near = q < sg.cum[0];
+        const int64_t p = q + (near ? sg.beg[0] : q < sg.cum[1] ? sg.beg[1] : sg.beg[2]);
+        const int2 win = ((const int2*)g.rwin)[(int64_t)cd.cclass * g.max_lines + p];
+        const int kc = g.rkc[p];
+        const Real S = ((const Real*)g.rS)[(int64_t)cd.slot * g.max_lines + p];
+        const double nu = g.rnu[p];
+        const float gref = g.rgref[p], nexp = g.rnexp[p];
+        const double gpre = g.rgpre ? g.rgpre[p] : 0.0;
+        int klo = max(win.x, tlo), khi = min(win.y, thi);
+        if (near) {
+          const int f = kc >> m.fine_sh;
+          klo = max(klo, (f - gap) << m.fine_sh);
+          khi = min(khi, ((f + gap + 1) << m.fine_sh) - 1);
+        }
+        if (win.x <= win.y && klo <= khi && S != (Real)0) {
+          if constexpr (sizeof(Real) == 4)
+            near_line_f32<PROF>(m, cd, ln, kc, klo, khi, g.rdel[p], (float)nu, S, gref, nexp, (float)gpre, row, tlo);
+          else
+            near_line_f64<PROF>(m, cd, ln, kc, klo, khi, nu, S, (double)gref, (double)nexp, gpre, row, tlo);
+        }
       }
     }
-  }
-  __syncthreads();
-  const int o = near_place(tid);
-  const double v = ((rows[0][o] + rows[1][o]) + rows[2][o]) + rows[3][o];
-  if (np == 1) {
-    const int64_t k = (int64_t)tlo + tid;
-    if (k <= thi) {
-      double* out = g.sigma + (int64_t)c * m.n_bins + k;
-      const double s = (sizeof(Real) == 4 ? exp(g.sb[cd.slot]) : 1.0) * v;
-      *out = g.accumulate ? *out + s : s;
+    __syncthreads();
+    const int o = near_place(tid);
+    const double v = ((rows[0][o] + rows[1][o]) + rows[2][o]) + rows[3][o];
+    if (np == 1) {
+      const int64_t k = (int64_t)tlo + tid;
+      if (k <= thi) {
+        double* out = g.sigma + (int64_t)c * m.n_bins + k;
+        const double s = (sizeof(Real) == 4 ? exp(g.sb[cd.slot]) : 1.0) * v;
+        *out = g.accumulate ? *out + s : s;
+      }
+    } else {
+      // rows of a split tile: part 0's after the extra parts' rows
+      const int64_t r = part == 0 ? (int64_t)kNearExtra + g.base[ct] : (int64_t)g.base[ct] + part - 1;
+      g.rows[r * kNearBins + tid] = v;
     }
-  } else {
-    // rows of a split tile: part 0's after the extra parts' rows
-    const int64_t r = part == 0 ? (int64_t)kNearExtra + g.base[ct] : (int64_t)g.base[ct] + part - 1;
-    g.rows[r * kNearBins + tid] = v;
+    __syncthreads();  // (the rows are the next part's)
   }
 }
 
@@ -505,7 +527,7 @@ __global__ __launch_bounds__(256) void k_near_reduce(NearArgs g) {
 
 size_t near_row_doubles() { return (size_t)2 * kNearExtra * kNearBins + kNearExtra; }
 
-void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate, hipStream_t s) {
+void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate, int64_t n_lines, hipStream_t s) {
   NearArgs a;
   a.m = m;
   a.cond = w.cond;
@@ -532,7 +554,9 @@ void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate
   const int cb = (int)std::min<int64_t>(1024, (a.n_ct + 255) / 256);
   hipLaunchKernelGGL(k_near_count, dim3(cb), dim3(256), 0, s, a);
   hipLaunchKernelGGL(k_near_plan, dim3(cb), dim3(256), 0, s, a);
-  const dim3 grid((unsigned)(a.n_ct + kNearExtra));
+  // about as many as there are parts (a line meets a tile or two); fewer take turns
+  a.extra_blocks = (int)std::min<int64_t>(kNearExtra, 8 + n_lines * m.n_cond / kNearChunk);
+  const dim3 grid((unsigned)(a.n_ct + a.extra_blocks));
 #define XS_N(PR)                                                                                        \
   if (m.profile == PR && m.prec == XS_FP32) hipLaunchKernelGGL((k_near<float, PR>), grid, dim3(256), 0, s, a); \
   else if (m.profile == PR) hipLaunchKernelGGL((k_near<double, PR>), grid, dim3(256), 0, s, a);

@@ -498,7 +498,7 @@ int profile_pass(xs_plan* p, double* sigma, int accumulate) {
   else if (!use_far(p)) {
     launch_gather(p->md, kernel_work(p), p->tiling, sigma, accumulate, p->stream);
   } else {
-    launch_near(p->md, kernel_work(p), sigma, accumulate, p->stream);
+    launch_near(p->md, kernel_work(p), sigma, accumulate, p->last_lines_in, p->stream);
     launch_far(p->md, kernel_work(p), p->far_lmax, p->far_end, sigma, p->stream);
   }
   return hip_check(hipGetLastError(), "profile launch");

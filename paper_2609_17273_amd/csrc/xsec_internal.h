@@ -204,7 +204,7 @@ void launch_scatter(const ModelDev& m, const Work& w, double* sigma, int accumul
 size_t near_row_doubles();  // what it takes of Work::part
 // sigma = (or +=) the points near each line, for the conditions with tile
 // expansions, and every point of the others
-void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate, hipStream_t s);
+void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate, int64_t n_lines, hipStream_t s);
 
 // ---- tile expansions (k_far.hip) ----
 int far_nodes(int prec);  // nodes per tile
