@@ -174,6 +174,26 @@ XS_HD int far_levels_of_grid(int32_t n_fine) {
   while (l < kFarLevels && (n_fine >> l) >= 3) ++l;
   return l;
 }
+// Moments: one row per cell of every level, level after level; and the cells of
+// level `l` or less that make up the leaves [lo, hi], one after the other: the
+// widest that begins at lo.
+XS_HD int64_t far_cells_before(int32_t n_fine, int l) {
+  int64_t r = 0;
+  for (int k = 0; k < l; ++k) r += far_tiles(n_fine, k);
+  return r;
+}
+XS_HD int far_widest(int32_t lo, int32_t hi, int l) {
+  int v = 0;
+  while (v < l && (lo & ((2 << v) - 1)) == 0 && hi - lo >= (2 << v) - 1) ++v;
+  return v;
+}
+// The lowest level whose tiles may take lines of half-widths up to gamma (in
+// points) through moments: half a cell of it.
+XS_HD int far_mom_level(int sh, double gamma) {
+  int l = 0;
+  while (l < kFarLevels && !(gamma <= 0.5 * (double)(1 << (sh + l)))) ++l;
+  return l;
+}
 // blocks of a level: 4 >> far_wide tiles each, or one slice of one tile
 XS_HD int32_t far_blocks(int32_t n_fine, int sh, int l) {
   const int w = far_wide(sh, l);

@@ -11,10 +11,12 @@
 //
 // What bounds a pass is the number of profile evaluations; measured on the
 // whole call, point by point and with expansions: 1e7 lines, 2e6 points, window
-// 5000 points, FP32 form 14.65 and 5.6 ms (near leaves 2.2, tiles 1.24, window
-// ends and sigma 0.78); 1e6 lines, FP64 form 3.33 and 2.1 ms; 48 conditions of
-// 1e6 lines, 2e5 points, FP32 form 113.2 and 13.0 ms.
+// 5000 points, FP32 form 14.65 and 2.76 ms (near leaves 1.27, tiles 0.35, window
+// ends and sigma 0.27); 1e6 lines, FP64 form 3.33 and 1.16 ms; 48 conditions of
+// 1e6 lines, 2e5 points, FP32 form 113.2 and 7.2 ms.
 //
+// k_far_leaves, k_far_moments, k_far_cells: the tiles whose lines' moments serve
+//   (below); k_far: the others, and short lists.
 // k_far: one wave (up to four for wider tiles, then slices of their lines)
 //   takes 64 lines at a time, one per lane, evaluates each at the tile's nodes
 //   into P registers of the lane, and adds the lanes once at the end, so a
@@ -47,6 +49,10 @@ struct FarArgs {
   double* rows;       // [n_cond][rows_per_cond][P]
   int64_t cond_rows;  // rows per condition
   double* sigma;
+  double* mom;        // [conditions of the launch][mom_cells][PM] moments, or null
+  int64_t mom_cells;  // cells of all levels
+  int32_t c0;         // first condition of the launch (not k_far_finish)
+  int32_t blocks;     // of k_far's levels
 };
 
 // The nodes' rational functions N/D, four over one reciprocal:
@@ -366,112 +372,394 @@ __device__ __forceinline__ int far_slot(int lane) {
   return ((lane >> 5) & 1) * (P / 2) + ((lane >> 4) & 1) * (P / 4);
 }
 
+// ---------------------------------------------------------------------------
+// Moments.  A Voigt profile in the far field is a Gaussian average of poles,
+//   S / pi Im E[1 / (nu - nu0 - i gamma - sigma t)],  t normal,
+// so about the centre c of a cell of lines its values are
+//   sum_n M_n / (nu - c)^(n+1),  M_n = S / pi Im E[(nu0 - c + i gamma + sigma t)^n],
+// and the M_n of all the cell's lines add up: a tile takes a cell, not each of its
+// lines, at PM operations a node.  The averages obey u_(n+1) = s u_n + n sigma^2
+// u_(n-1), s = nu0 - c + i gamma.  A wider cell's moments are those of its halves
+// moved to its centre (binomially), so a line is entered once, in its leaf,
+// instead of in the 20 tiles of its window.  Bin means average over the bin as
+// well, which is done to the moments of the leaf.
+//
+// With gamma <= half a cell a line lies within 0.71 cells of c and the nodes 1.5
+// away or more (of a narrower cell: within half the distance): the series ends
+// at 0.5^PM, 4e-9 for PM = 28 (FP32 form) and 4e-15 for 48.  The Gaussian's
+// part lies within 4.5 sigma at these orders, the nodes beyond 11 sigma.  Levels
+// whose cells are too small for the widest line (far_mom_level) take lines one by
+// one as before.
+//
+// The tiles of 1e7 lines FP32 (2e6 points) took 1.08 ms line by line, 0.35 by moments
+// (leaves 0.19, wider cells 0.05, tiles 0.11), 1e6 lines FP64 0.60 and 0.22, 48
+// conditions x 1e6 lines (of which 16 have lines too wide for most levels) 5.8
+// and 3.7.  The leaves are bound by the recurrence, seven operations a moment.
+// ---------------------------------------------------------------------------
+constexpr int kMoments32 = 28, kMoments64 = 48, kMomentsMax = 48;
+constexpr int kMomLeaves = 64, kMomLevels = 6;  // cells of a block of k_far_moments, levels it builds from them
+
+struct BinomTable {
+  double c[kMomentsMax + 1][kMomentsMax + 1];
+  constexpr BinomTable() : c() {
+    for (int n = 0; n <= kMomentsMax; ++n) {
+      c[n][0] = 1.0;
+      for (int k = 1; k <= n; ++k) c[n][k] = c[n - 1][k - 1] + (k < n ? c[n - 1][k] : 0.0);
+    }
+  }
+};
+static __device__ const BinomTable kBinom = BinomTable();
+static __device__ const double kFarX12[12] = XS_FAR_X12, kFarX20[20] = XS_FAR_X20;
+
+// the lowest level of the condition that uses moments
+__device__ __forceinline__ int far_cond_mom_level(const FarArgs& g, const CondDev& cd) {
+  const float* e = (const float*)g.counter;
+  const double n = fmax((double)e[kNexpMin] * cd.lnTr, (double)e[kNexpMax] * cd.lnTr);
+  return far_mom_level(cd.far.sh, (double)e[kGammaMax] * exp(n) * cd.pfac * 1.00001 / g.m.dnu);
+}
+
+// Moments of the leaves, a wave to a leaf and a line to a lane.
+template <typename Real, int PROF, int PM>
+__global__ __launch_bounds__(256, sizeof(Real) == 4 ? 4 : 2) void k_far_leaves(FarArgs g) {
+  constexpr bool F32 = sizeof(Real) == 4, LOR = PROF == XS_LORENTZ || PROF == XS_BIN_LORENTZ;
+  constexpr bool BIN = PROF == XS_BIN_LORENTZ || PROF == XS_BIN_VOIGT;
+  __shared__ double ma[4 * PM];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const CondDev& cd = g.cond[g.c0 + blockIdx.y];
+  const FarCond& fc = cd.far;
+  if (!fc.on || g.counter[kFarOff]) return;
+  const int lm = far_cond_mom_level(g, cd);
+  if (lm > fc.lmax) return;
+  const ModelDev& m = g.m;
+  const int nf = m.n_fine, f = blockIdx.x * 4 + wave;
+  if (f >= nf) return;
+  // in cells of the first level that uses them, so that the powers stay small
+  const double hp = (double)(1 << (fc.sh + lm)), ih = 1.0 / hp;
+  // (the edge cells' lines go point by point)
+  const bool any = f > 0 && f < nf - 1;
+  const uint32_t p0 = any ? g.off[f] : 0, p1 = any ? g.off[f + 1] : 0;
+  double acc64[PM];
+  Real acc[PM];
+#pragma unroll
+  for (int k = 0; k < PM; ++k) {
+    acc[k] = (Real)0;
+    if (F32) acc64[k] = 0.0;
+  }
+  const double centre = (double)(((int64_t)f << fc.sh) + (1 << fc.sh) / 2) - 0.5;
+  int since = 0;
+  for (uint32_t q0 = p0; q0 < p1; q0 += 64) {
+    const FarIn<Real> v = far_load<Real>(g, cd, min(q0 + lane, p1 - 1));
+    const Real S = q0 + lane < p1 ? v.S : (Real)0;
+    Real sr, si, sg2 = 0;
+    if constexpr (F32) {
+      const float gamma = fmaf(v.gr * __builtin_amdgcn_exp2f(v.ne * (float)(cd.lnTr / kLN2)), (float)cd.pfac, (float)v.gp);
+      const float pt = (float)(ih / m.dnu);
+      sr = fmaf(v.del, pt, (float)((v.kc - centre) * ih));
+      si = gamma * pt;
+      if constexpr (!LOR) {
+        const float sg = (float)v.nu * ((float)cd.dop * (float)0.84932180028801907 * pt);  // alpha / sqrt(2 ln 2)
+        sg2 = sg * sg;
+      }
+    } else {
+      const double del = (v.nu - nu_of_bin(m.nu0, m.dnu, v.kc)) - far_grid_residue(m.nu0, m.dnu, v.kc);
+      const double gamma = (double)v.gr * exp((double)v.ne * cd.lnTr) * cd.pfac + v.gp;
+      const double pt = ih / m.dnu;
+      sr = fma(del, pt, (v.kc - centre) * ih);
+      si = gamma * pt;
+      if constexpr (!LOR) {
+        const double sg = v.nu * (cd.dop * 0.84932180028801907 * pt);
+        sg2 = sg * sg;
+      }
+    }
+    Real pr = 1, pi = 0, ur = sr, ui = si;  // u_(n-1), u_n
+#pragma unroll
+    for (int n = 1; n <= PM; ++n) {
+      acc[n - 1] = fma(S, ui, acc[n - 1]);
+      if (n < PM) {
+        Real nr, ni;
+        if constexpr (LOR) {
+          nr = fma(sr, ur, -si * ui);
+          ni = fma(sr, ui, si * ur);
+        } else {
+          const Real e = (Real)n * sg2;
+          nr = fma(sr, ur, fma(-si, ui, e * pr));
+          ni = fma(sr, ui, fma(si, ur, e * pi));
+        }
+        pr = ur;
+        pi = ui;
+        ur = nr;
+        ui = ni;
+      }
+    }
+    if constexpr (F32) {
+      if (++since == 32) {
+        since = 0;
+#pragma unroll
+        for (int k = 0; k < PM; ++k) {
+          acc64[k] += (double)acc[k];
+          acc[k] = (Real)0;
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < PM; ++k) acc64[k] = F32 ? acc64[k] + (double)acc[k] : (double)acc[k];
+  far_fold<PM>(acc64, lane);
+  double* row = ma + wave * PM;
+  if ((lane & 15) == 0) {
+    const double f0 = ih / (kPI * m.dnu);
+    const int s0 = far_slot<PM>(lane);
+#pragma unroll
+    for (int i = 0; i < PM / 4; ++i) row[s0 + i] = acc64[i] * f0;
+  }
+  if constexpr (BIN) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // E[(s + b t)^n], t uniform: sum over k of C(n, 2k) b^(2k) / (2k + 1) M_(n-2k); b <= 1/32
+    const int n = lane + 1;
+    double v = 0.0, e = 1.0;
+    const double b2 = 0.25 * ih * ih;
+    if (n <= PM)
+      for (int k = 0; 2 * k < n && k <= 8; ++k) {
+        v = fma(kBinom.c[n][2 * k] * e / (double)(2 * k + 1), row[n - 2 * k - 1], v);
+        e *= b2;
+      }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (n <= PM) row[n - 1] = v;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  if (lane < PM) g.mom[((int64_t)blockIdx.y * g.mom_cells + f) * PM + lane] = row[lane];
+}
+
+// Moments of the kMomLevels levels above level `base`: a block has kMomLeaves of
+// its cells, a thread a moment of a wider cell.
+template <int PM>
+__global__ __launch_bounds__(256) void k_far_moments(FarArgs g, int base) {
+  __shared__ double ma[kMomLeaves * PM], mb[kMomLeaves / 2 * PM];
+  __shared__ double wt[PM][PM];  // [k - 1][n - 1]: what M_k of a half gives to M_n
+  const int tid = threadIdx.x;
+  const CondDev& cd = g.cond[g.c0 + blockIdx.y];
+  const FarCond& fc = cd.far;
+  if (!fc.on || g.counter[kFarOff] || base >= fc.lmax) return;
+  const int lm = far_cond_mom_level(g, cd);
+  if (lm > fc.lmax) return;
+  const int nf = g.m.n_fine, i0 = blockIdx.x * kMomLeaves;
+  double* const rows = g.mom + (int64_t)blockIdx.y * g.mom_cells * PM;
+  const int nc = min(kMomLeaves, far_tiles(nf, base) - i0);
+  const double* from = rows + (far_cells_before(nf, base) + i0) * PM;
+  for (int i = tid; i < kMomLeaves * PM; i += 256) ma[i] = i < nc * PM ? from[i] : 0.0;
+  __syncthreads();
+  for (int l = base; l < min(base + kMomLevels, fc.lmax); ++l) {
+    const double* src = (l - base) & 1 ? mb : ma;
+    double* dst = (l - base) & 1 ? ma : mb;
+    const int np = kMomLeaves / 2 >> (l - base);
+    // halves half a half's width from the centre, d = 2^-ed of the parent's
+    // unit, whose unit is 2^-er of it
+    const int hpar = max(l + 1, lm), ed = hpar - (l - 1), er = hpar - max(l, lm);
+    if (l == base || l <= lm) {  // (from the first level that uses them on always 2 and 1)
+      for (int i = tid; i < PM * PM; i += 256) {
+        const int k = i / PM + 1, n = i - (k - 1) * PM + 1;
+        wt[k - 1][n - 1] = n >= k ? ldexp(kBinom.c[n][k], -(ed * (n - k) + er * k)) : 0.0;
+      }
+      __syncthreads();
+    }
+    const int first = i0 >> (l + 1 - base), nt = far_tiles(nf, l + 1);
+    double* out = rows + (far_cells_before(nf, l + 1) + first) * PM;
+    for (int i = tid; i < np * PM; i += 256) {
+      const int c = i / PM, n = i - c * PM + 1;
+      const double *L = src + 2 * c * PM, *R = L + PM;
+      double v = 0.0, u = 0.0;
+      const int o = n & 1;
+#pragma unroll 4
+      for (int k = 0; k < PM; k += 2) {  // M_(k + 1), M_(k + 2)
+        const double w0 = wt[k][n - 1], w1 = wt[k + 1][n - 1];
+        v = fma(w0, o ? R[k] + L[k] : R[k] - L[k], v);
+        u = fma(w1, o ? R[k + 1] - L[k + 1] : R[k + 1] + L[k + 1], u);
+      }
+      v += u;
+      dst[i] = v;
+      if (first + c < nt) out[i] = v;
+    }
+    __syncthreads();
+  }
+}
+
+// The tiles of the levels that take their cells through moments: P lanes to a
+// tile, each one node.  A tile has three cells at the lower levels and up to a
+// dozen where windows end.  (A wave to a tile spent most of its time on the ranges:
+// 48 conditions x 25000 tiles 3.16 ms with the levels line by line, 2.66 so.)
+template <int P, int PM>
+__global__ __launch_bounds__(256) void k_far_cells(FarArgs g) {
+  constexpr int G = 64 / P;
+  __shared__ double sv[4][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const CondDev& cd = g.cond[g.c0 + blockIdx.y];
+  const FarCond& fc = cd.far;
+  if (!fc.on || g.counter[kFarOff]) return;
+  const int lm = far_cond_mom_level(g, cd), nf = g.m.n_fine;
+  if (lm > fc.lmax) return;
+  const int gi = lane / P, q = lane - gi * P;
+  int t = (blockIdx.x * 4 + wave) * G + gi, l = lm;
+  while (l <= fc.lmax && t >= far_tiles(nf, l)) t -= far_tiles(nf, l++);
+  const bool live = gi < G && l <= fc.lmax;
+  double v = 0.0;
+  if (live) {
+    CellRange r[4];
+    far_tile_ranges(fc, l, t, r);
+    const double half = (double)(1 << (l + fc.sh)) * 0.5;
+    const double node = (double)(t << (l + fc.sh)) + (half - 0.5) + half * (P == 12 ? kFarX12[q] : kFarX20[q]);
+    const double* const rows = g.mom + (int64_t)blockIdx.y * g.mom_cells * PM;
+    for (int left = 4; left > 0;) {
+      if (r[0].lo > r[0].hi) {
+        r[0] = r[1];
+        r[1] = r[2];
+        r[2] = r[3];
+        --left;
+        continue;
+      }
+      const int lv = far_widest(r[0].lo, r[0].hi, l), cell = r[0].lo >> lv;
+      r[0].lo += 1 << lv;
+      const double2* mo = (const double2*)(rows + (far_cells_before(nf, lv) + cell) * PM);
+      const double w = (double)(1 << (lv + fc.sh));
+      const double c = (double)cell * w + (w * 0.5 - 0.5);
+      const double inv = (double)(1 << (max(lv, lm) + fc.sh)) / (node - c);
+      double h = 0.0;
+#pragma unroll
+      for (int k = PM / 2 - 1; k >= 0; --k) {
+        const double2 a = mo[k];
+        h = fma(fma(h, inv, a.y), inv, a.x);
+      }
+      // (in cells' widths; the row holds the factor of the first level's)
+      v = fma(h * inv, ldexp(inv, -(max(lv, lm) - lm)), v);
+    }
+  }
+  sv[wave][lane] = v;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  if (live) {
+    const double* D = far_dct<P>();
+    double o = 0.0;
+#pragma unroll
+    for (int i = 0; i < P; ++i) o = fma(D[i * P + q], sv[wave][gi * P + i], o);
+    const int64_t row = far_rows_before(nf, fc.sh, l) + (int64_t)t * far_slices(fc.sh, l);
+    g.rows[((int64_t)(g.c0 + blockIdx.y) * g.cond_rows + row) * P + q] = o;
+  }
+}
+
 template <typename Real, int PROF, int P>
 __global__ __launch_bounds__(256, sizeof(Real) == 4 ? 4 : 3) void k_far(FarArgs g) {
   constexpr bool F32 = sizeof(Real) == 4;
   __shared__ double sv[4][P], st[4][P];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int c = blockIdx.y;
+  const int c = g.c0 + blockIdx.y;
   const CondDev& cd = g.cond[c];
   const FarCond& fc = cd.far;
   if (!fc.on || g.counter[kFarOff]) return;
   const ModelDev& m = g.m;
   const int nf = m.n_fine;
-  // the block's level: the widest tiles, which have the most lines, first
-  int b = blockIdx.x, l = fc.lmax;
-  for (; l >= 0; --l) {
-    const int nb = far_blocks(nf, fc.sh, l);
-    if (b < nb) break;
-    b -= nb;
-  }
-  if (l < 0) return;
-  const int lw = min(far_wide(fc.sh, l), 2), nw = 1 << lw, sl = far_slices(fc.sh, l);
-  const int t = lw < 2 ? (b << (2 - lw)) + (wave >> lw) : b / sl;
-  const int slice = lw < 2 ? 0 : b % sl;
-  // positions of the tile's lines: up to four ranges of sorted lines
-  CellRange r[4];
-  far_tile_ranges(fc, l, t, r);
-  uint32_t cum[4], beg[4], total = 0;
-  const bool live_tile = t < far_tiles(nf, l);
+  const int ltop = min(fc.lmax, (g.mom ? far_cond_mom_level(g, cd) : kFarLevels) - 1);
+  for (int item = blockIdx.x; item < g.blocks; item += gridDim.x) {
+    // the block's level: the widest tiles, which have the most lines, first (above
+    // them k_far_cells)
+    int b = item, l = ltop;
+    for (; l >= 0; --l) {
+      const int nb = far_blocks(nf, fc.sh, l);
+      if (b < nb) break;
+      b -= nb;
+    }
+    if (l < 0) return;
+    const int lw = min(far_wide(fc.sh, l), 2), nw = 1 << lw, sl = far_slices(fc.sh, l);
+    const int t = lw < 2 ? (b << (2 - lw)) + (wave >> lw) : b / sl;
+    const int slice = lw < 2 ? 0 : b % sl;
+    // positions of the tile's lines: up to four ranges of sorted lines
+    CellRange r[4];
+    far_tile_ranges(fc, l, t, r);
+    uint32_t cum[4], beg[4], total = 0;
+    const bool live_tile = t < far_tiles(nf, l);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const bool ok = live_tile && r[k].lo <= r[k].hi;
-    const uint32_t p0 = ok ? g.off[r[k].lo] : 0, p1 = ok ? g.off[r[k].hi + 1] : 0;
-    beg[k] = p0 - total;  // position q of the tile is line q + beg of its range
-    total += p1 - p0;
-    cum[k] = total;
-  }
-  double acc64[P];
-  Real acc[P];
+    for (int k = 0; k < 4; ++k) {
+      const bool ok = live_tile && r[k].lo <= r[k].hi;
+      const uint32_t p0 = ok ? g.off[r[k].lo] : 0, p1 = ok ? g.off[r[k].hi + 1] : 0;
+      beg[k] = p0 - total;  // position q of the tile is line q + beg of its range
+      total += p1 - p0;
+      cum[k] = total;
+    }
+    double acc64[P];
+    Real acc[P];
 #pragma unroll
-  for (int q = 0; q < P; ++q) {
-    acc[q] = (Real)0;
-    if (F32) acc64[q] = 0.0;
-  }
-  const int ts = t << (l + fc.sh);  // the tile's first point
-  const Real half = (Real)(1 << (l + fc.sh)) * (Real)0.5, mid = half - (Real)0.5;
-  const uint32_t stride = (uint32_t)(nw * sl) * 64u;
-  int since = 0;
-  auto at = [&](uint32_t q0) {
-    const uint32_t q = min(q0 + lane, total - 1);
-    return q + (q < cum[0] ? beg[0] : q < cum[1] ? beg[1] : q < cum[2] ? beg[2] : beg[3]);
-  };
-  uint32_t q0 = (uint32_t)((wave & (nw - 1)) + slice * nw) * 64u;
-  FarIn<Real> next;
-  if (q0 < total) next = far_load<Real>(g, cd, at(q0));
-  for (; q0 < total; q0 += stride) {
-    const FarIn<Real> cur = next;
-    if (q0 + stride < total) next = far_load<Real>(g, cd, at(q0 + stride));  // a batch ahead of its use
-    const FarLine<Real> L = far_line<Real, PROF>(g, cd, cur, q0 + lane < total, ts, mid);
-    if constexpr (F32) {
-      far_line_f32<PROF, P>(L.xc, half * L.a, L.a, L.y, L.c0, L.live, acc);
-      if (++since == 32) {
-        since = 0;
+    for (int q = 0; q < P; ++q) {
+      acc[q] = (Real)0;
+      if (F32) acc64[q] = 0.0;
+    }
+    const int ts = t << (l + fc.sh);  // the tile's first point
+    const Real half = (Real)(1 << (l + fc.sh)) * (Real)0.5, mid = half - (Real)0.5;
+    const uint32_t stride = (uint32_t)(nw * sl) * 64u;
+    int since = 0;
+    auto at = [&](uint32_t q0) {
+      const uint32_t q = min(q0 + lane, total - 1);
+      return q + (q < cum[0] ? beg[0] : q < cum[1] ? beg[1] : q < cum[2] ? beg[2] : beg[3]);
+    };
+    uint32_t q0 = (uint32_t)((wave & (nw - 1)) + slice * nw) * 64u;
+    FarIn<Real> next;
+    if (q0 < total) next = far_load<Real>(g, cd, at(q0));
+    for (; q0 < total; q0 += stride) {
+      const FarIn<Real> cur = next;
+      if (q0 + stride < total) next = far_load<Real>(g, cd, at(q0 + stride));  // a batch ahead of its use
+      const FarLine<Real> L = far_line<Real, PROF>(g, cd, cur, q0 + lane < total, ts, mid);
+      if constexpr (F32) {
+        far_line_f32<PROF, P>(L.xc, half * L.a, L.a, L.y, L.c0, L.live, acc);
+        if (++since == 32) {
+          since = 0;
 #pragma unroll
-        for (int k = 0; k < P; ++k) {
-          acc64[k] += (double)acc[k];
-          acc[k] = (Real)0;
+          for (int k = 0; k < P; ++k) {
+            acc64[k] += (double)acc[k];
+            acc[k] = (Real)0;
+          }
         }
+      } else {
+        far_line_f64<PROF, P>(L.xc, half * L.a, L.a, L.y, L.c0, L.live, acc);
       }
+    }
+    if constexpr (F32) {
+#pragma unroll
+      for (int k = 0; k < P; ++k) acc64[k] += (double)acc[k];
     } else {
-      far_line_f64<PROF, P>(L.xc, half * L.a, L.a, L.y, L.c0, L.live, acc);
+#pragma unroll
+      for (int k = 0; k < P; ++k) acc64[k] = acc[k];
     }
-  }
-  if constexpr (F32) {
+    far_fold<P>(acc64, lane);
+    if ((lane & 15) == 0) {
+      const int s0 = far_slot<P>(lane);
 #pragma unroll
-    for (int k = 0; k < P; ++k) acc64[k] += (double)acc[k];
-  } else {
-#pragma unroll
-    for (int k = 0; k < P; ++k) acc64[k] = acc[k];
-  }
-  far_fold<P>(acc64, lane);
-  if ((lane & 15) == 0) {
-    const int s0 = far_slot<P>(lane);
-#pragma unroll
-    for (int i = 0; i < P / 4; ++i) sv[wave][s0 + i] = acc64[i];
-  }
-  __syncthreads();
-  // the tile's waves, then node values to coefficients
-  const int tid = threadIdx.x, tiles = 4 >> lw;
-  if (tid < tiles * P) {
-    const int tg = tid / P, q = tid - tg * P;
-    double v = 0.0;
-    for (int w = 0; w < nw; ++w) v += sv[tg * nw + w][q];
-    st[tg][q] = v;
-  }
-  __syncthreads();
-  if (tid < tiles * P) {
-    const int tg = tid / P, k = tid - tg * P;
-    const int tt = lw < 2 ? (b << (2 - lw)) + tg : t;
-    if (tt < far_tiles(nf, l)) {
-      const double* D = far_dct<P>();
+      for (int i = 0; i < P / 4; ++i) sv[wave][s0 + i] = acc64[i];
+    }
+    __syncthreads();
+    // the tile's waves, then node values to coefficients
+    const int tid = threadIdx.x, tiles = 4 >> lw;
+    if (tid < tiles * P) {
+      const int tg = tid / P, q = tid - tg * P;
       double v = 0.0;
-#pragma unroll
-      for (int q = 0; q < P; ++q) v = fma(D[q * P + k], st[tg][q], v);
-      const int64_t row = far_rows_before(nf, fc.sh, l) + (int64_t)tt * sl + slice;
-      g.rows[((int64_t)c * g.cond_rows + row) * P + k] = v;
+      for (int w = 0; w < nw; ++w) v += sv[tg * nw + w][q];
+      st[tg][q] = v;
     }
+    __syncthreads();
+    if (tid < tiles * P) {
+      const int tg = tid / P, k = tid - tg * P;
+      const int tt = lw < 2 ? (b << (2 - lw)) + tg : t;
+      if (tt < far_tiles(nf, l)) {
+        const double* D = far_dct<P>();
+        double v = 0.0;
+#pragma unroll
+        for (int q = 0; q < P; ++q) v = fma(D[q * P + k], st[tg][q], v);
+        const int64_t row = far_rows_before(nf, fc.sh, l) + (int64_t)tt * sl + slice;
+        g.rows[((int64_t)c * g.cond_rows + row) * P + k] = v;
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -629,6 +917,7 @@ __global__ __launch_bounds__(256) void k_far_finish(FarArgs g) {
   const int k = ts + tid;
   if (k - lane >= m.n_bins) return;
   double slope = 0.0;  // FP64 form: in units of 1 / dnu
+  const int lm = g.mom ? far_cond_mom_level(g, cd) : kFarLevels;  // (k_far_cells has one row per tile)
   int64_t before = 0;
   for (int l = 0; l <= fc.lmax; ++l) {
     // tiles of 64 points or more hold all of the wave's points: their
@@ -640,7 +929,7 @@ __global__ __launch_bounds__(256) void k_far_finish(FarArgs g) {
     double co[P];
 #pragma unroll
     for (int q = 0; q < P; ++q) co[q] = r[q];
-    for (int s = 1; s < sl; ++s)
+    for (int s = 1; s < (l < lm ? sl : 1); ++s)
 #pragma unroll
       for (int q = 0; q < P; ++q) co[q] += r[s * P + q];
     // the point in the tile's variable: (k - centre) / half width
@@ -657,9 +946,19 @@ __global__ __launch_bounds__(256) void k_far_finish(FarArgs g) {
   }
 }
 
+// Moments cost three kernels that short grids leave idle (45 us) and then go by
+// cells, line by line costs go by lines: moments from so many cells on, or from so
+// many lines to a leaf.  Measured, tiles line by one / by moments: FP32 form,
+// 1.25e5 leaves, 4, 12, 80 lines each 395 / 300, 454 / 304, 1084 / 350 us; 1.25e4
+// leaves, 2 and 16 lines 41 / 66, 52 / 66; FP64 form, 31250 leaves, 16 and 32 lines
+// 648 / 209, 598 / 216, 3125 leaves, 19 lines 76 / 60.
+constexpr int64_t kMomCells32 = 32768, kMomCells64 = 2048;
+constexpr int kMomLines = 24;
+
 int far_nodes(int prec) { return prec == XS_FP32 ? 12 : 20; }
 
-void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, double* sigma, hipStream_t s) {
+void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, int64_t n_lines, double* sigma,
+                hipStream_t s) {
   FarArgs a;
   a.m = m;
   a.cond = w.cond;
@@ -680,15 +979,42 @@ void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, dou
   a.sigma = sigma;
   int64_t blocks = 0;
   for (int l = 0; l <= far_lmax; ++l) blocks += far_blocks(m.n_fine, m.fine_sh, l);
-  const dim3 grid((unsigned)blocks, m.n_cond), fin((unsigned)far_tiles(m.n_fine, end_min), m.n_cond);
-#define XS_F(PR)                                                                                       \
-  if (m.profile == PR && m.prec == XS_FP32) {                                                          \
-    hipLaunchKernelGGL((k_far<float, PR, 12>), grid, dim3(256), 0, s, a);                              \
-    hipLaunchKernelGGL((k_far_finish<float, PR, 12, 6>), fin, dim3(256), 0, s, a);                     \
-  } else if (m.profile == PR) {                                                                        \
-    hipLaunchKernelGGL((k_far<double, PR, 20>), grid, dim3(256), 0, s, a);                             \
-    hipLaunchKernelGGL((k_far_finish<double, PR, 20, 12>), fin, dim3(256), 0, s, a);                   \
-  }
+  a.blocks = (int32_t)blocks;
+  // the moments lie in the partial rows, which the near leaves have done with; as
+  // many conditions at a time as fit (lifetimes, whose widths have no bound
+  // here, go line by line)
+  const int pm = m.prec == XS_FP32 ? kMoments32 : kMoments64;
+  a.mom_cells = far_cells_before(m.n_fine, far_lmax + 1);
+  const int64_t fit = 2 * w.item_target * 1024 / (a.mom_cells * pm);
+  const bool many = (int64_t)m.n_fine * m.n_cond >= (m.prec == XS_FP32 ? kMomCells32 : kMomCells64) ||
+                    n_lines >= kMomLines * (int64_t)m.n_fine;
+  a.mom = many && fit > 0 && !w.rgpre ? w.part : nullptr;
+  const int at_once = a.mom ? (int)std::min<int64_t>(fit, m.n_cond) : m.n_cond;
+  const dim3 fin((unsigned)far_tiles(m.n_fine, end_min), m.n_cond);
+  const int per_block = 4 * (64 / far_nodes(m.prec));  // tiles of a block of k_far_cells
+  auto run = [&](auto leaves, auto moments, auto cells, auto far, auto finish) {
+    for (a.c0 = 0; a.c0 < m.n_cond; a.c0 += at_once) {
+      const int nc = std::min(at_once, m.n_cond - a.c0);
+      const auto go = [&](auto k, int64_t bl) { hipLaunchKernelGGL(k, dim3((unsigned)bl, nc), dim3(256), 0, s, a); };
+      if (a.mom) {
+        go(leaves, (m.n_fine + 3) / 4);
+        for (int b = 0; b < far_lmax; b += kMomLevels)
+          hipLaunchKernelGGL(moments, dim3((far_tiles(m.n_fine, b) + kMomLeaves - 1) / kMomLeaves, nc), dim3(256), 0, s,
+                             a, b);
+        go(cells, (a.mom_cells + per_block - 1) / per_block);
+      }
+      // (with moments most conditions have nothing left for it)
+      go(far, a.mom ? std::min<int64_t>(blocks, 4096) : blocks);
+    }
+    hipLaunchKernelGGL(finish, fin, dim3(256), 0, s, a);
+  };
+#define XS_F(PR)                                                                                                   \
+  if (m.profile == PR && m.prec == XS_FP32)                                                                        \
+    run(k_far_leaves<float, PR, kMoments32>, k_far_moments<kMoments32>, k_far_cells<12, kMoments32>,               \
+        k_far<float, PR, 12>, k_far_finish<float, PR, 12, 6>);                                                     \
+  else if (m.profile == PR)                                                                                        \
+    run(k_far_leaves<double, PR, kMoments64>, k_far_moments<kMoments64>, k_far_cells<20, kMoments64>,              \
+        k_far<double, PR, 20>, k_far_finish<double, PR, 20, 12>);
   XS_F(XS_VOIGT) XS_F(XS_LORENTZ) XS_F(XS_BIN_VOIGT) XS_F(XS_BIN_LORENTZ)
 #undef XS_F
 }

@@ -268,6 +268,7 @@ __global__ __launch_bounds__(256) void k_lines_pass1(ModelDev m, const SlotDev* 
     }
   __syncthreads();
   Totals tot;
+  float gmax = 0.0f, nlo = INFINITY, nhi = -INFINITY;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < ln.n; i += (int64_t)gridDim.x * 256) {
     const int32_t u = ln.up[i], l = ln.lo[i];
     int32_t kk = m.n_fine;
@@ -286,8 +287,12 @@ __global__ __launch_bounds__(256) void k_lines_pass1(ModelDev m, const SlotDev* 
         int64_t kc = home_bin(nu, m.nu0, m.dnu);
         int64_t fk = kc < 0 ? 0 : kc >> m.fine_sh;
         kk = (int32_t)(fk < m.n_fine - 1 ? fk : m.n_fine - 1);
-        put_pack((typename PackOf<LTE>::type*)lpack + i, f, nu, ln.gref ? ln.gref[i] : (float)ln.gref_scalar,
-                 ln.nexp ? ln.nexp[i] : (float)ln.nexp_scalar);
+        const float gref = ln.gref ? ln.gref[i] : (float)ln.gref_scalar;
+        const float nexp = ln.nexp ? ln.nexp[i] : (float)ln.nexp_scalar;
+        gmax = fmaxf(gmax, fabsf(gref));
+        nlo = fminf(nlo, nexp);
+        nhi = fmaxf(nhi, nexp);
+        put_pack((typename PackOf<LTE>::type*)lpack + i, f, nu, gref, nexp);
       }
       tot.pairs += window_pairs(m, cutc, cutm, nu, a, b);
       if (f32) {
@@ -303,16 +308,53 @@ __global__ __launch_bounds__(256) void k_lines_pass1(ModelDev m, const SlotDev* 
     if (REC) key[i] = kk;
   }
   block_totals(tot, scnt, part);  // (and a barrier)
+  if (REC) {
+    __shared__ float sext[4][3];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      gmax = fmaxf(gmax, __shfl_xor(gmax, o, 64));
+      nlo = fminf(nlo, __shfl_xor(nlo, o, 64));
+      nhi = fmaxf(nhi, __shfl_xor(nhi, o, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {
+      float* e = sext[threadIdx.x >> 6];
+      e[0] = gmax;
+      e[1] = nlo;
+      e[2] = nhi;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+      float r = sext[0][threadIdx.x];
+      for (int v = 1; v < 4; ++v) {
+        const float x = sext[v][threadIdx.x];
+        r = threadIdx.x == 1 ? fminf(r, x) : fmaxf(r, x);
+      }
+      ((float*)(part + 3 * (int64_t)gridDim.x))[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = r;
+    }
+  }
   if (f32)
     for (int q = threadIdx.x; q < m.n_slots; q += 256)
       if (bmax[q] > __hip_atomic_load(smax + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(smax + q, bmax[q]);
 }
 
 // Adds the blocks' totals, and sets the FP32 form's scale of every slot.
-__global__ __launch_bounds__(256) void k_line_totals(ModelDev m, const unsigned long long* part, int blocks,
+// (rec: and the extremes of the lines' widths)
+__global__ __launch_bounds__(512) void k_line_totals(ModelDev m, const unsigned long long* part, int blocks, int rec,
                                                      const unsigned long long* smax, double* sb,
-                                                     unsigned long long* stats) {
+                                                     unsigned long long* stats, int32_t* counter) {
   const int v = threadIdx.x >> 6, lane = threadIdx.x & 63;  // a wave per value
+  if (rec && v >= 4 && v < 7) {
+    const float* e = (const float*)(part + 3 * (int64_t)blocks) + (int64_t)(v - 4) * blocks;
+    float r = v == 5 ? INFINITY : -INFINITY;
+#pragma unroll 8
+    for (int b = lane; b < blocks; b += 64) r = v == 5 ? fminf(r, e[b]) : fmaxf(r, e[b]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const float x = __shfl_xor(r, o, 64);
+      r = v == 5 ? fminf(r, x) : fmaxf(r, x);
+    }
+    if (lane == 0) ((float*)counter)[kGammaMax + v - 4] = r;
+  }
   if (v < 3) {
     unsigned long long r = 0;
 #pragma unroll 8
@@ -325,12 +367,12 @@ __global__ __launch_bounds__(256) void k_line_totals(ModelDev m, const unsigned 
 
 static int line_blocks(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(kPass1Blocks, (n + 255) / 256)); }
 
-// The blocks' totals go to keyA, free until the sort's first pass: 24 bytes a
+// The blocks' totals go to keyA, free until the sort's first pass: 36 bytes a
 // block, which has 256 lines (the last fewer; the carve is at least 256 bytes).
 static unsigned long long* totals_part(const Work& w) { return reinterpret_cast<unsigned long long*>(w.keyA); }
-static void line_totals(const ModelDev& m, const Work& w, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_line_totals, dim3(1), dim3(256), 0, s, m, totals_part(w), line_blocks(n), w.smax, w.sb,
-                     w.stats);
+static void line_totals(const ModelDev& m, const Work& w, int64_t n, bool rec, hipStream_t s) {
+  hipLaunchKernelGGL(k_line_totals, dim3(1), dim3(512), 0, s, m, totals_part(w), line_blocks(n), (int)rec, w.smax,
+                     w.sb, w.stats, w.counter);
 }
 
 template <bool REC>
@@ -346,7 +388,7 @@ static void pass1(const ModelDev& m, const Work& w, const StatesView& st, const 
 void launch_lines_pass1(const ModelDev& m, const Work& w, const StatesView& st,
                         const LinesView& ln, hipStream_t s) {
   pass1<true>(m, w, st, ln, s);
-  line_totals(m, w, ln.n, s);
+  line_totals(m, w, ln.n, true, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -748,19 +790,18 @@ void launch_intensity_out(const ModelDev& m, const Work& w, const StatesView& st
                           const LinesView& ln, void* S, double* log_scale, hipStream_t s) {
   if (m.prec == XS_FP32) {
     pass1<false>(m, w, st, ln, s);
-    line_totals(m, w, ln.n, s);
+    line_totals(m, w, ln.n, false, s);
     if (ln.n > 0) intensity_out<false>(m, w, st, ln, S, log_scale, s);
   } else {
     intensity_out<true>(m, w, st, ln, S, log_scale, s);
-    line_totals(m, w, ln.n, s);
+    line_totals(m, w, ln.n, false, s);
   }
 }
 
 // Clear the work queue (a kernel, not a memset, so the step can be captured in a
-// graph); the counters of xs_prepare and its flag are kept.
+// graph); the counters of xs_prepare, kFarOff and on, are kept.
 __global__ void k_reset_queue(int32_t* counter) {
-  for (int q = threadIdx.x; q < kCounterInts; q += 64)
-    if (q != kFarOff) counter[q] = 0;
+  if (threadIdx.x < kFarOff) counter[threadIdx.x] = 0;
 }
 
 void launch_scan_i32(int32_t* a, int64_t n, int32_t* sums, hipStream_t s) { scan_excl(a, n, sums, s); }

@@ -499,7 +499,7 @@ int profile_pass(xs_plan* p, double* sigma, int accumulate) {
     launch_gather(p->md, kernel_work(p), p->tiling, sigma, accumulate, p->stream);
   } else {
     launch_near(p->md, kernel_work(p), sigma, accumulate, p->last_lines_in, p->stream);
-    launch_far(p->md, kernel_work(p), p->far_lmax, p->far_end, sigma, p->stream);
+    launch_far(p->md, kernel_work(p), p->far_lmax, p->far_end, p->last_lines_in, sigma, p->stream);
   }
   return hip_check(hipGetLastError(), "profile launch");
 }

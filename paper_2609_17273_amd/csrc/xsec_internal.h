@@ -32,9 +32,10 @@ constexpr int kSortItems = 16;    // keys per thread in the radix sort (4096 per
 // Device counters (int32): [0] gather work queue, [2..3] candidate total,
 // [4..5] lines per item or part, [6] parts beyond
 // tiles' first, [kFarOff] set by the
-// record pass where a line's values are not finite.
+// record pass where a line's values are not finite, [kGammaMax..kNexpMax] largest
+// |gamma_ref|, smallest and largest n_exp of the kept lines (floats).
 constexpr int kCounterInts = 64;
-constexpr int kFarOff = 9;
+constexpr int kFarOff = 9, kGammaMax = 10, kNexpMin = 11, kNexpMax = 12;
 constexpr int kSortBlock = 256 * kSortItems;
 // Lines are sorted by home bin >> sh: 64 points per key (the smallest bucket
 // size), or the leaves of the tile expansions.
@@ -211,7 +212,8 @@ int far_nodes(int prec);  // nodes per tile
 // sigma += the expansions of the lines' far tiles (levels up to far_lmax, the
 // conditions' largest)
 // (end_min: the conditions' lowest level of cut tiles)
-void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, double* sigma, hipStream_t s);
+void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, int64_t n_lines, double* sigma,
+                hipStream_t s);
 
 // ---- cooling function (k_cooling.hip) ----
 // doubles of Work::part the temperatures and partial sums take
