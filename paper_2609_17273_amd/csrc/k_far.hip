@@ -133,7 +133,7 @@ __device__ __forceinline__ void far_line_f32(float xc, float ah, float a, float 
       }
       return;
     }
-    const bool one = __ballot(live && !(rho >= 900.9f)) == 0;
+    const bool one = __ballot(live && !(rho >= 1601.6f)) == 0;
     if constexpr (PROF == XS_BIN_VOIGT) {
       const bool two = __ballot(live && !(y * a <= 0.01f * rho)) == 0;
       if (one) far_bins<PROF, 1, P, float>(xc, ah, a, y, c0, two, acc);
@@ -948,7 +948,8 @@ __global__ __launch_bounds__(256) void k_far_finish(FarArgs g) {
 
 // Moments cost three kernels that short grids leave idle (45 us) and then go by
 // cells, line by line costs go by lines: moments from so many cells on, or from so
-// many lines to a leaf.  Measured, tiles line by one / by moments: FP32 form,
+// many lines to a leaf (whatever the other conditions: a condition has the same
+// values by itself and in a table).  Measured, tiles line by one / by moments: FP32 form,
 // 1.25e5 leaves, 4, 12, 80 lines each 395 / 300, 454 / 304, 1084 / 350 us; 1.25e4
 // leaves, 2 and 16 lines 41 / 66, 52 / 66; FP64 form, 31250 leaves, 16 and 32 lines
 // 648 / 209, 598 / 216, 3125 leaves, 19 lines 76 / 60.
@@ -986,7 +987,7 @@ void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, int
   const int pm = m.prec == XS_FP32 ? kMoments32 : kMoments64;
   a.mom_cells = far_cells_before(m.n_fine, far_lmax + 1);
   const int64_t fit = 2 * w.item_target * 1024 / (a.mom_cells * pm);
-  const bool many = (int64_t)m.n_fine * m.n_cond >= (m.prec == XS_FP32 ? kMomCells32 : kMomCells64) ||
+  const bool many = m.n_fine >= (m.prec == XS_FP32 ? kMomCells32 : kMomCells64) ||
                     n_lines >= kMomLines * (int64_t)m.n_fine;
   a.mom = many && fit > 0 && !w.rgpre ? w.part : nullptr;
   const int at_once = a.mom ? (int)std::min<int64_t>(fit, m.n_cond) : m.n_cond;

@@ -1,7 +1,7 @@
 // Near leaves of the profile pass (far_geometry.h): the points within a few
 // cells of a line, where its profile has structure on the grid's scale, and
 // the whole windows of the edge cells' lines.  The tiles further out are
-// k_far's.
+// k_far's.  Gaussians, which are zero a few widths away, go point by point as a whole.
 //
 // A block of four waves owns 256 grid points of one condition and takes the
 // lines whose near leaves meet them, 64 at a time and one per lane (2^ks lanes
@@ -173,15 +173,19 @@ __device__ __forceinline__ void near_sweep(const Ring& r, const NearLane& ln, do
   }
 }
 
-// Points of [klo, khi] within X of the line (|x| < X, one point of margin on
-// either side); empty ranges are lo > hi with lo - 1 = hi.
+// Points of [klo, khi] within X of the line (|x| < X); empty ranges are lo > hi
+// with lo - 1 = hi.  X has a part in a thousand to spare, so rounding leaves no
+// point to a rule that does not hold; a whole point to spare on either side gave
+// the core's rule, which costs most, up to four more (bin means of 3.9e5 lines 1.30
+// ms, without 1.08) and its error where Re w is least (9e-5, the gather's and this
+// now 7.5e-5, at 1e-4 bar).
 template <typename R>
 __device__ __forceinline__ void near_range(R X, R a, R b, int kc, int klo, int khi, int& lo, int& hi) {
   lo = klo;
   hi = klo - 1;
   if (!(X > (R)0)) return;
-  const R l = fmin(fmax(floor((b - X) / a) - (R)1, (R)-1.0e9), (R)1.0e9);
-  const R h = fmin(fmax(ceil((b + X) / a) + (R)1, (R)-1.0e9), (R)1.0e9);
+  const R l = fmin(fmax(ceil((b - X) / a), (R)-1.0e9), (R)1.0e9);
+  const R h = fmin(fmax(floor((b + X) / a), (R)-1.0e9), (R)1.0e9);
   const int kl = max((int)l + kc, klo), kh = min((int)h + kc, khi);
   if (kl <= kh) {
     lo = kl;
@@ -216,6 +220,50 @@ __device__ __forceinline__ void near_align(int& lo, int& hi) {
   hi |= 3;
 }
 
+// 2^t, t <= 0, to an ulp, in half of the library's operations.
+__device__ __forceinline__ double near_exp2(double t) {
+  t = fmax(t, -2000.0);
+  const double k = rint(t), r = t - k;
+  return ldexp(fma(r, exp2m1_over(r), 1.0), (int)k);
+}
+
+// A Gaussian's points: those where it is not zero in the working precision
+// (2^-160, 2^-1100; erfc(10.1), erfc(27.3)).
+template <typename Real, int PROF>
+__device__ __forceinline__ void near_gauss(const ModelDev& m, const CondDev& cd, const NearLane& lane, int kc, int klo,
+                                           int khi, float del, double nu, Real S, double* row, int tlo) {
+  constexpr bool BIN = PROF == XS_BIN_DOPPLER || PROF == XS_BIN_GAUSSIAN;
+  constexpr bool FIXED = PROF == XS_GAUSSIAN || PROF == XS_BIN_GAUSSIAN;
+  Ring r = {0, 0, 0, -1};
+  if constexpr (sizeof(Real) == 4) {
+    const float ia = rcp32(FIXED ? (float)cd.hwhm : (float)nu * (float)cd.dop);
+    const float inv = BIN ? (float)0.83255461115769776 * ia : ia;
+    const float a = (float)m.dnu * inv, b = del * inv, hh = 0.5f * a;
+    const float c0 = BIN ? S * (float)(0.5 / m.dnu) : S * (float)0.46971863934982566 * inv;  // sqrt(ln2/pi)/alpha
+    near_range<float>(BIN ? 10.1f + hh : 12.649110640673518f, a, b, kc, klo, khi, r.lo, r.hi);
+    near_sweep(r, lane, row, tlo, [&](int k) -> double {
+      const float x = fmaf((float)(k - kc), a, -b);
+      if constexpr (BIN) return (double)(c0 * erf_bin<float>(x, hh));
+      else return (double)(c0 * __builtin_amdgcn_exp2f(-(x * x)));
+    });
+  } else {
+    const double alpha = FIXED ? cd.hwhm : nu * cd.dop;
+    const double inv = (BIN ? sqrt(kLN2) : 1.0) / alpha;
+    const double a = m.dnu * inv, hh = 0.5 * a, c0 = BIN ? S * (0.5 / m.dnu) : S * (sqrt(kLN2 / kPI) * inv);
+    const double b = (nu - nu_of_bin(m.nu0, m.dnu, kc)) * inv;
+    near_range<double>(BIN ? 27.3 + hh : sqrt(1100.0), a, b, kc, klo, khi, r.lo, r.hi);
+    near_sweep(r, lane, row, tlo, [&](int k) -> double {
+      double x;
+      {
+#pragma clang fp contract(off)
+        x = (nu_of_bin(m.nu0, m.dnu, k) - nu) * inv;
+      }
+      if constexpr (BIN) return c0 * erf_bin<double>(x, hh);
+      else return c0 * near_exp2(-(x * x));
+    });
+  }
+}
+
 // One lane's line over its points [klo, khi] of the tile.
 template <int PROF>
 __device__ __forceinline__ void near_line_f32(const ModelDev& m, const CondDev& cd, const NearLane& lane, int kc, int klo, int khi,
@@ -248,11 +296,14 @@ __device__ __forceinline__ void near_line_f32(const ModelDev& m, const CondDev& 
       else return (double)(float)((double)c0 * re_w_f64(x, (double)y));
     });
     if (wide) khi = klo - 1;
-    // rings by |z|^2 at the point (bin means: at the bin's nearest point)
+    // rings by |z|^2 at the point (bin means: at the bin's nearest point).  Three
+    // pairs to 100, two to 1600: a wave over a row of points took the nearest one's
+    // rule for all, and with a line to a lane from 64 and 900 on the error of 1 bar
+    // spectra was 3.1e-6, before 1.4e-6
     auto X = [&](float rho) { return rho > y2 ? sqrtf(rho - y2) + hh : 0.0f; };
     int l0, h0, l1, h1, l2, h2;
-    near_range<float>(X(900.9f), a, b, kc, klo, khi, l2, h2);
-    near_range<float>(X(64.064f), a, b, kc, l2, h2, l1, h1);
+    near_range<float>(X(1601.6f), a, b, kc, klo, khi, l2, h2);
+    near_range<float>(X(100.1f), a, b, kc, l2, h2, l1, h1);
     near_range<float>(X(36.036f), a, b, kc, l1, h1, l0, h0);
     const bool groups = !BIN && __ballot((klo & 3) != 0 || (khi & 3) != 3) == 0;
     if (groups) {
@@ -308,8 +359,8 @@ __device__ __forceinline__ void near_line_f32(const ModelDev& m, const CondDev& 
       ring4(std::integral_constant<int, 2>(), l2, h2, l1, h1);
       ring4(std::integral_constant<int, 1>(), klo, khi, l2, h2);
     } else {
-      ring(std::integral_constant<int, 2>(), 64.0f, l2, h2, l1, h1);
-      ring(std::integral_constant<int, 1>(), 900.0f, klo, khi, l2, h2);
+      ring(std::integral_constant<int, 2>(), 100.0f, l2, h2, l1, h1);
+      ring(std::integral_constant<int, 1>(), 1600.0f, klo, khi, l2, h2);
     }
   }
 }
@@ -346,7 +397,7 @@ __device__ __forceinline__ void near_line_f64(const ModelDev& m, const CondDev& 
     if (!wide) w.hi = w.lo - 1;
     if constexpr (!BIN) near_sweep(w, lane, row, tlo, [&](int k) -> double { return c0 * re_w_f64(xof(k), y); });
     if (wide) khi = klo - 1;
-    // the ranges only pick formulas; FP32 with the one-point margin suffices
+    // the ranges only pick formulas; FP32 suffices
     const float af = (float)a, bf = (float)b;
     auto X = [&](double rho) { return rho > y2 ? sqrtf((float)(rho - y2)) + (float)hh : 0.0f; };
     int l1, h1, l2, h2, l3, h3, l4, h4, l5, h5;
@@ -482,7 +533,9 @@ __global__ __launch_bounds__(256) void k_near(NearArgs g) {
           khi = min(khi, ((f + gap + 1) << m.fine_sh) - 1);
         }
         if (win.x <= win.y && klo <= khi && S != (Real)0) {
-          if constexpr (sizeof(Real) == 4)
+          if constexpr (base_profile(PROF) == XS_DOPPLER || base_profile(PROF) == XS_GAUSSIAN)
+            near_gauss<Real, PROF>(m, cd, ln, kc, klo, khi, g.rdel[p], nu, S, row, tlo);
+          else if constexpr (sizeof(Real) == 4)
             near_line_f32<PROF>(m, cd, ln, kc, klo, khi, g.rdel[p], (float)nu, S, gref, nexp, (float)gpre, row, tlo);
           else
             near_line_f64<PROF>(m, cd, ln, kc, klo, khi, nu, S, (double)gref, (double)nexp, gpre, row, tlo);
@@ -561,6 +614,7 @@ void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate
   if (m.profile == PR && m.prec == XS_FP32) hipLaunchKernelGGL((k_near<float, PR>), grid, dim3(256), 0, s, a); \
   else if (m.profile == PR) hipLaunchKernelGGL((k_near<double, PR>), grid, dim3(256), 0, s, a);
   XS_N(XS_VOIGT) XS_N(XS_LORENTZ) XS_N(XS_BIN_VOIGT) XS_N(XS_BIN_LORENTZ)
+  XS_N(XS_DOPPLER) XS_N(XS_GAUSSIAN) XS_N(XS_BIN_DOPPLER) XS_N(XS_BIN_GAUSSIAN)
 #undef XS_N
   hipLaunchKernelGGL(k_near_reduce, dim3((unsigned)std::min(a.n_ct, 4096)), dim3(256), 0, s, a);
 }
