@@ -106,12 +106,11 @@ __global__ __launch_bounds__(256) void k_near_count(NearArgs g) {
   if ((threadIdx.x & 63) == 0 && local) atomicAdd((unsigned long long*)(g.counter + 2), local);
 }
 
-__global__ __launch_bounds__(256) void k_near_plan(NearArgs g) {
-  const int64_t total = (int64_t) * (const unsigned long long*)(g.counter + 2);
+__device__ __forceinline__ void near_plan_tiles(const NearArgs& g, int64_t total, int64_t first, int64_t step) {
   int64_t chunk = (total + kNearExtra - 1) / kNearExtra;
   chunk = max(kNearChunk, (chunk + 63) / 64 * 64);
-  if (blockIdx.x == 0 && threadIdx.x == 0) *(int64_t*)(g.counter + 4) = chunk;
-  for (int64_t ct = (int64_t)blockIdx.x * 256 + threadIdx.x; ct < g.n_ct; ct += (int64_t)gridDim.x * 256) {
+  if (first == 0) *(int64_t*)(g.counter + 4) = chunk;
+  for (int64_t ct = first; ct < g.n_ct; ct += step) {
     const int64_t n = g.parts[ct];
     const int np = n <= chunk ? 1 : (int)((n + chunk - 1) / chunk);
     g.parts[ct] = np;
@@ -126,6 +125,29 @@ __global__ __launch_bounds__(256) void k_near_plan(NearArgs g) {
       }
     }
   }
+}
+
+__global__ __launch_bounds__(256) void k_near_plan(NearArgs g) {
+  near_plan_tiles(g, (int64_t) * (const unsigned long long*)(g.counter + 2), (int64_t)blockIdx.x * 256 + threadIdx.x,
+                  (int64_t)gridDim.x * 256);
+}
+
+// Both in one block, for short grids: a launch less (118 tiles 89 -> 81 us the whole
+// call; with 3907 tiles 61 -> 64).
+constexpr int kNearOnce = 1024;
+__global__ __launch_bounds__(1024) void k_near_plan_once(NearArgs g) {
+  __shared__ unsigned long long sum;
+  if (threadIdx.x == 0) sum = 0;
+  __syncthreads();
+  unsigned long long local = 0;
+  for (int ct = threadIdx.x; ct < g.n_ct; ct += 1024) {
+    const int64_t n = near_segments(g, g.cond[ct % g.m.n_cond], ct / g.m.n_cond).cum[kSegs - 1];
+    g.parts[ct] = (int32_t)n;  // (read by the same thread)
+    local += (unsigned long long)n;
+  }
+  if (local) atomicAdd(&sum, local);
+  __syncthreads();
+  near_plan_tiles(g, (int64_t)sum, threadIdx.x, 1024);
 }
 
 // Place of a tile's point in a wave's LDS row: the points of equal remainder
@@ -561,8 +583,10 @@ __global__ __launch_bounds__(256) void k_near(NearArgs g) {
   }
 }
 
-// Sum of the rows of split tiles, in the order of their parts.
+// Sum of the rows of split tiles, in the order of their parts; and the queue's
+// counters are cleared for the next pass, as they are by the preparation.
 __global__ __launch_bounds__(256) void k_near_reduce(NearArgs g) {
+  if (blockIdx.x == 0 && threadIdx.x < kFarOff) g.counter[threadIdx.x] = 0;
   for (int ct = blockIdx.x; ct < g.n_ct; ct += gridDim.x) {
     const int np = g.parts[ct];
     if (np <= 1) continue;
@@ -603,10 +627,13 @@ void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate
   a.sigma = sigma;
   a.accumulate = accumulate;
   a.n_ct = (int)((m.n_bins + kNearBins - 1) / kNearBins) * m.n_cond;
-  launch_reset_queue(w, s);
   const int cb = (int)std::min<int64_t>(1024, (a.n_ct + 255) / 256);
-  hipLaunchKernelGGL(k_near_count, dim3(cb), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(k_near_plan, dim3(cb), dim3(256), 0, s, a);
+  if (a.n_ct <= kNearOnce) {
+    hipLaunchKernelGGL(k_near_plan_once, dim3(1), dim3(1024), 0, s, a);
+  } else {
+    hipLaunchKernelGGL(k_near_count, dim3(cb), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_near_plan, dim3(cb), dim3(256), 0, s, a);
+  }
   // about as many as there are parts (a line meets a tile or two); fewer take turns
   a.extra_blocks = (int)std::min<int64_t>(kNearExtra, 8 + n_lines * m.n_cond / kNearChunk);
   const dim3 grid((unsigned)(a.n_ct + a.extra_blocks));
