@@ -11,9 +11,9 @@
 //
 // What bounds a pass is the number of profile evaluations; measured on the
 // whole call, point by point and with expansions: 1e7 lines, 2e6 points, window
-// 5000 points, FP32 form 14.65 and 2.76 ms (near leaves 1.27, tiles 0.35, window
-// ends and sigma 0.27); 1e6 lines, FP64 form 3.33 and 1.16 ms; 48 conditions of
-// 1e6 lines, 2e5 points, FP32 form 113.2 and 7.2 ms.
+// 5000 points, FP32 form 14.65 and 2.70 ms (near leaves 1.22, tiles 0.35, window
+// ends and sigma 0.27); 1e6 lines, FP64 form 3.33 and 1.10 ms; 48 conditions of
+// 1e6 lines, 2e5 points, FP32 form 113.2 and 7.1 ms.
 //
 // k_far_leaves, k_far_moments, k_far_cells: the tiles whose lines' moments serve
 //   (below); k_far: the others, and short lists.

@@ -38,17 +38,18 @@ struct __attribute__((aligned(32))) StatePackNLTE {
   int64_t vi;       // manifold index, or -1 when outside the table
 };
 
-// With pack or counter set it also writes the state records and clears the
+// With pack or clear set it also writes the state records and clears the
 // per-call counters, so that preparing lines starts with one kernel, not three
 // (a kernel of a few microseconds each where lists are short).
 __global__ __launch_bounds__(256) void k_partition(ModelDev m, const SlotDev* slots, StatesView st, double* qpart,
-                                                   void* pack, int32_t* counter, unsigned long long* stats) {
+                                                   void* pack, int clear, int32_t* counter,
+                                                   unsigned long long* stats) {
   __shared__ double sh[256];
   const int slot = blockIdx.y;
   const SlotDev sd = slots[slot];
   if (slot != 0) pack = nullptr;
-  if (counter && slot == 0 && blockIdx.x == 0) {
-    for (int q = threadIdx.x; q < kCounterInts; q += 256) counter[q] = 0;
+  if (clear && slot == 0 && blockIdx.x == 0) {
+    for (int q = threadIdx.x; q < clear; q += 256) counter[q] = 0;
     if (threadIdx.x < 8) stats[threadIdx.x] = 0ull;
   }
   double q = 0.0, dq = 0.0;
@@ -104,9 +105,9 @@ static void* state_pack(const ModelDev& m, const Work& w, const StatesView& st) 
   return (size_t)st.n * rec <= room && ((uintptr_t)w.keyB % 32) == 0 ? (void*)w.keyB : nullptr;
 }
 
-void launch_partition(const ModelDev& m, const Work& w, const StatesView& st, bool lines, hipStream_t s) {
+void launch_partition(const ModelDev& m, const Work& w, const StatesView& st, int clear, hipStream_t s) {
   hipLaunchKernelGGL(k_partition, dim3(kQBlocks, m.n_slots), dim3(256), 0, s, m, w.slot, st, w.qpart,
-                     lines ? state_pack(m, w, st) : (void*)nullptr, lines ? w.counter : (int32_t*)nullptr, w.stats);
+                     clear ? state_pack(m, w, st) : (void*)nullptr, clear, w.counter, w.stats);
   hipLaunchKernelGGL(k_partition_final, dim3(m.n_slots), dim3(256), 0, s, m, w.qpart, w.Q, w.dQ,
                      w.smax);
 }
@@ -785,7 +786,7 @@ static void intensity_out(const ModelDev& m, const Work& w, const StatesView& st
                      w.cut_mult, st, pack, ln, S, log_scale, totals_part(w));
 }
 
-// After launch_partition with lines set.
+// After launch_partition with clear set.
 void launch_intensity_out(const ModelDev& m, const Work& w, const StatesView& st,
                           const LinesView& ln, void* S, double* log_scale, hipStream_t s) {
   if (m.prec == XS_FP32) {

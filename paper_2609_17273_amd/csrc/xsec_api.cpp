@@ -467,7 +467,7 @@ Work kernel_work(const xs_plan* p) {
 int preprocess(xs_plan* p, const xs_states* st, const xs_lines* ln) {
   const StatesView sv = view(st);
   const LinesView lv = view(ln);
-  launch_partition(p->md, p->w, sv, true, p->stream);
+  launch_partition(p->md, p->w, sv, kCounterInts, p->stream);
   launch_lines_pass1(p->md, p->w, sv, lv, p->stream);
   int32_t *sk = nullptr, *svv = nullptr;
   launch_radix_sort(p->md, p->w, lv.n, p->md.n_fine, p->stream, &sk, &svv);
@@ -668,7 +668,7 @@ int xs_partition_function(xs_plan* p, const xs_states* st, double* Q, double* dQ
   int rc;
   if ((rc = check_call(p, st, nullptr))) return rc;
   if (!Q) return fail(XS_EINVAL, "Q is NULL");
-  launch_partition(p->md, p->w, view(st), false, p->stream);
+  launch_partition(p->md, p->w, view(st), 0, p->stream);
   launch_q_out(p->md, p->w, Q, dQdT, p->stream);
   return hip_check(hipGetLastError(), "partition launch");
 }
@@ -681,7 +681,7 @@ int xs_line_intensities(xs_plan* p, const xs_states* st, const xs_lines* ln, voi
   if (p->model.precision == XS_FP32 && !log_scale) return fail(XS_EINVAL, "log_scale is NULL (FP32 form)");
   const StatesView sv = view(st);
   const LinesView lv = view(ln);
-  launch_partition(p->md, p->w, sv, true, p->stream);
+  launch_partition(p->md, p->w, sv, kFarOff, p->stream);
   launch_intensity_out(p->md, p->w, sv, lv, S, log_scale, p->stream);
   return hip_check(hipGetLastError(), "intensity launch");
 }

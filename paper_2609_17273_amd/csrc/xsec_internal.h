@@ -42,7 +42,7 @@ constexpr int kSortBlock = 256 * kSortItems;
 constexpr int kFineSh = 6;
 // Leaves of 16 points (FP32 form) and 64 (FP64): smaller leaves leave fewer
 // points to the near kernel and give the tiles a level more.  Measured near +
-// tile kernels with 16 / 32 / 64 points: 1e7 lines FP32 3.45 / 3.90 / 4.02 ms,
+// tile kernels with 16 / 32 / 64 points, the tiles line by line: 1e7 lines FP32 3.45 / 3.90 / 4.02 ms,
 // 48 conditions x 1e6 lines FP32 11.1 / 11.2 / 12.4; 1e6 lines FP64 2.28 /
 // 1.79 / 1.61, 3.9e5 FP64 bin means 2.17 / 1.89 / 2.07 (20 nodes to a tile).
 constexpr int kLeafSh32 = 4, kLeafSh64 = 6;
@@ -179,8 +179,10 @@ struct Tiling {
 };
 
 // ---- launch wrappers (k_lines.hip) ----
-// lines: also clears the per-call counters and packs the states for the line passes
-void launch_partition(const ModelDev& m, const Work& w, const StatesView& st, bool lines, hipStream_t s);
+// clear > 0: also clears the first `clear` counters and the statistics, and packs
+// the states for the line passes (kCounterInts: a preparation; kFarOff: a stick
+// spectrum, which leaves the records of the last preparation and what belongs to them)
+void launch_partition(const ModelDev& m, const Work& w, const StatesView& st, int clear, hipStream_t s);
 void launch_lines_pass1(const ModelDev& m, const Work& w, const StatesView& st,
                         const LinesView& ln, hipStream_t s);
 // Stable sort of the int32 keys w.key[0..n) (values 0..max_key) with their

@@ -42,3 +42,24 @@ def test_moments_against_points(profile, prec, case):
         e = float(np.max(np.abs(got[c][m] - ref[c][m]) / ref[c][m]))
         log(f"[moments] profile {profile} prec {prec} {case} c{c}: {e:.2e}")
         assert e <= TOL[prec]
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+def test_sticks_between_prepare_and_pass(prec):
+    """A stick spectrum leaves the records of the last preparation, and with them
+    the widest line's half-width that chooses the moments' levels: the pass after
+    it gives the same bits as the one before."""
+    import torch
+    P = X()
+    wl = workload("voigt_1e7", n_states=20000, n_lines=70001, nu_hi=600.0, seed=99)
+    ln = wl.lines()
+    ds, dl = gpu_inputs(wl, ln)
+    plan = P.Plan(synth.VOIGT, 0, 0, prec, _Grid(300.0, 0.01, 15001), [C(300.0, p, 25.0) for p in (0.4, 20.0)], ln.n,
+                  mass_amu=wl.mass_amu)
+    plan.prepare(ds, dl)
+    a = plan.profile().clone()
+    plan.line_intensities(ds, dl)
+    b = plan.profile().clone()
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
+    plan.close()
