@@ -182,7 +182,9 @@ __device__ __forceinline__ int near_first(const NearLane& ln, int cnt) { return 
 struct Ring {
   int lo, hi, slo, shi;
 };
-template <typename F>
+// (PLAIN: points in order in the row, for profiles that never go by groups: four
+// operations less a point, two temperatures x 4 x 1e7 Doppler lines 634 -> 532 us)
+template <bool PLAIN = false, typename F>
 __device__ __forceinline__ void near_sweep(const Ring& r, const NearLane& ln, double* row, int tlo, F value) {
   const int skip = max(0, r.shi - r.slo + 1);
   const int n = near_count(ln, r.hi - r.lo + 1 - skip);
@@ -190,7 +192,7 @@ __device__ __forceinline__ void near_sweep(const Ring& r, const NearLane& ln, do
   for (int it = 0; it < n; ++it) {
     int k = r.lo + (i << ln.ks) + ln.sub;
     if (skip && k >= r.slo) k += skip;
-    atomicAdd(&row[near_place(k - tlo)], value(k));
+    atomicAdd(&row[PLAIN ? k - tlo : near_place(k - tlo)], value(k));
     i = i + 1 == n ? 0 : i + 1;
   }
 }
@@ -263,7 +265,7 @@ __device__ __forceinline__ void near_gauss(const ModelDev& m, const CondDev& cd,
     const float a = (float)m.dnu * inv, b = del * inv, hh = 0.5f * a;
     const float c0 = BIN ? S * (float)(0.5 / m.dnu) : S * (float)0.46971863934982566 * inv;  // sqrt(ln2/pi)/alpha
     near_range<float>(BIN ? 10.1f + hh : 12.649110640673518f, a, b, kc, klo, khi, r.lo, r.hi);
-    near_sweep(r, lane, row, tlo, [&](int k) -> double {
+    near_sweep<true>(r, lane, row, tlo, [&](int k) -> double {
       const float x = fmaf((float)(k - kc), a, -b);
       if constexpr (BIN) return (double)(c0 * erf_bin<float>(x, hh));
       else return (double)(c0 * __builtin_amdgcn_exp2f(-(x * x)));
@@ -274,7 +276,7 @@ __device__ __forceinline__ void near_gauss(const ModelDev& m, const CondDev& cd,
     const double a = m.dnu * inv, hh = 0.5 * a, c0 = BIN ? S * (0.5 / m.dnu) : S * (sqrt(kLN2 / kPI) * inv);
     const double b = (nu - nu_of_bin(m.nu0, m.dnu, kc)) * inv;
     near_range<double>(BIN ? 27.3 + hh : sqrt(1100.0), a, b, kc, klo, khi, r.lo, r.hi);
-    near_sweep(r, lane, row, tlo, [&](int k) -> double {
+    near_sweep<true>(r, lane, row, tlo, [&](int k) -> double {
       double x;
       {
 #pragma clang fp contract(off)
@@ -565,7 +567,7 @@ __global__ __launch_bounds__(256) void k_near(NearArgs g) {
       }
     }
     __syncthreads();
-    const int o = near_place(tid);
+    const int o = base_profile(PROF) == XS_DOPPLER || base_profile(PROF) == XS_GAUSSIAN ? tid : near_place(tid);
     const double v = ((rows[0][o] + rows[1][o]) + rows[2][o]) + rows[3][o];
     if (np == 1) {
       const int64_t k = (int64_t)tlo + tid;

@@ -496,7 +496,8 @@ bool use_far(const xs_plan* p) {
 // without expansions.  Measured, gather with its reduction and this: 1e4 lines on 1e6
 // points FP64 111 / 22 us; 1e6 lines on 2e6 points FP32 482 / 73, FP64 714 / 300, bin
 // means FP32 544 / 248; where lines reach 1500 points (4e7 points) FP32 2061 / 1665,
-// 4000 points FP64 (1e5 lines) 2025 / 868.  The gather stays for the allocation-free
+// 4000 points FP64 (1e5 lines) 2025 / 868; 4 x 6e7 lines on 6e5 points FP32 3224 /
+// 3038, FP64 14780 / 10836.  The gather stays for the allocation-free
 // call, whose scratch does not hold the parts' rows.
 bool use_near(const xs_plan* p) {
   const int b = base_profile(p->model.profile);
