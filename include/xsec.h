@@ -342,7 +342,8 @@ int xs_plan_replay(xs_plan* plan);
 /* Time the candidate kernel configurations on these inputs (sigma is used as
  * scratch and overwritten): the plan's bucket size and the other of 64 and
  * 256 points (the lines are re-bucketed in the plan's workspace), each with
- * 256-, 512- and 1024-point tiles and three launch modes; then, for LTE
+ * 256-, 512- and 1024-point tiles and three launch modes (profile passes that do
+ * not go through the gather: a new plan's only); then, for LTE
  * sampled profiles, the adjoint's grid of 4096, 8192, 16384 or 32768 blocks
  * (sigma serves as its cotangent).  Keeps the fastest and caches it under
  * cache_path (JSON, keyed by device, profile, precision, window size, line

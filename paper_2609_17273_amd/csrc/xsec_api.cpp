@@ -996,11 +996,15 @@ int xs_plan_autotune(xs_plan* p, const xs_states* st, const xs_lines* ln, double
   const int buckets[2] = {p->bucket_bins, p->bucket_bins == 64 ? 256 : 64};
   const int tiles[3] = {256, 512, 1024};
   const int modes[3][2] = {{0, 16}, {1, 16}, {1, 32}};
+  // (a pass that does not use the tiles is timed once, in a new plan's
+  // configuration: the others would differ by noise, and a shorter list that does
+  // use them would inherit it)
+  const bool tiled = !use_near(p) && !use_far(p);
   double best_ms = 1e300;
   xs_config cur;
   cur.chunk_lines = 0;
   cur.adj_blocks = p->tiling.adj_blocks;
-  for (int bi = 0; bi < 2 && !rc; ++bi) {
+  for (int bi = 0; bi < (tiled ? 2 : 1) && !rc; ++bi) {
     if (buckets[bi] != p->bucket_bins) {
       // re-bucket the lines (the workspace holds any bucket size)
       p->bucket_bins = buckets[bi];
@@ -1013,6 +1017,7 @@ int xs_plan_autotune(xs_plan* p, const xs_states* st, const xs_lines* ln, double
     cur.bucket_bins = p->bucket_bins;
     for (int si = 0; si < 3 && !rc; ++si) {
       for (int mi = 0; mi < 3 && !rc; ++mi) {
+        if (!tiled && (si != 0 || mi != 1)) continue;
         cur.tile_bins = tiles[si];
         cur.persistent = modes[mi][0];
         cur.waves_per_cu = modes[mi][1];
