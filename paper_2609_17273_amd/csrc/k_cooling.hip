@@ -182,7 +182,7 @@ int64_t cooling_doubles(int32_t nT) {
   return ((int64_t)nT + 31) / 32 * 32 + 2 * (int64_t)cooling_chunks(nT) * nT;
 }
 
-void launch_cooling(const ModelDev& m, const Work& w, const StatesView& st, const LinesView& ln,
+bool launch_cooling(const ModelDev& m, const Work& w, const StatesView& st, const LinesView& ln,
                     const double* T_dev, int32_t nT, double* W, double* Q, hipStream_t s) {
   const int64_t n = ln.n;
   const int bl = (int)std::max<int64_t>(1, std::min<int64_t>(kKeyBlocks, (n + 255) / 256));
@@ -194,7 +194,7 @@ void launch_cooling(const ModelDev& m, const Work& w, const StatesView& st, cons
   hipLaunchKernelGGL(k_cf_keys, dim3(bl), dim3(256), 0, s, st, ln, w.key, term, w.counter, w.stats,
                      cnt);
   int32_t *sk = w.key, *sv = nullptr;
-  launch_radix_sort(m, w, n, st.n, s, &sk, &sv);
+  if (!launch_radix_sort(m, w, n, st.n, s, &sk, &sv)) return false;
   const int chunks = cooling_chunks(nT);
   double* part = w.part + ((int64_t)nT + 31) / 32 * 32;
   // the states' weights: what is left of the partial rows, or (no room for 1024
@@ -215,6 +215,7 @@ void launch_cooling(const ModelDev& m, const Work& w, const StatesView& st, cons
                        T_dev, nT, s0 > 0, part);
   }
   hipLaunchKernelGGL(k_cf_final, dim3((nT + 15) / 16), dim3(256), 0, s, part, chunks, nT, W, Q, cnt, bl, w.stats);
+  return true;
 }
 
 }  // namespace xs

@@ -403,8 +403,6 @@ void launch_lines_pass1(const ModelDev& m, const Work& w, const StatesView& st,
 // Stability makes the sorted order, and so every later summation order,
 // deterministic.
 // ---------------------------------------------------------------------------
-constexpr int64_t kSortFew = 1 << 20;  // lines up to which 1024 keys make a block
-constexpr int kColBlocks = 64;  // up to here a block adds the columns in less than the three scan kernels take
 template <int RB, int ITEMS>
 __global__ __launch_bounds__(256) void k_sort_hist(const int32_t* keys, int64_t n, int shift,
                                                    int32_t* hist, int nblk, int col) {
@@ -607,24 +605,16 @@ static void sort_pass(const int32_t* ik, const int32_t* iv, int64_t n, int shift
                      ov);
 }
 
-void launch_radix_sort(const ModelDev& m, const Work& w, int64_t n, int64_t max_key, hipStream_t s,
+bool launch_radix_sort(const ModelDev& m, const Work& w, int64_t n, int64_t max_key, hipStream_t s,
                        int32_t** sorted_keys, int32_t** sorted_vals) {
-  (void)m;
-  int bits = 1;
-  while ((1ll << bits) <= (long long)max_key) ++bits;
-  const int passes = (bits + 9) / 10, rb = std::max(8, (bits + passes - 1) / passes);
-  const bool few = n <= kSortFew;
-  const int nblk = (int)((n + (few ? 1024 : kSortBlock) - 1) / (few ? 1024 : kSortBlock));
-  // the table: its own space, or the records' nu (8 bytes a line, written after
-  // the sort), or for a plan of less than 1024 lines (one block) the partition
-  // function's partial sums (4096 bytes)
-  const int64_t entries = (int64_t)nblk << rb;
-  int32_t *hist = w.hist, *sums = w.hsum;
-  if (entries > (int64_t)256 * w.n_sort_blocks) {
-    hist = reinterpret_cast<int32_t*>(w.rnu);
-    sums = hist + entries;
-    if (4 * (entries + entries / 1024 + 2) > 8 * w.max_lines) hist = reinterpret_cast<int32_t*>(w.qpart);
-  }
+  const SortPlan sp = sort_plan(n, max_key, w.max_lines, m.n_slots);
+  if (sp.place == kSortNowhere) return false;
+  const int passes = sp.passes, rb = sp.rb, nblk = sp.nblk;
+  const bool few = sp.few;
+  int32_t* const hist = sp.place == kSortInHist  ? w.hist
+                        : sp.place == kSortInRnu ? reinterpret_cast<int32_t*>(w.rnu)
+                                                 : reinterpret_cast<int32_t*>(w.qpart);
+  int32_t* const sums = sp.place == kSortInHist ? w.hsum : hist + sp.entries;
   const int32_t* ik = w.key;
   const int32_t* iv = nullptr;
   int32_t* ok = w.keyA;
@@ -643,6 +633,7 @@ void launch_radix_sort(const ModelDev& m, const Work& w, int64_t n, int64_t max_
   }
   *sorted_keys = const_cast<int32_t*>(ik);
   *sorted_vals = const_cast<int32_t*>(iv);
+  return true;
 }
 
 // ---------------------------------------------------------------------------

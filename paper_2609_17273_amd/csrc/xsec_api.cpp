@@ -358,7 +358,6 @@ size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool wit
               bool with_far = true) {
   const ModelDev& d = p->md;
   const int64_t L = p->max_lines;
-  const int nsb = (int)((L + kSortBlock - 1) / kSortBlock);
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
@@ -381,8 +380,8 @@ size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool wit
   // line pass's packed state table
   x.keyB = (int32_t*)take(4 * L);
   x.valB = (int32_t*)take(4 * L);
-  x.hist = (int32_t*)take(4 * (size_t)256 * nsb);
-  x.hsum = (int32_t*)take(4 * ((size_t)256 * nsb / 1024 + 2));
+  x.hist = (int32_t*)take(4 * (size_t)sort_hist_room(L));
+  x.hsum = (int32_t*)take(4 * ((size_t)sort_hist_room(L) / 1024 + 2));
   // cell offsets: the smallest cells the plan may use, so neither a change of
   // bucket size nor one of conditions needs a larger workspace
   const int sh = with_far ? leaf_sh(p) : kFineSh;
@@ -427,7 +426,6 @@ size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool wit
   x.cut_class = (double*)take(sizeof(double) * d.n_cut_classes);
   x.cut_mult = (int32_t*)take(sizeof(int32_t) * d.n_cut_classes);
   x.max_lines = L;
-  x.n_sort_blocks = nsb;
   if (w) *w = x;
   return o;
 }
@@ -470,7 +468,8 @@ int preprocess(xs_plan* p, const xs_states* st, const xs_lines* ln) {
   launch_partition(p->md, p->w, sv, kCounterInts, p->stream);
   launch_lines_pass1(p->md, p->w, sv, lv, p->stream);
   int32_t *sk = nullptr, *svv = nullptr;
-  launch_radix_sort(p->md, p->w, lv.n, p->md.n_fine, p->stream, &sk, &svv);
+  if (!launch_radix_sort(p->md, p->w, lv.n, p->md.n_fine, p->stream, &sk, &svv))
+    return fail(XS_EWORKSPACE, "no room for the sort's digit table");
   p->has_tau = st->lifetime != nullptr;
   launch_offsets_records(p->md, kernel_work(p), sv, lv, sk ? sk : p->w.keyA, svv ? svv : p->w.valA,
                          p->stream);
@@ -764,7 +763,8 @@ int xs_cooling_function(xs_plan* p, const xs_states* st, const xs_lines* ln, int
                                      hipMemcpyHostToDevice, p->stream), "cooling temperatures")))
     return rc;
   if ((rc = hip_check(hipStreamSynchronize(p->stream), "cooling temperatures sync"))) return rc;
-  launch_cooling(p->md, p->w, view(st), view(ln), p->w.part, n_T, W, Q, p->stream);
+  if (!launch_cooling(p->md, p->w, view(st), view(ln), p->w.part, n_T, W, Q, p->stream))
+    return fail(XS_EWORKSPACE, "no room for the sort's digit table");
   p->prepared = false;  // the records area now holds the cooling function's terms
   p->last_lines_in = ln->n;
   return hip_check(hipGetLastError(), "cooling launch");

@@ -6,6 +6,7 @@
 
 #include "../../include/xsec.h"
 #include "far_geometry.h"
+#include "sort_plan.h"
 
 namespace xs {
 
@@ -24,11 +25,9 @@ constexpr int kMaxCond = 256;
 constexpr int base_profile(int profile) {
   return profile < 4 ? profile : (profile < 8 ? profile - 4 : 3);
 }
-constexpr int kQBlocks = 256;     // partial sums per slot in the partition-function reduction
 constexpr int kItemsPerCU = 256;  // gather work items aimed at per compute unit when tiles are split
 constexpr int kAdjBlocks = 16384;    // blocks of the adjoint's grid in a new plan
 constexpr int kAdjBlocksMax = 32768;  // the most the configuration allows (sizes the partial sums)
-constexpr int kSortItems = 16;    // keys per thread in the radix sort (4096 per block)
 // Device counters (int32): [0] gather work queue, [2..3] candidate total,
 // [4..5] lines per item or part, [6] parts beyond
 // tiles' first, [kFarOff] set by the
@@ -36,7 +35,6 @@ constexpr int kSortItems = 16;    // keys per thread in the radix sort (4096 per
 // |gamma_ref|, smallest and largest n_exp of the kept lines (floats).
 constexpr int kCounterInts = 64;
 constexpr int kFarOff = 9, kGammaMax = 10, kNexpMin = 11, kNexpMax = 12;
-constexpr int kSortBlock = 256 * kSortItems;
 // Lines are sorted by home bin >> sh: 64 points per key (the smallest bucket
 // size), or the leaves of the tile expansions.
 constexpr int kFineSh = 6;
@@ -134,7 +132,7 @@ struct Work {
   int32_t* keyB;
   int32_t* valA;
   int32_t* valB;
-  int32_t* hist;            // [256 * n_sort_blocks] (+ scan block sums)
+  int32_t* hist;            // [sort_hist_room] digit table of the sort (sort_plan.h)
   int32_t* hsum;            // scan block sums
   int32_t* off;             // [n_fine + 1] offsets of the cells (2^fine_sh grid points) into the sorted records
   double* rnu;              // sorted records: nu
@@ -167,7 +165,6 @@ struct Work {
   double* cut_class;        // [n_cut_classes] distinct cut-offs
   int32_t* cut_mult;        // [n_cut_classes] conditions sharing each cut-off
   int64_t max_lines;
-  int32_t n_sort_blocks;
 };
 
 struct Tiling {
@@ -186,8 +183,9 @@ void launch_partition(const ModelDev& m, const Work& w, const StatesView& st, in
 void launch_lines_pass1(const ModelDev& m, const Work& w, const StatesView& st,
                         const LinesView& ln, hipStream_t s);
 // Stable sort of the int32 keys w.key[0..n) (values 0..max_key) with their
-// positions; returns the sorted keys and positions (ping-pong buffers).
-void launch_radix_sort(const ModelDev& m, const Work& w, int64_t n, int64_t max_key, hipStream_t s,
+// positions; returns the sorted keys and positions (ping-pong buffers), or false
+// if the workspace has no room for the digit table (nothing enqueued).
+bool launch_radix_sort(const ModelDev& m, const Work& w, int64_t n, int64_t max_key, hipStream_t s,
                        int32_t** sorted_keys, int32_t** sorted_vals);
 void launch_offsets_records(const ModelDev& m, const Work& w, const StatesView& st,
                             const LinesView& ln, const int32_t* skeys, const int32_t* svals, hipStream_t s);
@@ -220,7 +218,8 @@ void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, int
 // ---- cooling function (k_cooling.hip) ----
 // doubles of Work::part the temperatures and partial sums take
 int64_t cooling_doubles(int32_t nT);
-void launch_cooling(const ModelDev& m, const Work& w, const StatesView& st, const LinesView& ln,
+// false: no room for the sort (as launch_radix_sort)
+bool launch_cooling(const ModelDev& m, const Work& w, const StatesView& st, const LinesView& ln,
                     const double* T_dev, int32_t nT, double* W, double* Q, hipStream_t s);
 
 // ---- adjoint (k_adjoint.hip) ----
