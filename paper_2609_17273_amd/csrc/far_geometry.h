@@ -47,6 +47,7 @@ struct FarCond {
   int32_t cR, cL, xR, xL;
   int32_t gap_max;
   int32_t glev;    // level of the tiles that share a gap: lmax, and at least 256 points
+  int32_t mom;     // lowest level whose cells may take moments of the lines' Gaussians
   // gap of the tiles up to cell e: (gap0 + e gap1) / 2^32, at least one
   int64_t gap0, gap1;
 };
@@ -192,6 +193,17 @@ XS_HD int far_widest(int32_t lo, int32_t hi, int l) {
 XS_HD int far_mom_level(int sh, double gamma) {
   int l = 0;
   while (l < kFarLevels && !(gamma <= 0.5 * (double)(1 << (sh + l)))) ++l;
+  return l;
+}
+// The lowest level of whose cells a Gaussian's standard deviation sigma (in points) is at
+// most `cells`: moments are held in these cells' widths, where the n-th of a
+// Gaussian alone is sigma^n (n - 1)!!.  With 4 cells the 28 of the FP32 form stay
+// below 2e31 a line (6 cells 1.5e36, 8 past FP32's range), with 2^16 the 48 of the
+// FP64 form below 1e262.
+constexpr double kMomSigma32 = 4.0, kMomSigma64 = 65536.0;
+XS_HD int far_sigma_level(int sh, double sigma, double cells) {
+  int l = 0;
+  while (l < kFarLevels && !(sigma <= cells * (double)(1 << (sh + l)))) ++l;
   return l;
 }
 // blocks of a level: 4 >> far_wide tiles each, or one slice of one tile

@@ -388,8 +388,8 @@ __device__ __forceinline__ int far_slot(int lane) {
 // away or more (of a narrower cell: within half the distance): the series ends
 // at 0.5^PM, 4e-9 for PM = 28 (FP32 form) and 4e-15 for 48.  The Gaussian's
 // part lies within 4.5 sigma at these orders, the nodes beyond 11 sigma.  Levels
-// whose cells are too small for the widest line (far_mom_level) take lines one by
-// one as before.
+// whose cells are too small for the widest line (far_mom_level) or for the widest
+// Gaussian's powers (far_sigma_level) take lines one by one.
 //
 // The tiles of 1e7 lines FP32 (2e6 points) took 1.08 ms line by line, 0.35 by moments
 // (leaves 0.19, wider cells 0.05, tiles 0.11), 1e6 lines FP64 0.60 and 0.22, 48
@@ -415,7 +415,7 @@ static __device__ const double kFarX12[12] = XS_FAR_X12, kFarX20[20] = XS_FAR_X2
 __device__ __forceinline__ int far_cond_mom_level(const FarArgs& g, const CondDev& cd) {
   const float* e = (const float*)g.counter;
   const double n = fmax((double)e[kNexpMin] * cd.lnTr, (double)e[kNexpMax] * cd.lnTr);
-  return far_mom_level(cd.far.sh, (double)e[kGammaMax] * exp(n) * cd.pfac * 1.00001 / g.m.dnu);
+  return max(cd.far.mom, far_mom_level(cd.far.sh, (double)e[kGammaMax] * exp(n) * cd.pfac * 1.00001 / g.m.dnu));
 }
 
 // Moments of the leaves, a wave to a leaf and a line to a lane.

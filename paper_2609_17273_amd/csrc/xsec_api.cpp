@@ -241,7 +241,12 @@ FarCond far_condition(const xs_plan* p, const CondDev& cd) {
     if (!(std::fabs(g0) < double(1 << 28)) || !(g1 < 1.0)) return FarCond{};
   }
   const int64_t W = (int64_t)std::floor(r);
-  return far_make(W - 2, W + 2, d.n_fine, d.fine_sh, g0, g1);
+  FarCond c = far_make(W - 2, W + 2, d.n_fine, d.fine_sh, g0, g1);
+  // a kept line lies at most a cut-off beyond the grid; standard deviation alpha / sqrt(2 ln 2)
+  const double nu_end = d.nu0 + (double)(d.n_bins - 1) * d.dnu + cd.cut;
+  c.mom = far_sigma_level(d.fine_sh, nu_end * cd.dop / std::sqrt(2.0 * kLN2) / d.dnu,
+                          p->model.precision == XS_FP32 ? kMomSigma32 : kMomSigma64);
+  return c;
 }
 
 void derive(xs_plan* p) {
