@@ -236,7 +236,10 @@ int xs_plan_get_config(const xs_plan* plan, xs_config* cfg);
 
 /* Partition functions, Eq. (pf) (LTE) or Eq. (Q nlte 2T), one per condition,
  * in FP64: Q[n_cond] and, for LTE, dQdT[n_cond] = sum g (c2 E / T^2)
- * exp(-c2 E/T) (may be NULL; NaN for two temperatures).  Device outputs. */
+ * exp(-c2 E/T) (may be NULL; NaN for two temperatures).  Device outputs.
+ * This call and xs_line_intensities leave the records of the last xs_prepare
+ * and everything that a pass over them reads, whatever states and lines they
+ * are given. */
 int xs_partition_function(xs_plan* plan, const xs_states* states, double* Q, double* dQdT);
 
 /* Line intensities (stick spectrum) of every line for every condition,

@@ -426,6 +426,9 @@ size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool wit
     }
   }
   x.stats = (unsigned long long*)take(8 * 8);
+  // (the allocation-free call has neither a stick spectrum nor an adjoint)
+  x.own = nullptr;
+  if (with_adjoint) x.own = (double*)take(sizeof(double) * 4 * d.n_slots);
   x.adjpart = with_adjoint ? (double*)take(sizeof(double) * d.n_cond * 2 * 2 * kAdjBlocksMax) : nullptr;
   x.gmax = (unsigned long long*)take(sizeof(unsigned long long) * d.n_cond);
   x.cut_class = (double*)take(sizeof(double) * d.n_cut_classes);
@@ -463,6 +466,18 @@ int upload(xs_plan* p) {
 Work kernel_work(const xs_plan* p) {
   Work w = p->w;
   if (!p->has_tau) w.rgpre = nullptr;
+  return w;
+}
+
+// For partition functions and stick spectra: their own partition functions and
+// scales, since those of the last preparation belong to its records.
+Work own_work(const xs_plan* p) {
+  Work w = p->w;
+  const int32_t n = p->md.n_slots;
+  w.Q = w.own;
+  w.dQ = w.own + n;
+  w.sb = w.own + 2 * n;
+  w.smax = (unsigned long long*)(w.own + 3 * n);
   return w;
 }
 
@@ -673,8 +688,9 @@ int xs_partition_function(xs_plan* p, const xs_states* st, double* Q, double* dQ
   int rc;
   if ((rc = check_call(p, st, nullptr))) return rc;
   if (!Q) return fail(XS_EINVAL, "Q is NULL");
-  launch_partition(p->md, p->w, view(st), 0, p->stream);
-  launch_q_out(p->md, p->w, Q, dQdT, p->stream);
+  const Work w = own_work(p);
+  launch_partition(p->md, w, view(st), 0, p->stream);
+  launch_q_out(p->md, w, Q, dQdT, p->stream);
   return hip_check(hipGetLastError(), "partition launch");
 }
 
@@ -686,8 +702,9 @@ int xs_line_intensities(xs_plan* p, const xs_states* st, const xs_lines* ln, voi
   if (p->model.precision == XS_FP32 && !log_scale) return fail(XS_EINVAL, "log_scale is NULL (FP32 form)");
   const StatesView sv = view(st);
   const LinesView lv = view(ln);
-  launch_partition(p->md, p->w, sv, kFarOff, p->stream);
-  launch_intensity_out(p->md, p->w, sv, lv, S, log_scale, p->stream);
+  const Work w = own_work(p);
+  launch_partition(p->md, w, sv, kFarOff, p->stream);
+  launch_intensity_out(p->md, w, sv, lv, S, log_scale, p->stream);
   return hip_check(hipGetLastError(), "intensity launch");
 }
 

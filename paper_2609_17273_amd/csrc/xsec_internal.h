@@ -160,6 +160,7 @@ struct Work {
   double* cut_rows;         // [n_cond][n_cut_rows][2][nodes] moments of the cotangent over parts of cut tiles
   int64_t n_cut_rows;
   unsigned long long* stats;// [8]
+  double* own;              // [4][n_slots] Q, dQ, sb and smax of partition functions and stick spectra
   double* adjpart;          // [n_cond][2][2 kAdjBlocksMax]: the near and the far part's blocks
   unsigned long long* gmax; // [n_cond] max |dL/dsigma| per condition (bits; FP32 adjoint's scale)
   double* cut_class;        // [n_cut_classes] distinct cut-offs
