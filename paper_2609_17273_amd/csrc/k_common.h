@@ -136,7 +136,8 @@ __device__ __forceinline__ LineFac line_fac(int mode, int pop, const LineState& 
 // One slot's factors: c2 / (T ln 2) for T_rot (or T) and T_vib, in two parts.
 struct SlotFac {
   double rh, rl, vh, vl;
-  double iQ;
+  double iQ;   // 1 / Q = iQ 2^-eQ, iQ in (1, 2]: Q may be as small as FP64 holds, its reciprocal not
+  int eQ;
   double lnQ;  // (for ln|S|)
   double sb2;  // s_b / ln 2; 0 in the FP64 form
 };
@@ -152,7 +153,7 @@ __device__ __forceinline__ SlotFac slot_fac(const SlotDev& sd, int pop, double Q
   SlotFac f;
   two_part_rate(pop == XS_LTE ? sd.T : sd.Tr, f.rh, f.rl);
   two_part_rate(pop == XS_NLTE_2T ? sd.Tv : 1.0, f.vh, f.vl);
-  f.iQ = 1.0 / Q;
+  f.iQ = 1.0 / frexp(Q, &f.eQ);
   f.lnQ = log(Q);
   f.sb2 = sb / kLN2;
   return f;
@@ -199,7 +200,7 @@ __device__ __forceinline__ double intensity_value(const Intensity& o, const Slot
   const double t = (o.th - sc2) + q.sb2;
   const double k = fmin(fmax(rint(t), -5000.0), 5000.0);
   const double r = fabs(t) >= 5000.0 ? 0.0 : (((o.th - k) - sc2) + q.sb2) + o.tl;  // (a NaN stays one)
-  return ldexp(o.m * q.iQ * fma(-r, exp2m1_over(-r), 1.0), -(int)k);
+  return ldexp(o.m * q.iQ * fma(-r, exp2m1_over(-r), 1.0), -(int)k - q.eQ);
 }
 
 // ln|S|, with the log scale
