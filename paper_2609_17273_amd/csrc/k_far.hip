@@ -223,8 +223,8 @@ __device__ __forceinline__ void far_line_f64(double xc, double ah, double a, dou
         far_rational<P>(xc, ah, acc, [&](double x, double& N, double& D) { poly2_nd(B, x, N, D); });
       } else {
         const double k = c0 * (y * (2.0 / kPI)), y4 = 4.0 * y2;
-        // two nodes over one reciprocal (|x| < 64 on the tile's nearer side and
-        // below 5 times that on it, or y beyond: the products stay finite)
+        // two nodes over one reciprocal (three and four pairs: the products stay finite
+        // for |x|, y <= 1e9; six: for y <= 1e6)
         auto pairs = [&](auto np) {
 #pragma unroll
           for (int q = 0; q < P; q += 2) {
@@ -239,7 +239,18 @@ __device__ __forceinline__ void far_line_f64(double xc, double ah, double a, dou
         };
         if (all(400.0 * 1.001)) pairs(std::integral_constant<int, 3>());
         else if (all(144.0 * 1.001)) pairs(std::integral_constant<int, 4>());
-        else pairs(std::integral_constant<int, 6>());
+        else if (__ballot(live && !(y <= 1.0e6)) == 0) pairs(std::integral_constant<int, 6>());
+        else
+          // (a far wider line in the wave: its twelve factors of up to y^4 would overflow)
+#pragma unroll 1
+          for (int q = 0; q < P; ++q) {
+            const double x = fma(FarNodes<P>::x[q], ah, xc);
+            double N, D;
+            gh_nd<6>(x * x, y2, y4, N, D);
+            const double t = live ? k * N * rcp64(D) : 0.0;
+#pragma unroll
+            for (int h = 0; h < P; ++h) acc[h] += h == q ? t : 0.0;
+          }
       }
     }
   }
