@@ -19,8 +19,10 @@
 // through exactly one tile.  Only tiles of level `end` can be cut by a window
 // end: their cells whose windows may end inside are set apart (far_cut), and
 // their lines are added up to the window's end only.
-// Cells 0 and n_fine - 1, which also hold the lines beyond the grid, go point
-// by point over their whole windows.
+// Lines beyond the grid lie in cells -v .. -1 and n_fine .. n_fine + v - 1, which
+// differ from the others only in that no leaf belongs to them; v is a multiple of
+// the widest tile (far_virtual).  The outermost cells, -v and n_fine - 1 + v, which
+// also hold the lines further out, go point by point over their whole windows.
 #pragma once
 #include <stdint.h>
 
@@ -47,6 +49,7 @@ struct FarCond {
   int32_t cR, cL, xR, xL;
   int32_t gap_max;
   int32_t glev;    // level of the tiles that share a gap: lmax, and at least 256 points
+  int32_t v;       // cells of lines beyond either end of the grid
   int32_t mom;     // lowest level whose cells may take moments of the lines' Gaussians
   // gap of the tiles up to cell e: (gap0 + e gap1) / 2^32, at least one
   int64_t gap0, gap1;
@@ -63,7 +66,7 @@ XS_HD int32_t far_shl(int32_t a, int l) { return a * (1 << l); }  // a may be ne
 XS_HD int32_t far_tiles(int32_t n_fine, int l) { return (n_fine + (1 << l) - 1) >> l; }
 
 XS_HD int32_t far_gap(const FarCond& c, int l, int32_t t) {
-  const int64_t e = (int64_t)((t >> (c.glev - l)) + 1) << c.glev;
+  const int64_t e = (int64_t)((t >> (c.glev - l)) + 1) * ((int64_t)1 << c.glev);  // (t may be negative)
   const int64_t g = (c.gap0 + e * c.gap1) >> 32;
   return g < 1 ? 1 : g > c.gap_max ? c.gap_max : (int32_t)g;
 }
@@ -73,12 +76,12 @@ XS_HD int32_t far_apart(int32_t gap, int l) { return 1 + ((gap + (1 << l) - 1) >
 XS_HD CellRange far_left(const FarCond& c, int32_t gap, int l, int32_t t) {
   const int32_t hi = far_shl(t - far_apart(gap, l) + 1, l) - 1;
   const int32_t lo = l > c.end ? ((t + 1) << l) - c.cL : ((t >> (c.end - l)) << c.end) - c.xL;
-  return CellRange{far_max(1, lo), hi};
+  return CellRange{far_max(1 - c.v, lo), hi};
 }
 XS_HD CellRange far_right(const FarCond& c, int32_t gap, int l, int32_t t) {
   const int32_t lo = far_shl(t + far_apart(gap, l), l);
   const int32_t hi = l > c.end ? (t << l) + c.cR : (((t >> (c.end - l)) + 1) << c.end) + c.xR;
-  return CellRange{lo, far_min(c.n_fine - 2, hi)};
+  return CellRange{lo, far_min(c.n_fine - 2 + c.v, hi)};
 }
 
 // The leaves near cell f, n0..n1 (gap grows by at most one from a tile of level
@@ -151,9 +154,9 @@ XS_HD void far_cut_candidates(const FarCond& c, int32_t f0, int32_t f1, CellRang
 // cell f's take the leaves within gap of f.
 constexpr int kSegs = 3;
 XS_HD void far_segments(const FarCond& c, int32_t a, int32_t b, int32_t clo, int32_t chi, CellRange s[kSegs]) {
-  const int32_t last = c.n_fine - 1, gap = far_gap(c, 0, a);
-  s[0] = CellRange{far_max(far_max(a - gap, clo), 1), far_min(far_min(b + gap, chi), last - 1)};
-  s[1] = clo == 0 ? CellRange{0, 0} : CellRange{0, -1};
+  const int32_t first = -c.v, last = c.n_fine - 1 + c.v, gap = far_gap(c, 0, a);
+  s[0] = CellRange{far_max(far_max(a - gap, clo), first + 1), far_min(far_min(b + gap, chi), last - 1)};
+  s[1] = clo == first ? CellRange{first, first} : CellRange{0, -1};
   s[2] = chi == last ? CellRange{last, last} : CellRange{0, -1};
 }
 
@@ -174,6 +177,19 @@ XS_HD int far_levels_of_grid(int32_t n_fine) {
   int l = 0;
   while (l < kFarLevels && (n_fine >> l) >= 3) ++l;
   return l;
+}
+// Cells beyond either end of a grid for windows that reach Wx points: all that they
+// can touch, in whole tiles of level lmax, up to kFarVirtual (which bounds the
+// table of cells: at 16 points to a cell windows of a million points).
+// Measured, whole calls of Voigt spectra whose lines lie up to a cut-off of 25 cm^-1 beyond
+// a grid of 50 cm^-1 (5001 points), gather / these lines point by point / cells of
+// their own: 2e4 lines FP32 272 / 547 / 131 us, FP64 348 / 795 / 181; 1e6 lines FP32 2067 /
+// 1616 / 530, FP64 2970 / 3356 / 1123; bin means of 2e5 lines FP32 1557 / 2094 / 343.
+constexpr int32_t kFarVirtual = 1 << 16;
+XS_HD int32_t far_virtual(int sh, int lmax, int64_t Wx) {
+  const int64_t n = (Wx >> sh) + 2;
+  const int64_t v = ((n >> lmax) + 1) << lmax;
+  return v >= kFarVirtual ? kFarVirtual : (int32_t)v;
 }
 // Moments: one row per cell of every level, level after level; and the cells of
 // level `l` or less that make up the leaves [lo, hi], one after the other: the

@@ -1086,7 +1086,7 @@ __device__ __forceinline__ Sums3 far_window_sums(const AdjArgs& a, const CondDev
   const int f0 = wave_min(far ? f : 0x7fffffff), f1 = wave_max(far ? f : -0x7fffffff);
   if (f0 > f1) return Sums3{0.0, 0.0, 0.0};
   AdjLine<R> L;
-  L.kc = far ? kc : f0 << fc.sh;
+  L.kc = far ? kc : far_shl(f0, fc.sh);
   L.ad = far ? m.dnu * inv : 1.0;
   L.bd = far ? (nu - nu_of_bin(m.nu0, m.dnu, kc)) * inv : 0.0;
   L.y = far ? y : 1.0;
@@ -1220,7 +1220,7 @@ __global__ __launch_bounds__(256, (adj_waves<R, PROF, FAR>())) void k_adjoint(Ad
     for (int w = 0; w < 4; ++w) sdt[w][c] = sdp[w][c] = 0.0;
   __syncthreads();
   const bool far_on = FARP && a.far && !a.counter[kFarOff];
-  const int64_t nk = (FAR && !far_on) ? 0 : a.off[m.n_fine];
+  const int64_t nk = (FAR && !far_on) ? 0 : a.off[m.n_fine + m.fine_v];
   const int64_t nbatch = (nk + 63) >> 6;
   const double sqrt2ln2 = sqrt(2.0 * kLN2);
   for (int64_t bt = (int64_t)blockIdx.x * 4 + wave; bt < nbatch; bt += (int64_t)gridDim.x * 4) {
@@ -1260,12 +1260,12 @@ __global__ __launch_bounds__(256, (adj_waves<R, PROF, FAR>())) void k_adjoint(Ad
       if (use_far && on) {
         kc = a.rkc[p];
         f = kc >> cd.far.sh;
-        split = f >= 1 && f <= cd.far.n_fine - 2;
+        split = f >= 1 - cd.far.v && f <= cd.far.n_fine - 2 + cd.far.v;
         if (!FAR && split) {
           int32_t n0, n1;
           far_near(cd.far, f, n0, n1);
-          klo = max(klo, (int64_t)n0 << cd.far.sh);
-          khi = min(khi, ((int64_t)(n1 + 1) << cd.far.sh) - 1);
+          klo = max(klo, (int64_t)far_shl(n0, cd.far.sh));
+          khi = min(khi, (int64_t)far_shl(n1 + 1, cd.far.sh) - 1);
           on = klo <= khi;
         }
         if (FAR) on = split;
@@ -1424,7 +1424,7 @@ void launch_adjoint(const ModelDev& m, const Work& w, const StatesView& st, cons
   a.Q = w.Q;
   a.dQ = w.dQ;
   a.sb = w.sb;
-  a.off = w.off;
+  a.off = w.off + m.fine_v;
   a.rnu = w.rnu;
   a.rgref = w.rgref;
   a.rnexp = w.rnexp;

@@ -50,7 +50,7 @@ struct FarArgs {
   int64_t cond_rows;  // rows per condition
   double* sigma;
   double* mom;        // [conditions of the launch][mom_cells][PM] moments, or null
-  int64_t mom_cells;  // cells of all levels
+  int64_t mom_cells;  // cells of all levels, those beyond the grid with them
   int32_t c0;         // first condition of the launch (not k_far_finish)
   int32_t blocks;     // of k_far's levels
 };
@@ -443,12 +443,12 @@ __global__ __launch_bounds__(256, sizeof(Real) == 4 ? 4 : 2) void k_far_leaves(F
   const int lm = far_cond_mom_level(g, cd);
   if (lm > fc.lmax) return;
   const ModelDev& m = g.m;
-  const int nf = m.n_fine, f = blockIdx.x * 4 + wave;
-  if (f >= nf) return;
+  const int nk = fine_keys(m), key = blockIdx.x * 4 + wave, f = key - m.fine_v;
+  if (key >= nk) return;
   // in cells of the first level that uses them, so that the powers stay small
   const double hp = (double)(1 << (fc.sh + lm)), ih = 1.0 / hp;
-  // (the edge cells' lines go point by point)
-  const bool any = f > 0 && f < nf - 1;
+  // (the outermost cells' lines go point by point)
+  const bool any = key > 0 && key < nk - 1;
   const uint32_t p0 = any ? g.off[f] : 0, p1 = any ? g.off[f + 1] : 0;
   double acc64[PM];
   Real acc[PM];
@@ -457,7 +457,7 @@ __global__ __launch_bounds__(256, sizeof(Real) == 4 ? 4 : 2) void k_far_leaves(F
     acc[k] = (Real)0;
     if (F32) acc64[k] = 0.0;
   }
-  const double centre = (double)(((int64_t)f << fc.sh) + (1 << fc.sh) / 2) - 0.5;
+  const double centre = (double)(far_shl(f, fc.sh) + (1 << fc.sh) / 2) - 0.5;
   int since = 0;
   for (uint32_t q0 = p0; q0 < p1; q0 += 64) {
     const FarIn<Real> v = far_load<Real>(g, cd, min(q0 + lane, p1 - 1));
@@ -542,7 +542,7 @@ __global__ __launch_bounds__(256, sizeof(Real) == 4 ? 4 : 2) void k_far_leaves(F
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  if (lane < PM) g.mom[((int64_t)blockIdx.y * g.mom_cells + f) * PM + lane] = row[lane];
+  if (lane < PM) g.mom[((int64_t)blockIdx.y * g.mom_cells + key) * PM + lane] = row[lane];
 }
 
 // Moments of the kMomLevels levels above level `base`: a block has kMomLeaves of
@@ -557,7 +557,7 @@ __global__ __launch_bounds__(256) void k_far_moments(FarArgs g, int base) {
   if (!fc.on || g.counter[kFarOff] || base >= fc.lmax) return;
   const int lm = far_cond_mom_level(g, cd);
   if (lm > fc.lmax) return;
-  const int nf = g.m.n_fine, i0 = blockIdx.x * kMomLeaves;
+  const int nf = fine_keys(g.m), i0 = blockIdx.x * kMomLeaves;  // cells from the first beyond the grid on
   double* const rows = g.mom + (int64_t)blockIdx.y * g.mom_cells * PM;
   const int nc = min(kMomLeaves, far_tiles(nf, base) - i0);
   const double* from = rows + (far_cells_before(nf, base) + i0) * PM;
@@ -633,7 +633,7 @@ __global__ __launch_bounds__(256) void k_far_cells(FarArgs g) {
       }
       const int lv = far_widest(r[0].lo, r[0].hi, l), cell = r[0].lo >> lv;
       r[0].lo += 1 << lv;
-      const double2* mo = (const double2*)(rows + (far_cells_before(nf, lv) + cell) * PM);
+      const double2* mo = (const double2*)(rows + (far_cells_before(fine_keys(g.m), lv) + cell + (g.m.fine_v >> lv)) * PM);
       const double w = (double)(1 << (lv + fc.sh));
       const double c = (double)cell * w + (w * 0.5 - 0.5);
       const double inv = (double)(1 << (max(lv, lm) + fc.sh)) / (node - c);
@@ -975,7 +975,7 @@ void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, int
   a.m = m;
   a.cond = w.cond;
   a.sb = w.sb;
-  a.off = w.off;
+  a.off = w.off + m.fine_v;
   a.rnu = w.rnu;
   a.rgref = w.rgref;
   a.rnexp = w.rnexp;
@@ -996,7 +996,7 @@ void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, int
   // many conditions at a time as fit (lifetimes, whose widths have no bound
   // here, go line by line)
   const int pm = m.prec == XS_FP32 ? kMoments32 : kMoments64;
-  a.mom_cells = far_cells_before(m.n_fine, far_lmax + 1);
+  a.mom_cells = far_cells_before(fine_keys(m), far_lmax + 1);
   const int64_t fit = 2 * w.item_target * 1024 / (a.mom_cells * pm);
   const bool many = m.n_fine >= (m.prec == XS_FP32 ? kMomCells32 : kMomCells64) ||
                     n_lines >= kMomLines * (int64_t)m.n_fine;
@@ -1009,11 +1009,11 @@ void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, int
       const int nc = std::min(at_once, m.n_cond - a.c0);
       const auto go = [&](auto k, int64_t bl) { hipLaunchKernelGGL(k, dim3((unsigned)bl, nc), dim3(256), 0, s, a); };
       if (a.mom) {
-        go(leaves, (m.n_fine + 3) / 4);
+        go(leaves, (fine_keys(m) + 3) / 4);
         for (int b = 0; b < far_lmax; b += kMomLevels)
-          hipLaunchKernelGGL(moments, dim3((far_tiles(m.n_fine, b) + kMomLeaves - 1) / kMomLeaves, nc), dim3(256), 0, s,
+          hipLaunchKernelGGL(moments, dim3((far_tiles(fine_keys(m), b) + kMomLeaves - 1) / kMomLeaves, nc), dim3(256), 0, s,
                              a, b);
-        go(cells, (a.mom_cells + per_block - 1) / per_block);
+        go(cells, (far_cells_before(m.n_fine, far_lmax + 1) + per_block - 1) / per_block);
       }
       // (with moments most conditions have nothing left for it)
       go(far, a.mom ? std::min<int64_t>(blocks, 4096) : blocks);

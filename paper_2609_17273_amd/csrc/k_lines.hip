@@ -129,8 +129,8 @@ void launch_q_out(const ModelDev& m, const Work& w, double* Q, double* dQ, hipSt
 // Intensity pass 1: nu_i = E_u - E_l; keep lines with nu > 0 whose window
 // (widest cut-off) reaches the grid; key = k_c >> fine_sh for the home bin
 // k_c = rint((nu - nu0)/dnu), clamped to the grid (lines past either end
-// keep their wings, section "Spectral synthesis"); dropped lines get key
-// n_fine.  FP32 form: running max of ln|S| per slot.  Counters:
+// keep their wings, section "Spectral synthesis") and the fine_v cells beyond it; dropped
+// lines get key fine_keys.  FP32 form: running max of ln|S| per slot.  Counters:
 // kept lines and window pairs (exact windows per distinct cut-off).
 // ---------------------------------------------------------------------------
 // The states of one line, read once: from the packed table, or from the
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(256) void k_lines_pass1(ModelDev m, const SlotDev* 
   float gmax = 0.0f, nlo = INFINITY, nhi = -INFINITY;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < ln.n; i += (int64_t)gridDim.x * 256) {
     const int32_t u = ln.up[i], l = ln.lo[i];
-    int32_t kk = m.n_fine;
+    int32_t kk = fine_keys(m);
     LineState ls;
     if (!gather_line_states<MODE, LTE>(m, st, spack, u, l, ls)) {
       ++tot.bad;
@@ -286,8 +286,8 @@ __global__ __launch_bounds__(256) void k_lines_pass1(ModelDev m, const SlotDev* 
       const LineFac f = line_fac(m.mode, LTE ? XS_LTE : m.pop, ls, (double)ln.A[i], nu);
       if (REC) {
         int64_t kc = home_bin(nu, m.nu0, m.dnu);
-        int64_t fk = kc < 0 ? 0 : kc >> m.fine_sh;
-        kk = (int32_t)(fk < m.n_fine - 1 ? fk : m.n_fine - 1);
+        const int64_t fk = (kc >> m.fine_sh) + m.fine_v;
+        kk = (int32_t)(fk < 0 ? 0 : fk < fine_keys(m) - 1 ? fk : fine_keys(m) - 1);
         const float gref = ln.gref ? ln.gref[i] : (float)ln.gref_scalar;
         const float nexp = ln.nexp ? ln.nexp[i] : (float)ln.nexp_scalar;
         gmax = fmaxf(gmax, fabsf(gref));
@@ -637,9 +637,8 @@ bool launch_radix_sort(const ModelDev& m, const Work& w, int64_t n, int64_t max_
 }
 
 // ---------------------------------------------------------------------------
-// Cell offsets from the sorted keys (the dropped key is n_fine, and position
-// n acts as n_fine + 1, so every cell 0..n_fine gets its start; off[n_fine] =
-// kept lines),
+// Cell offsets from the sorted keys (the dropped key is n = fine_keys, and the position
+// after the last line acts as n + 1, so every cell 0..n gets its start; off[n] = kept lines),
 // and, in the same pass, the sorted line records: nu, gamma_ref, n_exp, original index, and the
 // intensity of every slot, S (FP64) or S~ = sign exp(ln|S| - s_b) (FP32).
 // ---------------------------------------------------------------------------
@@ -662,9 +661,9 @@ __global__ __launch_bounds__(256) void k_records(ModelDev m, const SlotDev* slot
   bool odd = false;
   for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p <= n; p += (int64_t)gridDim.x * 256) {
     {
-      const int k = (p < n) ? skeys[p] : m.n_fine + 1;
+      const int k = (p < n) ? skeys[p] : fine_keys(m) + 1;
       const int kp = (p > 0) ? skeys[p - 1] : -1;
-      for (int b = kp + 1; b <= k && b <= m.n_fine; ++b) off[b] = (int32_t)p;
+      for (int b = kp + 1; b <= k && b <= fine_keys(m); ++b) off[b] = (int32_t)p;
     }
     if (p >= nk) continue;
     const int32_t i = svals[p];

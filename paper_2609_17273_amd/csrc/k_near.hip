@@ -1,6 +1,6 @@
 // Near leaves of the profile pass (far_geometry.h): the points within a few
 // cells of a line, where its profile has structure on the grid's scale, and
-// the whole windows of the edge cells' lines.  The tiles further out are
+// the whole windows of the outermost cells' lines.  The tiles further out are
 // k_far's.  Gaussians, which are zero a few widths away, go point by point as a whole.
 //
 // A block of four waves owns 256 grid points of one condition and takes the
@@ -61,7 +61,7 @@ __device__ __forceinline__ NearSegs near_segments(const NearArgs& g, const CondD
   const int sh = g.m.fine_sh;
   const int a = t * (kNearBins >> sh), b = a + (kNearBins >> sh) - 1;
   const int reach = (cd.wbins >> sh) + 2;
-  const int clo = max(a - reach, 0), chi = min(b + reach, g.m.n_fine - 1);
+  const int clo = max(a - reach, -g.m.fine_v), chi = min(b + reach, g.m.n_fine - 1 + g.m.fine_v);
   CellRange s[kSegs];
   if (cd.far.on && !g.counter[kFarOff]) {
     far_segments(cd.far, a, b, clo, chi, s);
@@ -553,8 +553,8 @@ __global__ __launch_bounds__(256) void k_near(NearArgs g) {
         int klo = max(win.x, tlo), khi = min(win.y, thi);
         if (near) {
           const int f = kc >> m.fine_sh;
-          klo = max(klo, (f - gap) << m.fine_sh);
-          khi = min(khi, ((f + gap + 1) << m.fine_sh) - 1);
+          klo = max(klo, far_shl(f - gap, m.fine_sh));
+          khi = min(khi, far_shl(f + gap + 1, m.fine_sh) - 1);
         }
         if (win.x <= win.y && klo <= khi && S != (Real)0) {
           if constexpr (base_profile(PROF) == XS_DOPPLER || base_profile(PROF) == XS_GAUSSIAN)
@@ -611,7 +611,7 @@ void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate
   a.m = m;
   a.cond = w.cond;
   a.sb = w.sb;
-  a.off = w.off;
+  a.off = w.off + m.fine_v;
   a.rnu = w.rnu;
   a.rgref = w.rgref;
   a.rnexp = w.rnexp;

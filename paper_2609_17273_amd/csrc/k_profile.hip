@@ -172,8 +172,9 @@ __device__ __forceinline__ void tile_candidates(const GatherArgs& g, const CondD
   const int64_t lo = tlo - cd.wbins;
   const int64_t blo = max<int64_t>(0, lo >= 0 ? lo / m.bucket_bins : -1);
   const int64_t bhi = min<int64_t>(m.n_buckets - 1, (thi + cd.wbins) / m.bucket_bins);
-  plo = g.off[blo * m.fine_per_bucket];
-  phi = g.off[min((bhi + 1) * (int64_t)m.fine_per_bucket, (int64_t)m.n_fine)];
+  // (the first and the last bucket also have the lines beyond the grid)
+  plo = g.off[blo == 0 ? -(int64_t)m.fine_v : blo * m.fine_per_bucket];
+  phi = g.off[bhi == m.n_buckets - 1 ? m.n_fine + m.fine_v : (bhi + 1) * (int64_t)m.fine_per_bucket];
 }
 
 // Bin range where |x| < X, relative to k_c, in FP32 (the one-bin margin
@@ -1570,7 +1571,7 @@ void launch_gather(const ModelDev& m, const Work& w, const Tiling& t, double* si
   a.m = m;
   a.cond = w.cond;
   a.sb = w.sb;
-  a.off = w.off;
+  a.off = w.off + m.fine_v;
   a.rnu = w.rnu;
   a.rgref = w.rgref;
   a.rnexp = w.rnexp;
@@ -1674,7 +1675,7 @@ template <typename Real, int PROF>
 __global__ __launch_bounds__(256) void k_scatter(ScatterArgs g) {
   const ModelDev& m = g.m;
   const int lane = threadIdx.x & 63;
-  const int64_t nkept = g.off[m.n_fine];
+  const int64_t nkept = g.off[m.n_fine + m.fine_v];
   const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
   const int64_t total = nkept * m.n_cond;
   for (int64_t wi = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); wi < total;
@@ -1749,7 +1750,7 @@ __global__ __launch_bounds__(256) void k_scatter_bin(ScatterArgs g) {
   constexpr int BASE = PROF - 4;
   const ModelDev& m = g.m;
   const int lane = threadIdx.x & 63;
-  const int64_t nkept = g.off[m.n_fine];
+  const int64_t nkept = g.off[m.n_fine + m.fine_v];
   const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
   const int64_t total = nkept * m.n_cond;
   for (int64_t wi = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); wi < total;
@@ -1831,7 +1832,7 @@ template <typename Real, int PROF>
 __global__ __launch_bounds__(256) void k_scatter_pv(ScatterArgs g) {
   const ModelDev& m = g.m;
   const int lane = threadIdx.x & 63;
-  const int64_t nkept = g.off[m.n_fine];
+  const int64_t nkept = g.off[m.n_fine + m.fine_v];
   const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
   const int64_t total = nkept * m.n_cond;
   for (int64_t wi = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); wi < total;
@@ -1891,7 +1892,7 @@ void launch_scatter(const ModelDev& m, const Work& w, double* sigma, int accumul
   a.m = m;
   a.cond = w.cond;
   a.sb = w.sb;
-  a.off = w.off;
+  a.off = w.off + m.fine_v;
   a.rnu = w.rnu;
   a.rgref = w.rgref;
   a.rnexp = w.rnexp;

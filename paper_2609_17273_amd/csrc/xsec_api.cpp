@@ -268,6 +268,7 @@ void derive(xs_plan* p) {
   d.n_buckets = (int32_t)((p->grid.n_bins + p->bucket_bins - 1) / p->bucket_bins);
   auto cells = [&](int sh) {
     d.fine_sh = sh;
+    d.fine_v = 0;
     d.n_fine = (int32_t)((p->grid.n_bins + ((int64_t)1 << sh) - 1) >> sh);
     d.fine_per_bucket = p->bucket_bins >> sh;
   };
@@ -347,7 +348,13 @@ void derive(xs_plan* p) {
     }
     p->cdev.push_back(cd);
   }
-  if (p->far_lmax < 0) cells(kFineSh);  // no condition uses expansions
+  if (p->far_lmax < 0) {
+    cells(kFineSh);  // no condition uses expansions
+  } else {
+    // (a kept line's home bin is at most a cut-off and a point beyond the grid)
+    d.fine_v = far_virtual(d.fine_sh, p->far_lmax, (int64_t)(maxcut / d.dnu) + 2);
+    for (CondDev& cd : p->cdev) cd.far.v = d.fine_v;
+  }
   d.n_slots = (int32_t)p->sdev.size();
   d.n_cut_classes = (int32_t)p->cut_class.size();
   d.max_cut = maxcut;
@@ -391,7 +398,7 @@ size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool wit
   // bucket size nor one of conditions needs a larger workspace
   const int sh = with_far ? leaf_sh(p) : kFineSh;
   const int64_t cells = (p->grid.n_bins + ((int64_t)1 << sh) - 1) >> sh;
-  x.off = (int32_t*)take(4 * (size_t)(cells + 2));
+  x.off = (int32_t*)take(4 * (size_t)(cells + 2 + (with_far && far_capable(p) ? 2 * kFarVirtual : 0)));
   x.rnu = (double*)take(8 * L);
   x.rgref = (float*)take(4 * L);
   x.rnexp = (float*)take(4 * L);
@@ -488,7 +495,7 @@ int preprocess(xs_plan* p, const xs_states* st, const xs_lines* ln) {
   launch_partition(p->md, p->w, sv, kCounterInts, p->stream);
   launch_lines_pass1(p->md, p->w, sv, lv, p->stream);
   int32_t *sk = nullptr, *svv = nullptr;
-  if (!launch_radix_sort(p->md, p->w, lv.n, p->md.n_fine, p->stream, &sk, &svv))
+  if (!launch_radix_sort(p->md, p->w, lv.n, fine_keys(p->md), p->stream, &sk, &svv))
     return fail(XS_EWORKSPACE, "no room for the sort's digit table");
   p->has_tau = st->lifetime != nullptr;
   launch_offsets_records(p->md, kernel_work(p), sv, lv, sk ? sk : p->w.keyA, svv ? svv : p->w.valA,

@@ -75,11 +75,16 @@ struct ModelDev {
   int32_t bucket_bins, n_buckets;  // lines bucketed by k_c / bucket_bins
   // Lines are sorted by the finer key k_c >> fine_sh (key n_fine = dropped),
   // whatever the bucket size, so that neighbouring sorted lines have nearly
-  // equal home bins; a bucket is fine_per_bucket consecutive fine keys.
+  // equal home bins; a bucket is fine_per_bucket consecutive fine keys.  (With
+  // tile expansions the keys begin fine_v cells before the grid and end as many
+  // after it: see fine_v.)
   int32_t n_fine, fine_per_bucket, fine_sh;
+  int32_t fine_v;                  // cells of lines beyond either end of the grid: keys (k_c >> fine_sh) + fine_v
   int32_t n_cut_classes;           // distinct cut-offs (window statistics)
   double max_cut;
 };
+
+constexpr int fine_keys(const ModelDev& m) { return m.n_fine + 2 * m.fine_v; }  // the key of dropped lines
 
 // Views of the caller's inputs.
 struct StatesView {
@@ -134,7 +139,7 @@ struct Work {
   int32_t* valB;
   int32_t* hist;            // [sort_hist_room] digit table of the sort (sort_plan.h)
   int32_t* hsum;            // scan block sums
-  int32_t* off;             // [n_fine + 1] offsets of the cells (2^fine_sh grid points) into the sorted records
+  int32_t* off;             // [fine_keys + 1] offsets of the cells (2^fine_sh grid points) into the sorted records
   double* rnu;              // sorted records: nu
   float* rgref;             //                 gamma_ref
   float* rnexp;             //                 n_exp
