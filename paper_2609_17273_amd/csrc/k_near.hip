@@ -43,7 +43,7 @@ struct NearArgs {
   const int32_t* rwin;
   int64_t max_lines;
   int32_t* counter;         // [2..3] candidate total; [4..5] lines per part; [6] parts beyond the first
-  int32_t* parts;           // [n_ct] parts of each (tile, condition)
+  int32_t* parts;           // [n_ct] parts of each (tile, condition), 0: the gather's
   int32_t* base;            // [n_ct] first row of a split one
   int32_t* extra;           // [kNearExtra][2] (tile, condition) and part of the parts beyond the first
   double* rows;             // partial rows of split tiles
@@ -83,6 +83,11 @@ __device__ __forceinline__ NearSegs near_segments(const NearArgs& g, const CondD
   return r;
 }
 
+// The lines of a tile, or -1 where the condition's points are the gather's.
+__device__ __forceinline__ int64_t near_lines(const NearArgs& g, int c, int t) {
+  return g.cond[c].gather ? -1 : near_segments(g, g.cond[c], t).cum[kSegs - 1];
+}
+
 // Planning: candidates in all, then the parts of each tile.  A part holds at
 // least kNearChunk lines, and so many that the parts beyond the first stay
 // under kNearExtra: an even list is not split, and a list whose lines crowd
@@ -97,9 +102,9 @@ __global__ __launch_bounds__(256) void k_near_count(NearArgs g) {
   unsigned long long local = 0;
   for (int64_t ct = (int64_t)blockIdx.x * 256 + threadIdx.x; ct < g.n_ct; ct += (int64_t)gridDim.x * 256) {
     const int c = (int)(ct % g.m.n_cond), t = (int)(ct / g.m.n_cond);
-    const int64_t n = near_segments(g, g.cond[c], t).cum[kSegs - 1];
+    const int64_t n = near_lines(g, c, t);
     g.parts[ct] = (int32_t)n;
-    local += (unsigned long long)n;
+    local += (unsigned long long)max<int64_t>(n, 0);
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) local += __shfl_xor(local, o, 64);
@@ -112,7 +117,7 @@ __device__ __forceinline__ void near_plan_tiles(const NearArgs& g, int64_t total
   if (first == 0) *(int64_t*)(g.counter + 4) = chunk;
   for (int64_t ct = first; ct < g.n_ct; ct += step) {
     const int64_t n = g.parts[ct];
-    const int np = n <= chunk ? 1 : (int)((n + chunk - 1) / chunk);
+    const int np = n < 0 ? 0 : n <= chunk ? 1 : (int)((n + chunk - 1) / chunk);
     g.parts[ct] = np;
     g.base[ct] = 0;
     if (np > 1) {
@@ -141,9 +146,9 @@ __global__ __launch_bounds__(1024) void k_near_plan_once(NearArgs g) {
   __syncthreads();
   unsigned long long local = 0;
   for (int ct = threadIdx.x; ct < g.n_ct; ct += 1024) {
-    const int64_t n = near_segments(g, g.cond[ct % g.m.n_cond], ct / g.m.n_cond).cum[kSegs - 1];
+    const int64_t n = near_lines(g, ct % g.m.n_cond, ct / g.m.n_cond);
     g.parts[ct] = (int32_t)n;  // (read by the same thread)
-    local += (unsigned long long)n;
+    local += (unsigned long long)max<int64_t>(n, 0);
   }
   if (local) atomicAdd(&sum, local);
   __syncthreads();
@@ -524,6 +529,7 @@ __global__ __launch_bounds__(256) void k_near(NearArgs g) {
       ct = t * m.n_cond + (ct + t) % m.n_cond;
     }
     const int np = g.parts[ct];
+    if (np == 0) continue;  // the gather's
     const int c = ct % m.n_cond, t = ct / m.n_cond;
     const CondDev& cd = g.cond[c];
     const NearSegs sg = near_segments(g, cd, t);

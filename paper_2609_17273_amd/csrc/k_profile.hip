@@ -155,6 +155,7 @@ struct GatherArgs {
   int32_t n_ct;             // n_tiles * n_cond; ct = t * n_cond + c
   int32_t tile_bins;
   int32_t persistent;
+  int32_t some;             // only the conditions whose `gather` is set
   int64_t chunk_cfg;        // requested lines per work item (0: automatic)
   int64_t item_target;      // work items aimed at when tiles are split
 };
@@ -1502,6 +1503,10 @@ __global__ __launch_bounds__(256) void k_items_count(GatherArgs g, int32_t* cnt)
   unsigned long long local = 0;
   for (int64_t ct = (int64_t)blockIdx.x * 256 + threadIdx.x; ct < g.n_ct; ct += (int64_t)gridDim.x * 256) {
     const int c = (int)(ct % g.m.n_cond), t = (int)(ct / g.m.n_cond);
+    if (g.some && !g.cond[c].gather) {
+      cnt[ct] = -1;  // no work item
+      continue;
+    }
     int64_t tlo, thi, plo, phi;
     tile_candidates(g, g.cond[c], t, tlo, thi, plo, phi);
     cnt[ct] = (int32_t)(phi - plo);
@@ -1528,7 +1533,7 @@ __global__ __launch_bounds__(256) void k_items_split(GatherArgs g, const int32_t
   }
   for (int64_t ct = (int64_t)blockIdx.x * 256 + threadIdx.x; ct < g.n_ct; ct += (int64_t)gridDim.x * 256) {
     const int64_t n = cnt[ct];
-    const int nch = n == 0 ? 1 : (int)((n + chunk - 1) / chunk);
+    const int nch = n < 0 ? 0 : n == 0 ? 1 : (int)((n + chunk - 1) / chunk);
     ib[ct] = nch;
     pb[ct] = nch > 1 ? nch : 0;
   }
@@ -1566,7 +1571,7 @@ static void gather_dispatch(const GatherArgs& a, int M, int blocks, hipStream_t 
 }
 
 void launch_gather(const ModelDev& m, const Work& w, const Tiling& t, double* sigma,
-                   int accumulate, hipStream_t s) {
+                   int accumulate, bool some, hipStream_t s) {
   GatherArgs a;
   a.m = m;
   a.cond = w.cond;
@@ -1591,6 +1596,7 @@ void launch_gather(const ModelDev& m, const Work& w, const Tiling& t, double* si
   a.n_tiles = (int)((m.n_bins + t.tile_bins - 1) / t.tile_bins);
   a.n_ct = a.n_tiles * m.n_cond;
   a.persistent = t.persistent;
+  a.some = some;
   a.chunk_cfg = t.chunk_lines;
   a.item_target = w.item_target;
   // plan the work items

@@ -75,6 +75,7 @@ struct xs_plan {
   int far_lmax = -1;         // highest level of the conditions' tile expansions (-1: none)
   bool no_far = false;       // in the allocation-free call
   int far_end = 0;           // lowest of their levels of cut tiles
+  bool some_gather = false;  // a table with expansions has conditions for the gather
   bool has_tau = false;      // the last xs_prepare had state lifetimes (records hold their widths)
 };
 
@@ -249,6 +250,25 @@ FarCond far_condition(const xs_plan* p, const CondDev& cd) {
   return c;
 }
 
+// A condition without expansions in a table that has them (a window of less than 577
+// points, or one hardly wider than its Doppler cores): the near kernel takes its points
+// line by line, with an LDS add each, the gather by rows of 64 points, with one formula
+// for a row's worst point and some work per tile before it.  So the gather serves wide windows
+// around narrow cores, in the forms where a point outside the core costs less than the
+// add.  Measured, profile pass of seven conditions, near kernel / gather: 2e5 lines on 2e5 points,
+// cores of a point, 300, 400 and 570 points to a side: Voigt FP32 660 / 943, 952 / 940, 1338 / 997 us,
+// FP64 1310 / 1826, 1545 / 1908, 1876 / 2228; Lorentzian FP32 741 / 813, 1026 / 820, 1437 / 791,
+// FP64 695 / 888, 898 / 897, 1191 / 899; Voigt FP32 with cores of 10 points 742 /
+// 1195, 990 / 1243, 1374 / 1390, of 36 points (500) 1331 / 1849.
+bool gather_serves(const xs_plan* p, const CondDev& cd) {
+  const ModelDev& d = p->md;
+  const bool lorentz = base_profile(p->model.profile) == XS_LORENTZ;
+  if (p->model.precision == XS_FP64 && !lorentz) return false;
+  const double mid = std::fabs(d.nu0 + 0.5 * (double)(d.n_bins - 1) * d.dnu);
+  const double core = lorentz ? 0.0 : 8.08 * cd.dop / std::sqrt(kLN2) * mid / d.dnu;
+  return cd.cut / d.dnu > 350.0 + 18.0 * core;
+}
+
 void derive(xs_plan* p) {
   const xs_model& m = p->model;
   ModelDev& d = p->md;
@@ -279,6 +299,7 @@ void derive(xs_plan* p) {
   p->cut_class.clear();
   p->cut_mult.clear();
   p->far_lmax = -1;
+  p->some_gather = false;
   double maxcut = 0.0;
   for (const xs_condition& c : p->conds) {
     SlotDev s;
@@ -340,7 +361,7 @@ void derive(xs_plan* p) {
       p->cut_mult[cc] += 1;
     }
     cd.cclass = cc;
-    cd.pad = 0;
+    cd.gather = 0;
     cd.far = far_condition(p, cd);
     if (cd.far.on) {
       p->far_end = p->far_lmax < 0 ? cd.far.end : std::min(p->far_end, cd.far.end);
@@ -353,7 +374,11 @@ void derive(xs_plan* p) {
   } else {
     // (a kept line's home bin is at most a cut-off and a point beyond the grid)
     d.fine_v = far_virtual(d.fine_sh, p->far_lmax, (int64_t)(maxcut / d.dnu) + 2);
-    for (CondDev& cd : p->cdev) cd.far.v = d.fine_v;
+    for (CondDev& cd : p->cdev) {
+      cd.far.v = d.fine_v;
+      cd.gather = !cd.far.on && gather_serves(p, cd);
+      p->some_gather |= cd.gather != 0;
+    }
   }
   d.n_slots = (int32_t)p->sdev.size();
   d.n_cut_classes = (int32_t)p->cut_class.size();
@@ -537,8 +562,12 @@ int profile_pass(xs_plan* p, double* sigma, int accumulate) {
   else if (use_near(p)) {
     launch_near(p->md, kernel_work(p), sigma, accumulate, p->last_lines_in, p->stream);
   } else if (!use_far(p)) {
-    launch_gather(p->md, kernel_work(p), p->tiling, sigma, accumulate, p->stream);
+    launch_gather(p->md, kernel_work(p), p->tiling, sigma, accumulate, false, p->stream);
   } else {
+    if (p->some_gather) {
+      launch_gather(p->md, kernel_work(p), p->tiling, sigma, accumulate, true, p->stream);
+      launch_reset_queue(p->w, p->stream);
+    }
     launch_near(p->md, kernel_work(p), sigma, accumulate, p->last_lines_in, p->stream);
     launch_far(p->md, kernel_work(p), p->far_lmax, p->far_end, p->last_lines_in, sigma, p->stream);
   }
