@@ -661,9 +661,21 @@ __global__ __launch_bounds__(256) void k_records(ModelDev m, const SlotDev* slot
   bool odd = false;
   for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p <= n; p += (int64_t)gridDim.x * 256) {
     {
-      const int k = (p < n) ? skeys[p] : fine_keys(m) + 1;
+      const int k = min((p < n) ? skeys[p] : fine_keys(m) + 1, fine_keys(m));
       const int kp = (p > 0) ? skeys[p - 1] : -1;
-      for (int b = kp + 1; b <= k && b <= fine_keys(m); ++b) off[b] = (int32_t)p;
+      // empty cells, those beyond the grid's ends above all: many at a time are the wave's (one
+      // lane's stores of 200 in turn took 4 us)
+      constexpr int kFew = 8;
+      const unsigned long long here = __ballot(1);
+      const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(here >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)here, 0u));
+      for (unsigned long long many = __ballot(k - kp > kFew); many; many &= many - 1) {
+        const int s = __builtin_ctzll(many);
+        const int lo = __builtin_amdgcn_readlane(kp, s) + 1, hi = __builtin_amdgcn_readlane(k, s);
+        const int at = __builtin_amdgcn_readlane((int)p, s);
+        for (int b = lo + rank; b <= hi; b += __popcll(here)) off[b] = at;
+      }
+      if (k - kp <= kFew)
+        for (int b = kp + 1; b <= k; ++b) off[b] = (int32_t)p;
     }
     if (p >= nk) continue;
     const int32_t i = svals[p];
