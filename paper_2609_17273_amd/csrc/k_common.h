@@ -208,6 +208,25 @@ __device__ __forceinline__ double intensity_log(const Intensity& o, const SlotFa
   return (log(fabs(o.m)) - kLN2 * (o.th + o.tl)) - q.lnQ + sc;
 }
 
+// Puts the records of the odd lines back (OddLines), by one block.
+__device__ __forceinline__ void odd_restore(const ModelDev& m, const OddLines& o, int32_t* counter, float* rgref,
+                                            float* rnexp, void* rS, int64_t max_lines) {
+  if (!o.pos || !counter[kOddHidden]) return;
+  const int n = counter[kOddCount];
+  for (int j = threadIdx.x; j < n; j += blockDim.x) {
+    const int32_t p = o.pos[j];
+    rgref[p] = o.gref[j];
+    rnexp[p] = o.nexp[j];
+    for (int q = 0; q < m.n_slots; ++q) {
+      const double S = o.S[(int64_t)j * m.n_slots + q];
+      if (m.prec == XS_FP32) ((float*)rS)[(int64_t)q * max_lines + p] = (float)S;
+      else ((double*)rS)[(int64_t)q * max_lines + p] = S;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) counter[kOddHidden] = 0;
+}
+
 // Order-preserving map of doubles to unsigned keys (for an atomic max).
 __device__ __forceinline__ unsigned long long dbl_key(double v) {
   unsigned long long b = (unsigned long long)__double_as_longlong(v);

@@ -331,9 +331,10 @@ __device__ __forceinline__ FarLine<Real> far_line(const FarArgs& g, const CondDe
       L.c0 = PROF == XS_VOIGT ? S * inv * (1.0 / sqrt(kPI)) : S * (1.0 / (sqrt(kPI) * m.dnu));
     }
   }
-  if (!L.live) {
+  if (!L.live) {  // (no width makes a Lorentzian's x infinite)
     L.c0 = 0;
     L.y = 0;
+    if constexpr (PROF == XS_LORENTZ || PROF == XS_BIN_LORENTZ) inv = 1;
   }
   L.a = (Real)m.dnu * inv;
   L.xc = fma((Real)(ts - kc) + mid, L.a, -(del * inv));

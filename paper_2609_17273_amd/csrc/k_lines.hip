@@ -290,9 +290,11 @@ __global__ __launch_bounds__(256) void k_lines_pass1(ModelDev m, const SlotDev* 
         kk = (int32_t)(fk < 0 ? 0 : fk < fine_keys(m) - 1 ? fk : fine_keys(m) - 1);
         const float gref = ln.gref ? ln.gref[i] : (float)ln.gref_scalar;
         const float nexp = ln.nexp ? ln.nexp[i] : (float)ln.nexp_scalar;
-        gmax = fmaxf(gmax, fabsf(gref));
-        nlo = fminf(nlo, nexp);
-        nhi = fmaxf(nhi, nexp);
+        if (isfinite(gref) && isfinite(nexp)) {  // (others: OddLines)
+          gmax = fmaxf(gmax, fabsf(gref));
+          nlo = fminf(nlo, nexp);
+          nhi = fmaxf(nhi, nexp);
+        }
         put_pack((typename PackOf<LTE>::type*)lpack + i, f, nu, gref, nexp);
       }
       tot.pairs += window_pairs(m, cutc, cutm, nu, a, b);
@@ -650,7 +652,7 @@ __global__ __launch_bounds__(256) void k_records(ModelDev m, const SlotDev* slot
                                                  const unsigned long long* stats, int32_t* off, int far,
                                                  int64_t max_lines, double* rnu, float* rgref,
                                                  float* rnexp, double* rgpre, int32_t* ridx, double* rEs,
-                                                 void* rS,
+                                                 void* rS, int32_t* oddl,
                                                  const double* cut_class, int32_t* rkc, float* rdel,
                                                  int32_t* rwin, int32_t* counter) {
   __shared__ SlotFac sf[kMaxCond];
@@ -658,7 +660,6 @@ __global__ __launch_bounds__(256) void k_records(ModelDev m, const SlotDev* slot
     sf[q] = slot_fac(slots[q], m.pop, Q[q], m.prec == XS_FP32 ? sb[q] : 0.0);
   __syncthreads();
   const int64_t n = ln.n, nk = (int64_t)stats[1];
-  bool odd = false;
   for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p <= n; p += (int64_t)gridDim.x * 256) {
     {
       const int k = min((p < n) ? skeys[p] : fine_keys(m) + 1, fine_keys(m));
@@ -684,10 +685,11 @@ __global__ __launch_bounds__(256) void k_records(ModelDev m, const SlotDev* slot
     rnu[p] = nu;
     rgref[p] = lp.gref;
     rnexp[p] = lp.nexp;
+    double gpre = 0.0;
     if (rgpre) {
       // natural width of a predissociating upper state: HWHM 1/(4 pi c tau)
       const double tau = st.tau[ln.up[i]];
-      rgpre[p] = (tau > 0.0 && tau < INFINITY) ? 1.0 / (4.0 * kPI * kC * tau) : 0.0;
+      rgpre[p] = gpre = (tau > 0.0 && tau < INFINITY) ? 1.0 / (4.0 * kPI * kC * tau) : 0.0;
     }
     ridx[p] = i;
     if (LTE) rEs[p] = lp.er;
@@ -705,18 +707,24 @@ __global__ __launch_bounds__(256) void k_records(ModelDev m, const SlotDev* slot
     }
     const LineFac f = pack_fac(lp);
     const double sc = ln.lscale ? (double)ln.lscale[i] : 0.0;
+    bool odd = false;
     for (int q = 0; q < m.n_slots; ++q) {
       const double S = intensity_value(intensity<LTE>(m.mode, m.pop, f, sf[q]), sf[q], sc);
       if (m.prec == XS_FP32)
         ((float*)rS)[(int64_t)q * max_lines + p] = (float)S;
       else
         ((double*)rS)[(int64_t)q * max_lines + p] = S;
-      if (far) odd |= !isfinite(S);
+      if (far) odd |= m.prec == XS_FP32 ? !isfinite((float)S) : !isfinite(S);
     }
-    if (far) odd |= !isfinite(lp.gref) || !isfinite(lp.nexp);
+    // (far: with tile expansions) lines that are not finite, in a list (OddLines; k_near puts it in order)
+    const bool lor = m.profile == XS_LORENTZ || m.profile == XS_BIN_LORENTZ;
+    if (far && (odd || !isfinite(lp.gref) || !isfinite(lp.nexp) || (lor && lp.gref == 0.0f && gpre == 0.0)) &&
+        __hip_atomic_load(counter + kOddCount, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= kOddMax) {
+      const int at = atomicAdd(counter + kOddCount, 1);
+      if (at < kOddMax) oddl[at] = (int32_t)p;
+      else counter[kFarOff] = 1;
+    }
   }
-  // (far: with tile expansions) an expansion would spread such a line's infinities into not-a-numbers
-  if (__ballot(odd) && (threadIdx.x & 63) == 0) counter[kFarOff] = 1;
 }
 
 void launch_offsets_records(const ModelDev& m, const Work& w, const StatesView& st,
@@ -725,7 +733,7 @@ void launch_offsets_records(const ModelDev& m, const Work& w, const StatesView& 
   if (blocks > 8192) blocks = 8192;
   hipLaunchKernelGGL((m.pop == XS_LTE ? k_records<true> : k_records<false>), dim3((unsigned)blocks), dim3(256), 0, s,
                      m, w.slot, w.Q, w.sb, st, ln, (const void*)w.lpack, skeys, svals, w.stats, w.off,
-                     w.far_rows != nullptr, w.max_lines, w.rnu, w.rgref, w.rnexp, w.rgpre, w.ridx, w.rEs, w.rS,
+                     w.far_rows != nullptr, w.max_lines, w.rnu, w.rgref, w.rnexp, w.rgpre, w.ridx, w.rEs, w.rS, w.odd.pos,
                      w.cut_class, w.rkc, w.rdel, w.rwin, w.counter);
 }
 

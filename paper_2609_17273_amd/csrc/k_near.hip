@@ -34,13 +34,14 @@ struct NearArgs {
   const double* sb;
   const int32_t* off;
   const double* rnu;
-  const float* rgref;
-  const float* rnexp;
+  float* rgref;
+  float* rnexp;
   const double* rgpre;
-  const void* rS;
+  void* rS;
   const int32_t* rkc;
   const float* rdel;
   const int32_t* rwin;
+  OddLines odd;             // (no positions: Gaussians)
   int64_t max_lines;
   int32_t* counter;         // [2..3] candidate total; [4..5] lines per part; [6] parts beyond the first
   int32_t* parts;           // [n_ct] parts of each (tile, condition), 0: the gather's
@@ -53,9 +54,10 @@ struct NearArgs {
   int32_t extra_blocks;     // the first blocks of k_near's grid, which take the parts beyond the first
 };
 
-// Lines of tile t: segments of sorted lines.
+// Lines of tile t: segments of sorted lines, then (all: with them) the odd ones, which
+// have no intensity in the segments.
 struct NearSegs {
-  int64_t beg[kSegs], cum[kSegs];
+  int64_t beg[kSegs], cum[kSegs], all;
 };
 __device__ __forceinline__ NearSegs near_segments(const NearArgs& g, const CondDev& cd, int t) {
   const int sh = g.m.fine_sh;
@@ -80,12 +82,13 @@ __device__ __forceinline__ NearSegs near_segments(const NearArgs& g, const CondD
     total += p1 - p0;
     r.cum[k] = total;
   }
+  r.all = total + (g.odd.pos && !g.counter[kFarOff] ? g.counter[kOddCount] : 0);
   return r;
 }
 
 // The lines of a tile, or -1 where the condition's points are the gather's.
 __device__ __forceinline__ int64_t near_lines(const NearArgs& g, int c, int t) {
-  return g.cond[c].gather ? -1 : near_segments(g, g.cond[c], t).cum[kSegs - 1];
+  return g.cond[c].gather ? -1 : near_segments(g, g.cond[c], t).all;
 }
 
 // Planning: candidates in all, then the parts of each tile.  A part holds at
@@ -111,6 +114,39 @@ __global__ __launch_bounds__(256) void k_near_count(NearArgs g) {
   if ((threadIdx.x & 63) == 0 && local) atomicAdd((unsigned long long*)(g.counter + 2), local);
 }
 
+// Odd lines (OddLines), by one block: the list, filled in any order, is sorted, and
+// their records get no intensity and a width of one.
+__device__ __forceinline__ void near_hide_odd(const NearArgs& g) {
+  __shared__ int32_t pos[kOddMax];
+  const int n = g.odd.pos ? g.counter[kOddCount] : 0;
+  if (n == 0 || g.counter[kOddHidden] || g.counter[kFarOff]) return;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) pos[i] = g.odd.pos[i];
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const int32_t p = pos[i];
+    int j = 0;
+    for (int k = 0; k < n; ++k) j += pos[k] < p;
+    g.odd.pos[j] = p;
+    g.odd.gref[j] = g.rgref[p];
+    g.odd.nexp[j] = g.rnexp[p];
+    g.rgref[p] = 1.0f;
+    g.rnexp[p] = 0.0f;
+    for (int q = 0; q < g.m.n_slots; ++q) {
+      const int64_t at = (int64_t)q * g.max_lines + p;
+      double& S = g.odd.S[(int64_t)j * g.m.n_slots + q];
+      if (g.m.prec == XS_FP32) {
+        S = ((const float*)g.rS)[at];
+        ((float*)g.rS)[at] = 0.0f;
+      } else {
+        S = ((const double*)g.rS)[at];
+        ((double*)g.rS)[at] = 0.0;
+      }
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) g.counter[kOddHidden] = 1;
+}
+
 __device__ __forceinline__ void near_plan_tiles(const NearArgs& g, int64_t total, int64_t first, int64_t step) {
   int64_t chunk = (total + kNearExtra - 1) / kNearExtra;
   chunk = max(kNearChunk, (chunk + 63) / 64 * 64);
@@ -133,6 +169,7 @@ __device__ __forceinline__ void near_plan_tiles(const NearArgs& g, int64_t total
 }
 
 __global__ __launch_bounds__(256) void k_near_plan(NearArgs g) {
+  if (blockIdx.x == 0) near_hide_odd(g);
   near_plan_tiles(g, (int64_t) * (const unsigned long long*)(g.counter + 2), (int64_t)blockIdx.x * 256 + threadIdx.x,
                   (int64_t)gridDim.x * 256);
 }
@@ -142,6 +179,7 @@ __global__ __launch_bounds__(256) void k_near_plan(NearArgs g) {
 constexpr int kNearOnce = 1024;
 __global__ __launch_bounds__(1024) void k_near_plan_once(NearArgs g) {
   __shared__ unsigned long long sum;
+  near_hide_odd(g);
   if (threadIdx.x == 0) sum = 0;
   __syncthreads();
   unsigned long long local = 0;
@@ -508,6 +546,7 @@ __device__ __forceinline__ void near_line_f64(const ModelDev& m, const CondDev& 
 
 template <typename Real, int PROF>
 __global__ __launch_bounds__(256) void k_near(NearArgs g) {
+  constexpr bool GAUSS = base_profile(PROF) == XS_DOPPLER || base_profile(PROF) == XS_GAUSSIAN;
   __shared__ double rows[4][kNearRow];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -537,7 +576,7 @@ __global__ __launch_bounds__(256) void k_near(NearArgs g) {
     const int tlo = t * kNearBins, thi = (int)min<int64_t>((int64_t)tlo + kNearBins, m.n_bins) - 1;
     const int64_t chunk = *(const int64_t*)(g.counter + 4);
     const int64_t q0 = np > 1 ? part * chunk : 0;
-    const int64_t q1 = np > 1 ? min(sg.cum[kSegs - 1], q0 + chunk) : sg.cum[kSegs - 1];
+    const int64_t q1 = np > 1 ? min(sg.all, q0 + chunk) : sg.all;
 #pragma unroll
     for (int j = 0; j < kNearRow / 64; ++j) row[lane + 64 * j] = 0.0;
     __syncthreads();
@@ -549,12 +588,19 @@ __global__ __launch_bounds__(256) void k_near(NearArgs g) {
       const int64_t q = b0 + (tid >> ks);
       if (q < q1) {
         const bool near = q < sg.cum[0];
-        const int64_t p = q + (near ? sg.beg[0] : q < sg.cum[1] ? sg.beg[1] : sg.beg[2]);
+        int64_t p = q + (near ? sg.beg[0] : q < sg.cum[1] ? sg.beg[1] : sg.beg[2]);
+        if (!GAUSS && __builtin_expect(q >= sg.cum[kSegs - 1], 0)) p = g.odd.pos[q - sg.cum[kSegs - 1]];
         const int2 win = ((const int2*)g.rwin)[(int64_t)cd.cclass * g.max_lines + p];
         const int kc = g.rkc[p];
-        const Real S = ((const Real*)g.rS)[(int64_t)cd.slot * g.max_lines + p];
+        Real S = ((const Real*)g.rS)[(int64_t)cd.slot * g.max_lines + p];
         const double nu = g.rnu[p];
-        const float gref = g.rgref[p], nexp = g.rnexp[p];
+        float gref = g.rgref[p], nexp = g.rnexp[p];
+        if (!GAUSS && __builtin_expect(q >= sg.cum[kSegs - 1], 0)) {
+          const int64_t j = q - sg.cum[kSegs - 1];
+          S = (Real)g.odd.S[j * m.n_slots + cd.slot];
+          gref = g.odd.gref[j];
+          nexp = g.odd.nexp[j];
+        }
         const double gpre = g.rgpre ? g.rgpre[p] : 0.0;
         int klo = max(win.x, tlo), khi = min(win.y, thi);
         if (near) {
@@ -563,7 +609,7 @@ __global__ __launch_bounds__(256) void k_near(NearArgs g) {
           khi = min(khi, far_shl(f + gap + 1, m.fine_sh) - 1);
         }
         if (win.x <= win.y && klo <= khi && S != (Real)0) {
-          if constexpr (base_profile(PROF) == XS_DOPPLER || base_profile(PROF) == XS_GAUSSIAN)
+          if constexpr (GAUSS)
             near_gauss<Real, PROF>(m, cd, ln, kc, klo, khi, g.rdel[p], nu, S, row, tlo);
           else if constexpr (sizeof(Real) == 4)
             near_line_f32<PROF>(m, cd, ln, kc, klo, khi, g.rdel[p], (float)nu, S, gref, nexp, (float)gpre, row, tlo);
@@ -573,7 +619,7 @@ __global__ __launch_bounds__(256) void k_near(NearArgs g) {
       }
     }
     __syncthreads();
-    const int o = base_profile(PROF) == XS_DOPPLER || base_profile(PROF) == XS_GAUSSIAN ? tid : near_place(tid);
+    const int o = GAUSS ? tid : near_place(tid);
     const double v = ((rows[0][o] + rows[1][o]) + rows[2][o]) + rows[3][o];
     if (np == 1) {
       const int64_t k = (int64_t)tlo + tid;
@@ -626,6 +672,7 @@ void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate
   a.rkc = w.rkc;
   a.rdel = w.rdel;
   a.rwin = w.rwin;
+  a.odd = w.odd;
   a.max_lines = w.max_lines;
   a.counter = w.counter;
   a.parts = w.item_cnt;

@@ -1499,7 +1499,9 @@ __global__ __launch_bounds__(64, sizeof(Real) == 8 ? 3 : (PROF == XS_BIN_VOIGT ?
 }
 
 // Candidate count of every (tile, condition) and their total.
-__global__ __launch_bounds__(256) void k_items_count(GatherArgs g, int32_t* cnt) {
+__global__ __launch_bounds__(256) void k_items_count(GatherArgs g, int32_t* cnt, OddLines odd, float* rgref, float* rnexp,
+                                                     void* rS) {
+  if (blockIdx.x == 0) odd_restore(g.m, odd, g.counter, rgref, rnexp, rS, g.max_lines);
   unsigned long long local = 0;
   for (int64_t ct = (int64_t)blockIdx.x * 256 + threadIdx.x; ct < g.n_ct; ct += (int64_t)gridDim.x * 256) {
     const int c = (int)(ct % g.m.n_cond), t = (int)(ct / g.m.n_cond);
@@ -1602,7 +1604,8 @@ void launch_gather(const ModelDev& m, const Work& w, const Tiling& t, double* si
   // plan the work items
   launch_reset_queue(w, s);
   const int cb = (int)std::min<int64_t>(1024, (a.n_ct + 255) / 256);
-  hipLaunchKernelGGL(k_items_count, dim3(cb), dim3(256), 0, s, a, w.item_cnt);
+  hipLaunchKernelGGL(k_items_count, dim3(cb), dim3(256), 0, s, a, w.item_cnt, w.odd, w.rgref,
+                     w.rnexp, w.rS);
   hipLaunchKernelGGL(k_items_split, dim3(cb), dim3(256), 0, s, a, (const int32_t*)w.item_cnt,
                      w.item_base, w.part_base);
   launch_scan_i32(w.item_base, (int64_t)a.n_ct + 1, w.item_sums, s);

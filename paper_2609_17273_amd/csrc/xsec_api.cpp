@@ -447,8 +447,13 @@ size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool wit
     x.part = (double*)take(sizeof(double) * 2 * (size_t)x.item_target * 1024);
   }
   x.far_rows = x.cut_rows = nullptr;
+  x.odd = OddLines{};
   x.far_cond_rows = x.n_cut_rows = 0;
   if (with_far && far_capable(p)) {
+    x.odd.pos = (int32_t*)take(4 * kOddMax);
+    x.odd.gref = (float*)take(4 * kOddMax);
+    x.odd.nexp = (float*)take(4 * kOddMax);
+    x.odd.S = (double*)take(8 * (size_t)kOddMax * d.n_slots);
     x.far_cond_rows = far_rows_before((int32_t)cells, sh, far_levels_of_grid((int32_t)cells));
     x.far_rows = (double*)take(sizeof(double) * d.n_cond * (size_t)x.far_cond_rows * far_nodes(d.prec));
     if (adjoint_capable(p)) {

@@ -31,10 +31,12 @@ constexpr int kAdjBlocksMax = 32768;  // the most the configuration allows (size
 // Device counters (int32): [0] gather work queue, [2..3] candidate total,
 // [4..5] lines per item or part, [6] parts beyond
 // tiles' first, [kFarOff] set by the
-// record pass where a line's values are not finite, [kGammaMax..kNexpMax] largest
-// |gamma_ref|, smallest and largest n_exp of the kept lines (floats).
+// record pass where more than kOddMax lines have values that are not finite (they then all go
+// point by point), [kGammaMax..kNexpMax] largest
+// |gamma_ref|, smallest and largest n_exp of the kept lines (floats), [kOddCount] how many such lines,
+// [kOddHidden] whether their records are changed (OddLines).
 constexpr int kCounterInts = 64;
-constexpr int kFarOff = 9, kGammaMax = 10, kNexpMin = 11, kNexpMax = 12;
+constexpr int kFarOff = 9, kGammaMax = 10, kNexpMin = 11, kNexpMax = 12, kOddCount = 13, kOddHidden = 14;
 // Lines are sorted by home bin >> sh: 64 points per key (the smallest bucket
 // size), or the leaves of the tile expansions.
 constexpr int kFineSh = 6;
@@ -122,6 +124,18 @@ struct __attribute__((aligned(64))) LinePack {
   float gref, nexp;
 };
 
+// With tile expansions: the kept lines whose values may be other than finite (no finite
+// intensity in some slot, parameters of the width that are not, a Lorentzian of no width).
+// Expansions would spread them over whole tiles, moments over a cell's lines, so a pass with
+// expansions first gives their records no intensity and an ordinary width (saved here) and adds
+// them point by point itself (k_near.hip); whatever else reads the records puts them back first.
+constexpr int kOddMax = 1024;
+struct OddLines {
+  int32_t* pos;          // [kOddMax] sorted positions; null: a workspace without expansions
+  float *gref, *nexp;    // [kOddMax]
+  double* S;             // [kOddMax][n_slots]
+};
+
 // Workspace pointers (carved by the host runtime from the caller's buffer).
 struct Work {
   CondDev* cond;            // [n_cond]
@@ -164,6 +178,7 @@ struct Work {
   int64_t far_cond_rows;
   double* cut_rows;         // [n_cond][n_cut_rows][2][nodes] moments of the cotangent over parts of cut tiles
   int64_t n_cut_rows;
+  OddLines odd;
   unsigned long long* stats;// [8]
   double* own;              // [4][n_slots] Q, dQ, sb and smax of partition functions and stick spectra
   double* adjpart;          // [n_cond][2][2 kAdjBlocksMax]: the near and the far part's blocks
