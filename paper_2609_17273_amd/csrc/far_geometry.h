@@ -50,6 +50,7 @@ struct FarCond {
   int32_t gap_max;
   int32_t glev;    // level of the tiles that share a gap: lmax, and at least 256 points
   int32_t v;       // cells of lines beyond either end of the grid
+  int32_t span;    // cells between a wave's lines up to which the adjoint's far part pays
   int32_t mom;     // lowest level whose cells may take moments of the lines' Gaussians
   // gap of the tiles up to cell e: (gap0 + e gap1) / 2^32, at least one
   int64_t gap0, gap1;
@@ -190,6 +191,19 @@ XS_HD int32_t far_virtual(int sh, int lmax, int64_t Wx) {
   const int64_t n = (Wx >> sh) + 2;
   const int64_t v = ((n >> lmax) + 1) << lmax;
   return v >= kFarVirtual ? kFarVirtual : (int32_t)v;
+}
+// Adjoint: a wave's lines go through tiles together, every tile of any of them, so its
+// cost grows with the cells between its first and its last line; point by point it grows with
+// the window alone.  The most cells that pay, for windows of W points.  Measured, the whole
+// adjoint point by point / through tiles (Voigt, even lists, 2e5 points): FP32, window 1000, lines of a
+// wave over 2, 4, 8, 16 cells 477 / 348, 330 / 267, 220 / 251, 215 / 290 us; window 2500, 16, 32, 48 cells
+// 368 / 259, 381 / 328, 394 / 394; window 12500, 48 cells 1382 / 398; FP64 (cells of 64
+// points), window 1000, 1, 2, 4 cells 551 / 417, 328 / 303, 244 / 290; window 2500, 4, 7, on 2e6
+// points 8 cells 384 / 263, 353 / 286, 2604 / 1652.  A list of 3e5 lines in 100 cm^-1 and 100 over the other 19900,
+// whose last waves see every tile of the grid: 1.1 / 23.5 ms.
+XS_HD int32_t far_adj_span(int64_t W, bool f32) {
+  const int64_t n = W < 800 ? 0 : (W - 800) / (f32 ? 36 : 170);
+  return n > (1 << 30) ? 1 << 30 : (int32_t)n;
 }
 // Moments: one row per cell of every level, level after level; and the cells of
 // level `l` or less that make up the leaves [lo, hi], one after the other: the

@@ -1263,6 +1263,16 @@ __global__ __launch_bounds__(256, (adj_waves<R, PROF, FAR>())) void k_adjoint(Ad
         kc = a.rkc[p];
         f = kc >> cd.far.sh;
         split = f >= 1 - cd.far.v && f <= cd.far.n_fine - 2 + cd.far.v;
+      }
+      if (use_far) {
+        // lines much too far apart go point by point as a whole: twice the span that pays, since
+        // with some waves either way both parts last as long as their slowest waves (lists of an
+        // even 48 cells, window 2500: 394 us through tiles, 583 with the waves above 48 point by
+        // point; every lane votes; both parts see the same lines)
+        const int f0 = wave_min(split ? f : 0x7fffffff), f1 = wave_max(split ? f : -0x7fffffff);
+        if (f0 <= f1 && f1 - f0 > 2 * cd.far.span + 2) split = false;
+      }
+      if (use_far && on) {
         if (!FAR && split) {
           int32_t n0, n1;
           far_near(cd.far, f, n0, n1);

@@ -245,6 +245,7 @@ FarCond far_condition(const xs_plan* p, const CondDev& cd) {
   FarCond c = far_make(W - 2, W + 2, d.n_fine, d.fine_sh, g0, g1);
   // a kept line lies at most a cut-off beyond the grid; standard deviation alpha / sqrt(2 ln 2)
   const double nu_end = d.nu0 + (double)(d.n_bins - 1) * d.dnu + cd.cut;
+  c.span = far_adj_span(W, p->model.precision == XS_FP32);
   c.mom = far_sigma_level(d.fine_sh, nu_end * cd.dop / std::sqrt(2.0 * kLN2) / d.dnu,
                           p->model.precision == XS_FP32 ? kMomSigma32 : kMomSigma64);
   return c;
@@ -548,6 +549,17 @@ bool use_far(const xs_plan* p) {
              (p->model.precision == XS_FP32 ? kFarLines32 : kFarLines64) * ((p->grid.n_bins + 63) / 64);
 }
 
+// The adjoint through tiles: where they are used and, with the lines evenly over
+// the grid, waves would be within the span that pays (far_adj_span; the moments of the cotangent
+// alone cost 0.14 ms on 2e6 points).
+bool adjoint_far(const xs_plan* p) {
+  if (!use_far(p)) return false;
+  const double even = 64.0 * p->md.n_fine / (double)std::max<int64_t>(p->last_lines_in, 1);
+  for (const CondDev& cd : p->cdev)
+    if (cd.far.on && even <= cd.far.span + 1.0) return true;
+  return false;
+}
+
 // Gaussians go a line to a lane (k_near) over the points where they are not zero,
 // without expansions.  Measured, gather with its reduction and this: 1e4 lines on 1e6
 // points FP64 111 / 22 us; 1e6 lines on 2e6 points FP32 482 / 73, FP64 714 / 300, bin
@@ -787,7 +799,7 @@ int xs_profile_adjoint(xs_plan* p, const xs_states* st, const xs_lines* ln, cons
   if (!g || !dT || !dP || !dls) return fail(XS_EINVAL, "adjoint: dL_dsigma, dL_dT, dL_dP and dL_dlog_scale are required");
   if (ln->n != p->last_lines_in) return fail(XS_EINVAL, "adjoint: lines differ from the prepared ones");
   launch_adjoint(p->md, kernel_work(p), view(st), view(ln), g, dT, dP, dgref, dnexp, dls, ln->n,
-                 p->tiling.adj_blocks, use_far(p) ? p->far_lmax : -1, p->far_end, p->stream);
+                 p->tiling.adj_blocks, adjoint_far(p) ? p->far_lmax : -1, p->far_end, p->stream);
   return hip_check(hipGetLastError(), "adjoint launch");
 }
 
@@ -803,7 +815,7 @@ int xs_cross_section_adjoint(xs_plan* p, const xs_states* st, const xs_lines* ln
   if (!g || !dT || !dP || !dls) return fail(XS_EINVAL, "adjoint: dL_dsigma, dL_dT, dL_dP and dL_dlog_scale are required");
   if ((rc = preprocess(p, st, ln))) return rc;
   launch_adjoint(p->md, kernel_work(p), view(st), view(ln), g, dT, dP, dgref, dnexp, dls, ln->n,
-                 p->tiling.adj_blocks, use_far(p) ? p->far_lmax : -1, p->far_end, p->stream);
+                 p->tiling.adj_blocks, adjoint_far(p) ? p->far_lmax : -1, p->far_end, p->stream);
   return hip_check(hipGetLastError(), "adjoint launch");
 }
 
@@ -1112,7 +1124,7 @@ int xs_plan_autotune(xs_plan* p, const xs_states* st, const xs_lines* ln, double
       float ms_best;
       time3([&]() {
         launch_adjoint(p->md, kernel_work(p), view(st), view(ln), sigma, dTP, dTP + p->conds.size(), outs,
-                       outs + ln->n, outs + 2 * ln->n, ln->n, cand[ci], use_far(p) ? p->far_lmax : -1, p->far_end, p->stream);
+                       outs + ln->n, outs + 2 * ln->n, ln->n, cand[ci], adjoint_far(p) ? p->far_lmax : -1, p->far_end, p->stream);
         return hip_check(hipGetLastError(), "adjoint launch");
       }, ms_best);
       if (!rc && ms_best < adj_best) {
