@@ -845,7 +845,7 @@ __global__ __launch_bounds__(256) void k_adj_moments(AdjArgs a, int lmax) {
   const FarCond& fc = a.cond[c].far;
   if (!fc.on || a.counter[kOddCount]) return;
   // the wave's level: the widest tiles first
-  int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  int w = __builtin_amdgcn_readfirstlane((int)(long_block() * 4 + (threadIdx.x >> 6)));
   int l = min(lmax, fc.lmax);
   for (; l >= 0; --l) {
     const int n = far_wide(fc.sh, l) > 0 ? far_tiles(m.n_fine, l) : (int)((m.n_bins + 63) / 64);
@@ -1487,7 +1487,7 @@ void launch_adjoint(const ModelDev& m, const Work& w, const StatesView& st, cons
     int64_t waves = 0;
     for (int l = 0; l <= far_lmax; ++l)
       waves += far_wide(m.fine_sh, l) > 0 ? far_tiles(m.n_fine, l) : (m.n_bins + 63) / 64;
-    const dim3 mg((unsigned)((waves + 3) / 4), m.n_cond), cg((unsigned)far_tiles(m.n_fine, end_min), m.n_cond);
+    const dim3 mg = long_grid((waves + 3) / 4, m.n_cond), cg((unsigned)far_tiles(m.n_fine, end_min), m.n_cond);
     if (m.prec == XS_FP32) {
       hipLaunchKernelGGL((k_adj_moments<float, 12>), mg, dim3(256), 0, s, a, far_lmax);
       hipLaunchKernelGGL((k_adj_cut<float, 6>), cg, dim3(64), 0, s, a);

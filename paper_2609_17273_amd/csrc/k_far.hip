@@ -444,7 +444,7 @@ __global__ __launch_bounds__(256, sizeof(Real) == 4 ? 4 : 2) void k_far_leaves(F
   const int lm = far_cond_mom_level(g, cd);
   if (lm > fc.lmax) return;
   const ModelDev& m = g.m;
-  const int nk = fine_keys(m), key = blockIdx.x * 4 + wave, f = key - m.fine_v;
+  const int nk = fine_keys(m), key = long_block() * 4 + wave, f = key - m.fine_v;
   if (key >= nk) return;
   // in cells of the first level that uses them, so that the powers stay small
   const double hp = (double)(1 << (fc.sh + lm)), ih = 1.0 / hp;
@@ -822,7 +822,7 @@ __global__ __launch_bounds__(256) void k_far_finish(FarArgs g) {
   // FP64 rows in both forms: FP32 adds to LDS are several times slower
   __shared__ double row[2][PE * kFarEndBins];
   __shared__ double tot[2][kFarEndBins / 16][PE];
-  const int tid = threadIdx.x, lane = tid & 63, c = blockIdx.y, t = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, c = blockIdx.y, t = long_block();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const CondDev& cd = g.cond[c];
   const FarCond& fc = cd.far;
@@ -1003,12 +1003,12 @@ void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, int
                     n_lines >= kMomLines * (int64_t)m.n_fine;
   a.mom = many && fit > 0 && !w.rgpre ? w.part : nullptr;
   const int at_once = a.mom ? (int)std::min<int64_t>(fit, m.n_cond) : m.n_cond;
-  const dim3 fin((unsigned)far_tiles(m.n_fine, end_min), m.n_cond);
+  const dim3 fin = long_grid(far_tiles(m.n_fine, end_min), m.n_cond);
   const int per_block = 4 * (64 / far_nodes(m.prec));  // tiles of a block of k_far_cells
   auto run = [&](auto leaves, auto moments, auto cells, auto far, auto finish) {
     for (a.c0 = 0; a.c0 < m.n_cond; a.c0 += at_once) {
       const int nc = std::min(at_once, m.n_cond - a.c0);
-      const auto go = [&](auto k, int64_t bl) { hipLaunchKernelGGL(k, dim3((unsigned)bl, nc), dim3(256), 0, s, a); };
+      const auto go = [&](auto k, int64_t bl) { hipLaunchKernelGGL(k, long_grid(bl, nc), dim3(256), 0, s, a); };
       if (a.mom) {
         go(leaves, (fine_keys(m) + 3) / 4);
         for (int b = 0; b < far_lmax; b += kMomLevels)
@@ -1017,7 +1017,7 @@ void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, int
         go(cells, (far_cells_before(m.n_fine, far_lmax + 1) + per_block - 1) / per_block);
       }
       // (with moments most conditions have nothing left for it)
-      go(far, a.mom ? std::min<int64_t>(blocks, 4096) : blocks);
+      go(far, std::min<int64_t>(blocks, a.mom ? 4096 : 1 << 22));
     }
     hipLaunchKernelGGL(finish, fin, dim3(256), 0, s, a);
   };

@@ -554,9 +554,10 @@ __global__ __launch_bounds__(256) void k_near(NearArgs g) {
   double* row = rows[wave];
   // the grid's first blocks take the parts beyond tiles' first, the others one
   // tile each
-  const bool extras = (int)blockIdx.x < g.extra_blocks;
-  const int items = extras ? g.counter[6] : (int)gridDim.x;
-  for (int item = blockIdx.x; item < items; item += extras ? g.extra_blocks : (int)gridDim.x) {
+  const int block = long_block();
+  const bool extras = block < g.extra_blocks;
+  const int items = extras ? g.counter[6] : min(block + 1, g.n_ct + g.extra_blocks);
+  for (int item = block; item < items; item += extras ? g.extra_blocks : 1) {
     int ct = item - g.extra_blocks, part = 0;
     if (extras) {
       ct = g.extra[2 * item];
@@ -691,7 +692,7 @@ void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate
   }
   // about as many as there are parts (a line meets a tile or two); fewer take turns
   a.extra_blocks = (int)std::min<int64_t>(kNearExtra, 8 + n_lines * m.n_cond / kNearChunk);
-  const dim3 grid((unsigned)(a.n_ct + a.extra_blocks));
+  const dim3 grid = long_grid((int64_t)a.n_ct + a.extra_blocks);
 #define XS_N(PR)                                                                                        \
   if (m.profile == PR && m.prec == XS_FP32) hipLaunchKernelGGL((k_near<float, PR>), grid, dim3(256), 0, s, a); \
   else if (m.profile == PR) hipLaunchKernelGGL((k_near<double, PR>), grid, dim3(256), 0, s, a);

@@ -196,6 +196,16 @@ struct Tiling {
   int32_t adj_blocks;  // persistent blocks of the adjoint
 };
 
+// Grids of many blocks: HIP takes less than 2^32 threads along x, so beyond 2^22 blocks
+// the rest goes along z (up to 255 too many blocks, which find no work).
+inline dim3 long_grid(int64_t blocks, int y = 1) {
+  const int64_t x = blocks < 1 ? 1 : blocks < (1 << 22) ? blocks : (1 << 22);
+  return dim3((unsigned)x, (unsigned)y, (unsigned)((blocks + x - 1) / x < 1 ? 1 : (blocks + x - 1) / x));
+}
+#ifdef __HIPCC__
+__device__ __forceinline__ int long_block() { return (int)(blockIdx.z * gridDim.x + blockIdx.x); }
+#endif
+
 // ---- launch wrappers (k_lines.hip) ----
 // clear > 0: also clears the first `clear` counters and the statistics, and packs
 // the states for the line passes (kCounterInts: a preparation; kFarOff: a stick
