@@ -134,9 +134,10 @@ struct AdjArgs {
   int32_t far;    // take the windows' far tiles through their moments
   const int32_t* counter;
   const int32_t* rkc;
-  const void* mom;    // [n_cond][far_cond_rows][P] moments of every tile
+  int32_t c0, c1;     // conditions of the launch
+  const void* mom;    // [c1 - c0][cond_rows][P] moments of every tile
   int64_t cond_rows;
-  const void* cut;    // [n_cond][cut_rows][2][PE] moments of the parts of cut tiles
+  const void* cut;    // [c1 - c0][cut_rows][2][PE] moments of the parts of cut tiles
   int64_t cut_rows;   // groups of kCutGroup points
 };
 
@@ -841,7 +842,7 @@ __device__ __forceinline__ double adj_scale(const unsigned long long* gmax, int 
 template <typename R, int P>
 __global__ __launch_bounds__(256) void k_adj_moments(AdjArgs a, int lmax) {
   const ModelDev& m = a.m;
-  const int c = blockIdx.y, lane = threadIdx.x & 63;
+  const int c = a.c0 + blockIdx.y, lane = threadIdx.x & 63;
   const FarCond& fc = a.cond[c].far;
   if (!fc.on || a.counter[kOddCount]) return;
   // the wave's level: the widest tiles first
@@ -881,7 +882,7 @@ __global__ __launch_bounds__(256) void k_adj_moments(AdjArgs a, int lmax) {
     for (int k = 0; k < P; ++k) v = fma(D[q * P + k], acc[k], v);
     int64_t row = t;
     for (int k = 0; k < l; ++k) row += far_tiles(m.n_fine, k);
-    ((R*)a.mom)[((int64_t)c * a.cond_rows + row) * P + q] = (R)v;
+    ((R*)a.mom)[((int64_t)blockIdx.y * a.cond_rows + row) * P + q] = (R)v;
   }
 }
 
@@ -893,7 +894,7 @@ __global__ __launch_bounds__(64) void k_adj_cut(AdjArgs a) {
   constexpr int kGroups = kFarEndBins / kCutGroup;
   __shared__ double tau[kGroups][PE], node[kGroups][PE];
   const ModelDev& m = a.m;
-  const int c = blockIdx.y, lane = threadIdx.x, t = blockIdx.x;
+  const int c = a.c0 + blockIdx.y, lane = threadIdx.x, t = blockIdx.x;
   const FarCond& fc = a.cond[c].far;
   if (!fc.on || a.counter[kOddCount] || t >= far_tiles(m.n_fine, fc.end)) return;
   const int n = 1 << (fc.end + fc.sh), ng = n / kCutGroup;
@@ -932,7 +933,7 @@ __global__ __launch_bounds__(64) void k_adj_cut(AdjArgs a) {
     for (int h = 0; h < ng; ++h) {
       const int j = side == 0 ? h : ng - 1 - h;
       const int64_t row = (int64_t)t * ng + j;
-      if (row < a.cut_rows) ((R*)a.cut)[(((int64_t)c * a.cut_rows + row) * 2 + side) * PE + q] = (R)run;
+      if (row < a.cut_rows) ((R*)a.cut)[(((int64_t)blockIdx.y * a.cut_rows + row) * 2 + side) * PE + q] = (R)run;
       run += node[j][q];
     }
   }
@@ -1156,7 +1157,7 @@ __device__ __forceinline__ Sums3 far_window_sums(const AdjArgs& a, const CondDev
       const R xc = xat((R)(ts - L.kc) + (half - (R)0.5)), ah = half * L.a;
       int64_t row = tt;
       for (int k = 0; k < tl; ++k) row += far_tiles(m.n_fine, k);
-      const R* mu = (const R*)a.mom + ((int64_t)c * a.cond_rows + row) * P;
+      const R* mu = (const R*)a.mom + ((int64_t)(c - a.c0) * a.cond_rows + row) * P;
       if (sizeof(R) == 4 && ++since > kFlush / P) {
         far_flush<R, PROF>(L, F);
         since = 1;
@@ -1193,7 +1194,7 @@ __device__ __forceinline__ Sums3 far_window_sums(const AdjArgs& a, const CondDev
       const int j = mine ? (ke - ts) / kCutGroup : 0;
       const double rho = rho_of(ts, n);
       const R xc = xat((R)(ts - L.kc) + (half - (R)0.5)), ah = half * L.a;
-      const R* mu = (const R*)a.cut + (((int64_t)c * a.cut_rows + (int64_t)t * (n / kCutGroup) + j) * 2 + side) * PE;
+      const R* mu = (const R*)a.cut + (((int64_t)(c - a.c0) * a.cut_rows + (int64_t)t * (n / kCutGroup) + j) * 2 + side) * PE;
       far_terms<R, PROF, PE>(
           L, F, mine, wide_any, rho, [&](int q) -> R { return fma(far_x<R, PE>()[q], ah, xc); },
           [&](int q) { return mine ? mu[q] : (R)0; });
@@ -1257,13 +1258,13 @@ __global__ __launch_bounds__(256, (adj_waves<R, PROF, FAR>())) void k_adjoint(Ad
       nexp = (double)a.rnexp[p];
       gpre = a.rgpre ? a.rgpre[p] : 0.0;
       Es = a.rEs[p];
-      if (!FAR && far_on) {
+      if (far_on && (!FAR || a.c0 > 0)) {
         dls = a.fline[p];
         dgr = a.fline[a.max_lines + p];
         dne = a.fline[2 * a.max_lines + p];
       }
     }
-    for (int c = 0; c < m.n_cond; ++c) {
+    for (int c = FAR ? a.c0 : 0; c < (FAR ? a.c1 : m.n_cond); ++c) {
       const CondDev& cd = a.cond[c];
       const bool use_far = far_on && cd.far.on;
       if (FAR && !use_far) continue;
@@ -1386,7 +1387,7 @@ __global__ __launch_bounds__(256, (adj_waves<R, PROF, FAR>())) void k_adjoint(Ad
     }
   }
   __syncthreads();
-  for (int c = threadIdx.x; c < m.n_cond; c += 256) {
+  for (int c = (FAR ? a.c0 : 0) + threadIdx.x; c < (FAR ? a.c1 : m.n_cond); c += 256) {
     const double t = ((sdt[0][c] + sdt[1][c]) + sdt[2][c]) + sdt[3][c];
     const double q = ((sdp[0][c] + sdp[1][c]) + sdp[2][c]) + sdp[3][c];
     const int64_t at = a.part0 + blockIdx.x;
@@ -1446,6 +1447,13 @@ __global__ __launch_bounds__(256) void k_gmax(const double* g, int64_t n_bins, u
   if ((threadIdx.x & 63) == 0 && v) atomicMax(gmax + c, v);
 }
 
+// Rows of the moments of cut tiles' parts: of whole tiles, whose last may pass the
+// grid's end.
+static int64_t adj_cut_rows(const ModelDev& m) { return (m.n_bins + kFarEndBins) / kCutRowBins; }
+int64_t adj_far_doubles(const ModelDev& m, int64_t rows) {
+  return m.prec == XS_FP32 ? (12 * rows + 12 * adj_cut_rows(m) + 1) / 2 : 20 * rows + 24 * adj_cut_rows(m);
+}
+
 void launch_adjoint(const ModelDev& m, const Work& w, const StatesView& st, const LinesView& ln,
                     const double* g, double* dT, double* dP, double* dgref, double* dnexp,
                     double* dls, int64_t n_lines, int adj_blocks, int far_lmax, int end_min, hipStream_t s) {
@@ -1479,33 +1487,37 @@ void launch_adjoint(const ModelDev& m, const Work& w, const StatesView& st, cons
   a.far = far_lmax >= 0;
   a.counter = w.counter;
   a.rkc = w.rkc;
-  a.mom = w.far_rows;
-  a.cond_rows = w.far_cond_rows;
-  a.cut = w.cut_rows;
-  a.cut_rows = w.n_cut_rows;
-  if (a.far) {
-    int64_t waves = 0;
-    for (int l = 0; l <= far_lmax; ++l)
-      waves += far_wide(m.fine_sh, l) > 0 ? far_tiles(m.n_fine, l) : (m.n_bins + 63) / 64;
-    const dim3 mg = long_grid((waves + 3) / 4, m.n_cond), cg((unsigned)far_tiles(m.n_fine, end_min), m.n_cond);
-    if (m.prec == XS_FP32) {
-      hipLaunchKernelGGL((k_adj_moments<float, 12>), mg, dim3(256), 0, s, a, far_lmax);
-      hipLaunchKernelGGL((k_adj_cut<float, 6>), cg, dim3(64), 0, s, a);
-    } else {
-      hipLaunchKernelGGL((k_adj_moments<double, 20>), mg, dim3(256), 0, s, a, far_lmax);
-      hipLaunchKernelGGL((k_adj_cut<double, 12>), cg, dim3(64), 0, s, a);
-    }
-  }
   a.fline = (double*)w.lpack;  // free after the record pass: 64 bytes per line
   a.n_part = a.far ? 2 * adj_blocks : adj_blocks;
 #define XS_A(R, P, F) \
   if (m.profile == P) hipLaunchKernelGGL((k_adjoint<R, P, F>), dim3(adj_blocks), dim3(256), 0, s, a);
+  // the far part, for as many conditions at a time as their moments fit
   if (a.far) {
     a.part0 = adj_blocks;
-    if (m.prec == XS_FP32) {
-      XS_A(float, XS_LORENTZ, true) XS_A(float, XS_VOIGT, true)
-    } else {
-      XS_A(double, XS_LORENTZ, true) XS_A(double, XS_VOIGT, true)
+    a.cond_rows = far_cells_before(m.n_fine, far_lmax + 1);
+    a.cut_rows = adj_cut_rows(m);
+    const int64_t one = adj_far_doubles(m, a.cond_rows);
+    const int at_once = w.far_extra ? 1 : (int)std::min<int64_t>((part_doubles(w) - kAdjTail) / one, m.n_cond);
+    double* const space = w.far_extra ? w.far_extra : w.part;
+    a.mom = space;
+    int64_t waves = 0;
+    for (int l = 0; l <= far_lmax; ++l)
+      waves += far_wide(m.fine_sh, l) > 0 ? far_tiles(m.n_fine, l) : (m.n_bins + 63) / 64;
+    for (a.c0 = 0; a.c0 < m.n_cond; a.c0 = a.c1) {
+      a.c1 = std::min(a.c0 + at_once, m.n_cond);
+      const int nc = a.c1 - a.c0;
+      const dim3 mg = long_grid((waves + 3) / 4, nc), cg((unsigned)far_tiles(m.n_fine, end_min), nc);
+      if (m.prec == XS_FP32) {
+        a.cut = (float*)space + nc * a.cond_rows * 12;
+        hipLaunchKernelGGL((k_adj_moments<float, 12>), mg, dim3(256), 0, s, a, far_lmax);
+        hipLaunchKernelGGL((k_adj_cut<float, 6>), cg, dim3(64), 0, s, a);
+        XS_A(float, XS_LORENTZ, true) XS_A(float, XS_VOIGT, true)
+      } else {
+        a.cut = space + nc * a.cond_rows * 20;
+        hipLaunchKernelGGL((k_adj_moments<double, 20>), mg, dim3(256), 0, s, a, far_lmax);
+        hipLaunchKernelGGL((k_adj_cut<double, 12>), cg, dim3(64), 0, s, a);
+        XS_A(double, XS_LORENTZ, true) XS_A(double, XS_VOIGT, true)
+      }
     }
   }
   a.part0 = 0;

@@ -46,12 +46,12 @@ struct FarArgs {
   const int32_t* rwin;
   int64_t max_lines;
   const int32_t* counter;
-  double* rows;       // [n_cond][rows_per_cond][P]
+  double* rows;       // [conditions of the launch][cond_rows][P]
   int64_t cond_rows;  // rows per condition
   double* sigma;
   double* mom;        // [conditions of the launch][mom_cells][PM] moments, or null
   int64_t mom_cells;  // cells of all levels, those beyond the grid with them
-  int32_t c0;         // first condition of the launch (not k_far_finish)
+  int32_t c0;         // first condition of the launch
   int32_t blocks;     // of k_far's levels
 };
 
@@ -657,7 +657,7 @@ __global__ __launch_bounds__(256) void k_far_cells(FarArgs g) {
 #pragma unroll
     for (int i = 0; i < P; ++i) o = fma(D[i * P + q], sv[wave][gi * P + i], o);
     const int64_t row = far_rows_before(nf, fc.sh, l) + (int64_t)t * far_slices(fc.sh, l);
-    g.rows[((int64_t)(g.c0 + blockIdx.y) * g.cond_rows + row) * P + q] = o;
+    g.rows[((int64_t)blockIdx.y * g.cond_rows + row) * P + q] = o;
   }
 }
 
@@ -768,7 +768,7 @@ __global__ __launch_bounds__(256, sizeof(Real) == 4 ? 4 : 3) void k_far(FarArgs 
 #pragma unroll
         for (int q = 0; q < P; ++q) v = fma(D[q * P + k], st[tg][q], v);
         const int64_t row = far_rows_before(nf, fc.sh, l) + (int64_t)tt * sl + slice;
-        g.rows[((int64_t)c * g.cond_rows + row) * P + k] = v;
+        g.rows[((int64_t)blockIdx.y * g.cond_rows + row) * P + k] = v;
       }
     }
     __syncthreads();
@@ -822,7 +822,7 @@ __global__ __launch_bounds__(256) void k_far_finish(FarArgs g) {
   // FP64 rows in both forms: FP32 adds to LDS are several times slower
   __shared__ double row[2][PE * kFarEndBins];
   __shared__ double tot[2][kFarEndBins / 16][PE];
-  const int tid = threadIdx.x, lane = tid & 63, c = blockIdx.y, t = long_block();
+  const int tid = threadIdx.x, lane = tid & 63, c = g.c0 + blockIdx.y, t = long_block();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const CondDev& cd = g.cond[c];
   const FarCond& fc = cd.far;
@@ -936,7 +936,7 @@ __global__ __launch_bounds__(256) void k_far_finish(FarArgs g) {
     // coefficients are the wave's (scalar loads)
     const int lg = l + fc.sh, sl = far_slices(fc.sh, l);
     const int tl = lg >= 6 ? __builtin_amdgcn_readfirstlane(k >> lg) : min(k >> lg, far_tiles(nf, l) - 1);
-    const double* r = g.rows + ((int64_t)c * g.cond_rows + before + (int64_t)tl * sl) * P;
+    const double* r = g.rows + ((int64_t)blockIdx.y * g.cond_rows + before + (int64_t)tl * sl) * P;
     before += (int64_t)far_tiles(nf, l) * sl;
     double co[P];
 #pragma unroll
@@ -969,6 +969,7 @@ constexpr int64_t kMomCells32 = 32768, kMomCells64 = 2048;
 constexpr int kMomLines = 24;
 
 int far_nodes(int prec) { return prec == XS_FP32 ? 12 : 20; }
+int far_moments(int prec) { return prec == XS_FP32 ? kMoments32 : kMoments64; }
 
 void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, int64_t n_lines, double* sigma,
                 hipStream_t s) {
@@ -987,23 +988,23 @@ void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, int
   a.rwin = w.rwin;
   a.max_lines = w.max_lines;
   a.counter = w.counter;
-  a.rows = w.far_rows;
-  a.cond_rows = w.far_cond_rows;
+  a.cond_rows = far_rows_before(m.n_fine, m.fine_sh, far_lmax + 1);
   a.sigma = sigma;
   int64_t blocks = 0;
   for (int l = 0; l <= far_lmax; ++l) blocks += far_blocks(m.n_fine, m.fine_sh, l);
   a.blocks = (int32_t)blocks;
-  // the moments lie in the partial rows, which the near leaves have done with; as
+  // rows and moments lie in the partial rows, which the near leaves have done with; as
   // many conditions at a time as fit (lifetimes, whose widths have no bound
   // here, go line by line)
-  const int pm = m.prec == XS_FP32 ? kMoments32 : kMoments64;
   a.mom_cells = far_cells_before(fine_keys(m), far_lmax + 1);
-  const int64_t fit = 2 * w.item_target * 1024 / (a.mom_cells * pm);
+  const int64_t rows = a.cond_rows * far_nodes(m.prec), moments = a.mom_cells * far_moments(m.prec);
   const bool many = m.n_fine >= (m.prec == XS_FP32 ? kMomCells32 : kMomCells64) ||
                     n_lines >= kMomLines * (int64_t)m.n_fine;
-  a.mom = many && fit > 0 && !w.rgpre ? w.part : nullptr;
-  const int at_once = a.mom ? (int)std::min<int64_t>(fit, m.n_cond) : m.n_cond;
-  const dim3 fin = long_grid(far_tiles(m.n_fine, end_min), m.n_cond);
+  const bool mom = many && moments <= part_doubles(w) && !w.rgpre;
+  const int at_once =
+      w.far_extra ? 1 : (int)std::min<int64_t>(part_doubles(w) / (rows + (mom ? moments : 0)), m.n_cond);
+  a.rows = w.far_extra ? w.far_extra : w.part;
+  a.mom = !mom ? nullptr : w.far_extra ? w.part : w.part + at_once * rows;
   const int per_block = 4 * (64 / far_nodes(m.prec));  // tiles of a block of k_far_cells
   auto run = [&](auto leaves, auto moments, auto cells, auto far, auto finish) {
     for (a.c0 = 0; a.c0 < m.n_cond; a.c0 += at_once) {
@@ -1018,8 +1019,8 @@ void launch_far(const ModelDev& m, const Work& w, int far_lmax, int end_min, int
       }
       // (with moments most conditions have nothing left for it)
       go(far, std::min<int64_t>(blocks, a.mom ? 4096 : 1 << 22));
+      go(finish, far_tiles(m.n_fine, end_min));
     }
-    hipLaunchKernelGGL(finish, fin, dim3(256), 0, s, a);
   };
 #define XS_F(PR)                                                                                                   \
   if (m.profile == PR && m.prec == XS_FP32)                                                                        \

@@ -733,7 +733,7 @@ void launch_offsets_records(const ModelDev& m, const Work& w, const StatesView& 
   if (blocks > 8192) blocks = 8192;
   hipLaunchKernelGGL((m.pop == XS_LTE ? k_records<true> : k_records<false>), dim3((unsigned)blocks), dim3(256), 0, s,
                      m, w.slot, w.Q, w.sb, st, ln, (const void*)w.lpack, skeys, svals, w.stats, w.off,
-                     w.far_rows != nullptr, w.max_lines, w.rnu, w.rgref, w.rnexp, w.rgpre, w.ridx, w.rEs, w.rS, w.odd.pos,
+                     w.far_cond_rows > 0, w.max_lines, w.rnu, w.rgref, w.rnexp, w.rgpre, w.ridx, w.rEs, w.rS, w.odd.pos,
                      w.cut_class, w.rkc, w.rdel, w.rwin, w.counter);
 }
 

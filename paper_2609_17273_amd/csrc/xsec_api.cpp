@@ -389,8 +389,8 @@ void derive(xs_plan* p) {
 // item_target: gather work items aimed at when tiles are split (sizes the
 // partial-row buffer, 2 item_target rows); 0 = kItemsPerCU per compute unit.
 // with_adjoint: carve the adjoint's per-block partial sums (the
-// allocation-free forward path leaves them out).  with_far: carve the tile
-// expansions' rows, for as many levels as the grid can use, so that a change
+// allocation-free forward path leaves them out).  with_far: what the tile
+// expansions need, for as many levels as the grid can use, so that a change
 // of conditions never needs a larger workspace.
 size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool with_adjoint = true,
               bool with_far = true) {
@@ -447,21 +447,21 @@ size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool wit
     x.item_target = item_target > 0 ? item_target : kItemsPerCU * (int64_t)std::max(1, p->n_cu);
     x.part = (double*)take(sizeof(double) * 2 * (size_t)x.item_target * 1024);
   }
-  x.far_rows = x.cut_rows = nullptr;
   x.odd = OddLines{};
-  x.far_cond_rows = x.n_cut_rows = 0;
+  x.far_cond_rows = 0;
+  x.far_extra = nullptr;
   if (with_far && far_capable(p)) {
     x.odd.pos = (int32_t*)take(4 * kOddMax);
     x.odd.gref = (float*)take(4 * kOddMax);
     x.odd.nexp = (float*)take(4 * kOddMax);
     x.odd.S = (double*)take(8 * (size_t)kOddMax * d.n_slots);
     x.far_cond_rows = far_rows_before((int32_t)cells, sh, far_levels_of_grid((int32_t)cells));
-    x.far_rows = (double*)take(sizeof(double) * d.n_cond * (size_t)x.far_cond_rows * far_nodes(d.prec));
-    if (adjoint_capable(p)) {
-      // rows of whole tiles (the last one may pass the grid's end)
-      x.n_cut_rows = (p->grid.n_bins + kFarEndBins) / kCutRowBins;
-      x.cut_rows = (double*)take((size_t)(d.prec == XS_FP32 ? 4 * 6 : 8 * 12) * 2 * d.n_cond * (size_t)x.n_cut_rows);
-    }
+    const int levels = far_levels_of_grid((int32_t)cells);
+    const int64_t rows = x.far_cond_rows * far_nodes(d.prec);
+    const int64_t mom = far_cells_before((int32_t)cells + 2 * kFarVirtual, levels) * far_moments(d.prec);
+    const int64_t adj = adjoint_capable(p) ? adj_far_doubles(d, x.far_cond_rows) : 0;
+    if (rows + mom > part_doubles(x) || adj > part_doubles(x) - kAdjTail)
+      x.far_extra = (double*)take(sizeof(double) * (size_t)std::max(rows, adj));
   }
   x.stats = (unsigned long long*)take(8 * 8);
   // (the allocation-free call has neither a stick spectrum nor an adjoint)
@@ -1118,7 +1118,7 @@ int xs_plan_autotune(xs_plan* p, const xs_states* st, const xs_lines* ln, double
     const int cand[4] = {4096, 8192, 16384, 32768};
     // 64 B per line: room for three gradients after the far part's three
     double* outs = (double*)p->w.lpack + 3 * p->max_lines;
-    double* dTP = p->w.part;             // dL/dT, dL/dP
+    double* dTP = p->w.part + (part_doubles(p->w) - kAdjTail);  // dL/dT, dL/dP
     float adj_best = 1e30f;
     for (int ci = 0; ci < 4 && !rc; ++ci) {
       float ms_best;

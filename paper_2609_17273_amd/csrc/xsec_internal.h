@@ -174,10 +174,10 @@ struct Work {
   int32_t* item_sums;       // scan block sums
   double* part;             // [2 item_target][1024] partial rows
   int64_t item_target;      // work items aimed at when tiles are split
-  double* far_rows;         // [n_cond][far_cond_rows][nodes] expansion coefficients, or null
-  int64_t far_cond_rows;
-  double* cut_rows;         // [n_cond][n_cut_rows][2][nodes] moments of the cotangent over parts of cut tiles
-  int64_t n_cut_rows;
+  int64_t far_cond_rows;    // rows of a condition's tile expansions at the most levels, 0: none.  The rows (and
+                            // the adjoint's moments of the cotangent) lie in `part`, which the passes before them
+                            // have done with, for as many conditions at a time as fit
+  double* far_extra;        // or for one condition here, where the grid is too long for that (else null)
   OddLines odd;
   unsigned long long* stats;// [8]
   double* own;              // [4][n_slots] Q, dQ, sb and smax of partition functions and stick spectra
@@ -234,6 +234,7 @@ void launch_scatter(const ModelDev& m, const Work& w, double* sigma, int accumul
                     int64_t n_lines, hipStream_t s);
 
 // ---- near leaves (k_near.hip) ----
+inline int64_t part_doubles(const Work& w) { return 2 * w.item_target * 1024; }  // of Work::part
 size_t near_row_doubles();  // what it takes of Work::part
 // sigma = (or +=) the points near each line, for the conditions with tile
 // expansions, and every point of the others but those whose `gather` is set
@@ -241,6 +242,7 @@ void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate
 
 // ---- tile expansions (k_far.hip) ----
 int far_nodes(int prec);  // nodes per tile
+int far_moments(int prec);  // moments per cell
 // sigma += the expansions of the lines' far tiles (levels up to far_lmax, the
 // conditions' largest)
 // (end_min: the conditions' lowest level of cut tiles)
@@ -256,7 +258,11 @@ bool launch_cooling(const ModelDev& m, const Work& w, const StatesView& st, cons
 
 // ---- adjoint (k_adjoint.hip) ----
 // far_lmax, end_min: as launch_far's; far_lmax < 0: every window point by point
-constexpr int kCutRowBins = 16;  // grid points per row of Work::cut_rows
+constexpr int kCutRowBins = 16;  // grid points per row of moments of the parts of cut tiles
+// doubles of Work::part (or Work::far_extra) that one condition takes, of rows tile rows;
+// kAdjTail doubles at the end of Work::part are left to the caller
+constexpr int kAdjTail = 2 * kMaxCond;
+int64_t adj_far_doubles(const ModelDev& m, int64_t rows);
 void launch_adjoint(const ModelDev& m, const Work& w, const StatesView& st, const LinesView& ln,
                     const double* g, double* dT, double* dP, double* dgref, double* dnexp,
                     double* dls, int64_t n_lines, int adj_blocks, int far_lmax, int end_min, hipStream_t s);
