@@ -350,7 +350,7 @@ int xs_plan_replay(xs_plan* plan);
  * sampled profiles, the adjoint's grid of 4096, 8192, 16384 or 32768 blocks
  * (sigma serves as its cotangent).  Keeps the fastest and caches it under
  * cache_path (JSON, keyed by device, profile, precision, window size, line
- * count and number of conditions; NULL: no file).  A cached entry is reused
+ * count, number of conditions and, where the pass is not the gather's, its way; NULL: no file).  A cached entry is reused
  * without timing.  When the chosen bucket size is not the last one tried,
  * the next xs_cross_section re-buckets the lines. */
 int xs_plan_autotune(xs_plan* plan, const xs_states* states, const xs_lines* lines,

@@ -542,23 +542,27 @@ int preprocess(xs_plan* p, const xs_states* st, const xs_lines* ln) {
 // points 334 / 438, 480 / 449, 754 / 476 us; FP64 form with 4, 8, 16 lines 505 /
 // 740, 822 / 770, 1042 / 866 us (blocks of four waves since then: less still).
 constexpr int kFarLines32 = 4, kFarLines64 = 8;
-bool use_far(const xs_plan* p) {
+bool use_far(const xs_plan* p, int64_t n_lines) {
   return p->w.far_cond_rows > 0 && p->far_lmax >= 0 &&
          2 * p->w.item_target * 1024 >= (int64_t)near_row_doubles() &&
-         p->last_lines_in >=
+         n_lines >=
              (p->model.precision == XS_FP32 ? kFarLines32 : kFarLines64) * ((p->grid.n_bins + 63) / 64);
 }
+
+bool use_far(const xs_plan* p) { return use_far(p, p->last_lines_in); }
 
 // The adjoint through tiles: where they are used and, with the lines evenly over
 // the grid, waves would be within the span that pays (far_adj_span; the moments of the cotangent
 // alone cost 0.14 ms on 2e6 points).
-bool adjoint_far(const xs_plan* p) {
-  if (!use_far(p)) return false;
-  const double even = 64.0 * p->md.n_fine / (double)std::max<int64_t>(p->last_lines_in, 1);
+bool adjoint_far(const xs_plan* p, int64_t n_lines) {
+  if (!use_far(p, n_lines)) return false;
+  const double even = 64.0 * p->md.n_fine / (double)std::max<int64_t>(n_lines, 1);
   for (const CondDev& cd : p->cdev)
     if (cd.far.on && even <= cd.far.span + 1.0) return true;
   return false;
 }
+
+bool adjoint_far(const xs_plan* p) { return adjoint_far(p, p->last_lines_in); }
 
 // Gaussians go a line to a lane (k_near) over the points where they are not zero,
 // without expansions.  Measured, gather with its reduction and this: 1e4 lines on 1e6
@@ -996,9 +1000,12 @@ static std::string tune_key(const xs_plan* p, int64_t n_lines) {
   const int64_t wb = (int64_t)std::ceil(maxcut / p->grid.dnu);
   int lb = 0;
   while ((int64_t(1) << (lb + 1)) <= std::max<int64_t>(n_lines, 1)) ++lb;
+  // the way that the passes go, which the line count alone does not tell (a plan whose pass
+  // is the gather's has no mark: an entry tuned without one never was for another way)
+  const char* way = adjoint_far(p, n_lines) ? "|far,adj" : use_far(p, n_lines) ? "|far" : use_near(p) ? "|near" : "";
   char buf[256];
-  std::snprintf(buf, sizeof(buf), "%s|p%d|f%d|w%lld|n2^%d|c%d", p->arch.c_str(), p->model.profile,
-                p->model.precision, (long long)wb, lb, (int)p->conds.size());
+  std::snprintf(buf, sizeof(buf), "%s|p%d|f%d|w%lld|n2^%d|c%d%s", p->arch.c_str(), p->model.profile,
+                p->model.precision, (long long)wb, lb, (int)p->conds.size(), way);
   return buf;
 }
 
