@@ -421,7 +421,6 @@ struct BinomTable {
   }
 };
 static __device__ const BinomTable kBinom = BinomTable();
-static __device__ const double kFarX12[12] = XS_FAR_X12, kFarX20[20] = XS_FAR_X20;
 
 // the lowest level of the condition that uses moments
 __device__ __forceinline__ int far_cond_mom_level(const FarArgs& g, const CondDev& cd) {
@@ -622,7 +621,7 @@ __global__ __launch_bounds__(256) void k_far_cells(FarArgs g) {
     CellRange r[4];
     far_tile_ranges(fc, l, t, r);
     const double half = (double)(1 << (l + fc.sh)) * 0.5;
-    const double node = (double)(t << (l + fc.sh)) + (half - 0.5) + half * (P == 12 ? kFarX12[q] : kFarX20[q]);
+    const double node = (double)(t << (l + fc.sh)) + (half - 0.5) + half * far_x<double, P>()[q];
     const double* const rows = g.mom + (int64_t)blockIdx.y * g.mom_cells * PM;
     for (int left = 4; left > 0;) {
       if (r[0].lo > r[0].hi) {

@@ -5,8 +5,11 @@
 // the host first (no HIP call before validation succeeds), then enqueues the
 // path on the plan's stream:
 //   partition functions -> intensity pass 1 (keys, ln S max) -> stable radix
-//   sort by bucket -> bucket offsets + sorted records -> profile pass
-//   (gather or scatter) [-> adjoint].
+//   sort by cell -> cell offsets + sorted records -> profile pass [-> adjoint].
+// The profile pass is the scatter where a plan asks for it; else the near
+// kernel with tile expansions where the list is dense enough (use_far), the
+// near kernel alone for Gaussians, and the gather for the rest (and for single
+// conditions of a table that it serves better: gather_serves).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
