@@ -86,6 +86,7 @@ KERNEL_SOURCES = ["paper_2609_17273_amd/csrc/k_profile.hip", "paper_2609_17273_a
                   "paper_2609_17273_amd/csrc/k_common.h", "paper_2609_17273_amd/csrc/k_lines.hip",
                   "paper_2609_17273_amd/csrc/k_near.hip", "paper_2609_17273_amd/csrc/k_far.hip",
                   "paper_2609_17273_amd/csrc/k_voigt.h", "paper_2609_17273_amd/csrc/far_geometry.h",
+                  "paper_2609_17273_amd/csrc/far_tables.h", "paper_2609_17273_amd/csrc/sort_plan.h",
                   "paper_2609_17273_amd/csrc/xsec_internal.h"]
 
 # The Lorentzian and Voigt passes take the tiles away from a line through

@@ -151,7 +151,7 @@ XS_HD void far_cut_candidates(const FarCond& c, int32_t f0, int32_t f1, CellRang
 
 // Candidate cells of the leaves [a, b] (inside one tile of 256 points) for
 // the point-by-point part, among the cells [clo, chi] whose windows can reach
-// them: the cells near them, and the edge cells.  Of the lines of segment 0,
+// them: the cells near them, and the outermost ones.  Of the lines of segment 0,
 // cell f's take the leaves within gap of f.
 constexpr int kSegs = 3;
 XS_HD void far_segments(const FarCond& c, int32_t a, int32_t b, int32_t clo, int32_t chi, CellRange s[kSegs]) {

@@ -807,7 +807,8 @@ __device__ __forceinline__ Sums3 window_sums(bool on, int64_t klo, int64_t khi, 
 // most 256 points on each side: the groups of 16 points before the end enter
 // through their own moments (PE nodes), the end's group point by point.
 // Measured on 1e7 lines, FP32 form, window 5000 points: 15.5 ms point by point;
-// 6.1 ms with tiles (near part 3.0, tiles and ends 2.9, moments 0.2); 2e5
+// 6.2 ms with tiles (near part 3.0, tiles and ends 3.1, moments 0.2; VALU issue at 0.65
+// of its peak rate in both, half of the wave cycles being waits); 2e5
 // lines FP64: 0.90 and 0.44 ms.
 
 // Moments of every tile of a level (blockIdx.y: condition): a wave takes one
@@ -1277,7 +1278,7 @@ __global__ __launch_bounds__(256, (adj_waves<R, PROF, FAR>())) void k_adjoint(Ad
                 : ((const double*)a.rS)[(int64_t)cd.slot * a.max_lines + p];
         on = S != 0.0;
       }
-      // with tile expansions the lines of all but the edge cells split their
+      // with tile expansions the lines of all but the outermost cells split their
       // windows: the near leaves point by point, the rest through tiles
       int f = 0, kc = 0;
       bool split = false;

@@ -11,8 +11,8 @@
 //
 // What bounds a pass is the number of profile evaluations; measured on the
 // whole call, point by point and with expansions: 1e7 lines, 2e6 points, window
-// 5000 points, FP32 form 14.65 and 2.70 ms (near leaves 1.22, tiles 0.35, window
-// ends and sigma 0.27); 1e6 lines, FP64 form 3.33 and 1.10 ms; 48 conditions of
+// 5000 points, FP32 form 14.65 and 2.70 ms (near leaves 1.3, tiles 0.32, window
+// ends and sigma 0.18); 1e6 lines, FP64 form 3.33 and 1.10 ms; 48 conditions of
 // 1e6 lines, 2e5 points, FP32 form 113.2 and 7.1 ms.
 //
 // k_far_leaves, k_far_moments, k_far_cells: the tiles whose lines' moments serve
@@ -403,10 +403,11 @@ __device__ __forceinline__ int far_slot(int lane) {
 // whose cells are too small for the widest line (far_mom_level) or for the widest
 // Gaussian's powers (far_sigma_level) take lines one by one.
 //
-// The tiles of 1e7 lines FP32 (2e6 points) took 1.08 ms line by line, 0.35 by moments
-// (leaves 0.19, wider cells 0.05, tiles 0.11), 1e6 lines FP64 0.60 and 0.22, 48
+// The tiles of 1e7 lines FP32 (2e6 points) took 1.08 ms line by line, 0.32 by moments
+// (leaves 0.18, wider cells 0.04, tiles 0.10), 1e6 lines FP64 0.60 and 0.22, 48
 // conditions x 1e6 lines (of which 16 have lines too wide for most levels) 5.8
-// and 3.7.  The leaves are bound by the recurrence, seven operations a moment.
+// and 3.7.  The leaves are bound by the recurrence, seven operations a moment
+// (VALU issue at its peak rate in the FP32 form, 0.8 of it in FP64).
 // ---------------------------------------------------------------------------
 constexpr int kMoments32 = 28, kMoments64 = 48, kMomentsMax = 48;
 constexpr int kMomLeaves = 64, kMomLevels = 6;  // cells of a block of k_far_moments, levels it builds from them

@@ -16,9 +16,11 @@
 // different places of their ranges, so that few of a step's adds meet in one
 // point or bank.  The four rows are added in order, and a tile of many lines
 // is split into parts whose rows k_reduce adds in order, so the sums do not
-// depend on scheduling.  Bound by VALU issue and by
-// the LDS adds.  Measured against the gather's rows clipped to the near leaves
-// (64 points): 1e7 lines FP32 4.07 -> 1.22 ms with leaves of 16 points, 1e6 lines
+// depend on scheduling.  Bound by VALU issue: of one instruction a SIMD every four
+// cycles, on 1e7 lines, 0.90 (FP32 Voigt; waits on LDS are 3% of the wave cycles), 0.79 to
+// 0.87 (FP64), bin means 0.96 and 0.75 (FP64, two waves a SIMD).  Measured against the
+// gather's rows clipped to the near leaves
+// (64 points): 1e7 lines FP32 4.07 -> 1.3 ms with leaves of 16 points, 1e6 lines
 // FP64 1.30 -> 0.61 ms, 48 conditions x 1e6 lines FP32 9.39 -> 2.64 ms.
 #include <algorithm>
 

@@ -156,6 +156,7 @@ struct GatherArgs {
   int32_t tile_bins;
   int32_t persistent;
   int32_t some;             // only the conditions whose `gather` is set
+  int32_t end_key;          // n_fine + fine_v: off of it is the number of lines
   int64_t chunk_cfg;        // requested lines per work item (0: automatic)
   int64_t item_target;      // work items aimed at when tiles are split
 };
@@ -173,9 +174,10 @@ __device__ __forceinline__ void tile_candidates(const GatherArgs& g, const CondD
   const int64_t lo = tlo - cd.wbins;
   const int64_t blo = max<int64_t>(0, lo >= 0 ? lo / m.bucket_bins : -1);
   const int64_t bhi = min<int64_t>(m.n_buckets - 1, (thi + cd.wbins) / m.bucket_bins);
-  // (the first and the last bucket also have the lines beyond the grid)
-  plo = g.off[blo == 0 ? -(int64_t)m.fine_v : blo * m.fine_per_bucket];
-  phi = g.off[bhi == m.n_buckets - 1 ? m.n_fine + m.fine_v : (bhi + 1) * (int64_t)m.fine_per_bucket];
+  // (the first and the last bucket also have the lines beyond the grid: all before and
+  // all after them)
+  plo = blo == 0 ? 0 : g.off[blo * m.fine_per_bucket];
+  phi = g.off[bhi == m.n_buckets - 1 ? (int64_t)g.end_key : (bhi + 1) * (int64_t)m.fine_per_bucket];
 }
 
 // Bin range where |x| < X, relative to k_c, in FP32 (the one-bin margin
@@ -1599,6 +1601,7 @@ void launch_gather(const ModelDev& m, const Work& w, const Tiling& t, double* si
   a.n_ct = a.n_tiles * m.n_cond;
   a.persistent = t.persistent;
   a.some = some;
+  a.end_key = m.n_fine + m.fine_v;
   a.chunk_cfg = t.chunk_lines;
   a.item_target = w.item_target;
   // plan the work items
