@@ -356,6 +356,16 @@ struct FastSums {
 #pragma unroll
     for (int q = 0; q < (SY ? NP : 1); ++q) B[q][0] = B[q][1] = B[q][2] = B[q][3] = 0;
   }
+  __device__ __forceinline__ void plus(const FastSums& o) {
+    s1 += o.s1;
+    s2 += o.s2;
+    s3 += o.s3;
+    s4 += o.s4;
+#pragma unroll
+    for (int q = 0; q < (SY ? NP : 1); ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) B[q][i] += o.B[q][i];
+  }
   __device__ __forceinline__ void begin(const AdjLine<R>& L) {
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
@@ -542,7 +552,7 @@ struct FastSums {
 // (FP32 form: window ends take an FP32 cotangent and block sums as the points inside do;
 // in FP64 before.  Errors against FP64 over 150 lists of 1e4 to 2e5 lines, norms of the
 // gradients of log scale, gamma_ref and n_exp, with point-by-point FP64 ends / now, far part
-// included: 2.1e-7, 8.6e-7, 8.8e-7 / 1.2e-7, 4.8e-7, 4.9e-7 in the mean, 1.9e-4 / 5.8e-5 at most.)
+// included: 2.1e-7, 8.6e-7, 8.8e-7 / 1.2e-7, 4.6e-7, 4.7e-7 in the mean, 1.9e-4 / 5.8e-5 at most.)
 template <typename R, int PROF, int NP, bool SY = false, bool C0 = false, bool UF = false>
 __device__ __forceinline__ void fast_range(const AdjLine<R>& L, const GSrc<R>& G, int r0, int r1, bool mask,
                                            double& sA, double& sB, double& sC) {
@@ -807,9 +817,9 @@ __device__ __forceinline__ Sums3 window_sums(bool on, int64_t klo, int64_t khi, 
 // most 256 points on each side: the groups of 16 points before the end enter
 // through their own moments (PE nodes), the end's group point by point.
 // Measured on 1e7 lines, FP32 form, window 5000 points: 15.5 ms point by point;
-// 6.2 ms with tiles (near part 3.0, tiles and ends 3.1, moments 0.2; VALU issue at 0.65
-// of its peak rate in both, half of the wave cycles being waits); 2e5
-// lines FP64: 0.90 and 0.44 ms.
+// 6.0 ms with tiles (near part 3.0, tiles and ends 2.8, moments 0.2; VALU issue at two
+// thirds of its peak rate in both, half of the wave cycles being waits); 2e5
+// lines FP64: 0.90 and 0.38 ms.
 
 // Moments of every tile of a level (blockIdx.y: condition): a wave takes one
 // tile of 64 points or more, or 64 points' worth of smaller ones.
@@ -942,9 +952,11 @@ __global__ __launch_bounds__(64) void k_adj_cut(AdjArgs a) {
 
 // The far sums of one wave's lines.  The forms that most tiles take -- FP32:
 // one pair, as block sums or in the u-form, and two pairs as block sums --
-// add up over tiles and are flushed to FP64 after as many terms as a block of the near loops
-// (FP32 form; over all tiles errors of lines wide against the grid were up to 5e-6, flushed
-// 8e-7, point by point 1.5e-6); the others flush per tile.
+// add up over all tiles and are flushed to FP64 once; the others flush per tile.  FP32 form:
+// a tile's 12 terms are summed before they are added, so a sum has fewer additions in a row than
+// the 256 of a block of the near loops.  Errors of lines wide against the grid: one sum over all
+// terms up to 5e-6, by tiles 1.1e-6, flushed every 256 terms 8e-7, point by point 1.5e-6; far part
+// of 1e7 lines 2.81, 2.84, 3.12 ms (a flush inside the loop costs registers).
 template <typename R, int PROF>
 struct FarSums {
   FastSums<R, PROF, 1, PROF == XS_VOIGT> one;
@@ -991,16 +1003,6 @@ __device__ __forceinline__ void far_end(AdjLine<R>& L, FarSums<R, PROF>& F) {
   }
 }
 
-// The sums so far to FP64 (FP32 form: after as many terms as a block of the near loops).
-template <typename R, int PROF>
-__device__ __forceinline__ void far_flush(AdjLine<R>& L, FarSums<R, PROF>& F) {
-  far_end<R, PROF>(L, F);
-  if constexpr (PROF == XS_VOIGT) far_pair<R, PROF>(L, 0);
-  F.one.clear();
-  F.uform.clear();
-  F.two.clear();
-}
-
 // N terms (x, weight) of a tile or a cut, with the form the wave's smallest
 // |z|^2 on it (rho) allows.  Every lane of the wave takes part; a lane without
 // a share has weights 0 and any finite x.
@@ -1023,8 +1025,19 @@ __device__ __forceinline__ void far_terms(AdjLine<R>& L, FarSums<R, PROF>& F, bo
       }
     }
   };
+  // FP32 form: the tile's own sums first (FarSums)
+  auto block = [&](auto& S) {
+    if constexpr (sizeof(R) == 8) {
+      add(S);
+    } else {
+      auto T = S;
+      T.clear();
+      add(T);
+      S.plus(T);
+    }
+  };
   if constexpr (PROF == XS_LORENTZ) {
-    add(F.one);
+    block(F.one);
   } else {
     const double y = L.y, y2 = y * y;
     if (sizeof(R) == 4 && wide) {
@@ -1043,8 +1056,8 @@ __device__ __forceinline__ void far_terms(AdjLine<R>& L, FarSums<R, PROF>& F, bo
     auto all = [&](double r) { return __ballot(share && !(rho >= r * 1.001)) == 0; };
     using LV = Levels<R>;
     if (all(LV::rho[0])) {
-      if (F.one_sy) add(F.one);
-      else add(F.uform);
+      if (F.one_sy) block(F.one);
+      else block(F.uform);
       return;
     }
     // forms that flush per tile; L's one pair is put back afterwards
@@ -1056,7 +1069,7 @@ __device__ __forceinline__ void far_terms(AdjLine<R>& L, FarSums<R, PROF>& F, bo
     };
     if constexpr (sizeof(R) == 4) {
       if (F.two_sy) {
-        add(F.two);
+        block(F.two);
       } else {
         far_pair<R, PROF>(L, 1);
         once(FastSums<R, PROF, 2>());
@@ -1123,7 +1136,7 @@ __device__ __forceinline__ Sums3 far_window_sums(const AdjArgs& a, const CondDev
     return fma(xn, xn, L.y * L.y);
   };
   // ---- tiles taken whole.  64 candidates are examined at a time, one per lane ----
-  int done = 0, since = 0;
+  int done = 0;
   for (;;) {
     int l = -1, t = 0, total = 0;
     for (int k = 0; k <= fc.lmax; ++k) {
@@ -1159,10 +1172,6 @@ __device__ __forceinline__ Sums3 far_window_sums(const AdjArgs& a, const CondDev
       int64_t row = tt;
       for (int k = 0; k < tl; ++k) row += far_tiles(m.n_fine, k);
       const R* mu = (const R*)a.mom + ((int64_t)(c - a.c0) * a.cond_rows + row) * P;
-      if (sizeof(R) == 4 && ++since > kFlush / P) {
-        far_flush<R, PROF>(L, F);
-        since = 1;
-      }
       // (a lane without a line takes the weights as well: its sums are dropped)
       if (__ballot(far && !mine) == 0)
         far_terms<R, PROF, P>(
@@ -1177,7 +1186,6 @@ __device__ __forceinline__ Sums3 far_window_sums(const AdjArgs& a, const CondDev
     if (done >= total) break;
   }
   // ---- tiles that window ends cut ----
-  if constexpr (sizeof(R) == 4) far_flush<R, PROF>(L, F);
   CellRange cc[2];
   far_cut_candidates(fc, f0, f1, cc);
   const int n = 1 << (fc.end + fc.sh);

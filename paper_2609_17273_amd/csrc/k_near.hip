@@ -571,7 +571,7 @@ __global__ __launch_bounds__(256) void k_near(NearArgs g) {
       ct = t * m.n_cond + (ct + t) % m.n_cond;
     }
     const int np = g.parts[ct];
-    if (np == 0) continue;  // the gather's
+    if (!GAUSS && np == 0) continue;  // the gather's
     const int c = ct % m.n_cond, t = ct / m.n_cond;
     const CondDev& cd = g.cond[c];
     const NearSegs sg = near_segments(g, cd, t);
@@ -579,7 +579,8 @@ __global__ __launch_bounds__(256) void k_near(NearArgs g) {
     const int tlo = t * kNearBins, thi = (int)min<int64_t>((int64_t)tlo + kNearBins, m.n_bins) - 1;
     const int64_t chunk = *(const int64_t*)(g.counter + 4);
     const int64_t q0 = np > 1 ? part * chunk : 0;
-    const int64_t q1 = np > 1 ? min(sg.all, q0 + chunk) : sg.all;
+    const int64_t all = GAUSS ? sg.cum[kSegs - 1] : sg.all;  // (Gaussians: neither odd lines nor the gather's)
+    const int64_t q1 = np > 1 ? min(all, q0 + chunk) : all;
 #pragma unroll
     for (int j = 0; j < kNearRow / 64; ++j) row[lane + 64 * j] = 0.0;
     __syncthreads();

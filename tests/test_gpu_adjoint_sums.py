@@ -1,5 +1,6 @@
 """FP32 sums of the adjoint's far part, which goes over hundreds of tiles where windows
-are long: they pass to FP64 after as many terms (256) as the point-by-point blocks.
+are long: no more additions in a row than the 256 of the point-by-point blocks, which pass
+to FP64 then (a tile's terms first, then the tiles).
 
 Loss weights of one sign and lines wide against the grid (every term of d_log_scale has
 one sign, those of the widths' gradients change sign once): a sum of 256 FP32 terms
