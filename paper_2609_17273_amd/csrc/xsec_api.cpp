@@ -220,6 +220,16 @@ bool far_capable(const xs_plan* p) {
          (pr == XS_LORENTZ || pr == XS_VOIGT || pr == XS_BIN_LORENTZ || pr == XS_BIN_VOIGT);
 }
 
+// Expansions pay off once 64 grid points hold a few lines: a tile visit costs a
+// wave nearly the same for one line as for 64.  Measured on 1e6 points, window
+// 5000, point by point and with expansions: FP32 form with 2, 4, 8 lines on 64
+// points 334 / 438, 480 / 449, 754 / 476 us; FP64 form with 4, 8, 16 lines 505 /
+// 740, 822 / 770, 1042 / 866 us (blocks of four waves since then: less still).
+constexpr int kFarLines32 = 4, kFarLines64 = 8;
+int64_t far_lines(const xs_plan* p) {
+  return (p->model.precision == XS_FP32 ? kFarLines32 : kFarLines64) * ((p->grid.n_bins + 63) / 64);
+}
+
 bool adjoint_capable(const xs_plan* p) {
   return p->model.population == XS_LTE && p->model.profile < XS_BIN_DOPPLER;
 }
@@ -394,7 +404,8 @@ void derive(xs_plan* p) {
 // with_adjoint: carve the adjoint's per-block partial sums (the
 // allocation-free forward path leaves them out).  with_far: what the tile
 // expansions need, for as many levels as the grid can use, so that a change
-// of conditions never needs a larger workspace.
+// of conditions never needs a larger workspace (nothing where max_lines is too few for
+// them: a long grid's rows would be twice its sigma).
 size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool with_adjoint = true,
               bool with_far = true) {
   const ModelDev& d = p->md;
@@ -453,7 +464,7 @@ size_t layout(xs_plan* p, char* base, Work* w, int64_t item_target = 0, bool wit
   x.odd = OddLines{};
   x.far_cond_rows = 0;
   x.far_extra = nullptr;
-  if (with_far && far_capable(p)) {
+  if (with_far && far_capable(p) && L >= far_lines(p)) {
     x.odd.pos = (int32_t*)take(4 * kOddMax);
     x.odd.gref = (float*)take(4 * kOddMax);
     x.odd.nexp = (float*)take(4 * kOddMax);
@@ -539,17 +550,9 @@ int preprocess(xs_plan* p, const xs_states* st, const xs_lines* ln) {
   return hip_check(hipGetLastError(), "preprocess launch");
 }
 
-// Expansions pay off once 64 grid points hold a few lines: a tile visit costs a
-// wave nearly the same for one line as for 64.  Measured on 1e6 points, window
-// 5000, point by point and with expansions: FP32 form with 2, 4, 8 lines on 64
-// points 334 / 438, 480 / 449, 754 / 476 us; FP64 form with 4, 8, 16 lines 505 /
-// 740, 822 / 770, 1042 / 866 us (blocks of four waves since then: less still).
-constexpr int kFarLines32 = 4, kFarLines64 = 8;
 bool use_far(const xs_plan* p, int64_t n_lines) {
   return p->w.far_cond_rows > 0 && p->far_lmax >= 0 &&
-         2 * p->w.item_target * 1024 >= (int64_t)near_row_doubles() &&
-         n_lines >=
-             (p->model.precision == XS_FP32 ? kFarLines32 : kFarLines64) * ((p->grid.n_bins + 63) / 64);
+         2 * p->w.item_target * 1024 >= (int64_t)near_row_doubles() && n_lines >= far_lines(p);
 }
 
 bool use_far(const xs_plan* p) { return use_far(p, p->last_lines_in); }
