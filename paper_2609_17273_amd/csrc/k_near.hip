@@ -54,6 +54,7 @@ struct NearArgs {
   int32_t accumulate;
   int32_t n_ct;             // tiles * n_cond; ct = tile * n_cond + condition
   int32_t extra_blocks;     // the first blocks of k_near's grid, which take the parts beyond the first
+  int32_t rest;             // the conditions without tile expansions are the gather's
 };
 
 // Lines of tile t: segments of sorted lines, then (all: with them) the odd ones, which
@@ -90,7 +91,7 @@ __device__ __forceinline__ NearSegs near_segments(const NearArgs& g, const CondD
 
 // The lines of a tile, or -1 where the condition's points are the gather's.
 __device__ __forceinline__ int64_t near_lines(const NearArgs& g, int c, int t) {
-  return g.cond[c].gather ? -1 : near_segments(g, g.cond[c], t).all;
+  return g.rest && !g.cond[c].far.on ? -1 : near_segments(g, g.cond[c], t).all;
 }
 
 // Planning: candidates in all, then the parts of each tile.  A part holds at
@@ -662,7 +663,8 @@ __global__ __launch_bounds__(256) void k_near_reduce(NearArgs g) {
 
 size_t near_row_doubles() { return (size_t)2 * kNearExtra * kNearBins + kNearExtra; }
 
-void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate, int64_t n_lines, hipStream_t s) {
+void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate, bool rest, int64_t n_lines,
+                 hipStream_t s) {
   NearArgs a;
   a.m = m;
   a.cond = w.cond;
@@ -677,6 +679,7 @@ void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate
   a.rdel = w.rdel;
   a.rwin = w.rwin;
   a.odd = w.odd;
+  a.rest = rest;
   a.max_lines = w.max_lines;
   a.counter = w.counter;
   a.parts = w.item_cnt;

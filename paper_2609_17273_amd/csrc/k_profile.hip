@@ -155,7 +155,7 @@ struct GatherArgs {
   int32_t n_ct;             // n_tiles * n_cond; ct = t * n_cond + c
   int32_t tile_bins;
   int32_t persistent;
-  int32_t some;             // only the conditions whose `gather` is set
+  int32_t some;             // only the conditions without tile expansions
   int32_t end_key;          // n_fine + fine_v: off of it is the number of lines
   int64_t chunk_cfg;        // requested lines per work item (0: automatic)
   int64_t item_target;      // work items aimed at when tiles are split
@@ -1507,7 +1507,7 @@ __global__ __launch_bounds__(256) void k_items_count(GatherArgs g, int32_t* cnt,
   unsigned long long local = 0;
   for (int64_t ct = (int64_t)blockIdx.x * 256 + threadIdx.x; ct < g.n_ct; ct += (int64_t)gridDim.x * 256) {
     const int c = (int)(ct % g.m.n_cond), t = (int)(ct / g.m.n_cond);
-    if (g.some && !g.cond[c].gather) {
+    if (g.some && g.cond[c].far.on) {
       cnt[ct] = -1;  // no work item
       continue;
     }

@@ -8,8 +8,8 @@
 //   sort by cell -> cell offsets + sorted records -> profile pass [-> adjoint].
 // The profile pass is the scatter where a plan asks for it; else the near
 // kernel with tile expansions where the list is dense enough (use_far), the
-// near kernel alone for Gaussians, and the gather for the rest (and for single
-// conditions of a table that it serves better: gather_serves).
+// near kernel alone for Gaussians, and the gather for the rest (and for the
+// conditions of a table without expansions, where it serves them better: gather_serves).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -78,7 +78,9 @@ struct xs_plan {
   int far_lmax = -1;         // highest level of the conditions' tile expansions (-1: none)
   bool no_far = false;       // in the allocation-free call
   int far_end = 0;           // lowest of their levels of cut tiles
-  bool some_gather = false;  // a table with expansions has conditions for the gather
+  // of the conditions without expansions in a table that has them (gather_serves): window
+  // points to a side, and by how many they exceed gather_line
+  double rest_points = 0.0, rest_gain = 0.0;
   bool has_tau = false;      // the last xs_prepare had state lifetimes (records hold their widths)
 };
 
@@ -264,23 +266,38 @@ FarCond far_condition(const xs_plan* p, const CondDev& cd) {
   return c;
 }
 
-// A condition without expansions in a table that has them (a window of less than 577
-// points, or one hardly wider than its Doppler cores): the near kernel takes its points
+// Conditions without expansions in a table that has them (windows of less than 577
+// points, or hardly wider than their Doppler cores): the near kernel takes their points
 // line by line, with an LDS add each, the gather by rows of 64 points, with one formula
 // for a row's worst point and some work per tile before it.  So the gather serves wide windows
 // around narrow cores, in the forms where a point outside the core costs less than the
-// add.  Measured, profile pass of seven conditions, near kernel / gather: 2e5 lines on 2e5 points,
-// cores of a point, 300, 400 and 570 points to a side: Voigt FP32 660 / 943, 952 / 940, 1338 / 997 us,
-// FP64 1310 / 1826, 1545 / 1908, 1876 / 2228; Lorentzian FP32 741 / 813, 1026 / 820, 1437 / 791,
-// FP64 695 / 888, 898 / 897, 1191 / 899; Voigt FP32 with cores of 10 points 742 /
-// 1195, 990 / 1243, 1374 / 1390, of 36 points (500) 1331 / 1849.
-bool gather_serves(const xs_plan* p, const CondDev& cd) {
+// add: where the windows exceed gather_line points on average, and where there is work enough
+// for its plan and its waves (some 0.9 ms on long tables, 0.35 for a condition): near_points and more.
+// All such conditions of a table go one way, since a few in the gather take nearly as long
+// as seven.  Measured, what 1, 2, 4, 7 conditions add to a profile pass of 2e5 points, us, near kernel / gather:
+//   Voigt FP32, cores of 3 points, 400 points to a side, 2e5 lines 256 / 338, 294 / 507, 528 / 896,
+//   975 / 941, 1e6 lines 632 / 690, 1175 / 968, 2901 / 1784, 4335 / 3279; 300 points, 1e6 lines, seven: 3072 / 3084;
+//   cores of 12 points, 400 and 570, 1e6 lines, seven: 4443 / 5241, 6574 / 5780;
+//   Lorentzian FP32, 400 points, 2e5 lines 285 / 295, 334 / 474, 567 / 856, 1045 / 817, 1e6 lines
+//   746 / 587, 1353 / 752, 3275 / 968, 4812 / 1644; 300 points, seven 759 / 808, 3540 / 1487; FP64, 400 points, seven
+//   913 / 902 and 4194 / 2889;
+//   bin means of a Voigt FP32, cores of 3 points, 300 points, 2e5 lines 720 / 530, seven 2591 / 2146, 400 points
+//   932 / 538, seven 3320 / 2217; of 12 points, 570 points, seven 2184 / 3010 (1e6 lines 9294 / 12935).
+double gather_line(const xs_plan* p, const CondDev& cd) {
   const ModelDev& d = p->md;
-  const bool lorentz = base_profile(p->model.profile) == XS_LORENTZ;
-  if (p->model.precision == XS_FP64 && !lorentz) return false;
+  if (base_profile(p->model.profile) == XS_LORENTZ) return 200.0;
   const double mid = std::fabs(d.nu0 + 0.5 * (double)(d.n_bins - 1) * d.dnu);
-  const double core = lorentz ? 0.0 : 8.08 * cd.dop / std::sqrt(kLN2) * mid / d.dnu;
-  return cd.cut / d.dnu > 350.0 + 18.0 * core;
+  const double core = 8.08 * cd.dop / std::sqrt(kLN2) * mid / d.dnu;
+  return p->model.profile == XS_BIN_VOIGT ? 100.0 + 60.0 * core : 350.0 + 18.0 * core;
+}
+
+// near_points: of lines times window points, by what a point costs the near kernel.
+bool gather_serves(const xs_plan* p, int64_t n_lines) {
+  const bool f32 = p->model.precision == XS_FP32;
+  if (!(p->rest_gain > 0.0) || (!f32 && base_profile(p->model.profile) != XS_LORENTZ)) return false;
+  const double cost = p->model.profile == XS_BIN_VOIGT ? 6.0 : p->model.profile == XS_BIN_LORENTZ && !f32 ? 2.5 : 1.0;
+  constexpr double near_points = 4.5e8;
+  return cost * (double)n_lines * p->rest_points >= near_points;
 }
 
 void derive(xs_plan* p) {
@@ -313,7 +330,7 @@ void derive(xs_plan* p) {
   p->cut_class.clear();
   p->cut_mult.clear();
   p->far_lmax = -1;
-  p->some_gather = false;
+  p->rest_points = p->rest_gain = 0.0;
   double maxcut = 0.0;
   for (const xs_condition& c : p->conds) {
     SlotDev s;
@@ -375,7 +392,7 @@ void derive(xs_plan* p) {
       p->cut_mult[cc] += 1;
     }
     cd.cclass = cc;
-    cd.gather = 0;
+    cd.pad = 0;
     cd.far = far_condition(p, cd);
     if (cd.far.on) {
       p->far_end = p->far_lmax < 0 ? cd.far.end : std::min(p->far_end, cd.far.end);
@@ -390,8 +407,10 @@ void derive(xs_plan* p) {
     d.fine_v = far_virtual(d.fine_sh, p->far_lmax, (int64_t)(maxcut / d.dnu) + 2);
     for (CondDev& cd : p->cdev) {
       cd.far.v = d.fine_v;
-      cd.gather = !cd.far.on && gather_serves(p, cd);
-      p->some_gather |= cd.gather != 0;
+      if (!cd.far.on) {
+        p->rest_points += cd.cut / d.dnu;
+        p->rest_gain += cd.cut / d.dnu - gather_line(p, cd);
+      }
     }
   }
   d.n_slots = (int32_t)p->sdev.size();
@@ -587,15 +606,16 @@ int profile_pass(xs_plan* p, double* sigma, int accumulate) {
   if (p->model.algo == XS_SCATTER)
     launch_scatter(p->md, kernel_work(p), sigma, accumulate, 0, p->stream);
   else if (use_near(p)) {
-    launch_near(p->md, kernel_work(p), sigma, accumulate, p->last_lines_in, p->stream);
+    launch_near(p->md, kernel_work(p), sigma, accumulate, false, p->last_lines_in, p->stream);
   } else if (!use_far(p)) {
     launch_gather(p->md, kernel_work(p), p->tiling, sigma, accumulate, false, p->stream);
   } else {
-    if (p->some_gather) {
+    const bool rest = gather_serves(p, p->last_lines_in);
+    if (rest) {
       launch_gather(p->md, kernel_work(p), p->tiling, sigma, accumulate, true, p->stream);
       launch_reset_queue(p->w, p->stream);
     }
-    launch_near(p->md, kernel_work(p), sigma, accumulate, p->last_lines_in, p->stream);
+    launch_near(p->md, kernel_work(p), sigma, accumulate, rest, p->last_lines_in, p->stream);
     launch_far(p->md, kernel_work(p), p->far_lmax, p->far_end, p->last_lines_in, sigma, p->stream);
   }
   return hip_check(hipGetLastError(), "profile launch");

@@ -58,7 +58,7 @@ struct CondDev {
   int32_t slot;   // intensity slot (distinct T or (T_vib, T_rot))
   int32_t wbins;  // bound on |k - k_c| of a nonzero term: ceil(cut / dnu) + 2, less for a narrow Gaussian
   int32_t cclass; // cut-off class (index of the distinct cut-off)
-  int32_t gather; // in a table with tile expansions: its points go through the gather (far.on = 0)
+  int32_t pad;
   FarCond far;    // tile expansions (Lorentzian and Voigt forms)
 };
 
@@ -227,7 +227,7 @@ void launch_reset_queue(const Work& w, hipStream_t s);
 void launch_scan_i32(int32_t* a, int64_t n, int32_t* sums, hipStream_t s);  // exclusive, in place
 
 // ---- profile pass (k_profile.hip) ----
-// (some: only the conditions whose `gather` is set)
+// (some: only the conditions without tile expansions)
 void launch_gather(const ModelDev& m, const Work& w, const Tiling& t, double* sigma,
                    int accumulate, bool some, hipStream_t s);
 void launch_scatter(const ModelDev& m, const Work& w, double* sigma, int accumulate,
@@ -237,8 +237,9 @@ void launch_scatter(const ModelDev& m, const Work& w, double* sigma, int accumul
 inline int64_t part_doubles(const Work& w) { return 2 * w.item_target * 1024; }  // of Work::part
 size_t near_row_doubles();  // what it takes of Work::part
 // sigma = (or +=) the points near each line, for the conditions with tile
-// expansions, and every point of the others but those whose `gather` is set
-void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate, int64_t n_lines, hipStream_t s);
+// expansions, and every point of the others (rest: which are the gather's)
+void launch_near(const ModelDev& m, const Work& w, double* sigma, int accumulate, bool rest, int64_t n_lines,
+                 hipStream_t s);
 
 // ---- tile expansions (k_far.hip) ----
 int far_nodes(int prec);  // nodes per tile
