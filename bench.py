@@ -204,7 +204,7 @@ def valu_from_profiles(kernel_key: str, ms: float, sclk_mhz=None):
     VALU instruction per 16-lane SIMD per 4 cycles at 2.4 GHz, the clock of
     the 78.6 TFLOP/s peak (transcendentals counted as one instruction).  A
     share near 1 means the kernel keeps the VALU saturated.  The share of
-    all VALU instructions can exceed 1 (the FP32 adjoint reads 1.00-1.05):
+    all VALU instructions can exceed 1 (the FP32 adjoint read 1.00-1.05 point by point):
     transcendentals (reciprocals, exponentials) issue to a unit of their own
     and overlap the others, so issue_frac_excl_transcendental, the share of
     the rest, is reported too and stays at or below about 1.  The shader
