@@ -552,7 +552,9 @@ struct FastSums {
 // (FP32 form: window ends take an FP32 cotangent and block sums as the points inside do;
 // in FP64 before.  Errors against FP64 over 150 lists of 1e4 to 2e5 lines, norms of the
 // gradients of log scale, gamma_ref and n_exp, with point-by-point FP64 ends / now, far part
-// included: 2.1e-7, 8.6e-7, 8.8e-7 / 1.2e-7, 4.6e-7, 4.7e-7 in the mean, 1.9e-4 / 5.8e-5 at most.)
+// included: 2.1e-7, 8.6e-7, 8.8e-7 / 9.1e-8, 3.4e-7, 3.6e-7 in the mean, 1.9e-4 / 5.7e-05 at most.  Over 615
+// short or odd lists 1.1e-7, 2.0e-7, 2.1e-7 / 8.2e-8, 1.6e-7, 1.6e-7; but lists of a few lines whose windows the
+// grid's ends all cut, in FP64 as a whole before, have the FP32 form's errors now, 1e-6 where 2e-8.)
 template <typename R, int PROF, int NP, bool SY = false, bool C0 = false, bool UF = false>
 __device__ __forceinline__ void fast_range(const AdjLine<R>& L, const GSrc<R>& G, int r0, int r1, bool mask,
                                            double& sA, double& sB, double& sC) {
@@ -562,18 +564,20 @@ __device__ __forceinline__ void fast_range(const AdjLine<R>& L, const GSrc<R>& G
   const int nact = __popcll(act);
   // x at r = rb + j4 + jj as fma(rb + j4, a, nb + jj a): one conversion per
   // four points (nb + jj a rounds once, relative 6e-8 of at most 3.5 a, so x
-  // keeps a relative error below 5e-7 for every r != 0)
+  // keeps a relative error below 5e-7 for every r != 0; the fours begin at multiples of
+  // four, so that x at r = 0, of which 3.5 a may be any multiple, is nb itself)
   R nbj[4];
 #pragma unroll
   for (int jj = 0; jj < 4; ++jj) nbj[jj] = fma((R)jj, L.a, L.nb);
   using Sums = FastSums<R, PROF, NP, SY, C0, UF>;
   Sums S;
   S.begin(L);
-  for (int rb = r0; rb <= r1; rb += kFlush) {
-    const int n = min(kFlush, r1 - rb + 1);
+  for (int rb = r0, n; rb <= r1; rb += n) {
+    n = min(kFlush - (rb & 3), r1 - rb + 1);
     S.clear();
     auto run = [&](auto gsrc) {
       int j = 0;
+      for (; j < n && ((rb + j) & 3); ++j) S.add(L, fma((R)(rb + j), L.a, L.nb), gsrc(j));
       if (Sums::kFour && L.share4) {
         for (; j + 4 <= n; j += 4) {
           R x[4], gk[4];
